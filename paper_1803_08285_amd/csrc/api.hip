@@ -693,6 +693,9 @@ static int bb_route(int32_t nt, int32_t nf, int32_t npix, uint32_t flags, const 
     // launches, ~1.5e13 float64 FMAs/s for the tables (4 per segment, bin and
     // node; the rate rises to ~2e13 with more nodes) and ~3.3e11 items/s in
     // the map pass (twice that for antipodal seeds, read once per pixel pair).
+    // (The rates are those of the direct table sums; summed at Chebyshev nodes
+    // the tables take a fifth of that.  The rule is kept as it is: a query's
+    // route, and with it its bits, stays the same.)
     const double strip_cols = (double)(((int64_t)nf + 63) / 64 * 64);
     const double strips = 1.9e-4 + (double)nt * npix / 1.2e11 + (double)nt * strip_cols * npix / 4.2e13;
     const double table = have_grid ? 3e-5 + (double)nt * nb * r->grid.G * 4.0 / 1.5e13 +

@@ -172,3 +172,27 @@ def test_broken_antipodal_promise_gives_nan_maps(sg):
     assert torch.isfinite(Xok).all() and torch.equal(Gok, Gnp)
     # the pair pass and the one-pixel pass agree to the route's tolerance
     assert float((Xok - Xnp).abs().max()) <= 1e-6 * float(Xok.abs().max())
+
+
+@pytest.mark.parametrize("nb,df,bl,tight", [
+    (23, 1 / 32, "BC", True),    # the band about as many bins as nodes
+    (511, 1 / 32, "AC", True),   # a stage short of one bin
+    (4096, 1 / 32, "AB", True),  # several stages of every residue
+    (700, 1.0, "AD", False),     # about 200 nodes: one residue
+    (2000, 1.0, "AC", False),    # more than 256 nodes: two passes
+    (3500, 1.0, "AC", False),    # more than 512 nodes: the direct sums
+], ids=lambda v: str(v))
+def test_tables_from_few_nodes_vs_oracle(sg, oracle_mod, nb, df, bl, tight):
+    """The tables summed at their Chebyshev nodes (and, past 512 nodes, at every
+    grid node), over the node counts' edges: within the route's 1e-6 of S_bb."""
+    nside, nt, k0 = 2, 5, 9
+    g, t, C, w, H = _setup(sg, bl, nside, nt, k0, nb, df, 7 + nb)
+    tb = sg.baseline_delay_bound(synth.baseline_sites(bl)) if tight else 0.0
+    print(f"nb {nb} df {df}", flush=True)
+    Xbb, _ = sg.broadband_maps(C, w, sg.FGrid(F0, df), k0, g, t, None, 0, nb, tau_bound=tb, want_gamma=False,
+                               route="table")
+    torch.cuda.synchronize()
+    Xo, _, S = oracle_mod.maps(C.cpu().numpy(), w.cpu().numpy(), F0, df, k0, g.cpu().numpy(), t.cpu().numpy(),
+                               with_scale=True)
+    err = np.abs(Xbb.cpu().numpy().astype(np.float64) - Xo.sum(axis=0))
+    assert np.all(err <= TOL * S.sum(axis=0) + 1e-300), float((err / S.sum(axis=0)).max())
