@@ -14,6 +14,7 @@
 // reproducible for a given (npix, klo, khi).
 #include <type_traits>
 
+#include "broadband.h"
 #include "sgwb_internal.h"
 
 namespace sgwb {
@@ -228,11 +229,18 @@ template hipError_t launch_band<double>(const double *, const double *, const do
 // wave order: one fixed order for every call.
 constexpr int kFinishWaves = 8;
 
+// (blockIdx.y = 1: a second such sum, of part1 into out1.)
 __global__ __launch_bounds__(64 * kFinishWaves) void band_partial_finish_kernel(const double *__restrict__ part,
                                                                                 int64_t nrows, int32_t npix,
-                                                                                float *__restrict__ out)
+                                                                                float *__restrict__ out,
+                                                                                const double *__restrict__ part1,
+                                                                                float *__restrict__ out1)
 {
     __shared__ double red[kFinishWaves][64];
+    if (blockIdx.y) {
+        part = part1;
+        out = out1;
+    }
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int32_t p = blockIdx.x * 64 + lane;
     double acc = 0.0;
@@ -247,10 +255,11 @@ __global__ __launch_bounds__(64 * kFinishWaves) void band_partial_finish_kernel(
     out[p] = (float)sum;
 }
 
-hipError_t launch_band_partial_finish(const double *part, int64_t nrows, int32_t npix, float *out, hipStream_t s)
+hipError_t launch_band_partial_finish(const double *part, int64_t nrows, int32_t npix, float *out, hipStream_t s,
+                                      const double *part1, float *out1)
 {
-    hipLaunchKernelGGL(band_partial_finish_kernel, dim3((unsigned)((npix + 63) / 64)), dim3(64 * kFinishWaves), 0, s,
-                       part, nrows, npix, out);
+    hipLaunchKernelGGL(band_partial_finish_kernel, dim3((unsigned)((npix + 63) / 64), out1 ? 2 : 1),
+                       dim3(64 * kFinishWaves), 0, s, part, nrows, npix, out, part1, out1);
     return hipGetLastError();
 }
 
@@ -284,23 +293,35 @@ __global__ __launch_bounds__(kWeightThreads) void band_weight_kernel(const float
     if (threadIdx.x == 0) v[blockIdx.x] = red[0];
 }
 
-// Gbb[p] = sum_t v[t] gamma(t,p)^2 (float64, rounded once): kBandTChunks
-// segment chunks per pixel block write partial sums in segment order, then a
-// second kernel adds the chunks in order.  One thread per pixel, coalesced rows.
+// Gbb[p] = sum_t v[t] gamma(t,p)^2 (float64, rounded once): band_gamma_chunks()
+// segment chunks per pixel block write partial sums, then a second kernel adds
+// the chunks in order.  A chunk's sum is that of kBandSlices runs of
+// consecutive segments, each summed in segment order, then added in order: the
+// four waves of a workgroup take one run each for the same 64 pixels (coalesced
+// rows), so that a small map still fills the chip.
 constexpr int kBandTChunks = 32;
 
 __global__ __launch_bounds__(256) void band_gamma_kernel(const float *__restrict__ gamma, int32_t npix, int32_t nt,
-                                                         const double *__restrict__ v, double *__restrict__ part)
+                                                         int32_t per, const double *__restrict__ v,
+                                                         double *__restrict__ part)
 {
-    const int32_t p = blockIdx.x * 256 + threadIdx.x;
-    if (p >= npix) return;
-    const int32_t per = (nt + kBandTChunks - 1) / kBandTChunks;
-    const int32_t t0 = blockIdx.y * per, t1 = min(t0 + per, nt);
+    static_assert(kBandSlices == 4, "one wave a run");
+    __shared__ double red[kBandSlices][64];
+    const int lane = threadIdx.x & 63, sl = threadIdx.x >> 6;
+    const int32_t p = blockIdx.x * 64 + lane;
+    const int64_t pc = min(p, npix - 1);
+    const BandSlice run = band_slice(blockIdx.y, sl, per, nt);
     double acc = 0.0;
-    for (int32_t t = t0; t < t1; ++t) {
-        const double g = (double)gamma[(int64_t)t * npix + p];
+#pragma unroll 4
+    for (int32_t t = run.begin; t < run.end; ++t) {
+        const double g = (double)gamma[(int64_t)t * npix + pc];
         acc = fma(v[t], g * g, acc);
     }
+    red[sl][lane] = acc;
+    __syncthreads();
+    if (sl != 0 || p >= npix) return;
+#pragma unroll
+    for (int k = 1; k < kBandSlices; ++k) acc += red[k][lane];
     part[(int64_t)blockIdx.y * npix + p] = acc;
 }
 
@@ -323,8 +344,8 @@ hipError_t launch_band_gamma(const float *w, int64_t ldw, int32_t nt, const floa
 {
     double *v = scratch, *part = scratch + nt;
     hipLaunchKernelGGL(band_weight_kernel, dim3((unsigned)nt), dim3(kWeightThreads), 0, s, w, ldw, H, klo, khi, v);
-    hipLaunchKernelGGL(band_gamma_kernel, dim3((unsigned)((npix + 255) / 256), kBandTChunks), dim3(256), 0, s, gamma,
-                       npix, nt, v, part);
+    hipLaunchKernelGGL(band_gamma_kernel, dim3((unsigned)((npix + 63) / 64), kBandTChunks), dim3(256), 0, s, gamma,
+                       npix, nt, (nt + kBandTChunks - 1) / kBandTChunks, v, part);
     return launch_band_partial_finish(part, kBandTChunks, npix, Gbb, s);
 }
 

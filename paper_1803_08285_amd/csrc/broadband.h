@@ -22,8 +22,21 @@ size_t bb_workspace_bytes(int32_t nt, int32_t npix, int32_t nb, const BbGrid &g)
 // Gbb beside Xbb with the same bits: its scratch holds v[nt] (the band-summed
 // weights, from launch_band_weights) and then band_gamma_chunks() rows of
 // per-pixel partial sums, row r over segments [r per, (r + 1) per),
-// per = ceil(nt / band_gamma_chunks()), each summed in segment order.
+// per = ceil(nt / band_gamma_chunks()), as the sum of its kBandSlices runs
+// (band_slice), each summed in segment order.
 int32_t band_gamma_chunks();
+constexpr int kBandSlices = 4;
+struct BandSlice {
+    int32_t begin, end;
+};
+__device__ inline BandSlice band_slice(int32_t chunk, int sl, int32_t per, int32_t nt)
+{
+    const int32_t t0 = chunk * per, t1 = min(nt, t0 + per), sub = (per + kBandSlices - 1) / kBandSlices;
+    BandSlice r;
+    r.begin = min(t0 + sl * sub, t1);
+    r.end = min(t0 + (sl + 1) * sub, t1);
+    return r;
+}
 hipError_t launch_band_weights(const float *w, int64_t ldw, int32_t nt, const float *H, int32_t klo, int32_t khi,
                                double *v, hipStream_t s);
 // Xbb (and, with Gbb, Gbb) over columns [klo, khi) of C and w (absolute bins

@@ -274,70 +274,147 @@ __global__ __launch_bounds__(256) void bb_map_kernel(const float *__restrict__ g
 {
     const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (p >= npix) return;
-    const int32_t t0 = blockIdx.y * per, t1 = min(nt, t0 + per);
-    double gacc = 0.0;
+    double acc = 0.0, gacc = 0.0;  // sums of the chunk's runs so far
     const double inv_h = 1.0 / h, origin = (double)(m + 1);
     const double jmax = (double)(2 * m);
-    double acc = 0.0;
     bool bad = false;
     // segments kBbBatch at a time: their seed loads, then their table reads, are
     // issued together (segments past t1 repeat t1 - 1 with weight zero; no
     // branch, so that the compiler keeps the loads ahead of the arithmetic)
-    for (int32_t tq = t0; tq < t1; tq += kBbBatch) {
-        double ta[kBbBatch];
-        float g[kBbBatch];
+    for (int sl = 0; sl < kBandSlices; ++sl) {
+        const BandSlice run = band_slice(blockIdx.y, sl, per, nt);
+        const int32_t t1 = run.end;
+        double sum = 0.0, gsum = 0.0;
+        for (int32_t tq = run.begin; tq < t1; tq += kBbBatch) {
+            double ta[kBbBatch];
+            float g[kBbBatch];
 #pragma unroll
-        for (int e = 0; e < kBbBatch; ++e) {
-            const int64_t o = (int64_t)min(tq + e, t1 - 1) * npix + p;
-            ta[e] = tau[o];
-            g[e] = gamma[o];
-        }
-        float2 a[kBbBatch][4];
-        float x[kBbBatch];
+            for (int e = 0; e < kBbBatch; ++e) {
+                const int64_t o = (int64_t)min(tq + e, t1 - 1) * npix + p;
+                ta[e] = tau[o];
+                g[e] = gamma[o];
+            }
+            float2 a[kBbBatch][4];
+            float x[kBbBatch];
 #pragma unroll
-        for (int e = 0; e < kBbBatch; ++e) {
-            const double u = fma(ta[e], inv_h, origin);
-            const double jd = fmin(fmax(floor(u), 1.0), jmax);  // NaN and out-of-range delays stay inside the table
-            x[e] = (float)(u - jd);
-            const float2 *row = T + (int64_t)min(tq + e, t1 - 1) * G + ((int32_t)jd - 1);
+            for (int e = 0; e < kBbBatch; ++e) {
+                const double u = fma(ta[e], inv_h, origin);
+                const double jd = fmin(fmax(floor(u), 1.0), jmax);  // NaN and out-of-range delays stay inside the table
+                x[e] = (float)(u - jd);
+                const float2 *row = T + (int64_t)min(tq + e, t1 - 1) * G + ((int32_t)jd - 1);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) a[e][i] = row[i];
-        }
+                for (int i = 0; i < 4; ++i) a[e][i] = row[i];
+            }
 #pragma unroll
-        for (int e = 0; e < kBbBatch; ++e) {
-            const bool valid = tq + e < t1;
-            bad |= valid && !(fabs(ta[e]) <= bound);
-            // Lagrange weights of the nodes at -1, 0, 1, 2
-            const float xe = x[e], xp = xe + 1.0f, xm = xe - 1.0f, xm2 = xe - 2.0f;
-            const float l0 = -(1.0f / 6.0f) * xe * xm * xm2;
-            const float l1 = 0.5f * xp * xm * xm2;
-            const float l2 = -0.5f * xp * xe * xm2;
-            const float l3 = (1.0f / 6.0f) * xp * xe * xm;
-            const float yr = fmaf(l0, a[e][0].x, fmaf(l1, a[e][1].x, fmaf(l2, a[e][2].x, l3 * a[e][3].x)));
-            const float yi = fmaf(l0, a[e][0].y, fmaf(l1, a[e][1].y, fmaf(l2, a[e][2].y, l3 * a[e][3].y)));
-            // carrier e^{2 pi i f_c tau}: the phase reduced in float64
-            const double turns = fc * ta[e];
-            const float r = (float)(turns - rint(turns));
-            float sn, cs;
-            sincospif(2.0f * r, &sn, &cs);
-            acc = fma(valid ? (double)g[e] : 0.0, (double)fmaf(cs, yr, -sn * yi), acc);
-            if (GB) {
-                const double gd = (double)g[e];
-                const double ga = fma(v[min(tq + e, t1 - 1)], gd * gd, gacc);
-                gacc = valid ? ga : gacc;
+            for (int e = 0; e < kBbBatch; ++e) {
+                const bool valid = tq + e < t1;
+                bad |= valid && !(fabs(ta[e]) <= bound);
+                // Lagrange weights of the nodes at -1, 0, 1, 2
+                const float xe = x[e], xp = xe + 1.0f, xm = xe - 1.0f, xm2 = xe - 2.0f;
+                const float l0 = -(1.0f / 6.0f) * xe * xm * xm2;
+                const float l1 = 0.5f * xp * xm * xm2;
+                const float l2 = -0.5f * xp * xe * xm2;
+                const float l3 = (1.0f / 6.0f) * xp * xe * xm;
+                const float yr = fmaf(l0, a[e][0].x, fmaf(l1, a[e][1].x, fmaf(l2, a[e][2].x, l3 * a[e][3].x)));
+                const float yi = fmaf(l0, a[e][0].y, fmaf(l1, a[e][1].y, fmaf(l2, a[e][2].y, l3 * a[e][3].y)));
+                // carrier e^{2 pi i f_c tau}: the phase reduced in float64
+                const double turns = fc * ta[e];
+                const float r = (float)(turns - rint(turns));
+                float sn, cs;
+                sincospif(2.0f * r, &sn, &cs);
+                sum = fma(valid ? (double)g[e] : 0.0, (double)fmaf(cs, yr, -sn * yi), sum);
+                if (GB) {
+                    const double gd = (double)g[e];
+                    const double ga = fma(v[min(tq + e, t1 - 1)], gd * gd, gsum);
+                    gsum = valid ? ga : gsum;
+                }
             }
         }
+        acc += sum;
+        gacc += gsum;
     }
     part[(int64_t)blockIdx.y * npix + p] = bad ? (double)__builtin_nanf("") : acc;
     if (GB) gpart[(int64_t)blockIdx.y * npix + p] = gacc;
 }
 
-// The same sums for a pixel p of the northern half and its antipode pB at
-// once, from p's seeds alone: antipodal seeds have gamma(t,pB) = gamma(t,p)
-// and tau(t,pB) = -tau(t,p), and the delay grid is symmetric about zero, so
-// pB's value is the table read at -tau with the conjugate carrier.  The
-// seeds' promise is spot-checked (flags, one per part of the check): a failed
-// check makes both maps NaN everywhere.
+// A pixel pair's terms.  Antipodal seeds have gamma(t,pB) = gamma(t,p) and
+// tau(t,pB) = -tau(t,p), and the delay grid is symmetric about zero, so one
+// read of p's seeds serves both pixels: with u = |tau| / h, jd = floor(u) and
+// x = u - jd, the nodes of +|tau| are jd - 1 .. jd + 2 counted from the centre,
+// those of -|tau| their mirror images with the same weights, and the carriers
+// are conjugate.
+struct BbAt {
+    int32_t j;  // jd, in [0, m - 1] whatever the delay (NaN included)
+    float x;
+    float cs, sn;  // carrier e^{2 pi i f_c |tau|}
+};
+
+__device__ __forceinline__ BbAt bb_at(double ta, double inv_h, double jmax, double fc)
+{
+    BbAt r;
+    const double at = fabs(ta), u = at * inv_h;
+    const double jd = fmin(floor(u), jmax);
+    r.j = (int32_t)jd;
+    r.x = (float)(u - jd);
+    // the phase reduced to the nearest quarter turn in float64, sine and
+    // cosine by their series on |theta| <= pi / 4 (truncation below 2e-9),
+    // turned by the quadrant.  (A half-angle form without the quadrant was 4 %
+    // faster, but its rounding took the maps' error from 8.4e-8 to 1.4e-7.)
+    const double x4 = 4.0 * fc * at, q = rint(x4);
+    const float th = (float)(x4 - q) * 1.57079632679489662f, t2 = th * th;
+    const int k = (int)(q - 4.0 * floor(0.25 * q));
+    const float s =
+        th * fmaf(t2, fmaf(t2, fmaf(t2, fmaf(t2, 2.75573192e-6f, -1.98412698e-4f), 8.33333333e-3f), -1.66666667e-1f),
+                  1.0f);
+    const float c =
+        fmaf(t2, fmaf(t2, fmaf(t2, fmaf(t2, fmaf(t2, -2.75573192e-7f, 2.48015873e-5f), -1.38888889e-3f),
+                               4.16666667e-2f), -0.5f), 1.0f);
+    const float cr = (k & 1) ? s : c, sr = (k & 1) ? c : s;
+    r.cs = ((k + 1) & 2) ? -cr : cr;
+    r.sn = (k & 2) ? -sr : sr;
+    return r;
+}
+
+// Re[e^{2 pi i f_c tau} Y(tau)] at tau and at -tau (x, y) from the four nodes
+// (Y(+tau_j), Y(-tau_j)) around |tau|.
+__device__ __forceinline__ float2 bb_pair_value(const float4 (&e)[4], const BbAt &at, bool negative)
+{
+    // Lagrange weights of the nodes at -1, 0, 1, 2
+    const float x = at.x, xp = x + 1.0f, xm = x - 1.0f, xm2 = x - 2.0f;
+    const float outer = (1.0f / 6.0f) * x * xm, inner = 0.5f * xp * xm2;
+    const float l0 = -outer * xm2, l1 = inner * xm, l2 = -inner * x, l3 = outer * xp;
+    const float pr = fmaf(l0, e[0].x, fmaf(l1, e[1].x, fmaf(l2, e[2].x, l3 * e[3].x)));
+    const float pi = fmaf(l0, e[0].y, fmaf(l1, e[1].y, fmaf(l2, e[2].y, l3 * e[3].y)));
+    const float mr = fmaf(l0, e[0].z, fmaf(l1, e[1].z, fmaf(l2, e[2].z, l3 * e[3].z)));
+    const float mi = fmaf(l0, e[0].w, fmaf(l1, e[1].w, fmaf(l2, e[2].w, l3 * e[3].w)));
+    const float p = fmaf(at.cs, pr, -at.sn * pi), q = fmaf(at.cs, mr, at.sn * mi);
+    return negative ? make_float2(q, p) : make_float2(p, q);
+}
+
+// The chunk's sums of a pixel pair.  The antipodal promise is spot-checked
+// (flags, one per part of the check): a failed check makes both maps NaN.
+template <bool GB>
+__device__ __forceinline__ void bb_store_pair(int64_t p, int64_t npix, int64_t nside, const double *__restrict__ flags,
+                                              bool bad, double a, double b, double g, double *__restrict__ part,
+                                              double *__restrict__ gpart)
+{
+    bool broken = false;
+    for (int i = 0; i < kSymParts; ++i) broken |= flags[i] != 0.0;
+    const double nan = (double)__builtin_nanf("");
+    const int64_t pB = antipode_north(ring_of_north(p, nside), npix);
+    double *row = part + (int64_t)blockIdx.y * npix;
+    row[p] = bad || broken ? nan : a;
+    row[pB] = bad || broken ? nan : b;
+    if (GB) {
+        double *grow = gpart + (int64_t)blockIdx.y * npix;
+        grow[p] = broken ? nan : g;
+        grow[pB] = broken ? nan : g;
+    }
+}
+
+// Few pixels: the four waves of a workgroup take a run each of the chunk's
+// segments (band_slice) for the same 64 pixel pairs, reading the tables where
+// they are; bound by the latency of the segments in series, hence the split.
 template <bool GB>
 __global__ __launch_bounds__(256) void bb_map_pair_kernel(const float *__restrict__ gamma,
                                                           const double *__restrict__ tau, int32_t nt, int32_t npix,
@@ -346,79 +423,206 @@ __global__ __launch_bounds__(256) void bb_map_pair_kernel(const float *__restric
                                                           const double *__restrict__ flags, double *__restrict__ part,
                                                           const double *__restrict__ v, double *__restrict__ gpart)
 {
-    const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (p >= npix / 2) return;
-    const int64_t pB = antipode_north(ring_of_north(p, nside), npix);
-    const int32_t t0 = blockIdx.y * per, t1 = min(nt, t0 + per);
-    const double inv_h = 1.0 / h, origin = (double)(m + 1);
-    const double jmax = (double)(2 * m);
+    __shared__ double red[3][kBandSlices][64];
+    __shared__ int redbad[kBandSlices][64];
+    const int lane = threadIdx.x & 63, sl = threadIdx.x >> 6;
+    const int64_t p = (int64_t)blockIdx.x * 64 + lane, npairs = npix / 2, pc = p < npairs ? p : npairs - 1;
+    const BandSlice run = band_slice(blockIdx.y, sl, per, nt);
+    const double inv_h = 1.0 / h, jmax = (double)(m - 1);
     double accA = 0.0, accB = 0.0, gacc = 0.0;
     bool bad = false;
-    for (int32_t tq = t0; tq < t1; tq += kBbBatch) {
+    for (int32_t tq = run.begin; tq < run.end; tq += kBbBatch) {
         double ta[kBbBatch];
         float g[kBbBatch];
 #pragma unroll
         for (int e = 0; e < kBbBatch; ++e) {
-            const int64_t o = (int64_t)min(tq + e, t1 - 1) * npix + p;
+            const int64_t o = (int64_t)min(tq + e, run.end - 1) * npix + pc;
             ta[e] = tau[o];
             g[e] = gamma[o];
         }
-        float2 a[kBbBatch][2][4];
-        float x[kBbBatch][2];
-#pragma unroll
-        for (int e = 0; e < kBbBatch; ++e)
-#pragma unroll
-            for (int side = 0; side < 2; ++side) {
-                const double u = fma(side ? -ta[e] : ta[e], inv_h, origin);
-                const double jd = fmin(fmax(floor(u), 1.0), jmax);  // NaN and out-of-range delays stay inside the table
-                x[e][side] = (float)(u - jd);
-                const float2 *row = T + (int64_t)min(tq + e, t1 - 1) * G + ((int32_t)jd - 1);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) a[e][side][i] = row[i];
-            }
+        BbAt at[kBbBatch];
+        float4 n[kBbBatch][4];
 #pragma unroll
         for (int e = 0; e < kBbBatch; ++e) {
-            const bool valid = tq + e < t1;
-            bad |= valid && !(fabs(ta[e]) <= bound);
-            float yr[2], yi[2];
+            at[e] = bb_at(ta[e], inv_h, jmax, fc);
+            const float2 *row = T + (int64_t)min(tq + e, run.end - 1) * G + (m + 1);  // the centre node
 #pragma unroll
-            for (int side = 0; side < 2; ++side) {
-                // Lagrange weights of the nodes at -1, 0, 1, 2
-                const float xe = x[e][side], xp = xe + 1.0f, xm = xe - 1.0f, xm2 = xe - 2.0f;
-                const float l0 = -(1.0f / 6.0f) * xe * xm * xm2;
-                const float l1 = 0.5f * xp * xm * xm2;
-                const float l2 = -0.5f * xp * xe * xm2;
-                const float l3 = (1.0f / 6.0f) * xp * xe * xm;
-                const float2 *aa = a[e][side];
-                yr[side] = fmaf(l0, aa[0].x, fmaf(l1, aa[1].x, fmaf(l2, aa[2].x, l3 * aa[3].x)));
-                yi[side] = fmaf(l0, aa[0].y, fmaf(l1, aa[1].y, fmaf(l2, aa[2].y, l3 * aa[3].y)));
-            }
-            // carrier e^{2 pi i f_c tau} for p, its conjugate for pB
-            const double turns = fc * ta[e];
-            const float r = (float)(turns - rint(turns));
-            float sn, cs;
-            sincospif(2.0f * r, &sn, &cs);
-            const double wg = valid ? (double)g[e] : 0.0;
-            accA = fma(wg, (double)fmaf(cs, yr[0], -sn * yi[0]), accA);
-            accB = fma(wg, (double)fmaf(cs, yr[1], sn * yi[1]), accB);
-            if (GB) {
-                const double gd = (double)g[e];
-                const double ga = fma(v[min(tq + e, t1 - 1)], gd * gd, gacc);
-                gacc = valid ? ga : gacc;
+            for (int i = 0; i < 4; ++i) {
+                const float2 a = row[at[e].j - 1 + i], b = row[-(at[e].j - 1 + i)];
+                n[e][i] = make_float4(a.x, a.y, b.x, b.y);
             }
         }
+#pragma unroll
+        for (int e = 0; e < kBbBatch; ++e) {
+            const bool valid = e == 0 || tq + e < run.end;  // a segment past the run repeats its last
+            bad |= !(fabs(ta[e]) <= bound);
+            const float2 val = bb_pair_value(n[e], at[e], ta[e] < 0.0);
+            const double wg = valid ? (double)g[e] : 0.0;
+            accA = fma(wg, (double)val.x, accA);
+            accB = fma(wg, (double)val.y, accB);
+            if (GB) gacc = fma(v[min(tq + e, run.end - 1)], wg * (double)g[e], gacc);
+        }
     }
-    bool broken = false;
-    for (int i = 0; i < kSymParts; ++i) broken |= flags[i] != 0.0;
-    const double nan = (double)__builtin_nanf("");
-    double *row = part + (int64_t)blockIdx.y * npix;
-    row[p] = bad || broken ? nan : accA;
-    row[pB] = bad || broken ? nan : accB;
-    if (GB) {
-        double *grow = gpart + (int64_t)blockIdx.y * npix;
-        grow[p] = broken ? nan : gacc;
-        grow[pB] = broken ? nan : gacc;
+    red[0][sl][lane] = accA;
+    red[1][sl][lane] = accB;
+    red[2][sl][lane] = gacc;
+    redbad[sl][lane] = bad;
+    __syncthreads();
+    if (sl != 0 || p >= npairs) return;
+#pragma unroll
+    for (int k = 1; k < kBandSlices; ++k) {
+        accA += red[0][k][lane];
+        accB += red[1][k][lane];
+        gacc += red[2][k][lane];
+        bad |= redbad[k][lane] != 0;
     }
+    bb_store_pair<GB>(p, npix, nside, flags, bad, accA, accB, gacc, part, gpart);
+}
+
+// Many pixels: one pixel pair a thread over the chunk's runs in turn, the
+// segments' tables staged through LDS, kBbBatch at a time and double-buffered,
+// as (Y(+tau_j), Y(-tau_j)) per node counted from the centre (index j + 1 for
+// j = -1 .. m + 1), so a pair's four nodes are four 16-byte reads.  K: staged
+// entries per thread.  Bound by vector instructions (~90 a pair and segment, a
+// quarter of them float64) just ahead of the seeds' 12 bytes.  Full day,
+// nside 128, 4096 bins, AB: the pass 252 us, 348 us with the nodes read from
+// global memory by each pair.
+constexpr int kBbMapThreads = 512;
+constexpr int64_t kBbLdsPairs = 6144;
+
+template <bool GB, int K>
+__global__ __launch_bounds__(kBbMapThreads) void bb_map_pair_lds_kernel(
+    const float *__restrict__ gamma, const double *__restrict__ tau, int32_t nt, int32_t npix, int64_t nside,
+    const float2 *__restrict__ T, int32_t G, int32_t m, double h, double bound, double fc, int32_t per,
+    const double *__restrict__ flags, double *__restrict__ part, const double *__restrict__ v,
+    double *__restrict__ gpart)
+{
+    extern __shared__ float4 tab[];  // [2][kBbBatch][m + 3]
+    const int32_t E = m + 3;
+    const int64_t p = (int64_t)blockIdx.x * kBbMapThreads + threadIdx.x;
+    const int64_t npairs = npix / 2, pc = p < npairs ? p : npairs - 1;
+    const double inv_h = 1.0 / h, jmax = (double)(m - 1);
+    double totA = 0.0, totB = 0.0, totG = 0.0, accA = 0.0, accB = 0.0, gacc = 0.0;
+    bool bad = false;
+
+    // the batches of the chunk's runs, in order (uniform over the workgroup)
+    int sl = 0;
+    BandSlice run = band_slice(blockIdx.y, 0, per, nt);
+    int32_t tq = run.begin;
+    auto settle = [&]() {  // to the next batch; false past the last
+        while (tq >= run.end) {
+            if (++sl >= kBandSlices) return false;
+            run = band_slice(blockIdx.y, sl, per, nt);
+            tq = run.begin;
+        }
+        return true;
+    };
+    double ta[kBbBatch];
+    float g[kBbBatch];
+    float4 st[K];
+    auto fetch = [&]() {
+#pragma unroll
+        for (int e = 0; e < kBbBatch; ++e) {
+            const int64_t o = (int64_t)min(tq + e, run.end - 1) * npix + pc;
+            ta[e] = tau[o];
+            g[e] = gamma[o];
+        }
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int32_t i = min((int32_t)threadIdx.x + k * kBbMapThreads, kBbBatch * E - 1);
+            const int32_t e = i >= E ? 1 : 0, j = i - e * E - 1;
+            const float2 *row = T + (int64_t)min(tq + e, run.end - 1) * G + (m + 1);
+            const float2 a = row[j], b = row[-j];
+            st[k] = make_float4(a.x, a.y, b.x, b.y);
+        }
+    };
+    static_assert(kBbBatch == 2, "the staging index splits two segments");
+    auto put = [&](float4 *buf) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int32_t i = (int32_t)threadIdx.x + k * kBbMapThreads;
+            if (i < kBbBatch * E) buf[i] = st[k];
+        }
+    };
+    bool more = settle();
+    if (more) {
+        fetch();
+        put(tab);
+    }
+    __syncthreads();
+    int cur = 0;
+    while (more) {
+        double tc[kBbBatch];
+        float gc[kBbBatch];
+#pragma unroll
+        for (int e = 0; e < kBbBatch; ++e) {
+            tc[e] = ta[e];
+            gc[e] = g[e];
+        }
+        const int32_t t0 = tq, t1 = run.end;
+        const int sl0 = sl;
+        tq += kBbBatch;
+        more = settle();
+        if (more) fetch();
+        const float4 *buf = tab + cur * kBbBatch * E;
+#pragma unroll
+        for (int e = 0; e < kBbBatch; ++e) {
+            const bool valid = e == 0 || t0 + e < t1;  // a segment past the run repeats its last
+            const BbAt at = bb_at(tc[e], inv_h, jmax, fc);
+            float4 n[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) n[i] = buf[e * E + at.j + i];
+            bad |= !(fabs(tc[e]) <= bound);
+            const float2 val = bb_pair_value(n, at, tc[e] < 0.0);
+            const double gd = (double)gc[e], wg = valid ? gd : 0.0;
+            accA = fma(wg, (double)val.x, accA);
+            accB = fma(wg, (double)val.y, accB);
+            if (GB) gacc = fma(v[min(t0 + e, t1 - 1)], wg * gd, gacc);
+        }
+        if (!more || sl != sl0) {  // the run is done
+            totA += accA;
+            totB += accB;
+            totG += gacc;
+            accA = accB = gacc = 0.0;
+        }
+        cur ^= 1;
+        if (more) put(tab + cur * kBbBatch * E);
+        __syncthreads();
+    }
+    if (p >= npairs) return;
+    bb_store_pair<GB>(p, npix, nside, flags, bad, totA, totB, totG, part, gpart);
+}
+
+template <bool GB>
+static hipError_t launch_bb_map_pair(const float *gamma, const double *tau, int32_t nt, int32_t npix, int64_t nside,
+                                     const float2 *T, const BbGrid &g, double fc, int32_t nchunks, int32_t per,
+                                     const double *flags, double *part, const double *v, double *gpart, hipStream_t s)
+{
+    const int64_t npairs = npix / 2;
+    const int32_t entries = kBbBatch * (g.m + 3), k = (entries + kBbMapThreads - 1) / kBbMapThreads;
+    // The LDS form from kBbLdsPairs pixel pairs on, while the tables fit in 64 KB
+    // (at most 1021 intervals of |tau|).  Measured, full day, AB, 1531 bins, call
+    // (LDS / split form): nside 8 44.2 / 35.1, 16 45.8 / 37.6, 32 54.6 / 54.8, 64
+    // 105 / 143, 128 331 / 492 us; AC alike.
+    if (npairs >= kBbLdsPairs && k <= 4) {
+        const dim3 grid((unsigned)((npairs + kBbMapThreads - 1) / kBbMapThreads), (unsigned)nchunks);
+        const size_t lds = 2 * (size_t)entries * sizeof(float4);
+        auto go = [&](auto kern) {
+            hipLaunchKernelGGL(kern, grid, dim3(kBbMapThreads), lds, s, gamma, tau, nt, npix, nside, T, g.G, g.m, g.h,
+                               g.bound, fc, per, flags, part, v, gpart);
+        };
+        if (k == 1)
+            go(bb_map_pair_lds_kernel<GB, 1>);
+        else if (k == 2)
+            go(bb_map_pair_lds_kernel<GB, 2>);
+        else
+            go(bb_map_pair_lds_kernel<GB, 4>);
+    } else {
+        hipLaunchKernelGGL(bb_map_pair_kernel<GB>, dim3((unsigned)((npairs + 63) / 64), (unsigned)nchunks), dim3(256),
+                           0, s, gamma, tau, nt, npix, nside, T, g.G, g.m, g.h, g.bound, fc, per, flags, part, v,
+                           gpart);
+    }
+    return hipGetLastError();
 }
 
 hipError_t launch_broadband_table_maps(const float *C, const float *w, int64_t ldc, int32_t nt, int32_t klo,
@@ -454,20 +658,11 @@ hipError_t launch_broadband_table_maps(const float *C, const float *w, int64_t l
         double *flags = reinterpret_cast<double *>(ws + L.flags);
         e = launch_antipodal_check(gamma, tau, nt, npix, nside, flags, s);
         if (e != hipSuccess) return e;
-        const dim3 pgrid((unsigned)((npix / 2 + 255) / 256), (unsigned)nchunks);
-        if (Gbb)
-            hipLaunchKernelGGL(bb_map_pair_kernel<true>, pgrid, dim3(256), 0, s, gamma, tau, nt, npix, nside,
-                               (const float2 *)T, g.G, g.m, g.h, g.bound, fc, per, (const double *)flags, part,
-                               (const double *)v, gpart);
-        else
-            hipLaunchKernelGGL(bb_map_pair_kernel<false>, pgrid, dim3(256), 0, s, gamma, tau, nt, npix, nside,
-                               (const float2 *)T, g.G, g.m, g.h, g.bound, fc, per, (const double *)flags, part,
-                               (const double *)nullptr, (double *)nullptr);
-        e = hipGetLastError();
+        e = Gbb ? launch_bb_map_pair<true>(gamma, tau, nt, npix, nside, T, g, fc, nchunks, per, flags, part, v, gpart, s)
+                : launch_bb_map_pair<false>(gamma, tau, nt, npix, nside, T, g, fc, nchunks, per, flags, part, nullptr,
+                                            nullptr, s);
         if (e != hipSuccess) return e;
-        e = launch_band_partial_finish(part, nchunks, npix, Xbb, s);
-        if (e != hipSuccess || !Gbb) return e;
-        return launch_band_partial_finish(gpart, nchunks, npix, Gbb, s);
+        return launch_band_partial_finish(part, nchunks, npix, Xbb, s, gpart, Gbb);
     }
     const dim3 grid((unsigned)((npix + 255) / 256), (unsigned)nchunks);
     if (Gbb)
@@ -478,9 +673,7 @@ hipError_t launch_broadband_table_maps(const float *C, const float *w, int64_t l
                            g.m, g.h, g.bound, fc, per, part, (const double *)nullptr, (double *)nullptr);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    e = launch_band_partial_finish(part, nchunks, npix, Xbb, s);
-    if (e != hipSuccess || !Gbb) return e;
-    return launch_band_partial_finish(gpart, nchunks, npix, Gbb, s);
+    return launch_band_partial_finish(part, nchunks, npix, Xbb, s, gpart, Gbb);
 }
 
 

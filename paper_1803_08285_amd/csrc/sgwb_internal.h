@@ -148,8 +148,10 @@ hipError_t launch_network_sum(const MapList &l, int64_t n, float *out, hipStream
 hipError_t launch_contract(const float *M, int32_t nf, int32_t npix, const int32_t *pix, int32_t nsel, float *out,
                            hipStream_t s);
 
-// fused broadband sums: out[p] = sum_{r < nrows} part[r][p] (float64, fixed order, rounded once)
-hipError_t launch_band_partial_finish(const double *part, int64_t nrows, int32_t npix, float *out, hipStream_t s);
+// fused broadband sums: out[p] = sum_{r < nrows} part[r][p] (float64, fixed order, rounded once);
+// with out1 also out1 from part1, of as many rows
+hipError_t launch_band_partial_finish(const double *part, int64_t nrows, int32_t npix, float *out, hipStream_t s,
+                                      const double *part1 = nullptr, float *out1 = nullptr);
 int64_t xm_band_rows(const MapArgs &a);    // rows of the dirty map's partial-sum array
 // broadband Fisher diagonal from its definition with the band sum moved into
 // the weights: Gbb[p] = sum_t v[t] gamma(t,p)^2, v[t] = sum_{c in [klo,khi)} H[c] w[t][c]

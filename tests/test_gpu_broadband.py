@@ -196,3 +196,31 @@ def test_tables_from_few_nodes_vs_oracle(sg, oracle_mod, nb, df, bl, tight):
                                with_scale=True)
     err = np.abs(Xbb.cpu().numpy().astype(np.float64) - Xo.sum(axis=0))
     assert np.all(err <= TOL * S.sum(axis=0) + 1e-300), float((err / S.sum(axis=0)).max())
+
+
+@pytest.mark.parametrize("nb,nt,nside", [
+    (40, 40, 32),   # tables of up to 253 intervals: one staged entry a thread; runs of one segment
+    (100, 5, 32),   # up to 509: two; chunks and runs without segments
+    (200, 67, 32),  # up to 1021: four; odd runs
+    (300, 33, 32),  # longer tables: read where they are
+    (40, 130, 16),  # few pixels: the waves of a workgroup share a chunk
+], ids=lambda v: str(v))
+def test_pair_pass_forms_vs_oracle(sg, oracle_mod, nb, nt, nside):
+    """Each form of the pixel-pair pass at the edges of its tables and runs:
+    within the route's 1e-6 of S_bb on sampled pixels, and Gbb bitwise the
+    band call's."""
+    g, t, C, w, H = _setup(sg, "AC", nside, nt, 9, nb, 1.0, 17 + nb)
+    fg = sg.FGrid(F0, 1.0)
+    print(f"nb {nb} nt {nt} nside {nside}", flush=True)
+    Xbb, Gbb = sg.broadband_maps(C, w, fg, 9, g, t, H, 0, nb, tau_bound=0.0, route="table")
+    _, _, _, Gref = sg.make_maps_band(C, w, fg, 9, g, t, H, 0, nb, want_x=False, narrowband=False)
+    torch.cuda.synchronize()
+    assert torch.equal(Gbb, Gref)
+    pix = np.random.default_rng(nb).choice(12 * nside * nside, 40, replace=False)
+    pix[:4] = (0, 6 * nside * nside - 1, 6 * nside * nside, 12 * nside * nside - 1)
+    cols, pp = np.tile(np.arange(nb), pix.size), np.repeat(pix, nb)
+    Xo, _, S = oracle_mod.maps_at(C.cpu().numpy(), w.cpu().numpy(), F0, 1.0, 9, g.cpu().numpy(), t.cpu().numpy(),
+                                  cols, pp)
+    ref, Sb = Xo.reshape(pix.size, nb).sum(axis=1), S.reshape(pix.size, nb).sum(axis=1)
+    err = np.abs(Xbb.cpu().numpy()[pix].astype(np.float64) - ref)
+    assert np.all(err <= TOL * Sb + 1e-300), float((err / Sb).max())
