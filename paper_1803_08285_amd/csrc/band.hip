@@ -263,43 +263,24 @@ hipError_t launch_band_partial_finish(const double *part, int64_t nrows, int32_t
     return hipGetLastError();
 }
 
-// v[t] = sum_{c in [klo,khi)} H[c] w[t][c]: one workgroup of 1024 threads per
-// segment, per-thread strides over the bins in four interleaved partial sums,
-// then a fixed tree (float64).
-constexpr int kWeightThreads = 1024;
-
-__global__ __launch_bounds__(kWeightThreads) void band_weight_kernel(const float *__restrict__ w, int64_t ldw,
-                                                                     const float *__restrict__ H, int32_t klo,
-                                                                     int32_t khi, double *__restrict__ v)
+// v[t] = sum_{c in [klo,khi)} H[c] w[t][c] (band_weight): one workgroup per
+// segment.
+__global__ __launch_bounds__(kWeightLanes) void band_weight_kernel(const float *__restrict__ w, int64_t ldw,
+                                                                   const float *__restrict__ H, int32_t klo,
+                                                                   int32_t khi, double *__restrict__ v)
 {
-    __shared__ double red[kWeightThreads];
-    const float *row = w + (int64_t)blockIdx.x * ldw;
-    // four independent partial sums per thread (their loads go out together),
-    // added in a fixed order
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    int32_t c = klo + threadIdx.x;
-    for (; c + 3 * kWeightThreads < khi; c += 4 * kWeightThreads) {
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            acc[u] = fma((double)H[c + u * kWeightThreads], (double)row[c + u * kWeightThreads], acc[u]);
-    }
-    for (int u = 0; c < khi; c += kWeightThreads, ++u) acc[u] = fma((double)H[c], (double)row[c], acc[u]);
-    red[threadIdx.x] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
-    __syncthreads();
-    for (int st = kWeightThreads / 2; st > 0; st >>= 1) {
-        if ((int)threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) v[blockIdx.x] = red[0];
+    __shared__ double red[kWeightLanes];
+    const double sum = band_weight<kWeightLanes>(w + (int64_t)blockIdx.x * ldw, H, klo, khi, red);
+    if (threadIdx.x == 0) v[blockIdx.x] = sum;
 }
 
-// Gbb[p] = sum_t v[t] gamma(t,p)^2 (float64, rounded once): band_gamma_chunks()
+// Gbb[p] = sum_t v[t] gamma(t,p)^2 (float64, rounded once): band_gamma_chunks(npix)
 // segment chunks per pixel block write partial sums, then a second kernel adds
 // the chunks in order.  A chunk's sum is that of kBandSlices runs of
 // consecutive segments, each summed in segment order, then added in order: the
 // four waves of a workgroup take one run each for the same 64 pixels (coalesced
 // rows), so that a small map still fills the chip.
-constexpr int kBandTChunks = 32;
+
 
 __global__ __launch_bounds__(256) void band_gamma_kernel(const float *__restrict__ gamma, int32_t npix, int32_t nt,
                                                          int32_t per, const double *__restrict__ v,
@@ -325,12 +306,22 @@ __global__ __launch_bounds__(256) void band_gamma_kernel(const float *__restrict
     part[(int64_t)blockIdx.y * npix + p] = acc;
 }
 
-int32_t band_gamma_chunks() { return kBandTChunks; }
+// Up to kBandTChunks chunks (what the scratch holds), halved while the pixel
+// pass that shares them (512 pixel pairs a workgroup) still has 1536 workgroups,
+// two full rounds of the chip: every chunk writes and reads back 16 bytes a
+// pixel.  Full-day query, nside 128, 4096 bins, with 32 / 16 / 8 chunks: 363 / 350 / 332 us.
+int32_t band_gamma_chunks(int32_t npix)
+{
+    const int64_t blocks = ((int64_t)npix / 2 + 511) / 512;
+    int32_t n = kBandTChunks;
+    while (n > 4 && blocks * n > 1536) n /= 2;
+    return n;
+}
 
 hipError_t launch_band_weights(const float *w, int64_t ldw, int32_t nt, const float *H, int32_t klo, int32_t khi,
                                double *v, hipStream_t s)
 {
-    hipLaunchKernelGGL(band_weight_kernel, dim3((unsigned)nt), dim3(kWeightThreads), 0, s, w, ldw, H, klo, khi, v);
+    hipLaunchKernelGGL(band_weight_kernel, dim3((unsigned)nt), dim3(kWeightLanes), 0, s, w, ldw, H, klo, khi, v);
     return hipGetLastError();
 }
 
@@ -343,10 +334,11 @@ hipError_t launch_band_gamma(const float *w, int64_t ldw, int32_t nt, const floa
                              const float *gamma, int32_t npix, double *scratch, float *Gbb, hipStream_t s)
 {
     double *v = scratch, *part = scratch + nt;
-    hipLaunchKernelGGL(band_weight_kernel, dim3((unsigned)nt), dim3(kWeightThreads), 0, s, w, ldw, H, klo, khi, v);
-    hipLaunchKernelGGL(band_gamma_kernel, dim3((unsigned)((npix + 63) / 64), kBandTChunks), dim3(256), 0, s, gamma,
-                       npix, nt, (nt + kBandTChunks - 1) / kBandTChunks, v, part);
-    return launch_band_partial_finish(part, kBandTChunks, npix, Gbb, s);
+    hipLaunchKernelGGL(band_weight_kernel, dim3((unsigned)nt), dim3(kWeightLanes), 0, s, w, ldw, H, klo, khi, v);
+    const int32_t chunks = band_gamma_chunks(npix);
+    hipLaunchKernelGGL(band_gamma_kernel, dim3((unsigned)((npix + 63) / 64), (unsigned)chunks), dim3(256), 0, s, gamma,
+                       npix, nt, (nt + chunks - 1) / chunks, v, part);
+    return launch_band_partial_finish(part, chunks, npix, Gbb, s);
 }
 
 }  // namespace sgwb

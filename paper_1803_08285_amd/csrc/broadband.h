@@ -20,11 +20,12 @@ size_t bb_workspace_bytes(int32_t nt, int32_t npix, int32_t nb, const BbGrid &g)
 
 // The layout of launch_band_gamma's work (band.hip), for a pass that computes
 // Gbb beside Xbb with the same bits: its scratch holds v[nt] (the band-summed
-// weights, from launch_band_weights) and then band_gamma_chunks() rows of
+// weights, from launch_band_weights) and then band_gamma_chunks(npix) rows of
 // per-pixel partial sums, row r over segments [r per, (r + 1) per),
-// per = ceil(nt / band_gamma_chunks()), as the sum of its kBandSlices runs
+// per = ceil(nt / band_gamma_chunks(npix)), as the sum of its kBandSlices runs
 // (band_slice), each summed in segment order.
-int32_t band_gamma_chunks();
+constexpr int kBandTChunks = 32;  // chunks at most
+int32_t band_gamma_chunks(int32_t npix);
 constexpr int kBandSlices = 4;
 struct BandSlice {
     int32_t begin, end;
@@ -39,6 +40,46 @@ __device__ inline BandSlice band_slice(int32_t chunk, int sl, int32_t per, int32
 }
 hipError_t launch_band_weights(const float *w, int64_t ldw, int32_t nt, const float *H, int32_t klo, int32_t khi,
                                double *v, hipStream_t s);
+// sum_{c in [klo,khi)} H[c] row[c] in float64, in thread 0 of a workgroup of
+// THREADS: kWeightLanes lanes stride the bins with four interleaved partial
+// sums each (their loads go out together), then a fixed tree over the lanes; a
+// smaller workgroup's threads take kWeightLanes / THREADS lanes each, so the
+// order, and with it the bits, are the same.  red: THREADS words of LDS.
+constexpr int kWeightLanes = 1024;
+template <int THREADS>
+__device__ __forceinline__ double band_weight(const float *__restrict__ row, const float *__restrict__ H, int32_t klo,
+                                              int32_t khi, double *red)
+{
+    constexpr int kPer = kWeightLanes / THREADS;
+    double lane[kPer];
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        double acc[4] = {0.0, 0.0, 0.0, 0.0};
+        int32_t c = klo + (int32_t)threadIdx.x + i * THREADS;
+        for (; c + 3 * kWeightLanes < khi; c += 4 * kWeightLanes) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                acc[u] = fma((double)H[c + u * kWeightLanes], (double)row[c + u * kWeightLanes], acc[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < 3; ++u, c += kWeightLanes)
+            if (c < khi) acc[u] = fma((double)H[c], (double)row[c], acc[u]);
+        lane[i] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+    }
+    // the tree's first levels, within a thread
+#pragma unroll
+    for (int n = kPer / 2; n > 0; n >>= 1)
+#pragma unroll
+        for (int i = 0; i < n; ++i) lane[i] += lane[i + n];
+    red[threadIdx.x] = lane[0];
+    __syncthreads();
+    for (int st = THREADS / 2; st > 0; st >>= 1) {
+        if ((int)threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
+        __syncthreads();
+    }
+    return red[0];
+}
+
 // Xbb (and, with Gbb, Gbb) over columns [klo, khi) of C and w (absolute bins
 // k0 + klo ..); H is needed with Gbb
 // nside > 0: antipodal seeds (spot-checked), one thread per pixel pair

@@ -17,6 +17,8 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "broadband.h"
 
 namespace sgwb {
@@ -57,7 +59,7 @@ struct BbLayout {
 };
 static BbLayout bb_layout(int32_t nt, int32_t npix, const BbGrid &g)
 {
-    const size_t ntb = (size_t)band_gamma_chunks();  // the map pass's segment chunks
+    const size_t ntb = kBandTChunks;
     BbLayout L;
     L.t = 0;
     L.part = L.t + up256_((size_t)nt * g.G * sizeof(float2));
@@ -131,35 +133,49 @@ __global__ __launch_bounds__(kBbNodes) void bb_table_kernel(const float *__restr
 constexpr int kBbChebMax = 512;  // N at most (the LDS arrays; larger N take the direct kernel)
 constexpr int kBbTabThreads = 256;
 constexpr int kBbStage = 512;  // bins per LDS stage, at most
+constexpr int32_t kBbPrepNodes = 1024;  // grid nodes of a narrow band that one workgroup sums directly, at most
 
-// The node count for a grid, 0 where the direct kernel is used: no N of at most
-// kBbChebMax, or a band of so few bins that its direct sums cost no more (the
-// bins themselves then number about N).
-static int32_t bb_cheb_nodes(int32_t nb, const BbGrid &g)
+// The node count for a grid, 0 where the sums are taken at every grid node: no
+// N of at most kBbChebMax, or the longest chain of recurrence steps is no
+// shorter (the chains bound both forms while the segments do not fill the
+// chip): nb bins over 256 / N threads a node and then N terms for every 256th
+// grid node, one workgroup a segment (about 2048 run together), against nb
+// bins, one wave per 64 nodes and segment (about 8192 run together).
+static int32_t bb_cheb_nodes(int32_t nb, int32_t nt, const BbGrid &g)
 {
     const double half = nb > 1 ? 0.5 * kBbPhaseStep * (g.m + 1) : 0.0;  // Z / 2
     double term = 4.0;  // 4 (Z / 2)^N / N!
     for (int32_t n = 1; n <= kBbChebMax; ++n) {
         term *= half / n;
-        if (term <= 1e-13 && n > half) return nb >= 2 * n ? n : 0;
+        if (!(term <= 1e-13 && n > half)) continue;
+        const double R = n < kBbTabThreads ? kBbTabThreads / n : (double)kBbTabThreads / n;
+        const double nodes = nb / R + (double)n * ((g.G + kBbTabThreads - 1) / kBbTabThreads);
+        const double every = (double)nb * std::max(1.0, (double)nt * ((g.G + kBbNodes - 1) / kBbNodes) / 8192.0);
+        return nodes * std::max(1.0, nt / 2048.0) < every ? n : 0;
     }
     return 0;
 }
 
-// T[t][j] as bb_table_kernel defines it, through Chebyshev nodes.  One
-// workgroup a segment.  Node sums: thread (n, r) of R = 256 / N takes node
-// x_n = cos(pi (n + 1/2) / N) and the bins k = r mod R, by Horner's rule in
-// omega^R from the top bin down (|omega| = 1), the band staged through LDS as
-// y = w C in float64, the next stage's loads in flight; the R partial sums are
-// turned by omega^(r - kc) and added in order.  Then the series' coefficients
-// (cosine sums of the node values) and Clenshaw's recurrence at every grid
-// node, one node a thread.  Bound by the float64 FMAs of the node sums (4 per
-// bin and node) and the read of the band.  Full day, 4096 bins, AB: 46 us (the
-// direct sums over all 271 nodes 267 us); AC, 1531 bins: 26 against 101 us.
-__global__ __launch_bounds__(kBbTabThreads) void bb_cheb_table_kernel(const float *__restrict__ C,
-                                                                      const float *__restrict__ w, int64_t ldc,
-                                                                      int32_t klo, int32_t nb, int32_t G, int32_t m,
-                                                                      double dfh, int32_t N, float2 *__restrict__ T)
+// Everything a query needs before its map pass, in one launch.  Workgroup t <
+// nt: T[t][j] as bb_table_kernel defines it, and, with v, segment t's band
+// weight.  The last kSymParts workgroups, with flags: the antipodal spot check.
+//
+// The tables through Chebyshev nodes (N > 0).  Node sums: thread (n, r) of R =
+// 256 / N takes node x_n = cos(pi (n + 1/2) / N) and the bins k = r mod R, by
+// Horner's rule in omega^R from the top bin down (|omega| = 1), the band staged
+// through LDS as y = w C in float64, the next stage's loads in flight; the R
+// partial sums are turned by omega^(r - kc) and added in order.  Then the
+// series' coefficients (cosine sums of the node values) and Clenshaw's
+// recurrence at every grid node, one node a thread.  Bound by the float64 FMAs
+// of the node sums (4 per bin and node) and the read of the band.  Full day,
+// 4096 bins, AB: 46 us (the direct sums over all 271 nodes 267 us); AC, 1531
+// bins: 26 against 101 us.  N = 0: a band of at most kBbStage bins, staged
+// once, Horner's rule at every grid node.
+__global__ __launch_bounds__(kBbTabThreads) void bb_prep_kernel(
+    const float *__restrict__ C, const float *__restrict__ w, int64_t ldc, int32_t klo, int32_t nb, int32_t G,
+    int32_t m, double dfh, int32_t N, float2 *__restrict__ T, const float *__restrict__ H, double *__restrict__ v,
+    const float *__restrict__ gamma, const double *__restrict__ tau, int32_t nt, int64_t npix, int64_t nside,
+    double *__restrict__ flags)
 {
     __shared__ double2 stage[kBbStage];
     extern __shared__ double dyn[];
@@ -168,10 +184,50 @@ __global__ __launch_bounds__(kBbTabThreads) void bb_cheb_table_kernel(const floa
     double2 *const coef = reinterpret_cast<double2 *>(dyn + 6 * N);    // series coefficients
     const int tid = threadIdx.x;
     const int32_t t = blockIdx.x;
-    for (int32_t i = tid; i < 4 * N; i += kBbTabThreads) ct[i] = cospi(0.5 * i / N);
-    __syncthreads();
+    if (t >= nt) {
+        const int part = t - nt;
+        const int bad = __syncthreads_or(antipodal_mismatch(gamma, tau, nt, npix, nside, part, kSymParts));
+        if (tid == 0) flags[part] = bad ? 1.0 : 0.0;
+        return;
+    }
+    if (v) {
+        const double sum = band_weight<kBbTabThreads>(w + (int64_t)t * ldc, H, klo, klo + nb,
+                                                      reinterpret_cast<double *>(stage));
+        if (tid == 0) v[t] = sum;
+    }
     const int64_t row = (int64_t)t * ldc + klo;
     const double kc = 0.5 * (nb - 1);
+    auto bin = [&](int32_t k) {
+        if (k >= nb) return make_double2(0.0, 0.0);
+        const double wv = (double)w[row + k];
+        return make_double2(wv * (double)C[2 * (row + k)], wv * (double)C[2 * (row + k) + 1]);
+    };
+    if (N == 0) {
+        __syncthreads();  // the weight's sums are read
+        stage[tid] = bin(tid);
+        stage[tid + kBbTabThreads] = bin(tid + kBbTabThreads);
+        __syncthreads();
+        for (int32_t j = tid; j < G; j += kBbTabThreads) {
+            const double at = dfh * (double)(j - m - 1);  // df tau_j
+            double turns = at - rint(at), back = kc * at;
+            back -= rint(back);
+            double os, oc, bs, bc;
+            sincospi(2.0 * turns, &os, &oc);
+            sincospi(-2.0 * back, &bs, &bc);
+            double ar = 0.0, ai = 0.0;
+            for (int32_t k = nb - 1; k >= 0; --k) {
+                const double2 y = stage[k];
+                const double nr = fma(ar, oc, fma(-ai, os, y.x));
+                const double ni = fma(ar, os, fma(ai, oc, y.y));
+                ar = nr;
+                ai = ni;
+            }
+            T[(int64_t)t * G + j] = make_float2((float)(ar * bc - ai * bs), (float)(ar * bs + ai * bc));
+        }
+        return;
+    }
+    for (int32_t i = tid; i < 4 * N; i += kBbTabThreads) ct[i] = cospi(0.5 * i / N);
+    __syncthreads();
     for (int32_t n0 = 0; n0 < N; n0 += kBbTabThreads) {  // one pass unless N > 256
         const int32_t nn = min(N - n0, kBbTabThreads), R = kBbTabThreads / nn;
         const int32_t r = tid / nn, n = tid - r * nn;
@@ -182,11 +238,6 @@ __global__ __launch_bounds__(kBbTabThreads) void bb_cheb_table_kernel(const floa
         double os, oc;
         sincospi(2.0 * step, &os, &oc);
         const int32_t per = kBbStage / R, sb = per * R;  // bins per stage: per for every residue r
-        auto bin = [&](int32_t k) {
-            if (k >= nb) return make_double2(0.0, 0.0);
-            const double wv = (double)w[row + k];
-            return make_double2(wv * (double)C[2 * (row + k)], wv * (double)C[2 * (row + k) + 1]);
-        };
         int32_t kb = (nb - 1) / sb * sb;
         double2 y0 = bin(kb + tid), y1 = bin(kb + tid + kBbTabThreads);
         double ar = 0.0, ai = 0.0;
@@ -634,30 +685,32 @@ hipError_t launch_broadband_table_maps(const float *C, const float *w, int64_t l
     const BbLayout L = bb_layout(nt, npix, g);
     char *ws = reinterpret_cast<char *>(work);
     double *v = reinterpret_cast<double *>(ws + L.gam), *gpart = v + nt;
-    const int32_t nchunks = band_gamma_chunks(), per = (nt + nchunks - 1) / nchunks;
+    const int32_t nchunks = band_gamma_chunks(npix), per = (nt + nchunks - 1) / nchunks;
     if (!Xbb) {  // Gbb alone: the weight-side kernels by themselves
         return launch_band_gamma(w, ldc, nt, H, klo, khi, gamma, npix, v, Gbb, s);
     }
     float2 *T = reinterpret_cast<float2 *>(ws + L.t);
     double *part = reinterpret_cast<double *>(ws + L.part);
-    if (const int32_t N = bb_cheb_nodes(nb, g))
-        hipLaunchKernelGGL(bb_cheb_table_kernel, dim3((unsigned)nt), dim3(kBbTabThreads), 8 * N * sizeof(double), s, C,
-                           w, ldc, klo, nb, g.G, g.m, df * g.h, N, T);
-    else
+    double *flags = nside > 0 ? reinterpret_cast<double *>(ws + L.flags) : nullptr;
+    const int32_t N = bb_cheb_nodes(nb, nt, g);
+    hipError_t e;
+    if (N > 0 || (nb <= kBbStage && g.G <= kBbPrepNodes)) {
+        hipLaunchKernelGGL(bb_prep_kernel, dim3((unsigned)(nt + (flags ? kSymParts : 0))), dim3(kBbTabThreads),
+                           8 * N * sizeof(double), s, C, w, ldc, klo, nb, g.G, g.m, df * g.h, N, T, H,
+                           Gbb ? v : (double *)nullptr, gamma, tau, nt, (int64_t)npix, nside, flags);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    } else {  // many nodes: one wave per segment and 64 of them
         hipLaunchKernelGGL(bb_table_kernel, dim3((unsigned)nt, (unsigned)((g.G + kBbNodes - 1) / kBbNodes)),
                            dim3(kBbNodes), 0, s, C, w, ldc, klo, nb, g.G, g.m, df * g.h, T);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    if (Gbb) {
-        e = launch_band_weights(w, ldc, nt, H, klo, khi, v, s);
+        e = hipGetLastError();
+        if (e == hipSuccess && Gbb) e = launch_band_weights(w, ldc, nt, H, klo, khi, v, s);
+        if (e == hipSuccess && flags) e = launch_antipodal_check(gamma, tau, nt, npix, nside, flags, s);
         if (e != hipSuccess) return e;
     }
     // the band's centre: absolute bin k0 + klo + (nb - 1) / 2
     const double fc = f0 + ((double)(k0 + klo) + 0.5 * (nb - 1)) * df;
     if (nside > 0) {  // antipodal seeds: each thread a pixel pair
-        double *flags = reinterpret_cast<double *>(ws + L.flags);
-        e = launch_antipodal_check(gamma, tau, nt, npix, nside, flags, s);
-        if (e != hipSuccess) return e;
         e = Gbb ? launch_bb_map_pair<true>(gamma, tau, nt, npix, nside, T, g, fc, nchunks, per, flags, part, v, gpart, s)
                 : launch_bb_map_pair<false>(gamma, tau, nt, npix, nside, T, g, fc, nchunks, per, flags, part, nullptr,
                                             nullptr, s);

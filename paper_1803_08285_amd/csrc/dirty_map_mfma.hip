@@ -129,31 +129,24 @@ __global__ __launch_bounds__(256) void xm_tmax_kernel(const double *__restrict__
     if (threadIdx.x == 0) part[blockIdx.x] = red[0];
 }
 
+constexpr int kSymThreads = 1024;
+
 // Spot check of the antipodal symmetry that the pairing relies on: for the
 // first, middle and last segment and every northern pixel p,
 // gamma(t, a(p)) == gamma(t, p) and tau(t, a(p)) == -tau(t, p) exactly (the
 // geometry kernel writes them so; a NaN fails too).  One flag per workgroup.
-__global__ __launch_bounds__(256) void xm_symcheck_kernel(const float *__restrict__ gamma,
+__global__ __launch_bounds__(kSymThreads) void xm_symcheck_kernel(const float *__restrict__ gamma,
                                                           const double *__restrict__ tau, int32_t nt, int64_t npix,
                                                           int64_t nside, double *__restrict__ flags)
 {
-    const int64_t npairs = npix / 2, n = 3 * npairs;
-    int bad = 0;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
-        const int64_t r = i / npairs, p = i - r * npairs;
-        const int64_t t = r == 0 ? 0 : r == 1 ? nt / 2 : nt - 1;
-        const int64_t pb = antipode_north(ring_of_north(p, nside), npix);
-        const int64_t o = t * npix;
-        if (!(gamma[o + pb] == gamma[o + p]) || !(tau[o + pb] == -tau[o + p])) bad = 1;
-    }
-    bad = __syncthreads_or(bad);
+    const int bad = __syncthreads_or(antipodal_mismatch(gamma, tau, nt, npix, nside, blockIdx.x, kSymParts));
     if (threadIdx.x == 0) flags[blockIdx.x] = bad ? 1.0 : 0.0;
 }
 
 hipError_t launch_antipodal_check(const float *gamma, const double *tau, int32_t nt, int64_t npix, int64_t nside,
                                   double *flags, hipStream_t s)
 {
-    hipLaunchKernelGGL(xm_symcheck_kernel, dim3(kSymParts), dim3(256), 0, s, gamma, tau, nt, npix, nside, flags);
+    hipLaunchKernelGGL(xm_symcheck_kernel, dim3(kSymParts), dim3(kSymThreads), 0, s, gamma, tau, nt, npix, nside, flags);
     return hipGetLastError();
 }
 
@@ -854,7 +847,7 @@ static hipError_t launch_xm_seed_prep(const XmJob &j, hipStream_t s)
     const int parts = (int)std::min<int64_t>(kTmaxParts, (nt + 255) / 256);
     double *part = j.tmax + 2, *flags = j.tmax + 2 + kTmaxParts;
     hipLaunchKernelGGL(xm_tmax_kernel, dim3((unsigned)parts), dim3(256), 0, s, j.tau, nt, part);
-    hipLaunchKernelGGL(xm_symcheck_kernel, dim3(kSymParts), dim3(256), 0, s, j.gamma, j.tau, j.x.a.nt,
+    hipLaunchKernelGGL(xm_symcheck_kernel, dim3(kSymParts), dim3(kSymThreads), 0, s, j.gamma, j.tau, j.x.a.nt,
                        (int64_t)j.x.a.npix, j.x.a.nside, flags);
     hipLaunchKernelGGL(xm_tmax_final_kernel, dim3(1), dim3(256), 0, s, part, parts, flags, j.x.eta_scale,
                        j.x.a.tau_limit, j.tmax);

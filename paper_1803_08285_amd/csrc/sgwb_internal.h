@@ -42,7 +42,7 @@ __host__ __device__ inline RingPos ring_of_north(int64_t p, int64_t nside)
         r.len = 4 * i;
     } else {
         const int64_t q = p - ncap;
-        r.ring = q / (4 * nside) + nside;
+        r.ring = (q >> (__builtin_ctzll((unsigned long long)nside) + 2)) + nside;  // q / (4 nside): a power of two
         r.start = ncap + (r.ring - nside) * 4 * nside;
         r.len = 4 * nside;
     }
@@ -197,6 +197,31 @@ constexpr int kXFormRejected = -1;
 // segment, every northern pixel): flags[kSymParts] of 0.0 (pass) or 1.0, one per
 // workgroup, no atomics.
 constexpr int kSymParts = 64;
+// The check's share of one workgroup, part of nparts: true where a thread's
+// northern pixels (a fixed stride) break the symmetry in one of the three
+// segments (a NaN breaks it too).  The three segments' twelve loads go out
+// together.
+__device__ __forceinline__ bool antipodal_mismatch(const float *__restrict__ gamma, const double *__restrict__ tau,
+                                                   int32_t nt, int64_t npix, int64_t nside, int part, int nparts)
+{
+    const int64_t rows[3] = {0, (nt / 2) * npix, (nt - 1) * npix};
+    bool bad = false;
+    for (int64_t p = (int64_t)part * blockDim.x + threadIdx.x; p < npix / 2; p += (int64_t)nparts * blockDim.x) {
+        const int64_t pb = antipode_north(ring_of_north(p, nside), npix);
+        float g[3], gb[3];
+        double t[3], tb[3];
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+            g[r] = gamma[rows[r] + p];
+            gb[r] = gamma[rows[r] + pb];
+            t[r] = tau[rows[r] + p];
+            tb[r] = tau[rows[r] + pb];
+        }
+#pragma unroll
+        for (int r = 0; r < 3; ++r) bad |= !(gb[r] == g[r]) || !(tb[r] == -t[r]);
+    }
+    return bad;
+}
 hipError_t launch_antipodal_check(const float *gamma, const double *tau, int32_t nt, int64_t npix, int64_t nside,
                                   double *flags, hipStream_t s);
 bool xm_eligible(const MapArgs &a);
