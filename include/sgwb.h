@@ -266,8 +266,11 @@ int sgwb_fisher_overlap(const float *v, const float *u, const float *w, int64_t 
  * 24 kHz limit), so tau_p - tau_q is exact and G exactly symmetric; float32
  * accumulation over t, then over the ranks.  Delays are clamped to
  * |tau| <= 2 R_earth / c.
- * Workspace: at least sgwb_fisher_full_workspace_size() bytes (0 for
- * arguments out of range), 256-byte aligned, owned by the caller.
+ * Workspace: sgwb_fisher_full_workspace_size() bytes (0 for arguments out of
+ * range), 256-byte aligned, owned by the caller.  Up to 64 MiB of it holds partial
+ * sums of segment ranges, which fill the chip for small npix: a workspace short
+ * of that part is accepted and takes fewer ranges (the float32 sums then run in
+ * another order).
  * Errors: SGWB_EINVAL (null pointer, nt/nf/npix < 1, rank out of range, band
  * out of range or reaching above 24 kHz, bad grid, unknown flag bits or the
  * antipodal flag with a non-HEALPix npix, misaligned pointer, more than

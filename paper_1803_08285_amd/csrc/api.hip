@@ -440,11 +440,12 @@ int sgwb_fisher_full(const float *a, const float *b, int32_t rank, const float *
     if (ntile * (ntile + 1) / 2 > 0x7fffffff) return set_error(SGWB_EINVAL, "fisher_full: npix too large");
     if (!workspace || (uintptr_t)workspace % 256)
         return set_error(SGWB_EINVAL, "fisher_full: workspace null or not 256-byte aligned");
-    const size_t need = sgwb_fisher_full_workspace_size(fg, k0, chi, nt, npix);
+    // the size query adds room for partial sums that a call can do without
+    const size_t need = fisher_full_workspace_least(fg->f0_hz + (double)(k0 + chi - 1) * fg->df_hz, chi, nt, npix);
     if (workspace_bytes < need)
         return set_error(SGWB_ENOMEM, "fisher_full: workspace of %zu bytes needed, %zu given", need, workspace_bytes);
     return check_hip(launch_fisher_full(a, b, rank, H, nf, clo, chi, fg->f0_hz, fg->df_hz, k0, gamma, tau, nt, npix,
-                                        nside, G, workspace, stream),
+                                        nside, G, workspace, workspace_bytes, stream),
                      "full Fisher launch");
 }
 
@@ -498,12 +499,13 @@ int sgwb_fisher_full_general(const float *w, int64_t ldw, const float *H, int32_
         return set_error(SGWB_EINVAL, "fisher_full_general: misaligned pointer");
     if (!workspace || (uintptr_t)workspace % 256)
         return set_error(SGWB_EINVAL, "fisher_full_general: workspace null or not 256-byte aligned");
-    const size_t need = sgwb_fisher_full_general_workspace_size(fg, k0, clo, chi, nt, npix, flags);
+    // the size query adds room for partial sums that a call can do without
+    const size_t need = fisher_full_general_workspace_least(fg->f0_hz, fg->df_hz, k0, clo, chi, nt, npix, nside);
     if (workspace_bytes < need)
         return set_error(SGWB_ENOMEM, "fisher_full_general: workspace of %zu bytes needed, %zu given", need,
                          workspace_bytes);
     return check_hip(launch_fisher_full_general(w, ldw, H, clo, chi, fg->f0_hz, fg->df_hz, k0, gamma, tau, nt, npix,
-                                                nside, G, workspace, stream),
+                                                nside, G, workspace, workspace_bytes, stream),
                      "full Fisher (general weights) launch");
 }
 

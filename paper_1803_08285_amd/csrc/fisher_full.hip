@@ -87,6 +87,56 @@ __device__ __forceinline__ int32_t table_intervals(const unsigned long long *__r
     return min(J, (int32_t)ceil(2.0 * m / delta) + 2);
 }
 
+// Segment ranges of the matrix pass.  A workgroup of the streaming kernel owns
+// kStTiles tiles and one range of `per` segments, one workgroup a compute unit
+// at a time (LDS), so a matrix of few tiles leaves units idle: with n > 1 ranges
+// each writes its tiles' partial sums, which fisher_full_reduce_kernel adds in
+// range order.  The form without ranges stays where the tiles fill the chip's
+// rounds to within 10 % (there the partial sums would be extra traffic).  Every
+// kernel that computes the matrix sums range by range, so all give the same
+// bits.  Full day, ranges against none: nside 8, 2000 bins, general weights 270
+// against 1352 us, separable 290 against 1310; nside 16, 15 360 bins 1550
+// against 2184 and 946 against 1391; nside 32 (12 us of 12 140) keeps one range.
+constexpr int kStTiles = 4;
+constexpr int64_t kTileEntries = (int64_t)kFt * kFt;
+constexpr int64_t kRangeBytesMax = 64ll << 20;  // partial sums at most
+struct SegmentRanges {
+    int32_t n = 1, per = 1;
+    size_t bytes(int64_t ntiles) const { return n > 1 ? (size_t)(n * ntiles * kTileEntries) * sizeof(float) : 0; }
+};
+
+static int64_t fisher_tiles(int32_t npix, bool antipodal)
+{
+    const int64_t nrow = antipodal ? npix / 2 : npix, nT = (nrow + kFt - 1) / kFt;
+    return (antipodal ? 2 : 1) * (nT * (nT + 1) / 2);
+}
+
+// The ranges that minimise (rounds of 256 workgroups) x (segments a range and
+// kRangeCost more for a workgroup's start and its partial sums), with partial
+// sums of at most max_bytes.
+static SegmentRanges segment_ranges(int64_t ntiles, int32_t nt, size_t max_bytes)
+{
+    constexpr int64_t kUnits = 256, kRangeCost = 8;
+    const int64_t wgs = (ntiles + kStTiles - 1) / kStTiles;
+    auto cost = [&](int64_t n) {
+        return ((wgs * n + kUnits - 1) / kUnits) * ((nt + n - 1) / n + kRangeCost);
+    };
+    SegmentRanges best;
+    best.per = nt;
+    int64_t least = cost(1) * 9 / 10;
+    for (int32_t n = 2; n <= std::min(nt / 16, 64); ++n) {
+        SegmentRanges r;
+        r.per = (nt + n - 1) / n;
+        r.n = (nt + r.per - 1) / r.per;  // no empty range
+        if (r.n != n || r.bytes(ntiles) > max_bytes) continue;
+        if (cost(n) < least) {
+            least = cost(n);
+            best = r;
+        }
+    }
+    return best;
+}
+
 constexpr int kWaitVm0 = 0x0F70;  // s_waitcnt vmcnt(0), expcnt and lgkmcnt left at their maxima
 
 // Pass 1, entry j <= J and one chunk of kTabChunk bins: the chunk's share of
@@ -566,11 +616,43 @@ __device__ __forceinline__ bool seeds_rejected(const double *__restrict__ flags)
     return bad;
 }
 
+// G from the ranges' partial sums [range][tile][64][64], range order fixed; one
+// workgroup a tile.
+__global__ __launch_bounds__(256) void fisher_full_reduce_kernel(const float *__restrict__ sums, int32_t nranges,
+                                                                 int64_t ntiles, int32_t npix, int64_t nside,
+                                                                 int32_t accumulate, float *__restrict__ G)
+{
+    const int64_t nrow = nside > 0 ? npix / 2 : npix;
+    const int64_t nT = (nrow + kFt - 1) / kFt;
+    int64_t tr, tc;
+    bool ns;
+    fisher_tile(blockIdx.x, nT, nside > 0, tr, tc, ns);
+    for (int32_t e = threadIdx.x; e < kTileEntries; e += 256) {
+        const int64_t p = tr * kFt + e / kFt, q = tc * kFt + e % kFt;
+        if (p >= nrow || q >= nrow || (tr == tc && p > q)) continue;
+        float v = 0.0f;
+        for (int32_t r = 0; r < nranges; ++r) v += sums[(r * ntiles + blockIdx.x) * kTileEntries + e];
+        store_value(G, npix, nside, ns, p, q, v, accumulate);
+    }
+}
+
 __device__ __forceinline__ uint32_t abs_diff(uint32_t x, uint32_t y)
 {
     uint32_t d;
     asm("v_sad_u32 %0, %1, %2, 0" : "=v"(d) : "v"(x), "v"(y));
     return d;
+}
+
+// The sums of a range added to those of the earlier ones.
+__device__ __forceinline__ void end_range(float (&acc)[4][4], float (&tot)[4][4])
+{
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) {
+            tot[i][jj] += acc[i][jj];
+            acc[i][jj] = 0.0f;
+        }
 }
 
 // G tile (r, c) of the upper triangle; 256 threads, 4 x 4 entries each.  Per
@@ -584,7 +666,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 4))) voi
                                                           int64_t nside, const double *__restrict__ flags,
                                                           const float4 *__restrict__ cub, int32_t J,
                                                           const unsigned long long *__restrict__ bound,
-                                                          double delta, int32_t fb, int32_t accumulate,
+                                                          double delta, int32_t fb, int32_t per, int32_t accumulate,
                                                           float *__restrict__ G)
 {
     const int64_t seg_stride = a ? 0 : table_intervals(bound, delta, J);
@@ -596,7 +678,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 4))) voi
     bool ns;
     fisher_tile(blockIdx.x, nT, nside > 0, tr, tc, ns);
     const int ty = threadIdx.x / 16, tx = threadIdx.x % 16;
-    float acc[4][4] = {};
+    float acc[4][4] = {}, tot[4][4] = {};  // the current range's sums, the earlier ranges'
+    int32_t left = per;
     const char *cb = reinterpret_cast<const char *>(cub);
     const int ntu = seeds_rejected(flags) ? 0 : nt;
     for (int t0 = 0; t0 < ntu; t0 += kFtSeg) {
@@ -644,13 +727,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 4))) voi
                     const float W = fmaf(fmaf(fmaf(cc.w, x[i][jj], cc.z), x[i][jj], cc.y), x[i][jj], cc.x);
                     acc[i][jj] = fmaf(gp[i] * gq[jj], W, acc[i][jj]);
                 }
+            if (--left == 0) {
+                left = per;
+                end_range(acc, tot);
+            }
         }
     }
+    end_range(acc, tot);
     if (ntu != nt) {  // rejected seeds: the matrix is NaN
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
-            for (int jj = 0; jj < 4; ++jj) acc[i][jj] = __builtin_nanf("");
+            for (int jj = 0; jj < 4; ++jj) tot[i][jj] = __builtin_nanf("");
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i)
@@ -659,7 +747,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 4))) voi
             const int64_t p = tr * kFt + ty * 4 + i, q = tc * kFt + tx * 4 + jj;
             // a diagonal tile writes its upper triangle and the mirror of it
             if (p < nrow && q < nrow && (tr != tc || p <= q))
-                store_value(G, npix, nside, ns, p, q, acc[i][jj], accumulate);
+                store_value(G, npix, nside, ns, p, q, tot[i][jj], accumulate);
         }
 }
 
@@ -676,7 +764,7 @@ __global__ __launch_bounds__(512) void fisher_full_lds_kernel(const float *__res
                                                                int32_t npix, int64_t nside,
                                                                const double *__restrict__ flags,
                                                                const float4 *__restrict__ cub,
-                                                               int32_t J, int32_t fb, int64_t ntiles,
+                                                               int32_t J, int32_t fb, int64_t ntiles, int32_t per,
                                                                int32_t accumulate, float *__restrict__ G)
 {
     __shared__ float4 tab[kLdsTable];
@@ -706,7 +794,8 @@ __global__ __launch_bounds__(512) void fisher_full_lds_kernel(const float *__res
             pi[i] = (int32_t)(pv[i] ? p : last);
             qi[i] = (int32_t)(qv[i] ? q : last);
         }
-        float acc[4][4] = {};
+        float acc[4][4] = {}, tot[4][4] = {};  // the current range's sums, the earlier ranges'
+        int32_t left = per;
         float gp[4], gq[4];
         uint32_t up[4], uq[4];
 #pragma unroll
@@ -755,12 +844,17 @@ __global__ __launch_bounds__(512) void fisher_full_lds_kernel(const float *__res
                 gq[i] = qv[i] ? gqn[i] : 0.0f;
                 uq[i] = ucol(uqn[i]);
             }
+            if (--left == 0) {
+                left = per;
+                end_range(acc, tot);
+            }
         }
+        end_range(acc, tot);
         if (ntu != nt) {  // rejected seeds: the matrix is NaN
 #pragma unroll
             for (int i = 0; i < 4; ++i)
 #pragma unroll
-                for (int jj = 0; jj < 4; ++jj) acc[i][jj] = __builtin_nanf("");
+                for (int jj = 0; jj < 4; ++jj) tot[i][jj] = __builtin_nanf("");
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i)
@@ -768,7 +862,7 @@ __global__ __launch_bounds__(512) void fisher_full_lds_kernel(const float *__res
             for (int jj = 0; jj < 4; ++jj) {
                 const int64_t p = tr * kFt + ty * 4 + i, q = tc * kFt + tx * 4 + jj;
                 if (pv[i] && q < nrow && (tr != tc || p <= q))
-                    store_value(G, npix, nside, ns, p, q, acc[i][jj], accumulate);
+                    store_value(G, npix, nside, ns, p, q, tot[i][jj], accumulate);
             }
     }
 }
@@ -784,7 +878,6 @@ __global__ __launch_bounds__(512) void fisher_full_lds_kernel(const float *__res
 // first Jv intervals of each table are copied: those the seeds' delay bound
 // can reach.  Same term arithmetic as the other forms, so the same bits in the
 // same segment order.
-constexpr int kStTiles = 4;
 constexpr int kStWaves = 2 * kStTiles;  // 512 threads
 
 // n float4 from src into LDS at dst, 16 bytes a lane straight from global
@@ -839,6 +932,7 @@ __global__ __launch_bounds__(512) void fisher_full_stream_kernel(const float *__
                                                                  const float4 *__restrict__ cub, int32_t J,
                                                                  const unsigned long long *__restrict__ bound,
                                                                  double delta, int32_t fb, int64_t ntiles,
+                                                                 int32_t per, float *__restrict__ sums,
                                                                  int32_t accumulate, float *__restrict__ G)
 {
     constexpr int32_t kHalf = kLdsTable / 2;
@@ -865,13 +959,15 @@ __global__ __launch_bounds__(512) void fisher_full_stream_kernel(const float *__
     for (int j = 0; j < 4; ++j) qo[j] = (uint32_t)min(q0 + j, last_row) * 4u;
     const int32_t Jv = table_intervals(bound, delta, J);
     const bool rejected = seeds_rejected(flags);
-    const int32_t ntu = rejected ? 0 : nt;
+    // this workgroup's segments [tb, te); te = tb (none) for rejected seeds
+    const int32_t tb = (int32_t)blockIdx.y * per, te = rejected ? tb : min(nt, tb + per);
     float acc[8][4] = {};
     float gp[8], gq[4];
     uint32_t up[8], uq[4];
     {
-        const __amdgpu_buffer_rsrc_t rg = seg_rsrc(gamma, npix), ru = seg_rsrc(U, npix);
-        const float a0 = ONE ? a[0] : 1.0f;
+        const size_t o = (size_t)tb * (size_t)npix;
+        const __amdgpu_buffer_rsrc_t rg = seg_rsrc(gamma + o, npix), ru = seg_rsrc(U + o, npix);
+        const float a0 = ONE ? a[tb] : 1.0f;
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             gp[i] = a0 * __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rg, po[i], 0, 0));
@@ -936,12 +1032,12 @@ __global__ __launch_bounds__(512) void fisher_full_stream_kernel(const float *__
     auto none = [] {};
     if constexpr (ONE) {
         __shared__ float4 tab[kLdsTable];
-        if (ntu > 0) {
+        if (te > tb) {
             copy_lds(cub, tab, Jv);
             __builtin_amdgcn_s_waitcnt(kWaitVm0);
             __syncthreads();
         }
-        for (int32_t t = 0; t < ntu; ++t) segment(t, none, [](uint32_t i) { return tab[i]; });
+        for (int32_t t = tb; t < te; ++t) segment(t, none, [](uint32_t i) { return tab[i]; });
     } else {
     __shared__ float4 tab0[kHalf], tab1[kHalf];
     // a table longer than one array: intervals [0, kHalf) in tab0, the rest in tab1
@@ -954,28 +1050,28 @@ __global__ __launch_bounds__(512) void fisher_full_stream_kernel(const float *__
         // double-buffered stages of g tables each, tab0 and tab1 by turns
         const int32_t g = kHalf / Jv;
         auto stage = [&](int32_t s0, const float4 *cur, float4 *nxt) {
-            const int32_t s1 = min(s0 + g, nt);
+            const int32_t s1 = min(s0 + g, te);
             __builtin_amdgcn_s_waitcnt(kWaitVm0);  // this stage's tables have landed (this lane's share)
             __syncthreads();                        // ... every lane's; the previous stage is no longer read
             // the stage's first segment copies the next stage in, always (the
-            // last stage copies table 0 into the idle buffer), so that the
-            // count of copy instructions after its loads is known
-            const int32_t cs = s1 < nt ? s1 : 0, cn = s1 < nt ? min(g, nt - s1) * Jv : Jv;
+            // last stage copies the first table into the idle buffer), so that
+            // the count of copy instructions after its loads is known
+            const int32_t cs = s1 < te ? s1 : tb, cn = s1 < te ? min(g, te - s1) * Jv : Jv;
             segment(s0, [&] { copy_lds_half(cub + (size_t)cs * Jv, nxt, cn); }, [cur](uint32_t i) { return cur[i]; });
             for (int32_t t = s0 + 1; t < s1; ++t) {
                 const float4 *tt = cur + (size_t)(t - s0) * Jv;
                 segment(t, none, [tt](uint32_t i) { return tt[i]; });
             }
         };
-        if (ntu > 0) copy_lds(cub, tab0, min(g, nt) * Jv);
-        for (int32_t s0 = 0; s0 < ntu; s0 += 2 * g) {
+        if (te > tb) copy_lds(cub + (size_t)tb * Jv, tab0, min(g, te - tb) * Jv);
+        for (int32_t s0 = tb; s0 < te; s0 += 2 * g) {
             stage(s0, tab0, tab1);
-            if (s0 + g < ntu) stage(s0 + g, tab1, tab0);
+            if (s0 + g < te) stage(s0 + g, tab1, tab0);
         }
     } else {
         // one table at a time, spanning both arrays
-        for (int32_t t = 0; t < ntu; ++t) {
-            if (t > 0) __syncthreads();  // the previous table is no longer read
+        for (int32_t t = tb; t < te; ++t) {
+            if (t > tb) __syncthreads();  // the previous table is no longer read
             copy_split(cub + (size_t)t * Jv);
             __builtin_amdgcn_s_waitcnt(kWaitVm0);
             __syncthreads();
@@ -984,6 +1080,15 @@ __global__ __launch_bounds__(512) void fisher_full_stream_kernel(const float *__
     }
     }
     if (!active) return;
+    if (sums) {  // one range of several: its partial sums (rejected seeds: NaN)
+        float *out = sums + ((int64_t)blockIdx.y * ntiles + k) * kTileEntries + (ty * 8) * kFt + (wv & 1) * 32 + tx * 4;
+        const float nan = __builtin_nanf("");
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            *reinterpret_cast<float4 *>(out + i * kFt) =
+                rejected ? make_float4(nan, nan, nan, nan) : make_float4(acc[i][0], acc[i][1], acc[i][2], acc[i][3]);
+        return;
+    }
 #pragma unroll
     for (int i = 0; i < 8; ++i)
 #pragma unroll
@@ -1023,7 +1128,7 @@ static bool fisher_full_one_table_stream()
 static size_t up256(size_t n) { return (n + 255) & ~(size_t)255; }
 
 // nbins bounds the band width (the chunk count of the table pass).
-size_t fisher_full_workspace_bytes(double f_max, int32_t nbins, int32_t nt, int32_t npix)
+size_t fisher_full_workspace_least(double f_max, int32_t nbins, int32_t nt, int32_t npix)
 {
     double delta;
     int32_t J, fb;
@@ -1033,9 +1138,22 @@ size_t fisher_full_workspace_bytes(double f_max, int32_t nbins, int32_t nt, int3
            up256((size_t)nt * npix * sizeof(uint32_t)) + up256(kSymParts * sizeof(double));
 }
 
+// Partial sums of the segment ranges, behind the rest: for whichever of the
+// antipodal and the plain form needs more.
+size_t fisher_full_workspace_bytes(double f_max, int32_t nbins, int32_t nt, int32_t npix)
+{
+    size_t most = 0;
+    for (const bool anti : {false, true}) {
+        const int64_t ntiles = fisher_tiles(npix, anti);
+        most = std::max(most, segment_ranges(ntiles, nt, kRangeBytesMax).bytes(ntiles));
+    }
+    return fisher_full_workspace_least(f_max, nbins, nt, npix) + most;
+}
+
 hipError_t launch_fisher_full(const float *a, const float *b, int32_t rank, const float *H, int32_t nf, int32_t clo,
                               int32_t chi, double f0, double df, int64_t k0, const float *gamma, const double *tau,
-                              int32_t nt, int32_t npix, int64_t nside, float *G, void *work, hipStream_t s)
+                              int32_t nt, int32_t npix, int64_t nside, float *G, void *work, size_t work_bytes,
+                              hipStream_t s)
 {
     const double f_max = f0 + (double)(k0 + chi - 1) * df;
     double delta;
@@ -1061,9 +1179,14 @@ hipError_t launch_fisher_full(const float *a, const float *b, int32_t rank, cons
     hipLaunchKernelGGL(fixed_delay_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, tau, n,
                        std::ldexp(1.0, fb) / delta, U);
     // antipodal: the two triangles of the northern blocks; otherwise the whole upper triangle
-    const int64_t nrow = nside > 0 ? npix / 2 : npix;
-    const int64_t nT = (nrow + kFt - 1) / kFt, ntiles = (nside > 0 ? 2 : 1) * (nT * (nT + 1) / 2);
+    const int64_t ntiles = fisher_tiles(npix, nside > 0);
     if (ntiles > 0x7fffffff) return hipErrorInvalidValue;
+    // the ranges' partial sums take what the workspace holds past the rest (a
+    // workspace of the least size: one range)
+    const size_t least = fisher_full_workspace_least(f_max, chi, nt, npix);
+    const SegmentRanges sr = segment_ranges(
+        ntiles, nt, std::min<size_t>(kRangeBytesMax, work_bytes > least ? work_bytes - least : 0));
+    float *sums = sr.n > 1 ? reinterpret_cast<float *>(reinterpret_cast<char *>(work) + least) : nullptr;
     const bool lds = J <= kLdsTable && fisher_full_table_in_lds();
     int cus = 256;
     if (lds) {
@@ -1081,17 +1204,22 @@ hipError_t launch_fisher_full(const float *a, const float *b, int32_t rank, cons
         hipLaunchKernelGGL(delay_cubic_kernel, dim3((unsigned)((J + 255) / 256)), dim3(256), 0, s, part, nchunk, J,
                            cub);
         if (lds && fisher_full_one_table_stream()) {
-            hipLaunchKernelGGL(fisher_full_stream_kernel<true>, dim3((unsigned)((ntiles + kStTiles - 1) / kStTiles)),
+            hipLaunchKernelGGL(fisher_full_stream_kernel<true>,
+                               dim3((unsigned)((ntiles + kStTiles - 1) / kStTiles), (unsigned)sr.n),
                                dim3(kStWaves * 64), 0, s, ar, gamma, U, nt, npix, nside, flags, cub, J,
-                               (const unsigned long long *)nullptr, delta, fb, ntiles, (int32_t)(r > 0), G);
+                               (const unsigned long long *)nullptr, delta, fb, ntiles, sr.per, sums, (int32_t)(r > 0),
+                               G);
+            if (sums)
+                hipLaunchKernelGGL(fisher_full_reduce_kernel, dim3((unsigned)ntiles), dim3(256), 0, s, sums, sr.n,
+                                   ntiles, npix, nside, (int32_t)(r > 0), G);
         } else if (lds) {
             const int64_t grid = std::min<int64_t>(cus, (ntiles + 1) / 2);
             hipLaunchKernelGGL(fisher_full_lds_kernel, dim3((unsigned)grid), dim3(512), 0, s, ar, gamma, U, nt, npix,
-                               nside, flags, cub, J, fb, ntiles, (int32_t)(r > 0), G);
+                               nside, flags, cub, J, fb, ntiles, sr.per, (int32_t)(r > 0), G);
         } else {
             hipLaunchKernelGGL(fisher_full_kernel, dim3((unsigned)ntiles), dim3(256), 0, s, ar, gamma, U, nt, npix,
-                               nside, flags, cub, J, (const unsigned long long *)nullptr, delta, fb, (int32_t)(r > 0),
-                               G);
+                               nside, flags, cub, J, (const unsigned long long *)nullptr, delta, fb, sr.per,
+                               (int32_t)(r > 0), G);
         }
     }
     return hipGetLastError();
@@ -1103,23 +1231,26 @@ struct GeneralLayout {
     StripGrid sg;     // expanded basis (sg.S > 0) or direct
     int32_t nk = 0;   // K of the table contraction
     int64_t ntiles = 0;
+    SegmentRanges sr;  // their partial sums take the place of the tables' (part), read by then
     size_t part = 0, cub = 0, U = 0, flags = 0, bound = 0, mu = 0, nu = 0, total = 0;  // byte offsets (total: size)
 };
 
+// ranges: with room for the matrix pass's best segment ranges; without, those
+// that fit where the tables' partial sums were.
 static GeneralLayout general_layout(double f0, double df, int64_t k0, int32_t clo, int32_t chi, int32_t nt,
-                                    int32_t npix, int64_t nside)
+                                    int32_t npix, int64_t nside, bool ranges)
 {
     GeneralLayout L;
     double delta;
     fisher_table_geometry(f0 + (double)(k0 + chi - 1) * df, &delta, &L.J, &L.fb);
     L.sg = strip_grid(df, k0, clo, chi);
     L.nk = L.sg.S > 0 ? L.sg.n * kTxTerms : chi - clo;
-    const int64_t nrow = nside > 0 ? npix / 2 : npix;
-    const int64_t nT = (nrow + kFt - 1) / kFt;
-    L.ntiles = (nside > 0 ? 2 : 1) * (nT * (nT + 1) / 2);
+    L.ntiles = fisher_tiles(npix, nside > 0);
     size_t o = 0;
     L.part = o;
-    o += up256((size_t)table_split_cap(L.nk) * nt * (L.J + 1) * sizeof(double2));
+    const size_t tables = (size_t)table_split_cap(L.nk) * nt * (L.J + 1) * sizeof(double2);
+    L.sr = segment_ranges(L.ntiles, nt, ranges ? kRangeBytesMax : std::min<size_t>(kRangeBytesMax, tables));
+    o += up256(std::max(tables, L.sr.bytes(L.ntiles)));
     L.cub = o;
     o += up256((size_t)nt * L.J * sizeof(float4));
     L.U = o;
@@ -1141,14 +1272,22 @@ static GeneralLayout general_layout(double f0, double df, int64_t k0, int32_t cl
 size_t fisher_full_general_workspace_bytes(double f0, double df, int64_t k0, int32_t clo, int32_t chi, int32_t nt,
                                            int32_t npix, int64_t nside)
 {
-    return general_layout(f0, df, k0, clo, chi, nt, npix, nside).total;
+    return general_layout(f0, df, k0, clo, chi, nt, npix, nside, true).total;
+}
+
+size_t fisher_full_general_workspace_least(double f0, double df, int64_t k0, int32_t clo, int32_t chi, int32_t nt,
+                                           int32_t npix, int64_t nside)
+{
+    return general_layout(f0, df, k0, clo, chi, nt, npix, nside, false).total;
 }
 
 hipError_t launch_fisher_full_general(const float *w, int64_t ldw, const float *H, int32_t clo, int32_t chi,
                                       double f0, double df, int64_t k0, const float *gamma, const double *tau,
-                                      int32_t nt, int32_t npix, int64_t nside, float *G, void *work, hipStream_t s)
+                                      int32_t nt, int32_t npix, int64_t nside, float *G, void *work,
+                                      size_t work_bytes, hipStream_t s)
 {
-    const GeneralLayout L = general_layout(f0, df, k0, clo, chi, nt, npix, nside);
+    GeneralLayout L = general_layout(f0, df, k0, clo, chi, nt, npix, nside, true);
+    if (L.total > work_bytes) L = general_layout(f0, df, k0, clo, chi, nt, npix, nside, false);
     if (L.fb < kFracBitsMin || L.ntiles > 0x7fffffff) return hipErrorInvalidValue;
     double delta;
     int32_t J, fb;
@@ -1191,13 +1330,17 @@ hipError_t launch_fisher_full_general(const float *w, int64_t ldw, const float *
                        part, nt, L.nk, J, (const unsigned long long *)bound, delta, cub);
     if (J <= kLdsTable && fisher_full_table_in_lds()) {
         const int64_t grid = (L.ntiles + kStTiles - 1) / kStTiles;
-        hipLaunchKernelGGL(fisher_full_stream_kernel<false>, dim3((unsigned)grid), dim3(kStWaves * 64), 0, s,
-                           (const float *)nullptr, gamma, U, nt, npix, nside, flags, cub, J,
-                           (const unsigned long long *)bound, delta, fb, L.ntiles, (int32_t)0, G);
+        float *sums = L.sr.n > 1 ? reinterpret_cast<float *>(part) : nullptr;
+        hipLaunchKernelGGL(fisher_full_stream_kernel<false>, dim3((unsigned)grid, (unsigned)L.sr.n),
+                           dim3(kStWaves * 64), 0, s, (const float *)nullptr, gamma, U, nt, npix, nside, flags, cub,
+                           J, (const unsigned long long *)bound, delta, fb, L.ntiles, L.sr.per, sums, (int32_t)0, G);
+        if (sums)
+            hipLaunchKernelGGL(fisher_full_reduce_kernel, dim3((unsigned)L.ntiles), dim3(256), 0, s, sums, L.sr.n,
+                               L.ntiles, npix, nside, (int32_t)0, G);
     } else {
         hipLaunchKernelGGL(fisher_full_kernel, dim3((unsigned)L.ntiles), dim3(256), 0, s, (const float *)nullptr,
                            gamma, U, nt, npix, nside, flags, cub, J, (const unsigned long long *)bound, delta, fb,
-                           (int32_t)0, G);
+                           L.sr.per, (int32_t)0, G);
     }
     return hipGetLastError();
 }

@@ -161,12 +161,15 @@ hipError_t launch_band_gamma(const float *w, int64_t ldw, int32_t nt, const floa
                              const float *gamma, int32_t npix, double *scratch, float *Gbb, hipStream_t s);
 
 // full Fisher matrix of a band for separable weights, and its CG clean map
+// the workspace a call should get, and the least one it takes (see segment_ranges)
 size_t fisher_full_workspace_bytes(double f_max, int32_t nbins, int32_t nt, int32_t npix);
+size_t fisher_full_workspace_least(double f_max, int32_t nbins, int32_t nt, int32_t npix);
 bool fisher_full_band_ok(double f_max);
 // nside > 0: antipodal seeds (only the northern rows and their antipodes are computed)
 hipError_t launch_fisher_full(const float *a, const float *b, int32_t rank, const float *H, int32_t nf, int32_t clo,
                               int32_t chi, double f0, double df, int64_t k0, const float *gamma, const double *tau,
-                              int32_t nt, int32_t npix, int64_t nside, float *G, void *work, hipStream_t s);
+                              int32_t nt, int32_t npix, int64_t nside, float *G, void *work, size_t work_bytes,
+                              hipStream_t s);
 size_t cg_workspace_bytes(int32_t n);
 hipError_t launch_clean_map_cg(const float *G, const float *X, int32_t n, int32_t niter, float *P, void *work,
                                hipStream_t s);

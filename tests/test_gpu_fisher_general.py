@@ -269,3 +269,36 @@ def test_fisher_full_nside64_sampled(sg, oracle_mod, weights):
     assert torch.equal(G[npix - 1, :64], G[:64, npix - 1])
     del G
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("short", [False, True], ids=["sized", "least"])
+@pytest.mark.parametrize("nt,anti", [(31, True), (100, True), (257, False)])
+def test_segment_ranges_vs_oracle(sg, oracle_mod, nt, anti, short):
+    """A matrix of few tiles, its segments cut into ranges whose partial sums are
+    added in order (none below 32 segments; as many as fit in a workspace short
+    of the queried size): general and separable weights (of rank 2) against the
+    oracle, both matrices symmetric."""
+    nside, k0, nf, df = 4, 9000, 96, 1 / 32
+    g, t, w, H = _inputs(sg, "AC", nside, None, nt, k0, nf, df, 45)
+    npix, fg = g.shape[1], sg.FGrid(F0, df)
+    rng = np.random.default_rng(nt)
+    a = rng.uniform(0.5, 1.5, (2, nt)).astype(np.float32)
+    b = np.stack([w[0], w[1]]).astype(np.float32)
+    Hd = torch.from_numpy(H).cuda()
+    sizes = (sg.fisher_full_general_workspace_bytes(fg, k0, 0, nf, nt, npix, anti),
+             sg.fisher_full_workspace_bytes(fg, k0, nf, nt, npix))
+    # (the general call keeps its ranges' sums where its tables' were: no room to leave out here)
+    ws = [torch.empty(n - (256 if short and nt >= 32 and i == 1 else 0), dtype=torch.uint8, device="cuda")
+          for i, n in enumerate(sizes)]
+    print(f"nt {nt} anti {anti} short {short}", flush=True)
+    Gg = sg.fisher_full_general(torch.from_numpy(w).cuda(), Hd, fg, k0, 0, nf, g, t, workspace=ws[0], antipodal=anti)
+    Gs = sg.fisher_full(torch.from_numpy(a).cuda(), torch.from_numpy(b).cuda(), Hd, fg, k0, 0, nf, g, t,
+                        workspace=ws[1], antipodal=anti)
+    torch.cuda.synchronize()
+    gh, th = g.cpu().numpy().astype(np.float64), t.cpu().numpy()
+    sel = np.sort(rng.choice(npix, 40, replace=False))
+    for G, wt in ((Gg, w), (Gs, a.astype(np.float64).T @ b.astype(np.float64))):
+        Gh = G.cpu().numpy().astype(np.float64)
+        Go = _oracle(oracle_mod, wt, H, df, k0, 0, nf, gh, th, sel)
+        assert np.max(np.abs(Gh[np.ix_(sel, sel)] - Go) / _scale(wt, H, 0, nf, gh[:, sel])) <= 1e-5
+        assert np.array_equal(Gh, Gh.T)
