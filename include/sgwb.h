@@ -299,7 +299,9 @@ int sgwb_fisher_full(const float *a, const float *b, int32_t rank, const float *
  * values and derivatives summed over the band in float64 on the matrix cores:
  * over the bins (weights times generated cosines and sines) on grids coarser
  * than 1/8 Hz, else over Jacobi-Anger moments of 16- to 64-bin strips (eight
- * terms, truncation below 1.6e-9 of sum |H w|); then the same float32 cubic
+ * terms, truncation below 1.6e-9 of sum |H w|), at the Chebyshev nodes that
+ * determine the table to 1e-13 and from their series at its points (at every
+ * point for bands of more than about 2.5 kHz); then the same float32 cubic
  * interpolants, fixed-point delays
  * and float32 accumulation over t; same tolerance.  The tables stop at the
  * largest delay difference the seeds can have, 2 max|tau| (found on the

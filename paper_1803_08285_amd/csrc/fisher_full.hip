@@ -50,28 +50,52 @@ void fisher_table_geometry(double f_max, double *delta, int32_t *J, int32_t *fb)
 // Delay bound of a seed set, for tables no longer than its delay differences
 // need: max |tau| over all seeds (NaN counted as the Earth bound), as the bit
 // pattern of a non-negative double (ordered like the value), reduced with an
-// integer atomic max into *bound, which delay_bound_init_kernel zeroes first.
+// integer atomic max into *bound, which an earlier kernel zeroes; and, from the
+// same read, the fixed-point delays (fixed_delay).  Few, large workgroups: the
+// atomics on one address serialise (nside 16, 898 segments: 28 us for the bound
+// alone with 2048 workgroups, then 6 us for the delays; 12 us together).
 __global__ __launch_bounds__(64) void delay_bound_init_kernel(unsigned long long *__restrict__ bound)
 {
     if (threadIdx.x == 0) *bound = 0ull;
 }
 
-__global__ __launch_bounds__(256) void delay_bound_kernel(const double *__restrict__ tau, int64_t n,
-                                                          unsigned long long *__restrict__ bound)
+// Delays as biased fixed-point table coordinates: U = round(tau / delta 2^fb) + 2^30,
+// tau clamped to the Earth bound, so that |U_p - U_q| >> fb < J - 1.
+__device__ __forceinline__ uint32_t fixed_delay(double tau, double scale)
 {
-    __shared__ double red[256];
+    const double t = fmin(fmax(tau, -kMaxDelay), kMaxDelay);
+    return (uint32_t)((int64_t)llrint(t * scale) + (int64_t)kDelayBias);
+}
+
+constexpr int kBoundThreads = 1024;
+constexpr int kBoundBlocks = 512;
+
+__global__ __launch_bounds__(kBoundThreads) void delay_bound_kernel(const double *__restrict__ tau, int64_t n,
+                                                                    double scale,
+                                                                    unsigned long long *__restrict__ bound,
+                                                                    uint32_t *__restrict__ U)
+{
+    __shared__ double red[kBoundThreads / 64];
     double m = 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
-        const double v = tau[i];
-        m = fmax(m, v != v ? kMaxDelay : fabs(v));
+    const int64_t stride = (int64_t)gridDim.x * kBoundThreads;
+    for (int64_t i0 = (int64_t)blockIdx.x * kBoundThreads + threadIdx.x; i0 < n; i0 += 4 * stride) {
+        double v[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = tau[min(i0 + e * stride, n - 1)];  // past the end: the last again
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            m = fmax(m, v[e] != v[e] ? kMaxDelay : fabs(v[e]));
+            if (i0 + e * stride < n) U[i0 + e * stride] = fixed_delay(v[e], scale);
+        }
     }
-    red[threadIdx.x] = m;
+#pragma unroll
+    for (int h = 32; h > 0; h >>= 1) m = fmax(m, __shfl_xor(m, h));
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
     __syncthreads();
-    for (int h = 128; h > 0; h >>= 1) {
-        if (threadIdx.x < h) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + h]);
-        __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int i = 1; i < kBoundThreads / 64; ++i) m = fmax(m, red[i]);
+        atomicMax(bound, (unsigned long long)__double_as_longlong(m));
     }
-    if (threadIdx.x == 0) atomicMax(bound, (unsigned long long)__double_as_longlong(red[0]));
 }
 
 // Table intervals the seeds can reach: |tau_p - tau_q| <= 2 m with m their
@@ -229,6 +253,15 @@ __global__ __launch_bounds__(256) void delay_cubic_kernel(const double2 *__restr
 //    the widest power of two up to 64 with eta <= kTxEtaMax at the Earth bound
 //    (S = 64 at 1/32 Hz), so the dropped remainder is below 2 (eta/2)^8 / 8! =
 //    1.6e-9 of sum |H w|.
+// Points.  Wd_t(D) = Re[e^{2 pi i f_c D} Y_t(D)] with f_c the band's centre, and
+// Y_t, of frequencies within F of zero, is determined on [0, Jv delta] to float64
+// rounding by node_count() Chebyshev nodes, N ~ Z + 45 with Z = pi F Jv delta.  The
+// contraction runs on those N nodes (sum_c H w(t,c) e^{2 pi i f_c D_n}, cosine and
+// sine products of one weight operand, so no nu_n), and delay_nodes_table_kernel
+// evaluates Y_t and its derivative at the grid's points from their Chebyshev
+// series.  Full day, 20-500 Hz at 1/32 Hz, AC: N = 81 against 1745 points.  The
+// contraction at every grid point (value and derivative) stays for bands wider
+// than about 2.5 kHz (more nodes than kNodesMax at the Earth bound).
 // Per work item a 64-segment x 64-point tile over one range of K (bins, or
 // strip terms), the cosine / sine operand of each 32-deep chunk generated into
 // LDS (float64 phases reduced exactly, then advanced by float64 rotations; the
@@ -238,12 +271,30 @@ __global__ __launch_bounds__(256) void delay_cubic_kernel(const double2 *__restr
 // sums delay_cubic_general_kernel adds in a fixed order.
 typedef double dbl4 __attribute__((ext_vector_type(4)));
 
+constexpr int kNodesMax = 512;
+
+// Chebyshev nodes for a function of frequencies within F on an interval of
+// length L, half = pi F L / 2: the least N with 4 half^N / N! <= 1e-13, or one
+// more (Stirling's form of N!; Newton's iteration from above on a convex
+// function stays above the root), at most `most`.  float32 will do.
+__host__ __device__ inline int32_t node_count(double half, int32_t most)
+{
+    const float h = half > 1e-2 ? (float)half : 1e-2f;
+    float n = 5.5f * h + 40.0f;
+    for (int i = 0; i < 6; ++i) {
+        const float l = logf(n / h), f = n * (l - 1.0f) + 0.5f * logf(6.2831853f * n) - 31.4f;
+        n -= f / (l + 0.5f / n);
+    }
+    return n < most ? (int32_t)ceilf(n + 0.01f) : most;
+}
+
 constexpr int kTgM = 64;          // segments per tile (16 per wave)
 constexpr int kTgN = 64;          // grid points per tile (four 16-wide blocks)
 constexpr int kTgK = 32;          // K per chunk (eight 4-deep matrix-core steps)
 constexpr int kTgSplitsMax = 16;  // K ranges at most
 constexpr int kTgSplitsBuf = 4;   // partial sums held: kTgSplitsBuf x nt x (J + 1) points
 constexpr int kTgItems = 8192;    // work items aimed at
+constexpr int kNodeChunks = 4;    // chunks a range, at least, where the points are nodes
 constexpr int kTxTerms = 8;       // Jacobi-Anger terms per strip (expanded basis)
 constexpr double kTxEtaMax = 0.55;
 static_assert(kTgK % kTxTerms == 0, "a chunk holds whole strips");
@@ -262,14 +313,15 @@ __host__ __device__ __forceinline__ int32_t table_split_cap(int32_t nk)
 }
 
 // K ranges for a table of Jv intervals: about kTgItems work items, at least
-// 16 chunks a range (unless there is one range), at most kTgSplitsMax, and no
+// min_chunks chunks a range (unless there is one range), at most kTgSplitsMax, and no
 // more partial sums than the buffer holds (n (Jv + 1) <= cap (J + 1)).
-__host__ __device__ __forceinline__ TableSplit table_split(int32_t Jv, int32_t J, int32_t nt, int32_t nk)
+__host__ __device__ __forceinline__ TableSplit table_split(int32_t Jv, int32_t J, int32_t nt, int32_t nk,
+                                                           int32_t min_chunks = 16)
 {
     const int64_t tiles = (int64_t)((Jv + 1 + kTgN - 1) / kTgN) * ((nt + kTgM - 1) / kTgM);
     const int32_t nchunk = (nk + kTgK - 1) / kTgK;
     int64_t n = (kTgItems + tiles - 1) / tiles;
-    n = n < nchunk / 16 ? n : nchunk / 16;
+    n = n < nchunk / min_chunks ? n : nchunk / min_chunks;
     const int64_t fit = (int64_t)table_split_cap(nk) * (J + 1) / (Jv + 1);
     n = n < fit ? n : fit;
     n = n < kTgSplitsMax ? n : kTgSplitsMax;
@@ -381,6 +433,72 @@ __global__ __launch_bounds__(256) void table_moments_kernel(const float *__restr
     }
 }
 
+// The moments mu_n alone (the node contraction's), on the float64 matrix cores:
+// a wave takes 16 segments and, strip by strip, multiplies H w [16 x S] with
+// T_n(s_c) [S x 16] (eight columns used; the same for every strip, kept in
+// registers).  Lane l holds segment l % 16 and, of every 16 bins, the four from
+// 4 (l / 16) on, so its operands are 16-byte loads; the bins' order in the sum
+// is the instruction's.  Streams w.  Full day, 15 360 bins: 18 us (both
+// moments on the vector units 88 us).
+constexpr int kMuStrips = 4;  // strips per wave
+
+template <int S>
+__global__ __launch_bounds__(256) void table_mu_kernel(const float *__restrict__ w, int64_t ldw,
+                                                       const float *__restrict__ H, int32_t clo, int32_t chi,
+                                                       int64_t k0, int64_t first, int32_t nt, int32_t nstrips,
+                                                       double *__restrict__ mu)
+{
+    typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int n = lane & 15, kq = lane >> 4;
+    const int32_t t0 = blockIdx.y * 16, t = min(t0 + n, nt - 1);  // past the last: computed, not stored
+    __shared__ double tn[S][kTxTerms + 1];
+    if ((int)threadIdx.x < S) {
+        const double half = 0.5 * (S - 1), x = ((int)threadIdx.x - half) / half;
+        double *row = tn[threadIdx.x];
+        row[0] = 1.0;
+        row[1] = x;
+#pragma unroll
+        for (int k = 2; k < kTxTerms; ++k) row[k] = 2.0 * x * row[k - 1] - row[k - 2];
+    }
+    __syncthreads();
+    double cheb[S / 4];
+#pragma unroll
+    for (int i = 0; i < S / 4; ++i) cheb[i] = n < kTxTerms ? tn[16 * (i / 4) + 4 * kq + i % 4][n] : 0.0;
+    const float *wr = w + (int64_t)t * ldw;
+    const int32_t s0 = (blockIdx.x * 4 + wv) * kMuStrips;
+#pragma unroll
+    for (int e = 0; e < kMuStrips; ++e) {
+        const int32_t sg = s0 + e;
+        if (sg >= nstrips) break;
+        const int64_t c0 = (first + sg) * S - k0;  // the strip's first column
+        double h[S / 4];
+        if (c0 >= clo && c0 + S <= chi) {
+#pragma unroll
+            for (int q = 0; q < S / 16; ++q) {
+                const int64_t c = c0 + 16 * q + 4 * kq;
+                const f4u a = *reinterpret_cast<const f4u *>(wr + c), b = *reinterpret_cast<const f4u *>(H + c);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) h[4 * q + i] = (double)b[i] * (double)a[i];
+            }
+        } else {  // a strip over the band's end: zero outside
+#pragma unroll
+            for (int i = 0; i < S / 4; ++i) {
+                const int64_t c = c0 + 16 * (i / 4) + 4 * kq + i % 4;
+                h[i] = c >= clo && c < chi ? (double)H[c] * (double)wr[c] : 0.0;
+            }
+        }
+        dbl4 acc = dbl4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int i = 0; i < S / 4; ++i) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(h[i], cheb[i], acc, 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int32_t row = t0 + kq + 4 * r;
+            if (row < nt && n < kTxTerms) mu[(int64_t)row * nstrips * kTxTerms + (int64_t)sg * kTxTerms + n] = acc[r];
+        }
+    }
+}
+
 // eps_n J_n(eta) for n < kTxTerms (power series; eta <= kTxEtaMax, 12 terms
 // leave less than 1e-17).
 __device__ __forceinline__ void bessel_eps(double eta, double (&J)[kTxTerms])
@@ -401,8 +519,11 @@ __device__ __forceinline__ void bessel_eps(double eta, double (&J)[kTxTerms])
 }
 
 // EXP = false: A = w, H (direct basis over the bins; nk = nbins); EXP = true:
-// A = mu, nu (strip moments, nk = nstrips kTxTerms).
-template <bool EXP>
+// A = mu, nu (strip moments, nk = nstrips kTxTerms).  NODES: at the Chebyshev
+// nodes of [0, Jv delta] (half_rate = pi F / 2; at most `most`, the Earth bound's
+// count) the sums of H w e^{2 pi i f D}, real
+// and imaginary part; else at the grid's points the value and derivative.
+template <bool EXP, bool NODES>
 __global__ __launch_bounds__(256) void delay_table_gemm_kernel(const float *__restrict__ w, int64_t ldw,
                                                                const float *__restrict__ H,
                                                                const double *__restrict__ mu,
@@ -410,15 +531,17 @@ __global__ __launch_bounds__(256) void delay_table_gemm_kernel(const float *__re
                                                                int32_t clo, int32_t nk, double f0, double df,
                                                                int64_t k0, int32_t S, int64_t first, double delta,
                                                                int32_t J, const unsigned long long *__restrict__ bound,
-                                                               double2 *__restrict__ part)
+                                                               double half_rate, int32_t most, double2 *__restrict__ part)
 {
     __shared__ double bc[kTgK][kTgN], bs[kTgK][kTgN];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int kq = lane >> 4;
     const int gj = threadIdx.x & 63, gg = threadIdx.x >> 6;  // generation: point gj, K rows 8 gg .. 8 gg + 7
     const int32_t Jv = table_intervals(bound, delta, J);
-    const TableSplit sp = table_split(Jv, J, nt, nk);
-    const int32_t nx = (Jv + 1 + kTgN - 1) / kTgN, ny = (nt + kTgM - 1) / kTgM;
+    const double len = Jv * delta;
+    const int32_t np = NODES ? node_count(half_rate * len, most) : Jv + 1;  // points
+    const TableSplit sp = table_split(np - 1, J, nt, nk, NODES ? kNodeChunks : 16);
+    const int32_t nx = (np + kTgN - 1) / kTgN, ny = (nt + kTgM - 1) / kTgM;
     const int64_t items = (int64_t)nx * ny * sp.n;
     const float *hr = H + clo;
     const double half = 0.5 * (S - 1);
@@ -428,7 +551,8 @@ __global__ __launch_bounds__(256) void delay_table_gemm_kernel(const float *__re
         const int32_t by = (int32_t)(rest % ny), bz = (int32_t)(rest / ny);
         const int32_t j0 = bx * kTgN, t0 = by * kTgM;
         const int32_t cbeg = bz * sp.bins, cend = min(nk, cbeg + sp.bins);
-        const double D = (double)(j0 + gj) * delta;
+        const double D =
+            NODES ? 0.5 * len * (1.0 + cospi((j0 + gj + 0.5) / np)) : (double)(j0 + gj) * delta;
         double er, ei, Jn[kTxTerms];
         if (EXP) {
             bessel_eps(kTwoPi * half * df * D, Jn);
@@ -440,7 +564,7 @@ __global__ __launch_bounds__(256) void delay_table_gemm_kernel(const float *__re
         const bool rok = trow < nt;
         const float *wr = w + (int64_t)(rok ? trow : 0) * ldw + clo;
         const double *mr = EXP ? mu + (int64_t)(rok ? trow : 0) * nk : nullptr;
-        const double *vr = EXP ? nu + (int64_t)(rok ? trow : 0) * nk : nullptr;
+        const double *vr = EXP && !NODES ? nu + (int64_t)(rok ? trow : 0) * nk : nullptr;
         dbl4 av[4], ad[4];
 #pragma unroll
         for (int n = 0; n < 4; ++n) av[n] = ad[n] = dbl4{0.0, 0.0, 0.0, 0.0};
@@ -453,11 +577,11 @@ __global__ __launch_bounds__(256) void delay_table_gemm_kernel(const float *__re
                 const bool ok = rok && c < cend;
                 if (EXP) {
                     ak[ks] = ok ? mr[c] : 0.0;
-                    dk[ks] = ok ? vr[c] : 0.0;
+                    dk[ks] = NODES ? ak[ks] : ok ? vr[c] : 0.0;
                 } else {
                     const double h = ok ? (double)hr[c] * (double)wr[c] : 0.0;
                     ak[ks] = h;
-                    dk[ks] = -kTwoPi * delta * (f0 + (double)(k0 + clo + c) * df) * h;
+                    dk[ks] = NODES ? h : -kTwoPi * delta * (f0 + (double)(k0 + clo + c) * df) * h;
                 }
             }
             __syncthreads();  // the previous chunk's (or item's) operands are no longer read
@@ -467,7 +591,7 @@ __global__ __launch_bounds__(256) void delay_table_gemm_kernel(const float *__re
                 const double x = (f0 + ((double)(sgi * S) + half) * df) * D, r = x - rint(x);
                 double zr, zi;
                 sincospi(2.0 * r, &zi, &zr);
-                const double sd = -kTwoPi * delta;
+                const double sd = NODES ? 1.0 : -kTwoPi * delta;
 #pragma unroll
                 for (int n = 0; n < kTxTerms; ++n) {
                     // i^n e^{i theta}: real and imaginary parts
@@ -504,14 +628,14 @@ __global__ __launch_bounds__(256) void delay_table_gemm_kernel(const float *__re
         }
         // result layout (measured): register r of a lane holds row lane / 16 + 4 r
         // of the wave's 16, column lane % 16 of each block; partial sums of range
-        // bz at part + (bz nt + t) (Jv + 1) + j
+        // bz at part + (bz nt + t) np + j
 #pragma unroll
         for (int n = 0; n < 4; ++n)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int32_t t = t0 + 16 * wv + kq + 4 * r, j = j0 + 16 * n + (lane & 15);
-                if (t < nt && j <= Jv)
-                    part[((size_t)bz * nt + t) * (Jv + 1) + j] = make_double2(av[n][r], ad[n][r]);
+                if (t < nt && j < np)
+                    part[((size_t)bz * nt + t) * np + j] = make_double2(av[n][r], ad[n][r]);
             }
     }
 }
@@ -541,15 +665,149 @@ __global__ __launch_bounds__(256) void delay_cubic_general_kernel(const double2 
     cub[(size_t)blockIdx.y * Jv + j] = hermite_cubic(a, b);
 }
 
-// Delays as biased fixed-point table coordinates: U = round(tau / delta 2^fb) + 2^30,
-// tau clamped to the Earth bound, so that |U_p - U_q| >> fb < J - 1.
 __global__ __launch_bounds__(256) void fixed_delay_kernel(const double *__restrict__ tau, int64_t n, double scale,
                                                           uint32_t *__restrict__ U)
 {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    const double t = fmin(fmax(tau[i], -kMaxDelay), kMaxDelay);
-    U[i] = (uint32_t)((int64_t)llrint(t * scale) + (int64_t)kDelayBias);
+    if (i < n) U[i] = fixed_delay(tau[i], scale);
+}
+
+// Cubics of one segment's table (a workgroup) from the node sums: the K ranges'
+// partial sums in range order, turned to the band's centre f_c, the Chebyshev
+// series of Y_t and of its derivative, both evaluated at the grid's points by
+// Clenshaw's recurrence (two points and their mirror images a thread: x and -x
+// share the sums of the even and of the odd terms), and the interval's cubic as
+// delay_cubic_general_kernel writes it.  Bound by the reads of the series from
+// LDS (two 16-byte reads per term and thread) beside the recurrences' float64
+// FMAs.  Full day, 20-500 Hz, AC: 45 us (78 us a point a thread).
+constexpr int kTableThreads = 256;
+
+__global__ __launch_bounds__(kTableThreads) void delay_nodes_table_kernel(
+    const double2 *__restrict__ part, int32_t nt, int32_t nk, int32_t J,
+    const unsigned long long *__restrict__ bound, double delta, double fc, double half_rate, int32_t most,
+    float4 *__restrict__ cub)
+{
+    __shared__ double2 val[2 * kTableThreads], rev[2 * kTableThreads];
+    extern __shared__ double dyn[];
+    const int tid = threadIdx.x;
+    const int32_t t = blockIdx.x;
+    const int32_t Jv = table_intervals(bound, delta, J);
+    const double len = Jv * delta;
+    const int32_t N = node_count(half_rate * len, most);
+    double *const ct = dyn;                                          // cos(pi i / (2 N)), i < 4 N
+    double2 *const node = reinterpret_cast<double2 *>(dyn + 4 * N);  // Y_t at the nodes, then the derivative's series
+    double2 *const coef = node + N + 1;                              // Y_t's series
+    const TableSplit sp = table_split(N - 1, J, nt, nk, kNodeChunks);
+    for (int32_t i = tid; i < 4 * N; i += kTableThreads) ct[i] = cospi(0.5 * i / N);
+    __syncthreads();
+    for (int32_t n = tid; n < N; n += kTableThreads) {
+        double2 v = make_double2(0.0, 0.0);
+        // four loads together; ranges past the last add zero
+        for (int32_t q = 0; q < sp.n; q += 4) {
+            double2 u[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) u[e] = part[((size_t)min(q + e, sp.n - 1) * nt + t) * N + n];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                v.x += q + e < sp.n ? u[e].x : 0.0;
+                v.y += q + e < sp.n ? u[e].y : 0.0;
+            }
+        }
+        const double x = fc * (0.5 * len * (1.0 + ct[2 * n + 1])), r = x - rint(x);
+        double sn, cs;
+        sincospi(2.0 * r, &sn, &cs);
+        node[n] = make_double2(v.x * cs + v.y * sn, v.y * cs - v.x * sn);
+    }
+    __syncthreads();
+    // a_k = (2 - [k = 0]) / N sum_n Y_n cos(pi k (2 n + 1) / (2 N))
+    for (int32_t e = tid; e < 2 * N; e += kTableThreads) {
+        const int32_t k = e >> 1;
+        const double *v = reinterpret_cast<const double *>(node) + (e & 1);
+        double a = 0.0;
+        int32_t i = k;
+        for (int32_t n = 0; n < N; ++n) {
+            a = fma(v[2 * n], ct[i], a);
+            i += 2 * k;
+            if (i >= 4 * N) i -= 4 * N;
+        }
+        reinterpret_cast<double *>(coef)[e] = a * ((k ? 2.0 : 1.0) / N);
+    }
+    if (tid == 0) coef[N] = make_double2(0.0, 0.0);  // an odd N's last pair
+    __syncthreads();
+    // d/dx: b_k = (2 - [k = 0]) sum_{j > k, j - k odd} j a_j
+    for (int32_t e = tid; e < 2 * N; e += kTableThreads) {
+        const int32_t k = e >> 1;
+        const double *a = reinterpret_cast<const double *>(coef) + (e & 1);
+        double b = 0.0;
+        for (int32_t j = k + 1; j < N; j += 2) b = fma((double)j, a[2 * j], b);
+        reinterpret_cast<double *>(node)[e] = b * (k ? 2.0 : 1.0);
+    }
+    if (tid == 0) node[N] = make_double2(0.0, 0.0);
+    __syncthreads();
+    const double slope = 2.0 / Jv, turn = kTwoPi * fc * delta;  // delta dx/dD; delta times the carrier's rate
+    auto value = [&](int32_t j, double yr, double yi, double dr, double di) {
+        const double p = fc * ((double)j * delta), r = p - rint(p);
+        double sn, cs;
+        sincospi(2.0 * r, &sn, &cs);
+        // delta d/dD [e^{2 pi i f_c D} Y] = e^{..} (i turn Y + slope dY/dx)
+        const double gr = fma(slope, dr, -turn * yi), gi = fma(slope, di, turn * yr);
+        return make_double2(cs * yr - sn * yi, cs * gr - sn * gi);
+    };
+    const int32_t mid = (Jv + 1) / 2;  // intervals j < mid and their mirror images
+    constexpr int kPts = 2 * kTableThreads;
+    for (int32_t j0 = 0; j0 < mid; j0 += kPts - 1) {
+        int32_t j[2];
+        double x[2], y2[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            j[h] = min(j0 + h * kTableThreads + tid, mid);
+            x[h] = 2.0 * j[h] / Jv - 1.0;
+            y2[h] = 2.0 * (2.0 * x[h] * x[h] - 1.0);
+        }
+        // per series (Y real, imaginary, dY/dx real, imaginary): the even terms
+        // sum a_2k T_k(y) and the odd ones sum a_{2k+1} T_{2k+1}(x), by the same
+        // recurrence
+        double e1[2][4] = {}, e2[2][4] = {}, o1[2][4] = {}, o2[2][4] = {};
+#pragma unroll 2
+        for (int32_t k = (N - 1) / 2; k >= 0; --k) {
+            const double2 ae = coef[2 * k], be = node[2 * k], ao = coef[2 * k + 1], bo = node[2 * k + 1];
+            const double te[4] = {ae.x, ae.y, be.x, be.y}, to[4] = {ao.x, ao.y, bo.x, bo.y};
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const double ne = fma(y2[h], e1[h][q], te[q] - e2[h][q]);
+                    const double no = fma(y2[h], o1[h][q], to[q] - o2[h][q]);
+                    e2[h][q] = e1[h][q];
+                    e1[h][q] = ne;
+                    o2[h][q] = o1[h][q];
+                    o1[h][q] = no;
+                }
+        }
+        __syncthreads();  // the previous round's values are read
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            double ev[4], od[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                ev[q] = fma(-0.5 * y2[h], e2[h][q], e1[h][q]);  // b_0 - y b_1
+                od[q] = x[h] * (o1[h][q] - o2[h][q]);           // b_0 T_1 - b_1 T_{-1}
+            }
+            val[h * kTableThreads + tid] = value(j[h], ev[0] + od[0], ev[1] + od[1], ev[2] + od[2], ev[3] + od[3]);
+            rev[h * kTableThreads + tid] =
+                value(Jv - j[h], ev[0] - od[0], ev[1] - od[1], ev[2] - od[2], ev[3] - od[3]);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int32_t q = h * kTableThreads + tid, i = j0 + q;
+            if (q < kPts - 1 && i < mid) {
+                float4 *row = cub + (size_t)t * Jv;
+                row[i] = hermite_cubic(val[q], val[q + 1]);
+                if (Jv - 1 - i >= mid) row[Jv - 1 - i] = hermite_cubic(rev[q + 1], rev[q]);
+            }
+        }
+    }
 }
 
 // Upper-triangle tile k of an n x n tile grid: row r, column c >= r.
@@ -617,22 +875,48 @@ __device__ __forceinline__ bool seeds_rejected(const double *__restrict__ flags)
 }
 
 // G from the ranges' partial sums [range][tile][64][64], range order fixed; one
-// workgroup a tile.
+// workgroup a tile.  The values' two orders of indices (store_value) are
+// written along columns and, from LDS, along rows, so that every store is
+// coalesced; a diagonal tile is completed to a symmetric one, whose first order
+// holds the second.  nside 16, five ranges: 30 us (entry by entry 50 us).
 __global__ __launch_bounds__(256) void fisher_full_reduce_kernel(const float *__restrict__ sums, int32_t nranges,
                                                                  int64_t ntiles, int32_t npix, int64_t nside,
                                                                  int32_t accumulate, float *__restrict__ G)
 {
+    __shared__ float tile[kFt][kFt + 1];
     const int64_t nrow = nside > 0 ? npix / 2 : npix;
     const int64_t nT = (nrow + kFt - 1) / kFt;
     int64_t tr, tc;
     bool ns;
     fisher_tile(blockIdx.x, nT, nside > 0, tr, tc, ns);
-    for (int32_t e = threadIdx.x; e < kTileEntries; e += 256) {
-        const int64_t p = tr * kFt + e / kFt, q = tc * kFt + e % kFt;
-        if (p >= nrow || q >= nrow || (tr == tc && p > q)) continue;
-        float v = 0.0f;
-        for (int32_t r = 0; r < nranges; ++r) v += sums[(r * ntiles + blockIdx.x) * kTileEntries + e];
-        store_value(G, npix, nside, ns, p, q, v, accumulate);
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    float v[kFt / 4] = {};  // rows wv, wv + 4, ..: a range's loads go out together
+    for (int32_t r = 0; r < nranges; ++r) {
+        const float *src = sums + (r * ntiles + blockIdx.x) * kTileEntries + wv * kFt + lane;
+#pragma unroll
+        for (int i = 0; i < kFt / 4; ++i) v[i] += src[4 * i * kFt];
+    }
+#pragma unroll
+    for (int i = 0; i < kFt / 4; ++i) tile[wv + 4 * i][lane] = v[i];
+    __syncthreads();
+    auto put = [&](int64_t row, int64_t col, float v) {
+        float *e = G + row * npix + col;
+        *e = accumulate ? *e + v : v;
+    };
+    auto antipode = [&](int64_t p) { return antipode_north(ring_of_north(p, nside), npix); };
+    const bool diag = tr == tc;
+    // fast index: the column q in the first order (p, q), the row p in the second
+    for (int order = 0; order < (diag ? 1 : 2); ++order) {
+        const int64_t f = (order ? tr : tc) * kFt + lane;
+        if (f >= nrow) continue;
+        const int64_t af = nside > 0 ? antipode(f) : 0;
+        for (int i = wv; i < kFt; i += 4) {
+            const int64_t u = (order ? tc : tr) * kFt + i;
+            if (u >= nrow) break;
+            const float v = order ? tile[lane][i] : diag && i > lane ? tile[lane][i] : tile[i][lane];
+            put(u, ns ? af : f, v);
+            if (nside > 0) put(antipode(u), ns ? f : af, v);
+        }
     }
 }
 
@@ -1305,29 +1589,54 @@ hipError_t launch_fisher_full_general(const float *w, int64_t ldw, const float *
     }
     const int64_t n = (int64_t)nt * npix;
     hipLaunchKernelGGL(delay_bound_init_kernel, dim3(1), dim3(64), 0, s, bound);
-    hipLaunchKernelGGL(delay_bound_kernel, dim3((unsigned)std::min<int64_t>(2048, (n + 255) / 256)), dim3(256), 0,
-                       s, tau, n, bound);
-    hipLaunchKernelGGL(fixed_delay_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, tau, n,
-                       std::ldexp(1.0, fb) / delta, U);
+    hipLaunchKernelGGL(delay_bound_kernel,
+                       dim3((unsigned)std::min<int64_t>(kBoundBlocks, (n + kBoundThreads - 1) / kBoundThreads)),
+                       dim3(kBoundThreads), 0, s, tau, n, std::ldexp(1.0, fb) / delta, bound, U);
     int cus = 256, dev = 0;
     (void)hipGetDevice(&dev);
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) cus = 256;
     // persistent: two workgroups per compute unit (their registers allow two)
-    if (L.sg.S > 0) {
-        double *mu = reinterpret_cast<double *>(base + L.mu), *nu = reinterpret_cast<double *>(base + L.nu);
-        hipLaunchKernelGGL(table_moments_kernel, dim3((unsigned)((L.sg.n + kTxStrips - 1) / kTxStrips), (unsigned)nt),
-                           dim3(kTxStrips * kTxSplit), 0, s, w,
-                           ldw, H, clo, chi, f0, df, k0, L.sg.S, L.sg.first, L.sg.n, mu, nu);
-        hipLaunchKernelGGL(delay_table_gemm_kernel<true>, dim3((unsigned)(2 * cus)), dim3(256), 0, s, w, ldw, H,
-                           (const double *)mu, (const double *)nu, nt, clo, L.nk, f0, df, k0, L.sg.S, L.sg.first,
-                           delta, J, (const unsigned long long *)bound, part);
+    const dim3 grid_t((unsigned)(2 * cus));
+    const unsigned long long *bnd = bound;
+    double *mu = reinterpret_cast<double *>(base + L.mu), *nu = reinterpret_cast<double *>(base + L.nu);
+    const int32_t S = L.sg.S, ns = L.sg.n;
+    // nodes: Y_t's frequencies lie within F of the band's centre (the strips may
+    // reach past the band's ends)
+    const double half_rate = 0.5 * kPi * (0.5 * (chi - clo - 1) + S) * df;
+    const double fc = f0 + ((double)k0 + 0.5 * (clo + chi - 1)) * df;
+    const int32_t most = node_count(half_rate * J * delta, kNodesMax + 1);
+    if (most <= kNodesMax && most <= J) {
+        if (S == 64 || S == 32 || S == 16) {
+            auto *moments = S == 64 ? table_mu_kernel<64> : S == 32 ? table_mu_kernel<32> : table_mu_kernel<16>;
+            hipLaunchKernelGGL(moments,
+                               dim3((unsigned)((ns + 4 * kMuStrips - 1) / (4 * kMuStrips)), (unsigned)((nt + 15) / 16)),
+                               dim3(256), 0, s, w, ldw, H, clo, chi, k0, L.sg.first, nt, ns, mu);
+            hipLaunchKernelGGL((delay_table_gemm_kernel<true, true>), grid_t, dim3(256), 0, s, w, ldw, H,
+                               (const double *)mu, (const double *)nullptr, nt, clo, L.nk, f0, df, k0, S, L.sg.first,
+                               delta, J, bnd, half_rate, most, part);
+        } else {
+            hipLaunchKernelGGL((delay_table_gemm_kernel<false, true>), grid_t, dim3(256), 0, s, w, ldw, H,
+                               (const double *)nullptr, (const double *)nullptr, nt, clo, L.nk, f0, df, k0,
+                               (int32_t)0, (int64_t)0, delta, J, bnd, half_rate, most, part);
+        }
+        hipLaunchKernelGGL(delay_nodes_table_kernel, dim3((unsigned)nt), dim3(kTableThreads),
+                           (8 * (size_t)most + 4) * sizeof(double), s, part, nt, L.nk, J, bnd, delta, fc, half_rate, most, cub);
     } else {
-        hipLaunchKernelGGL(delay_table_gemm_kernel<false>, dim3((unsigned)(2 * cus)), dim3(256), 0, s, w, ldw, H,
-                           (const double *)nullptr, (const double *)nullptr, nt, clo, L.nk, f0, df, k0, (int32_t)0,
-                           (int64_t)0, delta, J, (const unsigned long long *)bound, part);
+        if (S > 0) {
+            hipLaunchKernelGGL(table_moments_kernel, dim3((unsigned)((ns + kTxStrips - 1) / kTxStrips), (unsigned)nt),
+                               dim3(kTxStrips * kTxSplit), 0, s, w, ldw, H, clo, chi, f0, df, k0, S, L.sg.first, ns,
+                               mu, nu);
+            hipLaunchKernelGGL((delay_table_gemm_kernel<true, false>), grid_t, dim3(256), 0, s, w, ldw, H,
+                               (const double *)mu, (const double *)nu, nt, clo, L.nk, f0, df, k0, S, L.sg.first,
+                               delta, J, bnd, half_rate, most, part);
+        } else {
+            hipLaunchKernelGGL((delay_table_gemm_kernel<false, false>), grid_t, dim3(256), 0, s, w, ldw, H,
+                               (const double *)nullptr, (const double *)nullptr, nt, clo, L.nk, f0, df, k0,
+                               (int32_t)0, (int64_t)0, delta, J, bnd, half_rate, most, part);
+        }
+        hipLaunchKernelGGL(delay_cubic_general_kernel, dim3((unsigned)((J + 255) / 256), (unsigned)nt), dim3(256), 0,
+                           s, part, nt, L.nk, J, bnd, delta, cub);
     }
-    hipLaunchKernelGGL(delay_cubic_general_kernel, dim3((unsigned)((J + 255) / 256), (unsigned)nt), dim3(256), 0, s,
-                       part, nt, L.nk, J, (const unsigned long long *)bound, delta, cub);
     if (J <= kLdsTable && fisher_full_table_in_lds()) {
         const int64_t grid = (L.ntiles + kStTiles - 1) / kStTiles;
         float *sums = L.sr.n > 1 ? reinterpret_cast<float *>(part) : nullptr;

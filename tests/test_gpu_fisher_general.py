@@ -302,3 +302,25 @@ def test_segment_ranges_vs_oracle(sg, oracle_mod, nt, anti, short):
         Go = _oracle(oracle_mod, wt, H, df, k0, 0, nf, gh, th, sel)
         assert np.max(np.abs(Gh[np.ix_(sel, sel)] - Go) / _scale(wt, H, 0, nf, gh[:, sel])) <= 1e-5
         assert np.array_equal(Gh, Gh.T)
+
+
+@pytest.mark.parametrize("bl,nt,k0,nf,df", [
+    ("AB", 17, 100, 3, 1 / 32),      # fewer bins than nodes, one segment past a group of 16
+    ("AC", 33, 61, 515, 1 / 32),     # strips cut at both ends
+    ("AC", 5, 7, 900, 0.125),        # 16-bin strips, a wide table
+    ("AD", 3, 0, 900, 1.0),          # over the bins; about 200 nodes
+    ("AD", 2, 0, 2200, 1.0),         # nearly 512 nodes at the Earth bound
+    ("AB", 2, 0, 3000, 1.0),         # more: the sums at every grid point
+], ids=lambda v: str(v))
+def test_tables_from_nodes_vs_oracle(sg, oracle_mod, bl, nt, k0, nf, df):
+    """The segments' tables from their Chebyshev nodes over the node counts and
+    bases they meet, and from every grid point past them."""
+    g, t, w, H = _inputs(sg, bl, 2, None, nt, k0, nf, df, 46)
+    print(f"{bl} nt {nt} nf {nf} df {df}", flush=True)
+    G = sg.fisher_full_general(torch.from_numpy(w).cuda(), torch.from_numpy(H).cuda(), sg.FGrid(F0, df), k0, 0, nf, g,
+                               t, antipodal=True)
+    torch.cuda.synchronize()
+    gh, th = g.cpu().numpy().astype(np.float64), t.cpu().numpy()
+    sel = np.arange(gh.shape[1])
+    Go = _oracle(oracle_mod, w, H, df, k0, 0, nf, gh, th, sel)
+    assert np.max(np.abs(G.cpu().numpy().astype(np.float64) - Go) / _scale(w, H, 0, nf, gh)) <= 1e-5
