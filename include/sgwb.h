@@ -372,10 +372,10 @@ int sgwb_reduce_band_f64(const double *X, const double *Gam, const double *H, in
  * X, Gam as sgwb_make_maps (same flags, same bits) and the broadband maps over
  * columns [k_lo, k_hi) of the same call, without reading the narrowband maps
  * back:
- *   Xbb(p) = sum_k X(k,p): where the matrix-core dirty map runs it also writes
- *     the float64 sum of each absolute 64-bin strip and one small kernel adds
- *     the strips in order, rounding once (equal to sgwb_reduce_band's Xbb up to
- *     the order of the float64 sums); otherwise the single-pass band kernel;
+ *   Xbb(p) = sum_k X(k,p): the dirty map also writes the float64 sum of each
+ *     absolute 64-bin strip and one small kernel adds the strips in order,
+ *     rounding once (equal to sgwb_reduce_band's Xbb up to the order of the
+ *     float64 sums);
  *   Gbb(p) = sum_k H(k) Gam(k,p) = sum_t v(t) gamma(t,p)^2, v(t) = sum_k H(k) w(t,k):
  *     the band sum moved into the weights, float64 throughout, rounded once (the
  *     exact band-summed diagonal; sgwb_reduce_band of the split-bf16 Gam meets it

@@ -621,26 +621,23 @@ int make_maps_band_seeded(const float *C, const float *w, int64_t ldc, int32_t n
             return set_error(SGWB_EINVAL,
                              "make_maps_band: Xbb without X needs the matrix-core dirty map (antipodal seeds, "
                              "df <= 0.0344 Hz, no vector-unit request)");
+        // the dirty map writes per-strip partial sums; one small kernel adds them
+        MapArgs ab = a;
+        ab.band_part = part_x;
+        ab.band_lo = k_lo;
+        ab.band_hi = k_hi;
         if (use_xm) {
-            // the dirty map writes per-strip partial sums; one small kernel adds them
-            MapArgs ab = a;
-            ab.band_part = part_x;
-            ab.band_lo = k_lo;
-            ab.band_hi = k_hi;
             const double *rec = nullptr;
             rc = check_hip(launch_dirty_map_mfma(ab, C, w, gamma, tau, X, ws + beam_bytes, stream, &rec, seeds),
                            "dirty-map (matrix cores) launch");
             if (rc) return rc;
             note_xform(kXFormDevice, rec, stream);
-            rc = check_hip(launch_band_partial_finish(part_x, xm_band_rows(a), npix, Xbb, stream), "band finish");
         } else {
-            rc = check_hip(launch_dirty_map<float>(a, C, w, gamma, tau, X, stream), "dirty-map kernel launch");
+            rc = check_hip(launch_dirty_map<float>(ab, C, w, gamma, tau, X, stream), "dirty-map kernel launch");
             if (rc) return rc;
             note_xform(SGWB_XFORM_VALU);
-            rc = check_hip(launch_band<float>(X, nullptr, nullptr, nf, npix, k_lo, k_hi, Xbb, nullptr, nullptr, 0,
-                                              stream),
-                           "band kernel launch");
         }
+        rc = check_hip(launch_band_partial_finish(part_x, xm_band_rows(a), npix, Xbb, stream), "band finish");
         if (rc) return rc;
     }
     if (Gbb) {

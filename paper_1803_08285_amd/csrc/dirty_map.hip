@@ -2,12 +2,14 @@
 // (Eq. eq_dirtymap split per frequency bin as in Eq. eq:narrowband) on gfx950.
 //
 // Work decomposition
-//   * A workgroup owns 256 pixel columns (one per lane) and one strip of S
+//   * A workgroup owns 64 pixel columns (one per lane) and one strip of S
 //     consecutive frequency bins that starts at an absolute bin k = 0 mod S
-//     (S = 64 in float32, 32 in float64).  Lanes of a wave read coalesced
-//     pixel-major rows of gamma and tau.
-//   * The weighted CSD y(t,k) = w(t,k) C(t,k) of the strip is staged in LDS,
-//     XTC segments at a time; every lane reads the same y (LDS broadcast).
+//     (S = 64 in float32, 32 in float64).  Its eight waves take an eighth of the
+//     segments each (consecutive ones), so that a small map still fills the
+//     chip; their sums meet in LDS and are added in wave order.
+//   * Per wave the weighted CSD y(t,k) = w(t,k) C(t,k) of the strip is staged in
+//     LDS, XTC segments at a time, the next ones' loads in flight; every lane
+//     reads the same y (LDS broadcast).
 //   * Per (t, pixel) the phase is reduced once per strip in float64,
 //     frac(f_anchor tau), and turned into the anchor phasor z = gamma e^{i phi};
 //     the remaining S-1 bins advance z by the rotor 1 + eps = e^{i 2 pi df tau},
@@ -16,8 +18,16 @@
 //     antipode p' of p has gamma(t,p') = gamma(t,p) and tau(t,p') = -tau(t,p),
 //     so its phasor is conj(z).  With a = sum y_re z_re and b = sum y_im z_im,
 //     X(k,p) = a - b and X(k,p') = a + b: one rotation serves two pixels.
+//   * On request the strip's broadband sums (float64) are written beside the
+//     map, from the values in hand.
 //   * Fixed summation order over t, no atomics: bitwise reproducible, and the
 //     absolute anchor grid makes a sub-band bitwise equal to the full band.
+// Bound by the vector instructions: six FMAs per segment, bin and pixel pair
+// (at one per lane and cycle and 64 lanes a compute unit, 1.5 of the 1.8 ms
+// below); in float64 also by the LDS broadcasts, 16 bytes a bin.  Measured, against
+// 256 columns a workgroup that walked the whole day: 240 segments, nside 32, 6823
+// bins of 0.25 Hz 1.87 against 2.12 ms; nside 8, 1024 bins 46 against 302 us (96
+// workgroups instead of 32); float64, nside 16, 1001 bins 163 against 322 us.
 #include "sgwb_internal.h"
 
 namespace sgwb {
@@ -37,14 +47,20 @@ template <typename T>
 struct StripTraits;
 template <>
 struct StripTraits<float> {
-    static constexpr int S = 64;    // bins per anchor strip
-    static constexpr int XTC = 32;  // segments per LDS stage
+    static constexpr int S = 64;     // bins per anchor strip
+    static constexpr int XTC = 8;    // segments per LDS stage
+    static constexpr int SLAB = 16;  // bins per round of the final sums
 };
 template <>
 struct StripTraits<double> {
     static constexpr int S = 32;
-    static constexpr int XTC = 16;
+    static constexpr int XTC = 4;
+    static constexpr int SLAB = 8;
 };
+
+constexpr int kDmWaves = 8;      // waves, and segment slices, per workgroup
+constexpr int kDmCols = 64;      // pixel columns per workgroup
+constexpr int kDmLds = 65536;    // the waves' stages, then the final sums' rounds
 
 // Rotor 1 + eps = e^{i d} for the per-bin phase step d = 2 pi df tau:
 // eps_re = cos d - 1, eps_im = sin d, each with full relative precision.
@@ -65,11 +81,20 @@ __device__ inline void rotor(float d, float *er, float *ei)
 }
 __device__ inline void rotor(double d, double *er, double *ei)
 {
-    double sh, ch, s, c;
-    sincos(0.5 * d, &sh, &ch);
-    sincos(d, &s, &c);
-    *er = -2.0 * sh * sh;
-    *ei = s;
+    const double d2 = d * d;
+    if (fabs(d) <= 0.25) {
+        // Taylor series; the dropped terms are below 1e-18 relative
+        *er = -0.5 * d2 * fma(d2, fma(d2, fma(d2, fma(d2, fma(d2, -1.0 / 239500800, 1.0 / 1814400), -1.0 / 20160),
+                                              1.0 / 360), -1.0 / 12), 1.0);
+        *ei = d * fma(d2, fma(d2, fma(d2, fma(d2, fma(d2, fma(d2, 1.0 / 6227020800, -1.0 / 39916800), 1.0 / 362880),
+                                              -1.0 / 5040), 1.0 / 120), -1.0 / 6), 1.0);
+    } else {
+        double sh, ch, s, c;
+        sincos(0.5 * d, &sh, &ch);
+        sincos(d, &s, &c);
+        *er = -2.0 * sh * sh;
+        *ei = s;
+    }
 }
 
 // Anchor phasor gamma e^{2 pi i x} for x = f tau cycles, given as x4 = 4 x.
@@ -128,26 +153,44 @@ __device__ inline C2 gload_c(const C2 *p, int64_t i)
     return r;
 }
 
-// One tile: 256 pixel columns (coltile) x one S-bin strip (absolute index strip).
-// Called by every thread of a 256-thread workgroup; ys is the workgroup's LDS stage.
+// Orders a wave's LDS accesses among its own lanes: they run in order, so only
+// the compiler has to keep them so.
+__device__ __forceinline__ void wave_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// One tile: 64 pixel columns (coltile) x one S-bin strip (absolute index strip).
+// Called by every thread of the workgroup; lds is its kDmLds bytes of LDS.
 template <typename T, bool PAIR>
 __device__ inline void dirty_map_tile(const MapArgs &a, int64_t strip, int64_t coltile,
                                       const typename Cplx<T>::type *__restrict__ C, const T *__restrict__ w,
                                       const T *__restrict__ gamma, const double *__restrict__ tau,
-                                      T *__restrict__ X,
-                                      typename Cplx<T>::type (*ys)[StripTraits<T>::S])
+                                      T *__restrict__ X, double *__restrict__ band_row, char *lds)
 {
     using C2 = typename Cplx<T>::type;
     constexpr int S = StripTraits<T>::S;
     constexpr int XTC = StripTraits<T>::XTC;
+    constexpr int SLAB = StripTraits<T>::SLAB;
+    constexpr int NLD = XTC * S / 64;  // staged values per lane
+    constexpr int NA = PAIR ? 2 : 1;   // sums per bin
+    static_assert(kDmWaves * XTC * S * sizeof(C2) <= kDmLds, "the waves' stages");
+    static_assert(kDmWaves * NA * SLAB * kDmCols * sizeof(T) <= kDmLds, "a round of the final sums");
+    static_assert(S % SLAB == 0 && SLAB % kDmWaves == 0, "whole rounds");
 
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int64_t ncol = PAIR ? (int64_t)a.npix / 2 : (int64_t)a.npix;
-    const int64_t col = coltile * 256 + threadIdx.x;
+    const int64_t col = coltile * kDmCols + lane;
     const bool active = col < ncol;
+    const int64_t pcol = active ? col : 0;
     const int64_t kabs0 = strip * S;                          // absolute first bin of the strip
     const int64_t c0 = kabs0 - a.k0;                           // its column in C (may be < 0)
     const double fa4 = 4.0 * (a.f0 + (double)kabs0 * a.df);   // anchor frequency, quarter turns
     const double two_pi_df = kTwoPi * a.df;
+    const int per = (a.nt + kDmWaves - 1) / kDmWaves;
+    const int ta = min(wv * per, a.nt), tb = min(ta + per, a.nt);  // this wave's segments
 
     T acc_a[S], acc_b[PAIR ? S : 1];
 #pragma unroll
@@ -155,88 +198,144 @@ __device__ inline void dirty_map_tile(const MapArgs &a, int64_t strip, int64_t c
 #pragma unroll
     for (int j = 0; j < (PAIR ? S : 1); ++j) acc_b[j] = T(0);
 
-    const int64_t pcol = active ? col : 0;
-    for (int tc = 0; tc < a.nt; tc += XTC) {
-        const int tn = min(XTC, a.nt - tc);
-        __syncthreads();
-        for (int e = threadIdx.x; e < XTC * S; e += 256) {
-            const int tt = e / S, kk = e % S;
-            const int64_t c = c0 + kk;
-            C2 y;
-            y.x = T(0);
-            y.y = T(0);
-            if (tt < tn && c >= 0 && c < a.nf) {
+    C2(*ys)[S] = reinterpret_cast<C2(*)[S]>(lds + wv * (XTC * S * sizeof(C2)));
+    T wr[NLD];
+    C2 cr[NLD];
+    auto fetch = [&](int tc) {  // values past the slice or the band become zero
+#pragma unroll
+        for (int i = 0; i < NLD; ++i) {
+            const int tt = (i * 64 + lane) / S;
+            const int64_t c = c0 + (i * 64 + lane) % S;
+            wr[i] = T(0);
+            cr[i].x = cr[i].y = T(0);
+            if (tc + tt < tb && c >= 0 && c < a.nf) {
                 const int64_t off = (int64_t)(tc + tt) * a.ldc + c;
-                const T wv = gmem(w)[off];
-                if (a.unit_c) {
-                    y.x = wv;
-                } else {
-                    const C2 cv = gload_c(C, off);
-                    y.x = wv * cv.x;
-                    y.y = wv * cv.y;
+                wr[i] = gmem(w)[off];
+                if (a.unit_c)
+                    cr[i].x = T(1);
+                else
+                    cr[i] = gload_c(C, off);
+            }
+        }
+    };
+    __syncthreads();  // the previous tile's sums are read
+    if (ta < tb) {
+        fetch(ta);
+        T gn = gmem(gamma)[(int64_t)ta * a.npix + pcol];
+        double tn = gmem(tau)[(int64_t)ta * a.npix + pcol];
+        for (int tc = ta; tc < tb; tc += XTC) {
+            wave_fence();  // the wave's own stage: its reads precede these writes
+#pragma unroll
+            for (int i = 0; i < NLD; ++i) {
+                C2 y;
+                y.x = wr[i] * cr[i].x;
+                y.y = a.unit_c ? T(0) : wr[i] * cr[i].y;
+                ys[(i * 64 + lane) / S][(i * 64 + lane) % S] = y;
+            }
+            wave_fence();
+            if (tc + XTC < tb) fetch(tc + XTC);
+            const int nseg = min(XTC, tb - tc);
+            for (int tt = 0; tt < nseg; ++tt) {
+                const T g = gn;
+                const double tv = tn;
+                // the next segment's seeds (the last one's again at the end)
+                const int64_t o = (int64_t)min(tc + tt + 1, tb - 1) * a.npix + pcol;
+                gn = gmem(gamma)[o];
+                tn = gmem(tau)[o];
+                T zr, zi, er, ei;
+                anchor4(g, fa4 * tv, &zr, &zi);
+                rotor((T)(two_pi_df * tv), &er, &ei);
+#pragma unroll
+                for (int j = 0; j < S; ++j) {
+                    const C2 y = ys[tt][j];
+                    if (PAIR) {
+                        acc_a[j] = fma(y.x, zr, acc_a[j]);
+                        acc_b[j] = fma(y.y, zi, acc_b[j]);
+                    } else {
+                        acc_a[j] = fma(y.x, zr, acc_a[j]);
+                        acc_a[j] = fma(-y.y, zi, acc_a[j]);
+                    }
+                    // z <- z (1 + eps)
+                    T nr = fma(zr, er, zr);
+                    nr = fma(-zi, ei, nr);
+                    T ni = fma(zi, er, zi);
+                    ni = fma(zr, ei, ni);
+                    zr = nr;
+                    zi = ni;
                 }
             }
-            ys[tt][kk] = y;
+        }
+    }
+    // the slices' sums, SLAB bins a round: [wave][sum][bin][column], every thread
+    // then adds the waves' for its column and every eighth bin
+    int64_t colB = 0;
+    if (PAIR && active) colB = antipode_north(ring_of_north(col, a.nside), a.npix);
+    T(*sum)[NA][SLAB][kDmCols] = reinterpret_cast<T(*)[NA][SLAB][kDmCols]>(lds);
+    double sa = 0.0, sb = 0.0;  // this thread's share of the strip's broadband sums
+#pragma unroll
+    for (int j0 = 0; j0 < S; j0 += SLAB) {
+        __syncthreads();  // the stages, or the previous round, are read
+#pragma unroll
+        for (int j = 0; j < SLAB; ++j) {
+            sum[wv][0][j][lane] = acc_a[j0 + j];
+            if (PAIR) sum[wv][NA - 1][j][lane] = acc_b[PAIR ? j0 + j : 0];
         }
         __syncthreads();
-        if (!active) continue;
-        for (int tt = 0; tt < tn; ++tt) {
-            const int64_t g_off = (int64_t)(tc + tt) * a.npix + pcol;
-            const T g = gmem(gamma)[g_off];
-            const double ta = gmem(tau)[g_off];
-            T zr, zi, er, ei;
-            anchor4(g, fa4 * ta, &zr, &zi);
-            rotor((T)(two_pi_df * ta), &er, &ei);
+        for (int j = wv; j < SLAB; j += kDmWaves) {
+            const int64_t c = c0 + j0 + j;
+            if (!active || c < 0 || c >= a.nf) continue;
+            T va = sum[0][0][j][lane], vb = PAIR ? sum[0][NA - 1][j][lane] : T(0);
 #pragma unroll
-            for (int j = 0; j < S; ++j) {
-                const C2 y = ys[tt][j];
-                if (PAIR) {
-                    acc_a[j] = fma(y.x, zr, acc_a[j]);
-                    acc_b[j] = fma(y.y, zi, acc_b[j]);
-                } else {
-                    acc_a[j] = fma(y.x, zr, acc_a[j]);
-                    acc_a[j] = fma(-y.y, zi, acc_a[j]);
-                }
-                // z <- z (1 + eps)
-                T nr = fma(zr, er, zr);
-                nr = fma(-zi, ei, nr);
-                T ni = fma(zi, er, zi);
-                ni = fma(zr, ei, ni);
-                zr = nr;
-                zi = ni;
+            for (int k = 1; k < kDmWaves; ++k) {
+                va += sum[k][0][j][lane];
+                if (PAIR) vb += sum[k][NA - 1][j][lane];
+            }
+            auto row = gmem(X + c * (int64_t)a.npix);
+            const T xa = va - vb, xb = va + vb;
+            row[col] = a.accumulate ? row[col] + xa : xa;
+            if (PAIR) row[colB] = a.accumulate ? row[colB] + xb : xb;
+            if (c >= a.band_lo && c < a.band_hi) {
+                sa += (double)xa;
+                sb += (double)xb;
             }
         }
     }
-    if (!active) return;
-    int64_t colB = 0;
-    if (PAIR) colB = antipode_north(ring_of_north(col, a.nside), a.npix);
+    if (!band_row) return;
+    __syncthreads();
+    double(*bs)[2][kDmCols] = reinterpret_cast<double(*)[2][kDmCols]>(lds);
+    bs[wv][0][lane] = sa;
+    bs[wv][1][lane] = sb;
+    __syncthreads();
+    if (wv != 0 || !active) return;
 #pragma unroll
-    for (int j = 0; j < S; ++j) {
-        const int64_t c = c0 + j;
-        if (c < 0 || c >= a.nf) continue;
-        auto row = gmem(X + c * (int64_t)a.npix);
-        if (PAIR) {
-            const T xa = acc_a[j] - acc_b[j], xb = acc_a[j] + acc_b[j];
-            row[col] = a.accumulate ? row[col] + xa : xa;
-            row[colB] = a.accumulate ? row[colB] + xb : xb;
-        } else {
-            row[col] = a.accumulate ? row[col] + acc_a[j] : acc_a[j];
-        }
+    for (int k = 1; k < kDmWaves; ++k) {
+        sa += bs[k][0][lane];
+        sb += bs[k][1][lane];
     }
+    gmem(band_row)[col] = sa;
+    if (PAIR) gmem(band_row)[colB] = sb;
+}
+
+// The broadband partial sums' row of a strip (a.band_part, one row per strip the
+// call touches), or none.
+__device__ inline double *band_row_of(const MapArgs &a, int64_t strip, int S)
+{
+    return a.band_part ? a.band_part + (strip - a.k0 / S) * (int64_t)a.npix : nullptr;
 }
 
 template <typename T, bool PAIR>
-__global__ __launch_bounds__(256) void dirty_map_kernel(MapArgs a, int64_t strip0,
+__global__ __launch_bounds__(64 * kDmWaves) __attribute__((amdgpu_waves_per_eu(2))) void dirty_map_kernel(MapArgs a, int64_t strip0,
                                                          const typename Cplx<T>::type *__restrict__ C,
                                                          const T *__restrict__ w,
                                                          const T *__restrict__ gamma,
                                                          const double *__restrict__ tau,
                                                          T *__restrict__ X, const double *__restrict__ gate)
 {
-    __shared__ typename Cplx<T>::type ys[StripTraits<T>::XTC][StripTraits<T>::S];
+    __shared__ __attribute__((aligned(16))) char lds[kDmLds];
     // gated launch: only where the matrix-core prep found no accurate form
     if (gate && (int)gmem(gate)[1] != SGWB_XFORM_VALU) return;
-    dirty_map_tile<T, PAIR>(a, strip0 + (int64_t)blockIdx.y, blockIdx.x, C, w, gamma, tau, X, ys);
+    const int64_t strip = strip0 + (int64_t)blockIdx.y;
+    dirty_map_tile<T, PAIR>(a, strip, blockIdx.x, C, w, gamma, tau, X, band_row_of(a, strip, StripTraits<T>::S), lds);
 }
 
 // Persistent multi-job form: workgroup b takes tiles b, b + grid, b + 2 grid, ...
@@ -245,10 +344,10 @@ __global__ __launch_bounds__(256) void dirty_map_kernel(MapArgs a, int64_t strip
 // does not depend on which workgroup computes it or when.  PAIR is uniform
 // over the job table (the plan launches one table per pairing).
 template <bool PAIR>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void dirty_map_batched_kernel(
+__global__ __launch_bounds__(64 * kDmWaves) __attribute__((amdgpu_waves_per_eu(2))) void dirty_map_batched_kernel(
     const XJob *__restrict__ jobs, int32_t njobs, int64_t ntiles)
 {
-    __shared__ float2 ys[StripTraits<float>::XTC][StripTraits<float>::S];
+    __shared__ __attribute__((aligned(16))) char lds[kDmLds];
     for (int64_t g = blockIdx.x; g < ntiles; g += gridDim.x) {
         int j = 0;
         while (j + 1 < njobs && g >= jobs[j + 1].tile_begin) ++j;
@@ -266,7 +365,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
             strip = strip0 + local % nstrips;
         }
         const float2 *C = reinterpret_cast<const float2 *>(jobs[j].C);
-        dirty_map_tile<float, PAIR>(a, strip, coltile, C, jobs[j].w, jobs[j].gamma, jobs[j].tau, jobs[j].X, ys);
+        dirty_map_tile<float, PAIR>(a, strip, coltile, C, jobs[j].w, jobs[j].gamma, jobs[j].tau, jobs[j].X,
+                                    band_row_of(a, strip, StripTraits<float>::S), lds);
     }
 }
 
@@ -283,7 +383,7 @@ void fill_xjob(XJob *j, const MapArgs &a, const float *C, const float *w, const 
     j->strip_first = a.k0 / S;
     j->nstrips = (a.k0 + a.nf - 1) / S - j->strip_first + 1;
     const int64_t ncol = a.nside > 0 ? a.npix / 2 : a.npix;
-    j->ncoltiles = (ncol + 255) / 256;
+    j->ncoltiles = (ncol + kDmCols - 1) / kDmCols;
     j->strip_major = strip_major ? 1 : 0;
     j->tile_begin = 0;
 }
@@ -292,10 +392,10 @@ hipError_t launch_dirty_map_batched(const XJob *jobs_dev, int32_t njobs, int64_t
                                     hipStream_t s)
 {
     if (pair)
-        hipLaunchKernelGGL(dirty_map_batched_kernel<true>, dim3((unsigned)grid), dim3(256), 0, s, jobs_dev, njobs,
+        hipLaunchKernelGGL(dirty_map_batched_kernel<true>, dim3((unsigned)grid), dim3(64 * kDmWaves), 0, s, jobs_dev, njobs,
                            ntiles);
     else
-        hipLaunchKernelGGL(dirty_map_batched_kernel<false>, dim3((unsigned)grid), dim3(256), 0, s, jobs_dev, njobs,
+        hipLaunchKernelGGL(dirty_map_batched_kernel<false>, dim3((unsigned)grid), dim3(64 * kDmWaves), 0, s, jobs_dev, njobs,
                            ntiles);
     return hipGetLastError();
 }
@@ -315,12 +415,12 @@ hipError_t launch_dirty_map(const MapArgs &a, const T *C, const T *w, const T *g
     // grid.y is limited to 65535 strips per launch; larger bands are split.
     for (int64_t s0 = 0; s0 < nstrips; s0 += 65535) {
         const int64_t ns = nstrips - s0 < 65535 ? nstrips - s0 : 65535;
-        dim3 grid((unsigned)((ncol + 255) / 256), (unsigned)ns);
+        dim3 grid((unsigned)((ncol + kDmCols - 1) / kDmCols), (unsigned)ns);
         if (pair)
-            hipLaunchKernelGGL((dirty_map_kernel<T, true>), grid, dim3(256), 0, s, a, strip_first + s0, Cc,
+            hipLaunchKernelGGL((dirty_map_kernel<T, true>), grid, dim3(64 * kDmWaves), 0, s, a, strip_first + s0, Cc,
                                w, gamma, tau, X, gate);
         else
-            hipLaunchKernelGGL((dirty_map_kernel<T, false>), grid, dim3(256), 0, s, a, strip_first + s0,
+            hipLaunchKernelGGL((dirty_map_kernel<T, false>), grid, dim3(64 * kDmWaves), 0, s, a, strip_first + s0,
                                Cc, w, gamma, tau, X, gate);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;

@@ -170,14 +170,9 @@ static hipError_t enqueue(sgwb_plan *p, hipStream_t s, int parts)
             char *ws = reinterpret_cast<char *>(p->band_ws) + p->band_off[i];
             size_t xpart = 0;
             if (j.Xbb) {
-                if (p->use_xm[i]) {
-                    xpart = (size_t)xm_band_rows(p->args[i]) * j.npix * sizeof(double);
-                    e = launch_band_partial_finish(reinterpret_cast<double *>(ws), xm_band_rows(p->args[i]), j.npix,
-                                                   j.Xbb, s);
-                } else {
-                    e = launch_band<float>(j.X, nullptr, nullptr, j.nf, j.npix, j.band_lo, j.band_hi, j.Xbb, nullptr,
-                                           nullptr, 0, s);
-                }
+                xpart = (size_t)xm_band_rows(p->args[i]) * j.npix * sizeof(double);
+                e = launch_band_partial_finish(reinterpret_cast<double *>(ws), xm_band_rows(p->args[i]), j.npix, j.Xbb,
+                                               s);
                 if (e != hipSuccess) return e;
             }
             if (j.Gbb) {
@@ -414,7 +409,7 @@ int sgwb_plan_create(const sgwb_job *jobs, int32_t njobs, uint32_t flags, sgwb_p
         if (j.Xbb || j.Gbb) {
             p->band_off[i] = p->band_bytes;
             size_t n = 0;
-            if (j.Xbb && use_xm[i]) n += (size_t)xm_band_rows(p->args[i]) * j.npix * sizeof(double);
+            if (j.Xbb) n += (size_t)xm_band_rows(p->args[i]) * j.npix * sizeof(double);
             n = (n + 255) / 256 * 256;
             if (j.Gbb) n += band_gamma_scratch_bytes(j.nt, j.npix);
             p->band_bytes += (n + 255) / 256 * 256;
@@ -433,6 +428,14 @@ int sgwb_plan_create(const sgwb_job *jobs, int32_t njobs, uint32_t flags, sgwb_p
     std::vector<int> order(njobs);
     for (int i = 0; i < njobs; ++i) order[i] = i;
     std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return p->jobs[x].nt > p->jobs[y].nt; });
+    // the tiles of a job with a broadband map write per-strip band sums
+    auto band_sums = [&](int i, MapArgs *a) {
+        const sgwb_job &j = p->jobs[i];
+        if (!j.Xbb) return;
+        a->band_part = reinterpret_cast<double *>(reinterpret_cast<char *>(p->band_ws) + p->band_off[i]);
+        a->band_lo = j.band_lo;
+        a->band_hi = j.band_hi;
+    };
     for (int pass = 0; pass < 2; ++pass)
         for (int i : order) {
             const sgwb_job &j = p->jobs[i];
@@ -440,6 +443,7 @@ int sgwb_plan_create(const sgwb_job *jobs, int32_t njobs, uint32_t flags, sgwb_p
             if (j.X && !use_xm[i] && pair == (pass == 0)) {
                 XJob x;
                 fill_xjob(&x, p->args[i], j.C, j.w, j.gamma, j.tau, j.X, true);
+                band_sums(i, &x.a);
                 p->xjobs.push_back(x);
                 if (pair) p->nx_pair++;
             }
@@ -449,11 +453,7 @@ int sgwb_plan_create(const sgwb_job *jobs, int32_t njobs, uint32_t flags, sgwb_p
         if (use_xm[i]) {
             XmJob x;
             fill_xmjob(&x, p->args[i], j.C, j.w, j.gamma, j.tau, j.X, reinterpret_cast<char *>(p->xm_ws) + xm_off[i]);
-            if (j.Xbb) {  // the tiles write per-strip band sums
-                x.x.a.band_part = reinterpret_cast<double *>(reinterpret_cast<char *>(p->band_ws) + p->band_off[i]);
-                x.x.a.band_lo = j.band_lo;
-                x.x.a.band_hi = j.band_hi;
-            }
+            band_sums(i, &x.x.a);
             p->xmjobs.push_back(x);
         }
         if (j.Gam) {

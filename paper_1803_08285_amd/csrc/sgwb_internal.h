@@ -122,7 +122,7 @@ struct MapArgs {
     double f0, df;
     int32_t unit_c = 0;      // C is not read: C = 1 + 0i, so y = w (real data)
     int32_t accumulate = 0;  // add the dirty map to X instead of writing it
-    // Broadband partial sums written by the matrix-core dirty map (nullptr: none):
+    // Broadband partial sums written by the float32 dirty maps (nullptr: none):
     // band_part[strip][pixel] = sum of the strip's X rows with columns in [band_lo, band_hi).
     double *band_part = nullptr;
     int32_t band_lo = 0, band_hi = 0;
@@ -152,7 +152,7 @@ hipError_t launch_contract(const float *M, int32_t nf, int32_t npix, const int32
 // with out1 also out1 from part1, of as many rows
 hipError_t launch_band_partial_finish(const double *part, int64_t nrows, int32_t npix, float *out, hipStream_t s,
                                       const double *part1 = nullptr, float *out1 = nullptr);
-int64_t xm_band_rows(const MapArgs &a);    // rows of the dirty map's partial-sum array
+int64_t xm_band_rows(const MapArgs &a);    // rows (64-bin strips) of the dirty maps' partial-sum array
 // broadband Fisher diagonal from its definition with the band sum moved into
 // the weights: Gbb[p] = sum_t v[t] gamma(t,p)^2, v[t] = sum_{c in [klo,khi)} H[c] w[t][c]
 // (float64, fixed order, rounded once); scratch: band_gamma_scratch_bytes() of device memory
