@@ -80,3 +80,24 @@ def test_beam_4x4_matches_2x4_bitwise(sg, tmp_path):
     got = np.load(dst)
     for i, G in enumerate(ref):
         assert np.array_equal(got[f"G{i}"], G), f"case {CASES[i]}"
+
+
+@pytest.mark.parametrize("nt,nf,npix", [(1, 1, 12), (3, 63, 65), (15, 64, 64), (17, 65, 100), (33, 130, 768)])
+def test_float64_beam_at_tile_edges(nt, nf, npix):
+    """The float64 Fisher diagonal at the edges of its 64 x 64 tiles and 16-segment
+    steps, for any pixels (no pairing): sums of at most 33 positive terms, so
+    within 64 units of 2^-53 of the exact value; padding adds nothing."""
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU")
+    import paper_1803_08285_amd as sg
+
+    rng = np.random.default_rng(nt * 1000 + nf)
+    w, g = rng.uniform(0.1, 2.0, (nt, nf)), rng.normal(size=(nt, npix))
+    C = torch.zeros((nt, nf), dtype=torch.complex128, device="cuda")
+    G = torch.full((nf, npix), -1.0, dtype=torch.float64, device="cuda")
+    sg.make_maps(C, torch.from_numpy(w).cuda(), sg.FGrid(20.0, 0.25), 0, torch.from_numpy(g).cuda(),
+                 torch.zeros((nt, npix), dtype=torch.float64, device="cuda"), antipodal=False, want_x=False,
+                 out=(None, G))
+    torch.cuda.synchronize()
+    ref = (w.astype(np.longdouble).T @ (g.astype(np.longdouble) ** 2)).astype(np.float64)
+    assert np.all(np.abs(G.cpu().numpy() - ref) <= 64 * 2.0 ** -53 * ref)
