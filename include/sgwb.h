@@ -333,7 +333,10 @@ int sgwb_fisher_full_general(const float *w, int64_t ldw, const float *H, int32_
  * float32 [n] (device); P float32 [n] (overwritten).  Vectors, dot products
  * and the matrix-vector products run in float64 with fixed-order sums; the
  * step scalars stay on the device (no host synchronisation).
- * Workspace: at least sgwb_clean_map_workspace_size() bytes, 256-byte aligned.
+ * Workspace: sgwb_clean_map_workspace_size() bytes, 256-byte aligned (for n up to
+ * 3072 it holds two sets of vectors, for one kernel per step; down to
+ * 4 n + ceil(n / 4) + 2 ceil(n / 256) float64 words are accepted and take three
+ * kernels, with the same bits).
  * Errors: SGWB_EINVAL (null pointer, n < 1, niter < 0, misaligned pointer),
  * SGWB_ENOMEM (workspace too small).                                          */
 size_t sgwb_clean_map_workspace_size(int32_t n);

@@ -523,10 +523,10 @@ int sgwb_clean_map_cg(const float *G, const float *X, int32_t n, int32_t niter, 
         return set_error(SGWB_EINVAL, "clean_map_cg: misaligned pointer");
     if (!workspace || (uintptr_t)workspace % 256)
         return set_error(SGWB_EINVAL, "clean_map_cg: workspace null or not 256-byte aligned");
-    if (workspace_bytes < cg_workspace_bytes(n))
+    if (workspace_bytes < cg_workspace_least(n))
         return set_error(SGWB_ENOMEM, "clean_map_cg: workspace of %zu bytes needed, %zu given",
-                         cg_workspace_bytes(n), workspace_bytes);
-    return check_hip(launch_clean_map_cg(G, X, n, niter, P, workspace, stream), "clean-map launch");
+                         cg_workspace_least(n), workspace_bytes);
+    return check_hip(launch_clean_map_cg(G, X, n, niter, P, workspace, workspace_bytes, stream), "clean-map launch");
 }
 
 int sgwb_make_maps_f64(const double *C, const double *w, int64_t ldc, int32_t nt, int32_t nf,

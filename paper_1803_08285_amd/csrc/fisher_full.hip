@@ -1655,7 +1655,9 @@ hipError_t launch_fisher_full_general(const float *w, int64_t ldw, const float *
 }
 
 // ---- conjugate gradient on G P = X (float64 vectors, fixed-order sums) ----
-// Three kernels per iteration: q = G p with the partial sums of p.q; the step
+// Up to kCgFusedMax unknowns (whole and aligned groups of four): one kernel per
+// iteration (cg_fused_kernel below).
+// Larger: three kernels per iteration: q = G p with the partial sums of p.q; the step
 // (every block adds the p.q partials itself, in one fixed order, so all agree
 // on alpha) with the partial sums of r.r; the new direction (likewise for
 // beta).  The scalars never leave the device.
@@ -1801,15 +1803,272 @@ __global__ __launch_bounds__(256) void cg_out_kernel(const double *__restrict__ 
     if (j < n) P[j] = (float)x[j];
 }
 
-size_t cg_workspace_bytes(int32_t n)
+// One iteration in one kernel, for vectors that a workgroup holds in registers.
+// Every workgroup forms the whole of the step from the last iteration's vectors:
+//   alpha = rr / pq, r' = r - alpha q, rr' = r'.r', p' = r' + (rr' / rr) p,
+// then its own rows: q' = G p', their shares of p'.q', x + alpha p, and stores r',
+// p', q', x there.  Vectors and partial sums alternate between two sets, so a
+// workgroup never reads what another writes.  Every sum runs in the order of the
+// three-kernel form below, so the iterates are the same bits (an iterate of an
+// ill-conditioned matrix can turn a last bit into its leading ones).  That form
+// is bound by its launches (nside 16: 5.8 + 4.0 + 2.7 us and the gaps between
+// them, 15 us an iteration, of which the matrix's 38 MB are ~5); this takes 10.3
+// us (nside 8: 6 against 11), its own latencies: two sums over the workgroup
+// before the matrix's rows can be used.  More threads a workgroup were slower
+// (384 threads 214 us, 768 306 for 20 iterations at nside 16, 256 192).  At nside
+// 32 every workgroup would read 300 KB of vectors beside its rows: 149 us an
+// iteration against 114, so it keeps three kernels.
+constexpr int kCgThreads = 256;
+constexpr int32_t kCgFusedMax = 3072;
+
+struct CgSet {  // one set of the iteration's vectors, the shares of p.q (four rows each) and r.r
+    double *r, *p, *q, *pq, *rr;
+};
+
+// The sum of one value a thread, the same in every thread, as cg_block_sum's
+// tree adds them: the waves first, then the lanes (a butterfly gives every lane
+// the tree's bits).
+__device__ __forceinline__ double cg_tree(double v, double *red)
+{
+    red[threadIdx.x] = v;
+    __syncthreads();
+    const int l = threadIdx.x & 63;
+    double s = (red[l] + red[l + 128]) + (red[l + 64] + red[l + 192]);
+#pragma unroll
+    for (int h = 32; h > 0; h >>= 1) s += __shfl_xor(s, h);
+    __syncthreads();
+    return s;
+}
+
+// r.r as the three-kernel form adds it: a tree over each 256 consecutive
+// elements (those of one wave and column group: lane l holds 4 l .. 4 l + 3), then
+// a tree over those sums.  Lanes take over two, then one of the four elements
+// each, so that nine exchanges a group do.  part: 16 words of LDS.
+template <int CH>
+__device__ __forceinline__ double cg_square(const double (&r)[CH][4], double *part)
+{
+    static_assert(4 * CH <= 16, "at most 16 blocks of 256");
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    if (threadIdx.x < 16) part[threadIdx.x] = 0.0;
+    __syncthreads();
+    const bool b5 = lane & 32, b4 = lane & 16;
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+        double v[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            v[e] = r[c][e] * r[c][e];
+            asm volatile("" : "+v"(v[e]));  // the rounded square: not fused into the sum
+        }
+        double a0 = (b5 ? v[2] : v[0]) + __shfl_xor(b5 ? v[0] : v[2], 32);
+        double a1 = (b5 ? v[3] : v[1]) + __shfl_xor(b5 ? v[1] : v[3], 32);
+        double a = (b4 ? a1 : a0) + __shfl_xor(b4 ? a0 : a1, 16);
+#pragma unroll
+        for (int h = 8; h > 0; h >>= 1) a += __shfl_xor(a, h);
+        a += __shfl_xor(a, 32);
+        a += __shfl_xor(a, 16);
+        if (lane == 0) part[wv + 4 * c] = a;
+    }
+    __syncthreads();
+    double s = part[lane & 15];
+#pragma unroll
+    for (int h = 8; h > 0; h >>= 1) s += __shfl_xor(s, h);
+    return s;
+}
+
+__device__ __forceinline__ double cg_ratio(double num, double den, double guard)
+{
+    return den != 0.0 && guard != 0.0 ? num / den : 0.0;
+}
+
+// CH: groups of four consecutive columns per thread; ROWS per workgroup, the
+// first AHEAD of them loaded before the step is formed.  n % 4 = 0.
+template <int CH, int ROWS, int AHEAD>
+__global__ __launch_bounds__(kCgThreads) void cg_fused_kernel(const float *__restrict__ G,
+                                                              const float *__restrict__ X, int32_t n, int32_t first,
+                                                              int32_t npart, CgSet in, CgSet out,
+                                                              double *__restrict__ x)
+{
+    static_assert(ROWS % 4 == 0, "shares of four rows");
+    __shared__ double red[kCgThreads], part[16], sums[kCgThreads / 64][ROWS][64], rowp[ROWS], rowq[ROWS];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int32_t r0 = blockIdx.x * ROWS;
+    // first column of group c; past the last: the last group again, with zeros in
+    // the vectors
+    auto col = [&](int c) { return 4 * ((int32_t)threadIdx.x + c * kCgThreads); };
+    auto load_row = [&](int i, float4 (&g)[CH]) {
+        const float *row = G + (int64_t)min(r0 + i, n - 1) * n;
+#pragma unroll
+        for (int c = 0; c < CH; ++c) g[c] = *reinterpret_cast<const float4 *>(row + min(col(c), n - 4));
+    };
+    auto load_cols = [&](const double *src, int c, double (&d)[4]) {
+        const double2 *v = reinterpret_cast<const double2 *>(src + min(col(c), n - 4));
+        const double2 lo = v[0], hi = v[1];
+        d[0] = lo.x;
+        d[1] = lo.y;
+        d[2] = hi.x;
+        d[3] = hi.y;
+    };
+    float4 g[AHEAD][CH];
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i) load_row(i, g[i]);
+    double p[CH][4], alpha = 0.0, beta = 0.0;
+    if (first) {  // p = r = X
+#pragma unroll
+        for (int c = 0; c < CH; ++c)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) p[c][e] = col(c) < n ? (double)X[col(c) + e] : 0.0;
+        const double rr = cg_square<CH>(p, part);
+        if (blockIdx.x == 0 && threadIdx.x == 0) *out.rr = rr;
+    } else {
+        double r[CH][4], q[CH][4], v = 0.0;
+        for (int32_t j = threadIdx.x; j < npart; j += kCgThreads) v += in.pq[j];
+        const double rr = *in.rr;
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            load_cols(in.r, c, r[c]);
+            load_cols(in.q, c, q[c]);
+            load_cols(in.p, c, p[c]);
+        }
+        const double pq = cg_tree(v, red);
+        alpha = cg_ratio(rr, pq, rr);
+#pragma unroll
+        for (int c = 0; c < CH; ++c)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const double rj = r[c][e] - alpha * q[c][e];
+                r[c][e] = col(c) < n ? rj : 0.0;
+            }
+        const double rrn = cg_square<CH>(r, part);
+        beta = cg_ratio(rrn, rr, rr);
+        if (blockIdx.x == 0 && threadIdx.x == 0) *out.rr = rrn;
+#pragma unroll
+        for (int c = 0; c < CH; ++c)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const double pj = r[c][e] + beta * p[c][e];
+                p[c][e] = col(c) < n ? pj : 0.0;
+            }
+    }
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) {
+        float4 h[CH];
+        if (i >= AHEAD) load_row(i, h);
+        double s = 0.0;
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            const float4 u = i < AHEAD ? g[i < AHEAD ? i : 0][c] : h[c];
+            const double t =
+                (double)u.x * p[c][0] + (double)u.y * p[c][1] + (double)u.z * p[c][2] + (double)u.w * p[c][3];
+            s += col(c) < n ? t : 0.0;
+        }
+        sums[wv][i][lane] = s;
+    }
+    __syncthreads();
+    // the rows' sums, ROWS / 4 a wave, as the tree adds them
+#pragma unroll
+    for (int k = 0; k < ROWS / 4; ++k) {
+        const int i = wv * (ROWS / 4) + k;
+        double s = (sums[0][i][lane] + sums[2][i][lane]) + (sums[1][i][lane] + sums[3][i][lane]);
+#pragma unroll
+        for (int h = 32; h > 0; h >>= 1) s += __shfl_xor(s, h);
+        if (lane == 0) rowq[i] = s;
+    }
+    __syncthreads();
+    // this workgroup's rows, one a thread, then their shares of p'.q'
+    if (threadIdx.x < ROWS) {
+        const int32_t row = r0 + threadIdx.x;
+        double pj = 0.0;
+        if (row < n) {
+            double rj;
+            if (first) {
+                rj = pj = (double)X[row];
+                x[row] = 0.0;
+            } else {
+                const double pold = in.p[row];
+                rj = in.r[row] - alpha * in.q[row];
+                pj = rj + beta * pold;
+                x[row] += alpha * pold;
+            }
+            out.r[row] = rj;
+            out.p[row] = pj;
+            out.q[row] = rowq[threadIdx.x];
+        }
+        rowp[threadIdx.x] = pj;
+    }
+    __syncthreads();
+    if (threadIdx.x < ROWS / 4 && r0 + 4 * (int)threadIdx.x < n) {
+        double d = 0.0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) d += rowp[4 * threadIdx.x + i] * rowq[4 * threadIdx.x + i];
+        out.pq[blockIdx.x * (ROWS / 4) + threadIdx.x] = d;
+    }
+}
+
+// P = x + alpha p, with the last iteration's alpha
+__global__ __launch_bounds__(kCgThreads) void cg_fused_out_kernel(CgSet in, const double *__restrict__ x, int32_t n,
+                                                                  int32_t npart, float *__restrict__ P)
+{
+    __shared__ double red[kCgThreads];
+    double v = 0.0;
+    for (int32_t j = threadIdx.x; j < npart; j += kCgThreads) v += in.pq[j];
+    const double pq = cg_tree(v, red), rr = *in.rr, alpha = cg_ratio(rr, pq, rr);
+    const int32_t j = blockIdx.x * kCgThreads + threadIdx.x;
+    if (j < n) P[j] = (float)(x[j] + alpha * in.p[j]);
+}
+
+size_t cg_workspace_least(int32_t n)
 {
     const size_t nb = ((size_t)n + 255) / 256, nm = ((size_t)n + kCgRows - 1) / kCgRows;
     return (4 * (size_t)n + nm + 2 * nb) * sizeof(double);
 }
 
-hipError_t launch_clean_map_cg(const float *G, const float *X, int32_t n, int32_t niter, float *P, void *work,
-                               hipStream_t s)
+// A set's shares of p.q and its rr, in an even number of words (the vectors of
+// the next set stay 16-byte aligned).
+static size_t cg_set_tail(size_t nm) { return (nm + 2) / 2 * 2; }
+
+static bool cg_fused(int32_t n) { return n % 4 == 0 && n <= kCgFusedMax; }
+
+size_t cg_workspace_bytes(int32_t n)
 {
+    if (!cg_fused(n)) return cg_workspace_least(n);
+    return (7 * (size_t)n + 2 * cg_set_tail((size_t)n / kCgRows)) * sizeof(double);
+}
+
+static hipError_t launch_cg_fused(const float *G, const float *X, int32_t n, int32_t niter, float *P, double *work,
+                                  hipStream_t s)
+{
+    // rows per workgroup: enough workgroups for every unit, and no more, since
+    // each reads all of the vectors
+    const bool small = n <= 1024;
+    const int rows = small ? 4 : 8;
+    const int32_t nm = n / kCgRows;
+    double *x = work;
+    CgSet set[2];
+    double *w = x + n;
+    for (CgSet &c : set) {
+        c.r = w;
+        c.p = w + n;
+        c.q = w + 2 * (size_t)n;
+        c.pq = w + 3 * (size_t)n;
+        c.rr = c.pq + nm;
+        w = c.pq + cg_set_tail((size_t)nm);
+    }
+    auto *kern = small ? cg_fused_kernel<1, 4, 4> : cg_fused_kernel<3, 8, 4>;
+    for (int32_t it = 0; it < niter; ++it)
+        hipLaunchKernelGGL(kern, dim3((unsigned)((n + rows - 1) / rows)), dim3(kCgThreads), 0, s, G, X, n,
+                           (int32_t)(it == 0), nm, set[(it + 1) & 1], set[it & 1], x);
+    hipLaunchKernelGGL(cg_fused_out_kernel, dim3((unsigned)((n + kCgThreads - 1) / kCgThreads)), dim3(kCgThreads), 0,
+                       s, set[(niter + 1) & 1], (const double *)x, n, nm, P);
+    return hipGetLastError();
+}
+
+hipError_t launch_clean_map_cg(const float *G, const float *X, int32_t n, int32_t niter, float *P, void *work,
+                               size_t work_bytes, hipStream_t s)
+{
+    // (a workspace of the least size takes the three-kernel form)
+    if (niter > 0 && cg_fused(n) && work_bytes >= cg_workspace_bytes(n) && reinterpret_cast<uintptr_t>(G) % 16 == 0)
+        return launch_cg_fused(G, X, n, niter, P, reinterpret_cast<double *>(work), s);
     const int32_t nb = (n + 255) / 256, nm = (n + kCgRows - 1) / kCgRows;
     double *x = reinterpret_cast<double *>(work), *r = x + n, *p = r + n, *q = p + n;
     double *pq_part = q + n, *rr_a = pq_part + nm, *rr_b = rr_a + nb;  // r.r partials, this and the next iterate

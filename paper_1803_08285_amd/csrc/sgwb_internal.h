@@ -170,9 +170,10 @@ hipError_t launch_fisher_full(const float *a, const float *b, int32_t rank, cons
                               int32_t chi, double f0, double df, int64_t k0, const float *gamma, const double *tau,
                               int32_t nt, int32_t npix, int64_t nside, float *G, void *work, size_t work_bytes,
                               hipStream_t s);
-size_t cg_workspace_bytes(int32_t n);
+size_t cg_workspace_bytes(int32_t n);  // what a call should get
+size_t cg_workspace_least(int32_t n);  // the least it takes (more kernels an iteration)
 hipError_t launch_clean_map_cg(const float *G, const float *X, int32_t n, int32_t niter, float *P, void *work,
-                               hipStream_t s);
+                               size_t work_bytes, hipStream_t s);
 
 // Folding of several sidereal days into one (float32 in and out, float64 sums).
 hipError_t launch_fold(const float *C, const float *sv, const uint8_t *present, int64_t ldc, int32_t ndays, int32_t nt,

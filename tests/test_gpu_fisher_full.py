@@ -282,3 +282,29 @@ def test_fisher_full_stream_and_persistent_forms_agree_bitwise(sg, monkeypatch, 
     monkeypatch.delenv("SGWB_FISHER_ONE_TABLE")
     torch.cuda.synchronize()
     assert torch.equal(G1, G2)
+
+
+@pytest.mark.parametrize("n,niter", [(1, 1), (4, 2), (1023, 3), (1024, 8), (1025, 8), (2047, 2), (3072, 9), (3073, 9)])
+def test_clean_map_cg_forms_vs_oracle(sg, oracle_mod, n, niter):
+    """The clean map at the edges of its one-kernel form (columns per thread, rows
+    per workgroup) and in the three-kernel form that a workspace of the least
+    size, or a matrix that is not 16-byte aligned, takes: within 1e-6 of the
+    oracle's iterate of the same matrix; one kernel or three, the same bits."""
+    rng = np.random.default_rng(n)
+    M = rng.standard_normal((n, min(n, 400) + 7)).astype(np.float32)
+    A = M @ M.T / n + 0.2 * np.eye(n, dtype=np.float32)
+    A = np.triu(A) + np.triu(A, 1).T
+    X = rng.standard_normal(n).astype(np.float32)
+    Po = oracle_mod.cg(A.astype(np.float64), X.astype(np.float64), niter)
+    Xd = torch.from_numpy(X).cuda()
+    buf = torch.empty(n * n + 1, device="cuda")
+    least = (4 * n + -(-n // 4) + 2 * -(-n // 256)) * 8
+    for off, ws in ((0, None), (1, None), (0, torch.empty(least, dtype=torch.uint8, device="cuda"))):
+        G = buf[off:off + n * n].view(n, n)
+        G.copy_(torch.from_numpy(A))
+        print(f"n {n} offset {off} workspace {ws is not None}", flush=True)
+        P = sg.clean_map_cg(G, Xd, niter, workspace=ws)
+        torch.cuda.synchronize()
+        P0 = P if ws is None and off == 0 else P0
+        assert off or torch.equal(P, P0)
+        assert np.linalg.norm(P.double().cpu().numpy() - Po) <= 1e-6 * np.linalg.norm(Po)
