@@ -73,11 +73,15 @@ __device__ __forceinline__ double band_weight(const float *__restrict__ row, con
         for (int i = 0; i < n; ++i) lane[i] += lane[i + n];
     red[threadIdx.x] = lane[0];
     __syncthreads();
-    for (int st = THREADS / 2; st > 0; st >>= 1) {
+    for (int st = THREADS / 2; st >= 64; st >>= 1) {
         if ((int)threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
         __syncthreads();
     }
-    return red[0];
+    // the first wave's lanes: the same pairs (a butterfly, so thread 0 has the tree's sum)
+    double sum = red[threadIdx.x & 63];
+#pragma unroll
+    for (int st = 32; st > 0; st >>= 1) sum += __shfl_xor(sum, st);
+    return sum;
 }
 
 // Xbb (and, with Gbb, Gbb) over columns [klo, khi) of C and w (absolute bins

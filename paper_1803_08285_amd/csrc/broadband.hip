@@ -33,6 +33,7 @@ constexpr double kBbPhaseStep = 0.03;
 constexpr int32_t kBbMaxHalf = 1 << 20;  // m: at most 2^21 + 3 nodes per table
 constexpr int kBbNodes = 64;  // table nodes per workgroup (one wave)
 constexpr int kBbBatch = 2;  // segments whose loads the map pass issues together
+constexpr int kBbRunBatch = 4;  // the same where a run is split over the waves
 
 bool bb_grid(int32_t nb, double df, double bound, BbGrid *g)
 {
@@ -161,16 +162,19 @@ static int32_t bb_cheb_nodes(int32_t nb, int32_t nt, const BbGrid &g)
 // weight.  The last kSymParts workgroups, with flags: the antipodal spot check.
 //
 // The tables through Chebyshev nodes (N > 0).  Node sums: thread (n, r) of R =
-// 256 / N takes node x_n = cos(pi (n + 1/2) / N) and the bins k = r mod R, by
-// Horner's rule in omega^R from the top bin down (|omega| = 1), the band staged
-// through LDS as y = w C in float64, the next stage's loads in flight; the R
-// partial sums are turned by omega^(r - kc) and added in order.  Then the
-// series' coefficients (cosine sums of the node values) and Clenshaw's
-// recurrence at every grid node, one node a thread.  Bound by the float64 FMAs
-// of the node sums (4 per bin and node) and the read of the band.  Full day,
-// 4096 bins, AB: 46 us (the direct sums over all 271 nodes 267 us); AC, 1531
-// bins: 26 against 101 us.  N = 0: a band of at most kBbStage bins, staged
-// once, Horner's rule at every grid node.
+// 256 / ceil(N / 2) takes the nodes x_n = cos(pi (n + 1/2) / N) and x_{N-1-n} =
+// -x_n, whose omega are conjugate, and the bins k = r mod R, by Horner's rule in
+// omega^R from the top bin down (|omega| = 1), the band staged through LDS as y =
+// w C in float64, the next stage's loads in flight; the R partial sums are turned
+// by omega^(r - kc) and added in a fixed order.  Then the series' coefficients
+// (cosine sums of the node values) and Clenshaw's recurrence at the grid's nodes,
+// two mirror images a thread (x and -x share the sums of the even and of the odd
+// terms).  Bound by the float64 FMAs of the node sums (4 per bin and node), the
+// LDS reads beside them (16 bytes per bin and two nodes) and the read of the
+// band.  Full day, 4096 bins, AB: 38 us (one node a thread 46 us, the direct
+// sums over all 271 nodes 267 us); AC, 1531 bins: 25 against 26 and 101 us.  N =
+// 0: a band of at most kBbStage bins, staged once, Horner's rule at every grid
+// node.
 __global__ __launch_bounds__(kBbTabThreads) void bb_prep_kernel(
     const float *__restrict__ C, const float *__restrict__ w, int64_t ldc, int32_t klo, int32_t nb, int32_t G,
     int32_t m, double dfh, int32_t N, float2 *__restrict__ T, const float *__restrict__ H, double *__restrict__ v,
@@ -190,11 +194,6 @@ __global__ __launch_bounds__(kBbTabThreads) void bb_prep_kernel(
         if (tid == 0) flags[part] = bad ? 1.0 : 0.0;
         return;
     }
-    if (v) {
-        const double sum = band_weight<kBbTabThreads>(w + (int64_t)t * ldc, H, klo, klo + nb,
-                                                      reinterpret_cast<double *>(stage));
-        if (tid == 0) v[t] = sum;
-    }
     const int64_t row = (int64_t)t * ldc + klo;
     const double kc = 0.5 * (nb - 1);
     auto bin = [&](int32_t k) {
@@ -202,10 +201,21 @@ __global__ __launch_bounds__(kBbTabThreads) void bb_prep_kernel(
         const double wv = (double)w[row + k];
         return make_double2(wv * (double)C[2 * (row + k)], wv * (double)C[2 * (row + k) + 1]);
     };
+    // threads per node pair, bins per stage (per for every residue r); the first
+    // (top) stage's values are under way before anything else
+    const int32_t half = (N + 1) / 2;
+    const int32_t R = N > 0 ? kBbTabThreads / half : 1, per = kBbStage / R, sb = per * R;
+    int32_t kb = N > 0 ? (nb - 1) / sb * sb : 0;
+    double2 y0 = bin(kb + tid), y1 = bin(kb + tid + kBbTabThreads);
+    if (v) {
+        const double sum = band_weight<kBbTabThreads>(w + (int64_t)t * ldc, H, klo, klo + nb,
+                                                      reinterpret_cast<double *>(stage));
+        if (tid == 0) v[t] = sum;
+    }
     if (N == 0) {
         __syncthreads();  // the weight's sums are read
-        stage[tid] = bin(tid);
-        stage[tid + kBbTabThreads] = bin(tid + kBbTabThreads);
+        stage[tid] = y0;
+        stage[tid + kBbTabThreads] = y1;
         __syncthreads();
         for (int32_t j = tid; j < G; j += kBbTabThreads) {
             const double at = dfh * (double)(j - m - 1);  // df tau_j
@@ -228,38 +238,37 @@ __global__ __launch_bounds__(kBbTabThreads) void bb_prep_kernel(
     }
     for (int32_t i = tid; i < 4 * N; i += kBbTabThreads) ct[i] = cospi(0.5 * i / N);
     __syncthreads();
-    for (int32_t n0 = 0; n0 < N; n0 += kBbTabThreads) {  // one pass unless N > 256
-        const int32_t nn = min(N - n0, kBbTabThreads), R = kBbTabThreads / nn;
-        const int32_t r = tid / nn, n = tid - r * nn;
+    {
+        const int32_t r = tid / half, n = tid - r * half;
         const bool active = r < R;
-        const double turns = dfh * (m + 1) * ct[2 * (n0 + n) + 1];  // df tau_n
+        const double turns = dfh * (m + 1) * ct[2 * n + 1];  // df tau_n
         double step = R * turns;
         step -= rint(step);
         double os, oc;
         sincospi(2.0 * step, &os, &oc);
-        const int32_t per = kBbStage / R, sb = per * R;  // bins per stage: per for every residue r
-        int32_t kb = (nb - 1) / sb * sb;
-        double2 y0 = bin(kb + tid), y1 = bin(kb + tid + kBbTabThreads);
-        double ar = 0.0, ai = 0.0;
+        double ar = 0.0, ai = 0.0, br = 0.0, bi = 0.0;  // at x_n and at -x_n
         for (; kb >= 0; kb -= sb) {
             __syncthreads();  // the previous stage's reads are done
             stage[tid] = y0;
             stage[tid + kBbTabThreads] = y1;  // past sb: not read
             __syncthreads();
+            const int32_t top = min(per - 1, (nb - 1 - kb) / R);  // bins past the band are zeros
             if (kb > 0) {
                 y0 = bin(kb - sb + tid);
                 y1 = bin(kb - sb + tid + kBbTabThreads);
             }
             if (active) {
-                // bins past the band were staged as zeros: above the top bin
-                // they keep the sum at exactly zero
 #pragma unroll 4
-                for (int32_t q = per - 1; q >= 0; --q) {
+                for (int32_t q = top; q >= 0; --q) {
                     const double2 y = stage[q * R + r];
                     const double nr = fma(ar, oc, fma(-ai, os, y.x));
                     const double ni = fma(ar, os, fma(ai, oc, y.y));
+                    const double mr = fma(br, oc, fma(bi, os, y.x));
+                    const double mi = fma(br, -os, fma(bi, oc, y.y));
                     ar = nr;
                     ai = ni;
+                    br = mr;
+                    bi = mi;
                 }
             }
         }
@@ -268,15 +277,27 @@ __global__ __launch_bounds__(kBbTabThreads) void bb_prep_kernel(
         double bs, bc;
         sincospi(2.0 * back, &bs, &bc);
         __syncthreads();
-        stage[tid] = make_double2(ar * bc - ai * bs, ar * bs + ai * bc);
+        // partial sums [node][r]: node n and, behind, node N - 1 - n
+        if (active) {
+            stage[n * R + r] = make_double2(ar * bc - ai * bs, ar * bs + ai * bc);
+            stage[(half + n) * R + r] = make_double2(br * bc + bi * bs, bi * bc - br * bs);
+        }
         __syncthreads();
-        if (tid < nn) {
-            double2 a = stage[tid];
-            for (int32_t q = 1; q < R; ++q) {
-                a.x += stage[q * nn + tid].x;
-                a.y += stage[q * nn + tid].y;
+        // up to eight lanes a node: every u-th partial sum, then a butterfly
+        int32_t u = 8;
+        while (u > 1 && 2 * half * u > kBbTabThreads) u >>= 1;
+        for (int32_t e = tid; e < 2 * half * u; e += kBbTabThreads) {
+            const int32_t q = e / u;
+            double2 a = make_double2(0.0, 0.0);
+            for (int32_t i = e % u; i < R; i += u) {
+                a.x += stage[q * R + i].x;
+                a.y += stage[q * R + i].y;
             }
-            node[n0 + tid] = a;
+            for (int32_t h = u / 2; h > 0; h >>= 1) {
+                a.x += __shfl_xor(a.x, h);
+                a.y += __shfl_xor(a.y, h);
+            }
+            if (e % u == 0) node[q < half ? q : N - 1 - (q - half)] = a;
         }
         __syncthreads();
     }
@@ -293,20 +314,32 @@ __global__ __launch_bounds__(kBbTabThreads) void bb_prep_kernel(
         }
         reinterpret_cast<double *>(coef)[e] = a * ((k ? 2.0 : 1.0) / N);
     }
+    if (tid == 0) coef[N] = make_double2(0.0, 0.0);  // an odd N's last pair
     __syncthreads();
-    for (int32_t j = tid; j < G; j += kBbTabThreads) {
-        const double x = (double)(j - m - 1) / (m + 1), x2 = 2.0 * x;
-        double br = 0.0, bi = 0.0, cr = 0.0, ci = 0.0;  // b_{k+1}, b_{k+2}
-        for (int32_t k = N - 1; k > 0; --k) {
-            const double2 a = coef[k];
-            const double nr = fma(x2, br, a.x - cr), ni = fma(x2, bi, a.y - ci);
-            cr = br;
-            ci = bi;
-            br = nr;
-            bi = ni;
+    float2 *Tc = T + (int64_t)t * G + (m + 1);  // the centre node
+    for (int32_t j = tid; j <= m + 1; j += kBbTabThreads) {
+        const double x = (double)j / (m + 1), y2 = 2.0 * (2.0 * x * x - 1.0);
+        // the even terms sum a_2k T_k(y) and the odd ones sum a_{2k+1} T_{2k+1}(x), by
+        // the same recurrence
+        double e1r = 0.0, e1i = 0.0, e2r = 0.0, e2i = 0.0, o1r = 0.0, o1i = 0.0, o2r = 0.0, o2i = 0.0;
+#pragma unroll 2
+        for (int32_t k = (N - 1) / 2; k >= 0; --k) {
+            const double2 ae = coef[2 * k], ao = coef[2 * k + 1];
+            const double er = fma(y2, e1r, ae.x - e2r), ei = fma(y2, e1i, ae.y - e2i);
+            const double dr = fma(y2, o1r, ao.x - o2r), di = fma(y2, o1i, ao.y - o2i);
+            e2r = e1r;
+            e2i = e1i;
+            e1r = er;
+            e1i = ei;
+            o2r = o1r;
+            o2i = o1i;
+            o1r = dr;
+            o1i = di;
         }
-        const double2 a = coef[0];
-        T[(int64_t)t * G + j] = make_float2((float)fma(x, br, a.x - cr), (float)fma(x, bi, a.y - ci));
+        const double er = fma(-0.5 * y2, e2r, e1r), ei = fma(-0.5 * y2, e2i, e1i);  // b_0 - y b_1
+        const double dr = x * (o1r - o2r), di = x * (o1i - o2i);                     // b_0 T_1 - b_1 T_{-1}
+        Tc[j] = make_float2((float)(er + dr), (float)(ei + di));
+        Tc[-j] = make_float2((float)(er - dr), (float)(ei - di));
     }
 }
 
@@ -482,19 +515,19 @@ __global__ __launch_bounds__(256) void bb_map_pair_kernel(const float *__restric
     const double inv_h = 1.0 / h, jmax = (double)(m - 1);
     double accA = 0.0, accB = 0.0, gacc = 0.0;
     bool bad = false;
-    for (int32_t tq = run.begin; tq < run.end; tq += kBbBatch) {
-        double ta[kBbBatch];
-        float g[kBbBatch];
+    for (int32_t tq = run.begin; tq < run.end; tq += kBbRunBatch) {
+        double ta[kBbRunBatch];
+        float g[kBbRunBatch];
 #pragma unroll
-        for (int e = 0; e < kBbBatch; ++e) {
+        for (int e = 0; e < kBbRunBatch; ++e) {
             const int64_t o = (int64_t)min(tq + e, run.end - 1) * npix + pc;
             ta[e] = tau[o];
             g[e] = gamma[o];
         }
-        BbAt at[kBbBatch];
-        float4 n[kBbBatch][4];
+        BbAt at[kBbRunBatch];
+        float4 n[kBbRunBatch][4];
 #pragma unroll
-        for (int e = 0; e < kBbBatch; ++e) {
+        for (int e = 0; e < kBbRunBatch; ++e) {
             at[e] = bb_at(ta[e], inv_h, jmax, fc);
             const float2 *row = T + (int64_t)min(tq + e, run.end - 1) * G + (m + 1);  // the centre node
 #pragma unroll
@@ -504,7 +537,7 @@ __global__ __launch_bounds__(256) void bb_map_pair_kernel(const float *__restric
             }
         }
 #pragma unroll
-        for (int e = 0; e < kBbBatch; ++e) {
+        for (int e = 0; e < kBbRunBatch; ++e) {
             const bool valid = e == 0 || tq + e < run.end;  // a segment past the run repeats its last
             bad |= !(fabs(ta[e]) <= bound);
             const float2 val = bb_pair_value(n[e], at[e], ta[e] < 0.0);
@@ -696,7 +729,7 @@ hipError_t launch_broadband_table_maps(const float *C, const float *w, int64_t l
     hipError_t e;
     if (N > 0 || (nb <= kBbStage && g.G <= kBbPrepNodes)) {
         hipLaunchKernelGGL(bb_prep_kernel, dim3((unsigned)(nt + (flags ? kSymParts : 0))), dim3(kBbTabThreads),
-                           8 * N * sizeof(double), s, C, w, ldc, klo, nb, g.G, g.m, df * g.h, N, T, H,
+                           (8 * N + 2) * sizeof(double), s, C, w, ldc, klo, nb, g.G, g.m, df * g.h, N, T, H,
                            Gbb ? v : (double *)nullptr, gamma, tau, nt, (int64_t)npix, nside, flags);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
