@@ -165,12 +165,33 @@ def _check(rc: int, what: str):
         raise SgwbError(f"{what}: {L.sgwb_status_string(rc).decode()} ({rc}): {L.sgwb_last_error().decode()}")
 
 
-def _stream(device=None) -> int:
-    return torch.cuda.current_stream(device).cuda_stream
+def _stream() -> int:
+    """The current stream of the current device.  (Its raw handle, without the
+    Stream object: a small query's call is bound by its host work.)"""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+
+
+class _on:
+    """``with _on(tensor)``: its device is current (torch.cuda.device for a tensor's
+    own device, whose index needs no look-up)."""
+
+    __slots__ = ("idx", "prev")
+
+    def __init__(self, t: torch.Tensor):
+        self.idx = t.get_device()
+        if self.idx < 0:
+            raise ValueError(f"Expected a cuda device, but got: {t.device}")
+
+    def __enter__(self):
+        self.prev = torch.cuda._exchange_device(self.idx)
+
+    def __exit__(self, *exc):
+        torch.cuda._maybe_exchange_device(self.prev)
+        return False
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _require(t: torch.Tensor, name: str, dtype, shape=None, cols_contig=True):
@@ -178,8 +199,8 @@ def _require(t: torch.Tensor, name: str, dtype, shape=None, cols_contig=True):
         raise SgwbError(f"{name} must be a device tensor")
     if t.dtype != dtype:
         raise SgwbError(f"{name} must be {dtype}, got {t.dtype}")
-    if shape is not None and tuple(t.shape) != tuple(shape):
-        raise SgwbError(f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
+    if shape is not None and t.shape != shape:
+        raise SgwbError(f"{name} has shape {tuple(t.shape)}, expected {shape}")
     if cols_contig and t.dim() == 2 and t.stride(1) != 1:
         raise SgwbError(f"{name} must have unit stride along its last axis")
 
@@ -238,7 +259,7 @@ def build_geometry(sites, nside: int, tgrid: TGrid, dtype=torch.float32, device=
     bl = _baseline(sites)
     tg = _TGrid(int(tgrid.nt), float(tgrid.t0), float(tgrid.stride), float(tgrid.dur))
     fn = lib().sgwb_build_geometry if dtype == torch.float32 else lib().sgwb_build_geometry_f64
-    with torch.cuda.device(gamma.device):
+    with _on(gamma):
         _check(fn(ctypes.byref(bl), int(nside), ctypes.byref(tg), _ptr(gamma), _ptr(tau), _stream()),
                "build_geometry")
     return gamma, tau
@@ -310,7 +331,7 @@ def make_maps(C: torch.Tensor, w: torch.Tensor, fgrid: FGrid, k0: int, gamma: to
     flags = (SGWB_MAPS_ANTIPODAL if antipodal else 0) | (SGWB_MAPS_VALU_X if x_kernel == "valu" else 0)
     fg = _FGrid(float(fgrid.f0), float(fgrid.df))
     Cr = torch.view_as_real(C)
-    with torch.cuda.device(dev):
+    with _on(C):
         if f64:
             rc = lib().sgwb_make_maps_f64(_ptr(Cr), _ptr(w), int(w.stride(0)), nt, nf, ctypes.byref(fg), int(k0),
                                           _ptr(gamma), _ptr(tau), npix, flags, _ptr(X), _ptr(G), _stream())
@@ -376,7 +397,7 @@ def make_maps_band(C: torch.Tensor, w: torch.Tensor, fgrid: FGrid, k0: int, gamm
         raise SgwbError("x_kernel must be 'auto' or 'valu'")
     flags = (SGWB_MAPS_ANTIPODAL if antipodal else 0) | (SGWB_MAPS_VALU_X if x_kernel == "valu" else 0)
     fg = _FGrid(float(fgrid.f0), float(fgrid.df))
-    with torch.cuda.device(dev):
+    with _on(C):
         if noalloc:
             if workspace is not None:
                 raise SgwbError("make_maps_band: noalloc takes no workspace")
@@ -456,7 +477,7 @@ def broadband_maps(C: torch.Tensor, w: torch.Tensor, fgrid: FGrid, k0: int, gamm
             _require_contig(t, name)
     flags = (SGWB_MAPS_ANTIPODAL if antipodal else 0) | _BB_ROUTES[route]
     fg = _FGrid(float(fgrid.f0), float(fgrid.df))
-    with torch.cuda.device(dev):
+    with _on(C):
         if workspace is None:
             need = broadband_maps_workspace_bytes(nt, nf, npix, fgrid, k_lo, k_hi, tau_bound, antipodal, route)
             workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=dev)
@@ -482,7 +503,7 @@ def network_sum(maps, out=None):
     _require(out, "out", torch.float32, shape)
     _require_contig(out, "out")
     arr = (ctypes.c_void_p * len(maps))(*[m.data_ptr() for m in maps])
-    with torch.cuda.device(dev):
+    with _on(maps[0]):
         rc = lib().sgwb_network_sum(arr, len(maps), int(out.numel()), _ptr(out), _stream())
     _check(rc, "network_sum")
     return out
@@ -503,7 +524,7 @@ def contract_pixels(M: torch.Tensor, pix: torch.Tensor | None = None, out=None):
         if nsel and (int(p.min()) < 0 or int(p.max()) >= npix):
             raise SgwbError("contract_pixels: pixel index out of range")
     out = torch.empty(nf, dtype=torch.float32, device=M.device) if out is None else out
-    with torch.cuda.device(M.device):
+    with _on(M):
         rc = lib().sgwb_contract_pixels(_ptr(M2), nf, npix, _ptr(p) if p is not None else None, nsel, _ptr(out),
                                         _stream())
     _check(rc, "contract_pixels")
@@ -543,7 +564,7 @@ def fold(C: torch.Tensor, sinv: torch.Tensor, present: torch.Tensor, W: float, o
                         ("x", x, torch.complex64)):
         _require(t, name, dt, (nt, nf))
         _require_contig(t, name)
-    with torch.cuda.device(dev):
+    with _on(sinv):
         rc = lib().sgwb_fold(_ptr(torch.view_as_real(C)), _ptr(sinv), _ptr(pres), int(sinv.stride(1)), ndays, nt, nf,
                              float(W), _ptr(v), _ptr(u), _ptr(w), _ptr(torch.view_as_real(x)), _stream())
     _check(rc, "fold")
@@ -577,7 +598,7 @@ def fisher_overlap(v: torch.Tensor, u: torch.Tensor, wn: torch.Tensor, fgrid: FG
     _require_contig(G, "Gam")
     flags = (SGWB_MAPS_ANTIPODAL if antipodal else 0) | (SGWB_MAPS_VALU_X if x_kernel == "valu" else 0)
     fg = _FGrid(float(fgrid.f0), float(fgrid.df))
-    with torch.cuda.device(dev):
+    with _on(v):
         if workspace is None:
             need = fisher_overlap_workspace_bytes(nt, nf, npix, antipodal)
             workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=dev)
@@ -618,7 +639,7 @@ def fisher_full(a: torch.Tensor, b: torch.Tensor, H: torch.Tensor, fgrid: FGrid,
     _require(G, "G", torch.float32, (npix, npix))
     _require_contig(G, "G")
     fg = _FGrid(float(fgrid.f0), float(fgrid.df))
-    with torch.cuda.device(dev):
+    with _on(gamma):
         if workspace is None:
             need = fisher_full_workspace_bytes(fgrid, k0, khi, nt, npix)
             workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=dev)
@@ -662,7 +683,7 @@ def fisher_full_general(w: torch.Tensor, H: torch.Tensor, fgrid: FGrid, k0: int,
     _require(G, "G", torch.float32, (npix, npix))
     _require_contig(G, "G")
     fg = _FGrid(float(fgrid.f0), float(fgrid.df))
-    with torch.cuda.device(dev):
+    with _on(gamma):
         if workspace is None:
             need = fisher_full_general_workspace_bytes(fgrid, k0, klo, khi, nt, npix, antipodal)
             workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=dev)
@@ -687,7 +708,7 @@ def clean_map_cg(G: torch.Tensor, X: torch.Tensor, niter: int, out=None, workspa
     P = out if out is not None else torch.empty(n, dtype=torch.float32, device=dev)
     _require(P, "P", torch.float32, (n,))
     _require_contig(P, "P")
-    with torch.cuda.device(dev):
+    with _on(X):
         if workspace is None:
             workspace = torch.empty(max(int(lib().sgwb_clean_map_workspace_size(n)), 256), dtype=torch.uint8,
                                     device=dev)
@@ -727,7 +748,7 @@ def reduce_band(X: torch.Tensor | None, G: torch.Tensor | None, H: torch.Tensor 
         Xbb = torch.empty(npix, dtype=rdt, device=ref.device)
     if G is not None and Gbb is None:
         Gbb = torch.empty(npix, dtype=rdt, device=ref.device)
-    with torch.cuda.device(ref.device):
+    with _on(ref):
         if rdt == torch.float64:
             rc = lib().sgwb_reduce_band_f64(_ptr(X), _ptr(G), _ptr(H) if G is not None else None, nf, npix,
                                             int(k_lo), int(k_hi), _ptr(Xbb), _ptr(Gbb), _stream())
