@@ -55,10 +55,12 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kXmS = 64;       // bins per strip
 constexpr int kXmT = 16;       // segments per chunk (MFMA K)
-constexpr int kXmParts = 8;    // m0h m0l m1h m1l m2h m2l m3 m4
-constexpr int kXmWaves = 8;    // waves per workgroup
+constexpr int kXmParts = 8;    // m0h m0l m1h m1l m2h m3 m4 m2l: a four-term form needs the first six
+constexpr int kXmWaves = 4;    // waves per workgroup
 constexpr int kXmPairs = 32 * kXmWaves;  // pixel pairs per workgroup
-constexpr int kXmFrags = 2 * 2 * kXmParts;  // component x bin block x part
+constexpr int kXmFrags = 2 * kXmParts * 2;  // component x part x bin block
+// place of term m's part in that order
+__host__ __device__ constexpr int xm_part(int m, bool lo) { return m < 2 ? 2 * m + lo : m == 2 ? (lo ? 7 : 4) : m + 2; }
 // per-term scale exponents 2^g_m (B side) and 2^-g_m (A side)
 __host__ __device__ constexpr int xm_g(int m) { return m == 0 ? 0 : m == 1 ? 2 : m == 2 ? 5 : m == 3 ? 9 : 14; }
 constexpr int kXmBShift = 12;  // common scale 2^12 of the pixel-side operands
@@ -74,13 +76,24 @@ __device__ __forceinline__ float rounded(float x)
 }
 
 
+// Fixed-point reduction of the phase (xm_phase).
+constexpr double kXmTurns = 1.5 * 1048576.0;  // 1.5 2^20: last place 2^-32
+constexpr double kXmMaxTurns = 524288.0;      // 2^19
+
 // Host check that a matrix-core form can apply: |eta| <= kXmEtaMax (where
 // 2 (eta/2)^5 / 120 <= 1e-6) for every delay of a baseline on the Earth
-// (|tau| <= 2 R / c, i.e. df <= 0.0344 Hz); tile indices in 32 bits.
+// (|tau| <= 2 R / c, i.e. df <= 0.0344 Hz); tile indices in 32 bits; the offsets
+// of a chunk's seeds in 32 bits (nside <= 1024); every phase below the range of
+// the fixed-point reduction, also for the delay differences of the overlap
+// terms (|tau'| <= 4 R / c: frequencies below 6e6 Hz).
 bool xm_eligible(const MapArgs &a)
 {
     const double eta_max = kTwoPi * 31.5 * a.df * 2.0 * kEarthRadius / kLightSpeed;
     if (a.nside <= 0 || !(eta_max <= kXmEtaMax)) return false;
+    if ((int64_t)(a.npix / 2) * 16 * kXmT > 0xffffffffll) return false;
+    const double fmax = std::max(std::fabs(a.f0 + a.df * (double)(a.k0 - kXmS)),
+                                 std::fabs(a.f0 + a.df * (double)(a.k0 + a.nf + kXmS)));
+    if (!(fmax * 4.0 * kEarthRadius / kLightSpeed < kXmMaxTurns)) return false;
     const int64_t nstrips = (a.k0 + a.nf - 1) / kXmS - a.k0 / kXmS + 1;
     const int64_t npblocks = (a.npix / 2 + kXmPairs - 1) / kXmPairs;
     return nstrips * npblocks <= 0x7fffffff;
@@ -197,11 +210,22 @@ __global__ __launch_bounds__(64 * kXmScaleWaves) void xm_scale_kernel(XmArgs x, 
     const int64_t c = (x.strip_first * kXmS + i) - x.a.k0;  // column in C
     float mx = 0.0f;
     if (c >= 0 && c < x.a.nf) {
-        for (int t = wv; t < x.a.nt; t += kXmScaleWaves) {
-            const int64_t off = (int64_t)t * x.a.ldc + c;
-            const float2 cv = x.a.unit_c ? make_float2(1.0f, 0.0f) : C[off];
-            const float wt = w[off];
-            mx = fmaxf(mx, fmaxf(fabsf(wt * cv.x), fabsf(wt * cv.y)));
+        // Eight segments a pass, so that their loads go out together: with one,
+        // the few workgroups of a sub-band wait out 56 memory latencies in a row.
+        // (Rows past the last read it again.)
+        constexpr int kBatch = 8;
+        for (int t0 = wv; t0 < x.a.nt; t0 += kXmScaleWaves * kBatch) {
+            float2 cv[kBatch];
+            float wt[kBatch];
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) {
+                const int64_t off = (int64_t)min(t0 + u * kXmScaleWaves, x.a.nt - 1) * x.a.ldc + c;
+                cv[u] = x.a.unit_c ? make_float2(1.0f, 0.0f) : C[off];
+                wt[u] = w[off];
+            }
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u)
+                mx = fmaxf(mx, fmaxf(fabsf(wt[u] * cv[u].x), fabsf(wt[u] * cv[u].y)));
         }
     }
     red[wv][lane] = mx;
@@ -230,10 +254,13 @@ __device__ __forceinline__ float cheb(int m, float s)
     }
 }
 
-// A fragments: [strip][chunk][comp][jb][part][lane] of uint4 (8 x f16, k = 8 (lane/32) + e).
+// A fragments: [strip][chunk][comp][part][jb][lane] of uint4 (8 x f16, k = 8 (lane/32) + e),
+// the parts that the call's form reads (none, if it is not a matrix-core form).
+// Bound by what it writes: 48 of the 64 bytes per segment, bin and component
+// in the four-term form.
 __global__ __launch_bounds__(256) void xm_afrag_kernel(XmArgs x, const float2 *__restrict__ C,
                                                        const float *__restrict__ w, const int *__restrict__ e_in,
-                                                       uint4 *__restrict__ A)
+                                                       const double *__restrict__ rec, uint4 *__restrict__ A)
 {
 #pragma clang fp contract(off)  // hi and lo from the same rounded float32 value
     const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -245,6 +272,8 @@ __global__ __launch_bounds__(256) void xm_afrag_kernel(XmArgs x, const float2 *_
     const int64_t strip = sc / x.nchunks, chunk = sc % x.nchunks;
     const int comp = cj >> 1, jb = cj & 1;
     if (comp && x.a.unit_c) return;  // real data: the second component is never read
+    const int form = (int)rec[1];
+    if (form != SGWB_XFORM_MFMA4 && form != SGWB_XFORM_MFMA5 && form != SGWB_XFORM_MFMA5S) return;
     const int j = jb * 32 + (lane & 31);
     const int64_t c = (x.strip_first + strip) * kXmS + j - x.a.k0;
     const int t0 = (int)chunk * kXmT + (lane >> 5) * 8;
@@ -262,9 +291,11 @@ __global__ __launch_bounds__(256) void xm_afrag_kernel(XmArgs x, const float2 *_
         }
         y[e] = v;
     }
-    uint4 *out = A + (sc * 4 + cj) * kXmParts * 64 + lane;
+    // streaming stores: 1.2-1.6 GB at the full band, read back only by the main kernel
+    u32x4 *out = reinterpret_cast<u32x4 *>(A) + (sc * kXmFrags + comp * kXmParts * 2 + jb) * 64 + lane;
 #pragma unroll
     for (int m = 0; m < 5; ++m) {
+        if (m == 4 && form == SGWB_XFORM_MFMA4) break;
         const float tm = cheb(m, s) * ldexpf(1.0f, -xm_g(m));
         h8 hi, lo;
 #pragma unroll
@@ -273,14 +304,9 @@ __global__ __launch_bounds__(256) void xm_afrag_kernel(XmArgs x, const float2 *_
             hi[e] = (_Float16)v;
             lo[e] = (_Float16)(v - (float)hi[e]);
         }
-        // streaming stores: 1.6 GB at the full band, read back only by the main kernel
-        u32x4 *o = reinterpret_cast<u32x4 *>(out);
-        if (m < 3) {
-            __builtin_nontemporal_store(__builtin_bit_cast(u32x4, hi), o + (2 * m) * 64);
-            __builtin_nontemporal_store(__builtin_bit_cast(u32x4, lo), o + (2 * m + 1) * 64);
-        } else {
-            __builtin_nontemporal_store(__builtin_bit_cast(u32x4, hi), o + (m + 3) * 64);
-        }
+        __builtin_nontemporal_store(__builtin_bit_cast(u32x4, hi), out + 2 * xm_part(m, false) * 64);
+        if (m < 2 || (m == 2 && form == SGWB_XFORM_MFMA5S))
+            __builtin_nontemporal_store(__builtin_bit_cast(u32x4, lo), out + 2 * xm_part(m, true) * 64);
     }
 }
 
@@ -292,21 +318,26 @@ struct XmItem {
     float a[5];
 };
 
-// The phase f_c tau is reduced to r = f_c tau - rint(f_c tau) in float64 (|f_c tau|
-// reaches ~70 turns); e^{2 pi i r} then comes from the half angle h = pi r,
+// The phase x = f_c tau (in turns, ~70 at most on the Earth at 1.7 kHz) is reduced in
+// one float64 operation: x + 1.5 2^20, rounded to that value's last place of
+// 2^-32 turns (7e-10 rad at most), has x's fraction in its low 32 bits, as a signed
+// integer u in units of 2^-32 turns (for |x| < 2^19, which xm_eligible sees to).
+// e^{2 pi i u} then comes from the half angle h = pi u 2^-32,
 // |h| <= pi/2, as cos 2h = 1 - 2 sin^2 h, sin 2h = 2 sin h cos h, with
 // near-minimax polynomials for sin h (odd, degree 9) and cos h (even, degree
 // 10), fitted on |h| <= pi/2 by reweighted least squares on Chebyshev nodes
 // (largest error 7e-9 and 2e-10 before float32 rounding); no quadrant
-// selects.  eps_m J_m(eta) 2^(g_m + kXmBShift) are Horner series in
+// selects.  (The float64 product, its rint, the difference and the conversion
+// from float64 that this takes the place of were four instructions of 18, each
+// as dear as two of the others.)
+// eps_m J_m(eta) 2^(g_m + kXmBShift) are Horner series in
 // eta^2 (|eta| <= 0.3; the dropped terms are below 2e-8 of J_0 ~ 1).  The common factor
 // 2^kXmBShift keeps the float16 lo halves of the pixel-side operands in the
 // normal range (the matrix cores flush float16 subnormals).
 __device__ __forceinline__ void xm_phase(double ta, double fc, XmItem &it)
 {
-    const double xt = fc * ta;
-    const float r = (float)(xt - rint(xt));
-    const float h = r * 3.14159265358979324f, h2 = h * h;
+    const int32_t u = (int32_t)(uint32_t)__double_as_longlong(fma(fc, ta, kXmTurns));
+    const float h = (float)u * (3.14159265358979324f / 4294967296.0f), h2 = h * h;
     const float sh =
         h * fmaf(h2, fmaf(h2, fmaf(h2, fmaf(h2, 2.60522491e-6f, -1.98090753e-4f), 8.33305106e-3f), -1.66666580e-1f),
                  9.99999996e-1f);
@@ -392,14 +423,13 @@ template <int M, bool SPLIT, int NC>
 __device__ __forceinline__ XmFrags xm_frags(const uint4 (*As)[64], int lane)
 {
     XmFrags fr;
-    const int ph = M < 3 ? 2 * M : M + 3;  // part index of the hi (or only) A fragment
 #pragma unroll
     for (int comp = 0; comp < NC; ++comp)
 #pragma unroll
         for (int jb = 0; jb < 2; ++jb) {
-            const int f = (comp * 2 + jb) * kXmParts;
-            fr.h[comp][jb] = As[f + ph][lane];
-            if (SPLIT) fr.l[comp][jb] = As[f + ph + 1][lane];
+            const int f = comp * kXmParts * 2 + jb;
+            fr.h[comp][jb] = As[f + 2 * xm_part(M, false)][lane];
+            if (SPLIT) fr.l[comp][jb] = As[f + 2 * xm_part(M, true)][lane];
         }
     return fr;
 }
@@ -441,21 +471,22 @@ __device__ __forceinline__ void xm_term(const XmItem (&items)[8], const XmFrags 
         if (SPLIT) l4[c] = make_uint4(bl[c][0], bl[c][1], bl[c][2], bl[c][3]);
     }
 #pragma unroll
-    for (int comp = 0; comp < NC; ++comp)
-#pragma unroll
-        for (int jb = 0; jb < 2; ++jb) {
-            if (SPLIT) {
-                acc[comp][jb] = mfma16(fr.l[comp][jb], h4[comp], acc[comp][jb]);
-                acc[comp][jb] = mfma16(fr.h[comp][jb], l4[comp], acc[comp][jb]);
-            }
-            acc[comp][jb] = mfma16(fr.h[comp][jb], h4[comp], acc[comp][jb]);
+    for (int comp = 0; comp < NC; ++comp) {
+        if (SPLIT) {
+            acc[comp][0] = mfma16(fr.l[comp][0], h4[comp], acc[comp][0]);
+            acc[comp][1] = mfma16(fr.l[comp][1], h4[comp], acc[comp][1]);
+            acc[comp][1] = mfma16(fr.h[comp][1], l4[comp], acc[comp][1]);
+            acc[comp][0] = mfma16(fr.h[comp][0], l4[comp], acc[comp][0]);
         }
+        acc[comp][0] = mfma16(fr.h[comp][0], h4[comp], acc[comp][0]);
+        acc[comp][1] = mfma16(fr.h[comp][1], h4[comp], acc[comp][1]);
+    }
 }
 
-// One chunk of data-side fragments (kXmFrags x 64 uint4, 32 KiB; the first
-// 16 KiB for real data) from global memory straight into LDS: each wave moves
-// 64 consecutive uint4 per instruction (lane l to slot l of the wave's base),
-// four (two) instructions per thread for the 512 threads.
+// One chunk of data-side fragments (up to kXmFrags x 64 uint4, 32 KiB: the 24 KiB
+// that a four-term form reads, half of either for real data) from global memory
+// straight into LDS: each wave moves 64 consecutive uint4 per instruction (lane
+// l to slot l of the wave's base).
 constexpr int kVmcnt0 = 0x0F70;  // s_waitcnt vmcnt(0), expcnt and lgkmcnt left at their maxima
 
 // Global-memory view of a pointer.  The multi-job kernel reads its pointers
@@ -469,21 +500,43 @@ __device__ __forceinline__ __attribute__((address_space(1))) T *gmem(T *p)
     return (__attribute__((address_space(1))) T *)p;
 }
 
-// With real data (NC = 1) only the first component's half is copied: the
-// second component's operands are zero and never read.
-template <int NC>
-__device__ __forceinline__ void stage_frags(const uint4 *__restrict__ src, uint4 *dst)
+template <class T>
+__device__ __forceinline__ __attribute__((address_space(3))) T *lds_ptr(T *p)
 {
-    const char *base = reinterpret_cast<const char *>(src);
-    const uint32_t off = threadIdx.x * 16u;
-    const int w0 = threadIdx.x & ~63;
-#pragma unroll
-    for (int i = 0; i < 2 * NC; ++i)
-        __builtin_amdgcn_global_load_lds(base + (off + (uint32_t)i * 8192u), dst + i * 512 + w0, 16, 0, 0);
+    return (__attribute__((address_space(3))) T *)p;
 }
 
-// One tile: 256 pixel pairs (block pblock) x one strip (index strip_rel within
-// the call's strips).  Called by all 512 threads of the workgroup.  NC = 1 for
+// A bounded view of global memory at a wave-uniform address: loads beyond
+// `bytes` give zero.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_view(const void *p, int64_t bytes)
+{
+    const uint64_t a = (uint64_t)(uintptr_t)p;
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32));
+    const uint64_t n = bytes < 0 ? 0 : (uint64_t)bytes > 0xffffffffull ? 0xffffffffull : (uint64_t)bytes;
+    return __builtin_amdgcn_make_buffer_rsrc((void *)(((uint64_t)hi << 32) | lo), 0,
+                                             __builtin_amdgcn_readfirstlane((int)(uint32_t)n), 0x00020000);
+}
+
+// With real data (NC = 1) only the first component's half is copied: the
+// second component's operands are zero and never read.
+template <int NC, int NT>
+__device__ __forceinline__ void stage_frags(const uint4 *__restrict__ src, uint4 *dst)
+{
+    constexpr int rows = NT == 4 ? 12 : 16;  // of a component's 16
+    static_assert(rows % kXmWaves == 0, "one row of 64 uint4 per wave and instruction");
+    const auto view = buffer_view(src, kXmFrags * 64 * (int64_t)sizeof(uint4));
+    const uint32_t off = threadIdx.x * 16u;
+    const int w0 = __builtin_amdgcn_readfirstlane(threadIdx.x) & ~63;
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int r = c * 16; r < c * 16 + rows; r += kXmWaves)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(view, lds_ptr(dst + r * 64 + w0), 16, off, r * 1024, 0, 0);
+}
+
+// One tile: 128 pixel pairs (block pblock) x one strip (index strip_rel within
+// the call's strips).  Called by all threads of the workgroup.  NC = 1 for
 // real data (C = 1): the imaginary component, identically zero, is skipped.
 template <int NC, int NT, bool SPLIT2>
 __device__ __forceinline__ void xm_tile_n(const XmArgs &x, int64_t strip_rel, int64_t pblock,
@@ -510,30 +563,37 @@ __device__ __forceinline__ void xm_tile_n(const XmArgs &x, int64_t strip_rel, in
             for (int r = 0; r < 16; ++r) acc[c][jb][r] = 0.0f;
 
     // the barrier orders this tile's first copy into LDS after the previous tile's reads
-    static_assert(kXmFrags * 64 == 4 * 64 * kXmWaves, "staging width: four uint4 per thread");
     __syncthreads();
 
-    // seeds (delays and amplitudes) of this lane's 8 segments, loaded one chunk ahead
-    float4 aN[8];
+    // Seeds (delays and amplitudes) of this lane's 8 segments, loaded one chunk
+    // ahead through buffer views: the chunk's first row is the view's base, the
+    // row within the chunk a scalar offset and the lane's place a vector offset
+    // that never changes, so a load costs no vector instruction for its address
+    // (64-bit row addresses took 40 per chunk, 16 of them quarter-rate).  A view
+    // ends with the last segment: padding rows of the last chunk read zero,
+    // which their zero data-side operands turn into exactly nothing.  A row of
+    // delays and one of amplitudes have the same number of bytes.
+    f32x4 aN[8];
     float a4N[8];
     double tN[8];
-    // Segments past the end of the day (the last chunk's padding) take the
-    // last segment's seeds: their data-side operands are zero, so they add
-    // exactly nothing, and the loads stay unconditional.
+    const uint32_t row = (uint32_t)npairs * 16u;
+    const uint32_t aoff = (uint32_t)(lane >> 5) * 8u * row + (uint32_t)pc * 16u;
+    const uint32_t toff = aoff - (uint32_t)pc * 8u, a4off = aoff >> 2;
     auto load_seeds = [&](int64_t ch) {
-        const int t0 = (int)ch * kXmT + (lane >> 5) * 8;
+        const int64_t first = ch * kXmT, left = x.a.nt - first;  // rows from the chunk's first to the end
+        const auto va = buffer_view(amp + first * npairs, left * row);
+        const auto vt = buffer_view(tau + first * x.a.npix, left * row);
+        const auto v4 = buffer_view(amp4 + first * npairs, left * (row >> 2));
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            const int t = min(t0 + e, x.a.nt - 1);
-            const int64_t q = (int64_t)t * npairs + pc;
-            const f32x4 v = gmem(reinterpret_cast<const f32x4 *>(amp))[q];
-            aN[e] = make_float4(v.x, v.y, v.z, v.w);
-            if (NT == 5) a4N[e] = gmem(amp4)[q];
-            tN[e] = gmem(tau)[(int64_t)t * x.a.npix + pc];
+            aN[e] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(va, aoff, e * row, 0));
+            if (NT == 5)
+                a4N[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(v4, a4off, e * (row >> 2), 0));
+            tN[e] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(vt, toff, e * row, 0));
         }
     };
     load_seeds(0);
-    stage_frags<NC>(Ast, &As0[0][0]);
+    stage_frags<NC, NT>(Ast, &As0[0][0]);
     // chunk 0's seeds and operands have landed: the loop starts with nothing in flight
     __builtin_amdgcn_s_waitcnt(kVmcnt0);
     __syncthreads();
@@ -557,10 +617,15 @@ __device__ __forceinline__ void xm_tile_n(const XmArgs &x, int64_t strip_rel, in
             items[e].a[4] = NT == 5 ? a4N[e] : 0.0f;
         }
         // issued after the seeds are consumed, so no wait for them holds the copy up
-        if (more) stage_frags<NC>(Ast + (ch + 1) * kXmFrags * 64, &Anext[0][0]);
+        if (more) stage_frags<NC, NT>(Ast + (ch + 1) * kXmFrags * 64, &Anext[0][0]);
         // unconditional (the last chunk reloads its own seeds, unused): a
         // conditional load would be joined by register copies that wait for it
         load_seeds(more ? ch + 1 : ch);
+        // the scheduler would move these loads to the chunk's end, where their
+        // whole latency is waited for
+        __builtin_amdgcn_sched_barrier(0);
+        // a wave in its products goes before one in its vector phase
+        __builtin_amdgcn_s_setprio(1);
         // smallest terms first: fixed order; each term's fragments are read
         // one term ahead
         if (NT == 5) {
@@ -575,6 +640,7 @@ __device__ __forceinline__ void xm_tile_n(const XmArgs &x, int64_t strip_rel, in
         const XmFrags f0 = xm_frags<0, true, NC>(Acur, lane);
         xm_term<1, true, NC>(items, f1, acc);
         xm_term<0, true, NC>(items, f0, acc);
+        __builtin_amdgcn_s_setprio(0);
         __builtin_amdgcn_s_waitcnt(kVmcnt0);  // the copy into Anext (and the seeds) have landed
         __syncthreads();
     };
@@ -587,7 +653,8 @@ __device__ __forceinline__ void xm_tile_n(const XmArgs &x, int64_t strip_rel, in
     const int64_t pB = antipode_north(ring_of_north(p, x.a.nside), x.a.npix);
     const int64_t col0 = strip * kXmS - x.a.k0;
     double sa = 0.0, sb = 0.0;  // this lane's share of the strip's broadband sums
-    if (X && x.a.accumulate) {
+    if constexpr (NC == 1) {
+        // Real data are the neighbour terms that are added into a map.
         // Read-modify-write of the map: every load is issued before any is
         // used (one wait for the tile instead of two round trips per output):
         // the strip's scale exponents (all 64 exist) and the old values at a
@@ -720,12 +787,12 @@ __device__ __forceinline__ void xm_tile(const XmArgs &x, int64_t strip_rel, int6
 constexpr int kXcds = 8;
 
 // Order of the (strip, pixel block) tiles: blocks of kXmPB pixel blocks, all
-// strips inside a block, pixel blocks fastest.  The ~32 workgroups resident on
-// one XCD then cover 8 strips x 4 pixel blocks and share, chunk by chunk, the
-// seeds of 4 pixel blocks (48 KB each) and the data operands of 8 strips
-// (32 KB each) through that XCD's L2: ~14 KB fetched per tile-chunk instead of
-// 80.  A bijection for any strip and block counts.
-constexpr uint32_t kXmPB = 4;
+// strips inside a block, pixel blocks fastest.  The ~64 workgroups resident on
+// one XCD then cover 8 strips x 8 pixel blocks and share, chunk by chunk, the
+// seeds of 8 pixel blocks (24 KB each) and the data operands of 8 strips
+// (24-32 KB each) through that XCD's L2.  A bijection for any strip and block
+// counts.
+constexpr uint32_t kXmPB = 8;
 __device__ __forceinline__ void xm_tile_coords(uint32_t T, uint32_t nstrips, uint32_t npb, uint32_t &strip,
                                                uint32_t &pb)
 {
@@ -751,8 +818,19 @@ __device__ __forceinline__ int64_t xcd_tile(int64_t L, int64_t n)
     return xcd_range_begin(L % kXcds, n) + L / kXcds;
 }
 
+// Bound by the matrix products (36 % of the cycles) and the vector work that
+// builds their pixel-side operands (40 %), and on the full band by the package's
+// power cap.  Four waves a workgroup, so that two workgroups share a compute unit
+// and one's vector phase runs beside the other's products (eight waves of one
+// workgroup meet at every chunk's barrier in the same phase), and so that the
+// last round of tiles is half as long.  Measured, a day at 1/32 Hz and nside 32,
+// whole calls: 98 strips with their Fisher diagonal 744 -> 633 us, the overlap
+// diagonal of that band 1210 -> 1008 us, the full band 16.04 -> 15.45 ms, against
+// one eight-wave workgroup with 64-bit seed addresses, every part copied and the
+// phase reduced by four float64 instructions (eight waves with the other changes:
+// 725 and 1164 us).
 template <int NC>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void xm_main_kernel(
+__global__ __launch_bounds__(64 * kXmWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void xm_main_kernel(
     XmArgs x, int64_t npblocks, const uint4 *__restrict__ A, const int *__restrict__ e_in,
     const double *__restrict__ tmax, const float4 *__restrict__ amp, const float *__restrict__ amp4,
     const double *__restrict__ tau, float *__restrict__ X)
@@ -772,7 +850,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // (A persistent loop over tiles was measured slower: its state pushed the
 // kernel to the register limit.)  A tile's result does not depend on which
 // workgroup computes it.
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void xm_batched_kernel(
+__global__ __launch_bounds__(64 * kXmWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void xm_batched_kernel(
     const XmJob *__restrict__ jobs, int32_t njobs)
 {
     __shared__ uint4 As0[kXmFrags][64], As1[kXmFrags][64];
@@ -826,7 +904,8 @@ void fill_xmjob(XmJob *j, const MapArgs &a, const float *C, const float *w, cons
 
 int64_t xmjob_tiles(const XmJob &j) { return j.x.nstrips * j.npblocks; }
 
-// Data-side preparation of a call: per-bin scales and the A fragments.
+// Data-side preparation of a call: per-bin scales and the A fragments (after
+// the seed side, whose form says which of them are needed).
 static hipError_t launch_xm_data_prep(const XmJob &j, hipStream_t s)
 {
     const float2 *Cc = reinterpret_cast<const float2 *>(j.C);
@@ -834,7 +913,7 @@ static hipError_t launch_xm_data_prep(const XmJob &j, hipStream_t s)
                        const_cast<int *>(j.e));
     const int64_t na = j.x.nstrips * j.x.nchunks * 4 * 64;
     hipLaunchKernelGGL(xm_afrag_kernel, dim3((unsigned)((na + 255) / 256)), dim3(256), 0, s, j.x, Cc, j.w, j.e,
-                       const_cast<uint4 *>(j.A));
+                       j.tmax, const_cast<uint4 *>(j.A));
     return hipGetLastError();
 }
 
@@ -859,8 +938,8 @@ static hipError_t launch_xm_seed_prep(const XmJob &j, hipStream_t s)
 
 hipError_t launch_xm_prep(const XmJob &j, hipStream_t s)
 {
-    const hipError_t e = launch_xm_data_prep(j, s);
-    return e != hipSuccess ? e : launch_xm_seed_prep(j, s);
+    const hipError_t e = launch_xm_seed_prep(j, s);
+    return e != hipSuccess ? e : launch_xm_data_prep(j, s);
 }
 
 size_t xm_seed_bytes(int32_t nt, int32_t npix)
@@ -891,7 +970,7 @@ hipError_t launch_xm_seed_products(const MapArgs &a, const float *gamma, const d
 hipError_t launch_xm_batched(const XmJob *jobs_dev, int32_t njobs, int64_t grid, hipStream_t s)
 {
     if (grid > 0x7fffffff) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(xm_batched_kernel, dim3((unsigned)grid), dim3(512), 0, s, jobs_dev, njobs);
+    hipLaunchKernelGGL(xm_batched_kernel, dim3((unsigned)grid), dim3(64 * kXmWaves), 0, s, jobs_dev, njobs);
     return hipGetLastError();
 }
 
@@ -908,10 +987,10 @@ hipError_t launch_xm_main(const XmJob &j, hipStream_t s)
     if (ntiles > 0x7fffffff) return hipErrorInvalidValue;
     if (ntiles == 0) return hipSuccess;
     if (j.x.a.unit_c)
-        hipLaunchKernelGGL(xm_main_kernel<1>, dim3((unsigned)ntiles), dim3(512), 0, s, j.x, j.npblocks, j.A, j.e,
+        hipLaunchKernelGGL(xm_main_kernel<1>, dim3((unsigned)ntiles), dim3(64 * kXmWaves), 0, s, j.x, j.npblocks, j.A, j.e,
                            j.tmax, j.amp, j.amp4, j.tau, j.X);
     else
-        hipLaunchKernelGGL(xm_main_kernel<2>, dim3((unsigned)ntiles), dim3(512), 0, s, j.x, j.npblocks, j.A, j.e,
+        hipLaunchKernelGGL(xm_main_kernel<2>, dim3((unsigned)ntiles), dim3(64 * kXmWaves), 0, s, j.x, j.npblocks, j.A, j.e,
                            j.tmax, j.amp, j.amp4, j.tau, j.X);
     return hipGetLastError();
 }
