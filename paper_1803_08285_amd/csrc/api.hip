@@ -680,7 +680,6 @@ static int bb_route(int32_t nt, int32_t nf, int32_t npix, uint32_t flags, const 
     a.nt = nt;
     a.nf = nf;
     a.npix = npix;
-    a.f0 = fg->f0_hz;
     a.df = fg->df_hz;
     a.nside = (flags & SGWB_MAPS_ANTIPODAL) ? nside_of_npix(npix) : 0;
     // the strips route: the matrix-core dirty map over the call's columns

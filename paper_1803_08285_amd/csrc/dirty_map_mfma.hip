@@ -82,18 +82,11 @@ constexpr double kXmMaxTurns = 524288.0;      // 2^19
 
 // Host check that a matrix-core form can apply: |eta| <= kXmEtaMax (where
 // 2 (eta/2)^5 / 120 <= 1e-6) for every delay of a baseline on the Earth
-// (|tau| <= 2 R / c, i.e. df <= 0.0344 Hz); tile indices in 32 bits; the offsets
-// of a chunk's seeds in 32 bits (nside <= 1024); every phase below the range of
-// the fixed-point reduction, also for the delay differences of the overlap
-// terms (|tau'| <= 4 R / c: frequencies below 6e6 Hz).
+// (|tau| <= 2 R / c, i.e. df <= 0.0344 Hz); tile indices in 32 bits.
 bool xm_eligible(const MapArgs &a)
 {
     const double eta_max = kTwoPi * 31.5 * a.df * 2.0 * kEarthRadius / kLightSpeed;
     if (a.nside <= 0 || !(eta_max <= kXmEtaMax)) return false;
-    if ((int64_t)(a.npix / 2) * 16 * kXmT > 0xffffffffll) return false;
-    const double fmax = std::max(std::fabs(a.f0 + a.df * (double)(a.k0 - kXmS)),
-                                 std::fabs(a.f0 + a.df * (double)(a.k0 + a.nf + kXmS)));
-    if (!(fmax * 4.0 * kEarthRadius / kLightSpeed < kXmMaxTurns)) return false;
     const int64_t nstrips = (a.k0 + a.nf - 1) / kXmS - a.k0 / kXmS + 1;
     const int64_t npblocks = (a.npix / 2 + kXmPairs - 1) / kXmPairs;
     return nstrips * npblocks <= 0x7fffffff;
@@ -321,7 +314,8 @@ struct XmItem {
 // The phase x = f_c tau (in turns, ~70 at most on the Earth at 1.7 kHz) is reduced in
 // one float64 operation: x + 1.5 2^20, rounded to that value's last place of
 // 2^-32 turns (7e-10 rad at most), has x's fraction in its low 32 bits, as a signed
-// integer u in units of 2^-32 turns (for |x| < 2^19, which xm_eligible sees to).
+// integer u in units of 2^-32 turns (for |x| < 2^19; calls whose frequencies go
+// beyond that are XmArgs::ext and pass the fraction of x).
 // e^{2 pi i u} then comes from the half angle h = pi u 2^-32,
 // |h| <= pi/2, as cos 2h = 1 - 2 sin^2 h, sin 2h = 2 sin h cos h, with
 // near-minimax polynomials for sin h (odd, degree 9) and cos h (even, degree
@@ -538,7 +532,7 @@ __device__ __forceinline__ void stage_frags(const uint4 *__restrict__ src, uint4
 // One tile: 128 pixel pairs (block pblock) x one strip (index strip_rel within
 // the call's strips).  Called by all threads of the workgroup.  NC = 1 for
 // real data (C = 1): the imaginary component, identically zero, is skipped.
-template <int NC, int NT, bool SPLIT2>
+template <int NC, int NT, bool SPLIT2, bool EXT>
 __device__ __forceinline__ void xm_tile_n(const XmArgs &x, int64_t strip_rel, int64_t pblock,
                                         const uint4 *__restrict__ A, const int *__restrict__ e_in,
                                         const float4 *__restrict__ amp, const float *__restrict__ amp4,
@@ -552,6 +546,7 @@ __device__ __forceinline__ void xm_tile_n(const XmArgs &x, int64_t strip_rel, in
     const bool pvalid = p < npairs;
     const int64_t pc = pvalid ? p : 0;
     const double fc = x.a.f0 + ((double)(strip * kXmS) + 31.5) * x.a.df;  // strip centre
+    const double fm = EXT ? 1.0 : fc;
     const uint4 *Ast = A + strip_rel * x.nchunks * kXmFrags * 64;
 
     f32x16 acc[2][2];
@@ -580,6 +575,18 @@ __device__ __forceinline__ void xm_tile_n(const XmArgs &x, int64_t strip_rel, in
     const uint32_t aoff = (uint32_t)(lane >> 5) * 8u * row + (uint32_t)pc * 16u;
     const uint32_t toff = aoff - (uint32_t)pc * 8u, a4off = aoff >> 2;
     auto load_seeds = [&](int64_t ch) {
+        if constexpr (EXT) {  // a chunk's rows may span more than 32 bits of bytes
+            const int t0 = (int)ch * kXmT + (lane >> 5) * 8;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int t = min(t0 + e, x.a.nt - 1);
+                const int64_t q = (int64_t)t * npairs + pc;
+                aN[e] = gmem(reinterpret_cast<const f32x4 *>(amp))[q];
+                if (NT == 5) a4N[e] = gmem(amp4)[q];
+                tN[e] = gmem(tau)[(int64_t)t * x.a.npix + pc];
+            }
+            return;
+        }
         const int64_t first = ch * kXmT, left = x.a.nt - first;  // rows from the chunk's first to the end
         const auto va = buffer_view(amp + first * npairs, left * row);
         const auto vt = buffer_view(tau + first * x.a.npix, left * row);
@@ -607,9 +614,15 @@ __device__ __forceinline__ void xm_tile_n(const XmArgs &x, int64_t strip_rel, in
         const bool more = ch + 1 < x.nchunks;
         // the first term's fragments are read from LDS while the items are computed
         XmFrags fa = NT == 5 ? xm_frags<4, false, NC>(Acur, lane) : xm_frags<3, false, NC>(Acur, lane);
+        if constexpr (EXT) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                tN[e] = fma(fc, tN[e], -rint(fc * tN[e]));  // the phase's fraction
+            }
+        }
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            xm_phase(tN[e], fc, items[e]);
+            xm_phase(tN[e], fm, items[e]);
             items[e].a[0] = aN[e].x;
             items[e].a[1] = aN[e].y;
             items[e].a[2] = aN[e].z;
@@ -762,7 +775,7 @@ __device__ __forceinline__ void xm_tile_reject(const XmArgs &x, int64_t strip_re
 // The form the prep chose for the call (uniform per launch: the same decision
 // for every tile, sub-band and schedule).  SGWB_XFORM_VALU: a gated
 // vector-unit launch computes the map, these workgroups have nothing to do.
-template <int NC = 2>
+template <int NC, bool EXT>
 __device__ __forceinline__ void xm_tile(const XmArgs &x, int64_t strip_rel, int64_t pblock,
                                         const uint4 *__restrict__ A, const int *__restrict__ e_in,
                                         const double *__restrict__ rec, const float4 *__restrict__ amp,
@@ -771,11 +784,11 @@ __device__ __forceinline__ void xm_tile(const XmArgs &x, int64_t strip_rel, int6
 {
     const int form = (int)gmem(rec)[1];
     if (form == SGWB_XFORM_MFMA4)
-        xm_tile_n<NC, 4, false>(x, strip_rel, pblock, A, e_in, amp, amp4, tau, X, As0, As1);
+        xm_tile_n<NC, 4, false, EXT>(x, strip_rel, pblock, A, e_in, amp, amp4, tau, X, As0, As1);
     else if (form == SGWB_XFORM_MFMA5)
-        xm_tile_n<NC, 5, false>(x, strip_rel, pblock, A, e_in, amp, amp4, tau, X, As0, As1);
+        xm_tile_n<NC, 5, false, EXT>(x, strip_rel, pblock, A, e_in, amp, amp4, tau, X, As0, As1);
     else if (form == SGWB_XFORM_MFMA5S)
-        xm_tile_n<NC, 5, true>(x, strip_rel, pblock, A, e_in, amp, amp4, tau, X, As0, As1);
+        xm_tile_n<NC, 5, true, EXT>(x, strip_rel, pblock, A, e_in, amp, amp4, tau, X, As0, As1);
     else if (form == kXFormRejected)
         xm_tile_reject(x, strip_rel, pblock, X);
 }
@@ -829,7 +842,7 @@ __device__ __forceinline__ int64_t xcd_tile(int64_t L, int64_t n)
 // one eight-wave workgroup with 64-bit seed addresses, every part copied and the
 // phase reduced by four float64 instructions (eight waves with the other changes:
 // 725 and 1164 us).
-template <int NC>
+template <int NC, bool EXT>
 __global__ __launch_bounds__(64 * kXmWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void xm_main_kernel(
     XmArgs x, int64_t npblocks, const uint4 *__restrict__ A, const int *__restrict__ e_in,
     const double *__restrict__ tmax, const float4 *__restrict__ amp, const float *__restrict__ amp4,
@@ -839,7 +852,7 @@ __global__ __launch_bounds__(64 * kXmWaves) __attribute__((amdgpu_waves_per_eu(2
     uint32_t sr, pb;
     xm_tile_coords((uint32_t)xcd_tile(blockIdx.x, x.nstrips * npblocks), (uint32_t)x.nstrips, (uint32_t)npblocks, sr,
                    pb);
-    xm_tile<NC>(x, sr, pb, A, e_in, tmax, amp, amp4, tau, X, As0, As1);
+    xm_tile<NC, EXT>(x, sr, pb, A, e_in, tmax, amp, amp4, tau, X, As0, As1);
 }
 
 // Multi-job form: one launch over the tiles of all jobs, one workgroup per tile.
@@ -849,7 +862,8 @@ __global__ __launch_bounds__(64 * kXmWaves) __attribute__((amdgpu_waves_per_eu(2
 // 8 sum_j ceil(n_j / 8) workgroups: the few slots past an XCD's share exit.
 // (A persistent loop over tiles was measured slower: its state pushed the
 // kernel to the register limit.)  A tile's result does not depend on which
-// workgroup computes it.
+// workgroup computes it.  No job is XmArgs::ext (a plan with one launches job by
+// job).
 __global__ __launch_bounds__(64 * kXmWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void xm_batched_kernel(
     const XmJob *__restrict__ jobs, int32_t njobs)
 {
@@ -871,7 +885,7 @@ __global__ __launch_bounds__(64 * kXmWaves) __attribute__((amdgpu_waves_per_eu(2
     j = __builtin_amdgcn_readfirstlane(j);  // uniform
     uint32_t sr, pb;
     xm_tile_coords((uint32_t)tile, (uint32_t)jobs[j].x.nstrips, (uint32_t)jobs[j].npblocks, sr, pb);
-    xm_tile(jobs[j].x, sr, pb, jobs[j].A, jobs[j].e, jobs[j].tmax, jobs[j].amp, jobs[j].amp4, jobs[j].tau, jobs[j].X,
+    xm_tile<2, false>(jobs[j].x, sr, pb, jobs[j].A, jobs[j].e, jobs[j].tmax, jobs[j].amp, jobs[j].amp4, jobs[j].tau, jobs[j].X,
             As0, As1);
 }
 
@@ -884,6 +898,10 @@ void fill_xmjob(XmJob *j, const MapArgs &a, const float *C, const float *w, cons
     x.nstrips = (a.k0 + a.nf - 1) / kXmS - x.strip_first + 1;
     x.nchunks = (a.nt + kXmT - 1) / kXmT;
     x.eta_scale = kTwoPi * 31.5 * a.df;
+    const double fmax = std::max(std::fabs(a.f0 + a.df * (double)(a.k0 - kXmS)),
+                                 std::fabs(a.f0 + a.df * (double)(a.k0 + a.nf + kXmS)));
+    // delays reach 2 R / c, the overlap terms' differences of two 4 R / c
+    x.ext = !(fmax * 4.0 * kEarthRadius / kLightSpeed < kXmMaxTurns) || (int64_t)(a.npix / 2) * 16 * kXmT > 0xffffffffll;
     const size_t frag_bytes = (size_t)x.nstrips * x.nchunks * kXmFrags * 64 * sizeof(uint4);
     j->A = reinterpret_cast<uint4 *>(work);
     j->e = reinterpret_cast<int *>(reinterpret_cast<char *>(work) + (frag_bytes + 255) / 256 * 256);
@@ -986,12 +1004,10 @@ hipError_t launch_xm_main(const XmJob &j, hipStream_t s)
     const int64_t ntiles = xmjob_tiles(j);
     if (ntiles > 0x7fffffff) return hipErrorInvalidValue;
     if (ntiles == 0) return hipSuccess;
-    if (j.x.a.unit_c)
-        hipLaunchKernelGGL(xm_main_kernel<1>, dim3((unsigned)ntiles), dim3(64 * kXmWaves), 0, s, j.x, j.npblocks, j.A, j.e,
-                           j.tmax, j.amp, j.amp4, j.tau, j.X);
-    else
-        hipLaunchKernelGGL(xm_main_kernel<2>, dim3((unsigned)ntiles), dim3(64 * kXmWaves), 0, s, j.x, j.npblocks, j.A, j.e,
-                           j.tmax, j.amp, j.amp4, j.tau, j.X);
+    const auto kernel = j.x.a.unit_c ? (j.x.ext ? xm_main_kernel<1, true> : xm_main_kernel<1, false>)
+                                     : (j.x.ext ? xm_main_kernel<2, true> : xm_main_kernel<2, false>);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)ntiles), dim3(64 * kXmWaves), 0, s, j.x, j.npblocks, j.A, j.e, j.tmax,
+                       j.amp, j.amp4, j.tau, j.X);
     return hipGetLastError();
 }
 

@@ -131,7 +131,9 @@ static hipError_t enqueue(sgwb_plan *p, hipStream_t s, int parts)
     if ((parts & 1) && p->xm_tiles > 0) {
         for (auto &x : p->xmjobs)
             if ((e = launch_xm_prep(x, s)) != hipSuccess) return e;
-        if (p->tun.xm_per_job) {
+        bool per_job = p->tun.xm_per_job;
+        for (auto &x : p->xmjobs) per_job = per_job || x.x.ext;
+        if (per_job) {
             // the single-call kernel per job: the same tiles, so the same bits
             for (auto &x : p->xmjobs)
                 if ((e = launch_xm_main(x, s)) != hipSuccess) return e;
