@@ -142,7 +142,8 @@ int sgwb_make_maps(const float *C, const float *w, int64_t ldc, int32_t nt, int3
  *   SGWB_XFORM_NONE    the call computed no dirty map (or failed);
  *   SGWB_XFORM_VALU    vector-unit recurrence (chosen on the host, or by the
  *                      device when no matrix-core form meets the delays);
- *   SGWB_XFORM_MFMA4   matrix cores, four terms (|eta| <= 0.07);
+ *   SGWB_XFORM_MFMA4   matrix cores, four terms (|eta| <= 0.07), or three over
+ *                      128-bin strips (overlap terms, |eta| <= 0.01 there);
  *   SGWB_XFORM_MFMA5   five terms, m = 2 unsplit (|eta| <= 0.17);
  *   SGWB_XFORM_MFMA5S  five terms, m = 2 split hi + lo (|eta| <= 0.29),
  *   SGWB_XFORM_TABLE   no narrowband map: sgwb_broadband_maps summed the band

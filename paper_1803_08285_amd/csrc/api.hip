@@ -230,7 +230,7 @@ int sgwb_last_x_form(int32_t *form)
         return set_error(SGWB_EINVAL, "last_x_form: the seeds failed the antipodal check or the delay bound "
                                       "(max |tau| = %.6g s); X was written as NaN", rec[0]);
     }
-    *form = code;
+    *form = code == kXFormWide ? SGWB_XFORM_MFMA4 : code;
     return SGWB_OK;
 }
 

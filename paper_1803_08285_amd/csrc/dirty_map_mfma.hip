@@ -92,6 +92,17 @@ bool xm_eligible(const MapArgs &a)
     return nstrips * npblocks <= 0x7fffffff;
 }
 
+// Real data whose delays are tiny (the overlap terms of a day's consecutive
+// segments: differences of a few 1e-4 s) take strips of twice the width, the
+// second 64 bins in the place of the second component: the pixel-side operands,
+// most of the vector work, then serve 128 bins.  Three terms are enough where
+// |eta| <= 0.01 over those (the dropped 2 J_3 is below 4.2e-8, the single
+// rounding of 2 J_2 <= 2.5e-5 below 1.3e-8).  Measured, the overlap diagonal of
+// 4101 bins at nside 32 (the whole call): 875 us, with 64-bin strips 1022 us.
+constexpr double kXmEtaWide = 0.01;
+constexpr double kXmWideScale = 63.5 / 31.5;  // eta of 128 bins over eta of 64
+constexpr int kXmWideS = 2 * kXmS;
+
 constexpr int kTmaxParts = 2048;  // partial maxima of |tau|
 // Form record of a call (float64 words): [0] largest |tau|, [1] form code,
 // then the partial maxima and the spot check's per-workgroup flags.
@@ -163,7 +174,8 @@ hipError_t launch_antipodal_check(const float *gamma, const double *tau, int32_t
 // enough, a gated vector-unit launch computes the map).
 __global__ __launch_bounds__(256) void xm_tmax_final_kernel(const double *__restrict__ part, int nparts,
                                                             const double *__restrict__ flags, double eta_scale,
-                                                            double tau_limit, double *__restrict__ rec)
+                                                            double tau_limit, int32_t unit_c,
+                                                            double *__restrict__ rec)
 {
     __shared__ double red[256];
     double m = 0.0;
@@ -178,6 +190,7 @@ __global__ __launch_bounds__(256) void xm_tmax_final_kernel(const double *__rest
         const double tm = red[0], eta = eta_scale * tm;
         int form;
         if (bad || !(tm <= tau_limit * (1.0 + 1e-9))) form = kXFormRejected;
+        else if (unit_c && eta * kXmWideScale <= kXmEtaWide) form = kXFormWide;
         else if (eta <= kXmEtaFour) form = SGWB_XFORM_MFMA4;
         else if (eta <= kXmEtaM2) form = SGWB_XFORM_MFMA5;
         else if (eta <= kXmEtaMax) form = SGWB_XFORM_MFMA5S;
@@ -247,6 +260,12 @@ __device__ __forceinline__ float cheb(int m, float s)
     }
 }
 
+// 128-bin strips of the call (real data).
+__device__ __forceinline__ int64_t xm_wide_strips(const XmArgs &x)
+{
+    return (x.a.k0 + x.a.nf - 1) / kXmWideS - x.a.k0 / kXmWideS + 1;
+}
+
 // A fragments: [strip][chunk][comp][part][jb][lane] of uint4 (8 x f16, k = 8 (lane/32) + e),
 // the parts that the call's form reads (none, if it is not a matrix-core form).
 // Bound by what it writes: 48 of the 64 bytes per segment, bin and component
@@ -256,31 +275,34 @@ __global__ __launch_bounds__(256) void xm_afrag_kernel(XmArgs x, const float2 *_
                                                        const double *__restrict__ rec, uint4 *__restrict__ A)
 {
 #pragma clang fp contract(off)  // hi and lo from the same rounded float32 value
+    const int form = (int)rec[1];
+    const bool wide = form == kXFormWide;
+    if (!wide && form != SGWB_XFORM_MFMA4 && form != SGWB_XFORM_MFMA5 && form != SGWB_XFORM_MFMA5S) return;
     const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int64_t total = x.nstrips * x.nchunks * 4 * 64;
+    const int64_t total = (wide ? xm_wide_strips(x) : x.nstrips) * x.nchunks * 4 * 64;
     if (gid >= total) return;
     const int lane = (int)(gid & 63);
     const int cj = (int)((gid >> 6) & 3);  // comp * 2 + jb
     const int64_t sc = gid >> 8;           // strip * nchunks + chunk
     const int64_t strip = sc / x.nchunks, chunk = sc % x.nchunks;
     const int comp = cj >> 1, jb = cj & 1;
-    if (comp && x.a.unit_c) return;  // real data: the second component is never read
-    const int form = (int)rec[1];
-    if (form != SGWB_XFORM_MFMA4 && form != SGWB_XFORM_MFMA5 && form != SGWB_XFORM_MFMA5S) return;
-    const int j = jb * 32 + (lane & 31);
-    const int64_t c = (x.strip_first + strip) * kXmS + j - x.a.k0;
+    if (!wide && comp && x.a.unit_c) return;  // real data: the second component is never read
+    const int j = (wide ? comp * kXmS : 0) + jb * 32 + (lane & 31);
+    const int64_t c = wide ? (x.a.k0 / kXmWideS + strip) * kXmWideS + j - x.a.k0
+                           : (x.strip_first + strip) * kXmS + j - x.a.k0;
+    const bool inside = c >= 0 && c < x.a.nf;
     const int t0 = (int)chunk * kXmT + (lane >> 5) * 8;
-    const float scale = ldexpf(1.0f, e_in[strip * kXmS + j]);
-    const float s = ((float)j - 31.5f) * (1.0f / 31.5f);
+    const float scale = inside ? ldexpf(1.0f, e_in[c + x.a.k0 - x.strip_first * kXmS]) : 0.0f;
+    const float s = wide ? ((float)j - 63.5f) * (1.0f / 63.5f) : ((float)j - 31.5f) * (1.0f / 31.5f);
     float y[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
         const int t = t0 + e;
         float v = 0.0f;
-        if (c >= 0 && c < x.a.nf && t < x.a.nt) {
+        if (inside && t < x.a.nt) {
             const int64_t off = (int64_t)t * x.a.ldc + c;
             const float2 cv = x.a.unit_c ? make_float2(1.0f, 0.0f) : C[off];
-            v = w[off] * (comp ? cv.y : cv.x) * scale;
+            v = w[off] * (comp && !wide ? cv.y : cv.x) * scale;
         }
         y[e] = v;
     }
@@ -288,7 +310,7 @@ __global__ __launch_bounds__(256) void xm_afrag_kernel(XmArgs x, const float2 *_
     u32x4 *out = reinterpret_cast<u32x4 *>(A) + (sc * kXmFrags + comp * kXmParts * 2 + jb) * 64 + lane;
 #pragma unroll
     for (int m = 0; m < 5; ++m) {
-        if (m == 4 && form == SGWB_XFORM_MFMA4) break;
+        if ((m == 4 && form == SGWB_XFORM_MFMA4) || (m == 3 && wide)) break;
         const float tm = cheb(m, s) * ldexpf(1.0f, -xm_g(m));
         h8 hi, lo;
 #pragma unroll
@@ -364,8 +386,8 @@ __device__ __forceinline__ void xm_amps(float g, double ta, float eta_scale, flo
 // amp[t][q] = (a_0, a_1, a_2, a_3), amp4[t][q] = a_4 for segment t and pixel
 // pair q (the pair's first pixel carries the seeds).
 __global__ __launch_bounds__(256) void xm_amp_kernel(XmArgs x, const float *__restrict__ gamma,
-                                                     const double *__restrict__ tau, float4 *__restrict__ amp,
-                                                     float *__restrict__ amp4)
+                                                     const double *__restrict__ tau, const double *__restrict__ rec,
+                                                     float4 *__restrict__ amp, float *__restrict__ amp4)
 {
     const int64_t npairs = x.a.npix / 2;
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -373,9 +395,10 @@ __global__ __launch_bounds__(256) void xm_amp_kernel(XmArgs x, const float *__re
     const int64_t t = i / npairs, q = i - t * npairs;
     const int64_t off = t * x.a.npix + q;
     float a[5];
-    xm_amps(gamma[off], tau[off], (float)x.eta_scale, a);
+    const bool wide = (int)rec[1] == kXFormWide;
+    xm_amps(gamma[off], tau[off], (float)(wide ? x.eta_scale * kXmWideScale : x.eta_scale), a);
     amp[i] = make_float4(a[0], a[1], a[2], a[3]);
-    amp4[i] = a[4];
+    if (!wide) amp4[i] = a[4];
 }
 
 // Split a float32 value into float16 hi + lo with plain float32 arithmetic: hi
@@ -413,12 +436,12 @@ struct XmFrags {
     uint4 h[2][2], l[2][2];
 };
 
-template <int M, bool SPLIT, int NC>
+template <int M, bool SPLIT, int NA>
 __device__ __forceinline__ XmFrags xm_frags(const uint4 (*As)[64], int lane)
 {
     XmFrags fr;
 #pragma unroll
-    for (int comp = 0; comp < NC; ++comp)
+    for (int comp = 0; comp < NA; ++comp)
 #pragma unroll
         for (int jb = 0; jb < 2; ++jb) {
             const int f = comp * kXmParts * 2 + jb;
@@ -428,7 +451,7 @@ __device__ __forceinline__ XmFrags xm_frags(const uint4 (*As)[64], int lane)
     return fr;
 }
 
-template <int M, bool SPLIT, int NC>
+template <int M, bool SPLIT, int NC, int NA>
 __device__ __forceinline__ void xm_term(const XmItem (&items)[8], const XmFrags &fr, f32x16 (&acc)[2][2])
 {
     // hi and lo must come from the same rounded float32 product
@@ -465,15 +488,16 @@ __device__ __forceinline__ void xm_term(const XmItem (&items)[8], const XmFrags 
         if (SPLIT) l4[c] = make_uint4(bl[c][0], bl[c][1], bl[c][2], bl[c][3]);
     }
 #pragma unroll
-    for (int comp = 0; comp < NC; ++comp) {
+    for (int comp = 0; comp < NA; ++comp) {
+        const int u = comp < NC ? comp : 0;  // both halves of a wide strip share their operand
         if (SPLIT) {
-            acc[comp][0] = mfma16(fr.l[comp][0], h4[comp], acc[comp][0]);
-            acc[comp][1] = mfma16(fr.l[comp][1], h4[comp], acc[comp][1]);
-            acc[comp][1] = mfma16(fr.h[comp][1], l4[comp], acc[comp][1]);
-            acc[comp][0] = mfma16(fr.h[comp][0], l4[comp], acc[comp][0]);
+            acc[comp][0] = mfma16(fr.l[comp][0], h4[u], acc[comp][0]);
+            acc[comp][1] = mfma16(fr.l[comp][1], h4[u], acc[comp][1]);
+            acc[comp][1] = mfma16(fr.h[comp][1], l4[u], acc[comp][1]);
+            acc[comp][0] = mfma16(fr.h[comp][0], l4[u], acc[comp][0]);
         }
-        acc[comp][0] = mfma16(fr.h[comp][0], h4[comp], acc[comp][0]);
-        acc[comp][1] = mfma16(fr.h[comp][1], h4[comp], acc[comp][1]);
+        acc[comp][0] = mfma16(fr.h[comp][0], h4[u], acc[comp][0]);
+        acc[comp][1] = mfma16(fr.h[comp][1], h4[u], acc[comp][1]);
     }
 }
 
@@ -512,18 +536,18 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_view(const void *p, int
                                              __builtin_amdgcn_readfirstlane((int)(uint32_t)n), 0x00020000);
 }
 
-// With real data (NC = 1) only the first component's half is copied: the
+// With real data (NA = 1) only the first component's half is copied: the
 // second component's operands are zero and never read.
-template <int NC, int NT>
+template <int NA, int NT>
 __device__ __forceinline__ void stage_frags(const uint4 *__restrict__ src, uint4 *dst)
 {
-    constexpr int rows = NT == 4 ? 12 : 16;  // of a component's 16
+    constexpr int rows = NT <= 4 ? 12 : 16;  // of a component's 16
     static_assert(rows % kXmWaves == 0, "one row of 64 uint4 per wave and instruction");
     const auto view = buffer_view(src, kXmFrags * 64 * (int64_t)sizeof(uint4));
     const uint32_t off = threadIdx.x * 16u;
     const int w0 = __builtin_amdgcn_readfirstlane(threadIdx.x) & ~63;
 #pragma unroll
-    for (int c = 0; c < NC; ++c)
+    for (int c = 0; c < NA; ++c)
 #pragma unroll
         for (int r = c * 16; r < c * 16 + rows; r += kXmWaves)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(view, lds_ptr(dst + r * 64 + w0), 16, off, r * 1024, 0, 0);
@@ -541,11 +565,13 @@ __device__ __forceinline__ void xm_tile_n(const XmArgs &x, int64_t strip_rel, in
 {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int64_t npairs = x.a.npix / 2;
-    const int64_t strip = x.strip_first + strip_rel;
+    constexpr bool WIDE = NT == 3;
+    constexpr int NA = NC == 2 || WIDE ? 2 : 1;  // components, or halves of a wide strip
+    const int64_t strip = (WIDE ? x.a.k0 / kXmWideS : x.strip_first) + strip_rel;
     const int64_t p = pblock * kXmPairs + wv * 32 + (lane & 31);
     const bool pvalid = p < npairs;
     const int64_t pc = pvalid ? p : 0;
-    const double fc = x.a.f0 + ((double)(strip * kXmS) + 31.5) * x.a.df;  // strip centre
+    const double fc = x.a.f0 + (WIDE ? (double)(strip * kXmWideS) + 63.5 : (double)(strip * kXmS) + 31.5) * x.a.df;  // strip centre
     const double fm = EXT ? 1.0 : fc;
     const uint4 *Ast = A + strip_rel * x.nchunks * kXmFrags * 64;
 
@@ -600,7 +626,7 @@ __device__ __forceinline__ void xm_tile_n(const XmArgs &x, int64_t strip_rel, in
         }
     };
     load_seeds(0);
-    stage_frags<NC, NT>(Ast, &As0[0][0]);
+    stage_frags<NA, NT>(Ast, &As0[0][0]);
     // chunk 0's seeds and operands have landed: the loop starts with nothing in flight
     __builtin_amdgcn_s_waitcnt(kVmcnt0);
     __syncthreads();
@@ -613,7 +639,7 @@ __device__ __forceinline__ void xm_tile_n(const XmArgs &x, int64_t strip_rel, in
     auto step = [&](int64_t ch, const uint4 (*Acur)[64], uint4 (*Anext)[64]) {
         const bool more = ch + 1 < x.nchunks;
         // the first term's fragments are read from LDS while the items are computed
-        XmFrags fa = NT == 5 ? xm_frags<4, false, NC>(Acur, lane) : xm_frags<3, false, NC>(Acur, lane);
+        XmFrags fa = xm_frags<NT - 1, false, NA>(Acur, lane);
         if constexpr (EXT) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
@@ -630,7 +656,7 @@ __device__ __forceinline__ void xm_tile_n(const XmArgs &x, int64_t strip_rel, in
             items[e].a[4] = NT == 5 ? a4N[e] : 0.0f;
         }
         // issued after the seeds are consumed, so no wait for them holds the copy up
-        if (more) stage_frags<NC, NT>(Ast + (ch + 1) * kXmFrags * 64, &Anext[0][0]);
+        if (more) stage_frags<NA, NT>(Ast + (ch + 1) * kXmFrags * 64, &Anext[0][0]);
         // unconditional (the last chunk reloads its own seeds, unused): a
         // conditional load would be joined by register copies that wait for it
         load_seeds(more ? ch + 1 : ch);
@@ -641,18 +667,21 @@ __device__ __forceinline__ void xm_tile_n(const XmArgs &x, int64_t strip_rel, in
         __builtin_amdgcn_s_setprio(1);
         // smallest terms first: fixed order; each term's fragments are read
         // one term ahead
-        if (NT == 5) {
-            const XmFrags f3 = xm_frags<3, false, NC>(Acur, lane);
-            xm_term<4, false, NC>(items, fa, acc);
+        if constexpr (NT == 5) {
+            const XmFrags f3 = xm_frags<3, false, NA>(Acur, lane);
+            xm_term<4, false, NC, NA>(items, fa, acc);
             fa = f3;
         }
-        const XmFrags f2 = xm_frags<2, SPLIT2, NC>(Acur, lane);
-        xm_term<3, false, NC>(items, fa, acc);
-        const XmFrags f1 = xm_frags<1, true, NC>(Acur, lane);
-        xm_term<2, SPLIT2, NC>(items, f2, acc);
-        const XmFrags f0 = xm_frags<0, true, NC>(Acur, lane);
-        xm_term<1, true, NC>(items, f1, acc);
-        xm_term<0, true, NC>(items, f0, acc);
+        if constexpr (!WIDE) {
+            const XmFrags f2 = xm_frags<2, SPLIT2, NA>(Acur, lane);
+            xm_term<3, false, NC, NA>(items, fa, acc);
+            fa = f2;
+        }
+        const XmFrags f1 = xm_frags<1, true, NA>(Acur, lane);
+        xm_term<2, SPLIT2, NC, NA>(items, fa, acc);
+        const XmFrags f0 = xm_frags<0, true, NA>(Acur, lane);
+        xm_term<1, true, NC, NA>(items, f1, acc);
+        xm_term<0, true, NC, NA>(items, f0, acc);
         __builtin_amdgcn_s_setprio(0);
         __builtin_amdgcn_s_waitcnt(kVmcnt0);  // the copy into Anext (and the seeds) have landed
         __syncthreads();
@@ -664,45 +693,43 @@ __device__ __forceinline__ void xm_tile_n(const XmArgs &x, int64_t strip_rel, in
 
     if (!pvalid) return;  // lanes l and l ^ 32 hold the same pair: both leave or both stay
     const int64_t pB = antipode_north(ring_of_north(p, x.a.nside), x.a.npix);
-    const int64_t col0 = strip * kXmS - x.a.k0;
+    const int64_t col0 = strip * (WIDE ? kXmWideS : kXmS) - x.a.k0;
     double sa = 0.0, sb = 0.0;  // this lane's share of the strip's broadband sums
     if constexpr (NC == 1) {
         // Real data are the neighbour terms that are added into a map.
-        // Read-modify-write of the map: every load is issued before any is
-        // used (one wait for the tile instead of two round trips per output):
-        // the strip's scale exponents (all 64 exist) and the old values at a
-        // clamped row.
-        int ex[2][16];
-        float olda[2][16], oldb[2][16];
+        // Read-modify-write of the map: the loads of 64 bins (32 in a wide strip,
+        // whose sums leave room for no more) are issued before any is used (one
+        // wait instead of two round trips per output): the scale exponents and
+        // the old values, at a clamped row.
+        constexpr int NB = WIDE ? 1 : 2;  // blocks of 32 bins a batch
 #pragma unroll
-        for (int jb = 0; jb < 2; ++jb)
+        for (int b = 0; b < 2 * NA; b += NB) {
+            int ex[NB][16];
+            float olda[NB][16], oldb[NB][16];
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int j = jb * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                const int64_t c = col0 + j, cc = c < 0 ? 0 : (c >= x.a.nf ? x.a.nf - 1 : c);
-                ex[jb][r] = gmem(e_in)[strip_rel * kXmS + j];
-                auto row = gmem(X + cc * (int64_t)x.a.npix);
-                olda[jb][r] = row[p];
-                oldb[jb][r] = row[pB];
-            }
+            for (int i = 0; i < NB; ++i)
 #pragma unroll
-        for (int jb = 0; jb < 2; ++jb)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int j = jb * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                const int64_t c = col0 + j;
-                if (c < 0 || c >= x.a.nf) continue;
-                const float inv = ldexpf(1.0f, -ex[jb][r] - kXmBShift);
-                const float pi = NC == 2 ? acc[1][jb][r] : 0.0f;
-                const float xa = (acc[0][jb][r] - pi) * inv, xb = (acc[0][jb][r] + pi) * inv;
-                auto row = gmem(X + c * (int64_t)x.a.npix);
-                row[p] = olda[jb][r] + xa;
-                row[pB] = oldb[jb][r] + xb;
-                if (c >= x.a.band_lo && c < x.a.band_hi) {
-                    sa += (double)xa;
-                    sb += (double)xb;
+                for (int r = 0; r < 16; ++r) {
+                    const int j = (b + i) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+                    const int64_t c = col0 + j, cc = c < 0 ? 0 : (c >= x.a.nf ? x.a.nf - 1 : c);
+                    ex[i][r] = gmem(e_in)[cc + x.a.k0 - x.strip_first * kXmS];
+                    auto row = gmem(X + cc * (int64_t)x.a.npix);
+                    olda[i][r] = row[p];
+                    oldb[i][r] = row[pB];
                 }
-            }
+#pragma unroll
+            for (int i = 0; i < NB; ++i)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int j = (b + i) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+                    const int64_t c = col0 + j;
+                    if (c < 0 || c >= x.a.nf) continue;
+                    const float v = acc[(b + i) >> 1][(b + i) & 1][r] * ldexpf(1.0f, -ex[i][r] - kXmBShift);
+                    auto row = gmem(X + c * (int64_t)x.a.npix);
+                    row[p] = olda[i][r] + v;
+                    row[pB] = oldb[i][r] + v;
+                }
+        }
     } else {
         // write-only: streaming stores (the map is not read back here), or
         // none at all for a broadband-only call.  Batching the exponent loads
@@ -715,7 +742,7 @@ __device__ __forceinline__ void xm_tile_n(const XmArgs &x, int64_t strip_rel, in
                 const int64_t c = col0 + j;
                 if (c < 0 || c >= x.a.nf) continue;
                 const float inv = ldexpf(1.0f, -gmem(e_in)[strip_rel * kXmS + j] - kXmBShift);
-                const float pi = NC == 2 ? acc[1][jb][r] : 0.0f;
+                const float pi = acc[1][jb][r];
                 const float xa = (acc[0][jb][r] - pi) * inv, xb = (acc[0][jb][r] + pi) * inv;
                 if (X) {
                     auto row = gmem(X + c * (int64_t)x.a.npix);
@@ -783,7 +810,9 @@ __device__ __forceinline__ void xm_tile(const XmArgs &x, int64_t strip_rel, int6
                                         float *__restrict__ X, uint4 (*As0)[64], uint4 (*As1)[64])
 {
     const int form = (int)gmem(rec)[1];
-    if (form == SGWB_XFORM_MFMA4)
+    if (NC == 1 && form == kXFormWide)
+        xm_tile_n<1, 3, false, EXT>(x, strip_rel, pblock, A, e_in, amp, amp4, tau, X, As0, As1);
+    else if (form == SGWB_XFORM_MFMA4)
         xm_tile_n<NC, 4, false, EXT>(x, strip_rel, pblock, A, e_in, amp, amp4, tau, X, As0, As1);
     else if (form == SGWB_XFORM_MFMA5)
         xm_tile_n<NC, 5, false, EXT>(x, strip_rel, pblock, A, e_in, amp, amp4, tau, X, As0, As1);
@@ -850,8 +879,12 @@ __global__ __launch_bounds__(64 * kXmWaves) __attribute__((amdgpu_waves_per_eu(2
 {
     __shared__ uint4 As0[kXmFrags][64], As1[kXmFrags][64];  // 2 x 32 KB
     uint32_t sr, pb;
-    xm_tile_coords((uint32_t)xcd_tile(blockIdx.x, x.nstrips * npblocks), (uint32_t)x.nstrips, (uint32_t)npblocks, sr,
-                   pb);
+    int64_t nstrips = x.nstrips;
+    if (NC == 1 && (int)gmem(tmax)[1] == kXFormWide) {
+        nstrips = xm_wide_strips(x);
+        if (blockIdx.x >= nstrips * npblocks) return;
+    }
+    xm_tile_coords((uint32_t)xcd_tile(blockIdx.x, nstrips * npblocks), (uint32_t)nstrips, (uint32_t)npblocks, sr, pb);
     xm_tile<NC, EXT>(x, sr, pb, A, e_in, tmax, amp, amp4, tau, X, As0, As1);
 }
 
@@ -947,10 +980,10 @@ static hipError_t launch_xm_seed_prep(const XmJob &j, hipStream_t s)
     hipLaunchKernelGGL(xm_symcheck_kernel, dim3(kSymParts), dim3(kSymThreads), 0, s, j.gamma, j.tau, j.x.a.nt,
                        (int64_t)j.x.a.npix, j.x.a.nside, flags);
     hipLaunchKernelGGL(xm_tmax_final_kernel, dim3(1), dim3(256), 0, s, part, parts, flags, j.x.eta_scale,
-                       j.x.a.tau_limit, j.tmax);
+                       j.x.a.tau_limit, j.x.a.unit_c, j.tmax);
     const int64_t ni = (int64_t)j.x.a.nt * (j.x.a.npix / 2);
-    hipLaunchKernelGGL(xm_amp_kernel, dim3((unsigned)((ni + 255) / 256)), dim3(256), 0, s, j.x, j.gamma, j.tau, j.amp,
-                       j.amp4);
+    hipLaunchKernelGGL(xm_amp_kernel, dim3((unsigned)((ni + 255) / 256)), dim3(256), 0, s, j.x, j.gamma, j.tau, j.tmax,
+                       j.amp, j.amp4);
     return hipGetLastError();
 }
 

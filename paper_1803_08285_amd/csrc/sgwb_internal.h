@@ -197,6 +197,7 @@ constexpr double kXmEtaMax = 0.29;
 // seeds fail the antipodal spot check or exceed the call's delay bound (the
 // map is then written as NaN).
 constexpr int kXFormRejected = -1;
+constexpr int kXFormWide = 64;  // real data in 128-bin strips, three terms (reported as SGWB_XFORM_MFMA4)
 // Spot check of the exact antipodal symmetry of seeds (first, middle and last
 // segment, every northern pixel): flags[kSymParts] of 0.0 (pass) or 1.0, one per
 // workgroup, no atomics.

@@ -140,3 +140,40 @@ def test_overlap_fisher_full_band_nside32_sampled(sg, oracle_mod):
     err_nb = np.abs((Gg - Gg0) - (Go - Go0)) / S_nb
     round_once = 2.0 ** -23 * np.abs(Gg) / S_nb
     assert np.max(err_nb - round_once) <= 1e-5
+
+
+# Real data with tiny pair delays take strips of 128 bins, others of 64: both
+# sides of the line (|eta| <= 0.01 over 128 bins), bands that begin and end
+# inside either strip, and down to one bin.
+STRIP_CASES = [  # baseline, nside, nt, df
+    ("AB", 4, 898, 1 / 32),   # eta over 128 bins 1e-3
+    ("AC", 2, 240, 1 / 32),   # 9e-3
+    ("AC", 2, 200, 1 / 32),   # beyond: 64-bin strips
+    ("BC", 4, 50, 1 / 32),
+]
+
+
+@pytest.mark.parametrize("bl,nside,nt,df", STRIP_CASES)
+def test_overlap_sub_bands_are_rows_of_the_band_and_meet_the_oracle(sg, oracle_mod, bl, nside, nt, df):
+    k0, nf = 64, 300
+    g, t, v, u, w = _inputs(sg, bl, nside, nt, k0, nf, df, 21)
+    vd, ud, wd = (torch.from_numpy(a).cuda() for a in (v, u, w))
+    G = sg.fisher_overlap(vd, ud, wd, sg.FGrid(F0, df), k0, g, t)
+    assert sg.last_x_form() == "mfma4"
+    npix = 12 * nside * nside
+    z = torch.zeros_like(vd)
+    G0 = sg.fisher_overlap(vd, z, z, sg.FGrid(F0, df), k0, g, t).cpu().numpy().astype(np.float64)
+    gh, th = g.cpu().numpy(), t.cpu().numpy()
+    rows = np.repeat(np.array([0, 1, 63, 64, 127, 128, 191, 192, 255, 256, nf - 1]), 4)
+    cols = np.random.default_rng(4).integers(0, npix, rows.size)
+    Go, _, S = oracle_mod.fisher_overlap_at(v, u, w, F0, df, k0, gh, th, rows, cols)
+    zh = np.zeros_like(v)
+    Go0, _, _ = oracle_mod.fisher_overlap_at(v, zh, zh, F0, df, k0, gh, th, rows, cols)
+    Gs = G.cpu().numpy()[rows, cols].astype(np.float64)
+    S_nb = S - np.abs(Go0)
+    err = np.abs((Gs - G0[rows, cols]) - (Go - Go0)) / S_nb
+    assert np.max(err - 2.0 ** -23 * np.abs(Gs) / S_nb) <= 1e-5
+    for lo, n in ((0, 1), (63, 1), (64, 1), (63, 2), (1, 130), (65, 127), (190, 110)):
+        cut = slice(lo, lo + n)
+        part = sg.fisher_overlap(*(a[:, cut].contiguous() for a in (vd, ud, wd)), sg.FGrid(F0, df), k0 + lo, g, t)
+        assert torch.equal(part, G[cut]), (lo, n)
