@@ -433,29 +433,54 @@ struct BbAt {
     float cs, sn;  // carrier e^{2 pi i f_c |tau|}
 };
 
-__device__ __forceinline__ BbAt bb_at(double ta, double inv_h, double jmax, double fc)
+// What bb_at needs of the grid and the carrier.
+struct BbScale {
+    double inv_h, fc4;  // intervals per second, quarter turns per second
+    int32_t jmax;       // the last interval
+    // intervals or quarter turns beyond the fixed-point forms (2^20 intervals,
+    // 2^21 quarter turns: at 40 ms frequencies above 1.2e7 Hz)
+    int32_t far;
+};
+
+// Cell and phase in fixed point: adding 2^20 to u leaves its integer part in the
+// high word and its fraction, to 2^-32, in the low one; adding 1.5 2^22 to the
+// quarter turns leaves the quadrant in the low word's two top bits and the
+// fraction, to 2^-30 (7e-10 rad at most), below.  One float64 operation each
+// where product, floor or rint, difference and conversions took six and nine
+// (a full day, nside 128, 4096 bins: the call 296 -> 286 us).
+__device__ __forceinline__ BbAt bb_at(double ta, const BbScale &c)
 {
     BbAt r;
-    const double at = fabs(ta), u = at * inv_h;
-    const double jd = fmin(floor(u), jmax);
-    r.j = (int32_t)jd;
-    r.x = (float)(u - jd);
-    // the phase reduced to the nearest quarter turn in float64, sine and
-    // cosine by their series on |theta| <= pi / 4 (truncation below 2e-9),
-    // turned by the quadrant.  (A half-angle form without the quadrant was 4 %
-    // faster, but its rounding took the maps' error from 8.4e-8 to 1.4e-7.)
-    const double x4 = 4.0 * fc * at, q = rint(x4);
-    const float th = (float)(x4 - q) * 1.57079632679489662f, t2 = th * th;
-    const int k = (int)(q - 4.0 * floor(0.25 * q));
+    const double at = fabs(ta);
+    uint32_t turn;  // the phase in units of 2^-30 quarter turns, mod 4
+    if (!c.far) {
+        const uint64_t b = (uint64_t)__double_as_longlong(fma(at, c.inv_h, 1048576.0));
+        const int32_t j = (int32_t)(b >> 32) & 0xfffff;
+        r.j = min(j, c.jmax);
+        r.x = fmaf((float)(uint32_t)b, 1.0f / 4294967296.0f, (float)(j - r.j));
+        turn = (uint32_t)__double_as_longlong(fma(c.fc4, at, 6291456.0));
+    } else {
+        const double u = at * c.inv_h, jd = fmin(floor(u), (double)c.jmax);
+        r.j = (int32_t)jd;
+        r.x = (float)(u - jd);
+        const double x4 = c.fc4 * at, whole = 4.0 * rint(0.25 * x4);
+        turn = (uint32_t)__double_as_longlong(fma(c.fc4, at, -whole) + 6291456.0);
+    }
+    // to the nearest quarter turn; sine and cosine by their series on |theta| <=
+    // pi / 4 (truncation below 2e-9), turned by the quadrant.  (A half-angle
+    // form without the quadrant was 4 % faster, but its rounding took the maps'
+    // error from 8.4e-8 to 1.4e-7.)
+    const uint32_t k = (turn + 0x20000000u) >> 30;
+    const float th = (float)(int32_t)(turn << 2) * (1.57079632679489662f / 4294967296.0f), t2 = th * th;
     const float s =
         th * fmaf(t2, fmaf(t2, fmaf(t2, fmaf(t2, 2.75573192e-6f, -1.98412698e-4f), 8.33333333e-3f), -1.66666667e-1f),
                   1.0f);
-    const float c =
+    const float c0 =
         fmaf(t2, fmaf(t2, fmaf(t2, fmaf(t2, fmaf(t2, -2.75573192e-7f, 2.48015873e-5f), -1.38888889e-3f),
                                4.16666667e-2f), -0.5f), 1.0f);
-    const float cr = (k & 1) ? s : c, sr = (k & 1) ? c : s;
-    r.cs = ((k + 1) & 2) ? -cr : cr;
-    r.sn = (k & 2) ? -sr : sr;
+    const float cr = (k & 1) ? s : c0, sr = (k & 1) ? c0 : s;
+    r.cs = __uint_as_float(__float_as_uint(cr) ^ (((k + 1) & 2) << 30));
+    r.sn = __uint_as_float(__float_as_uint(sr) ^ ((k & 2) << 30));
     return r;
 }
 
@@ -503,7 +528,7 @@ template <bool GB>
 __global__ __launch_bounds__(256) void bb_map_pair_kernel(const float *__restrict__ gamma,
                                                           const double *__restrict__ tau, int32_t nt, int32_t npix,
                                                           int64_t nside, const float2 *__restrict__ T, int32_t G,
-                                                          int32_t m, double h, double bound, double fc, int32_t per,
+                                                          int32_t m, double bound, BbScale scale, int32_t per,
                                                           const double *__restrict__ flags, double *__restrict__ part,
                                                           const double *__restrict__ v, double *__restrict__ gpart)
 {
@@ -512,7 +537,6 @@ __global__ __launch_bounds__(256) void bb_map_pair_kernel(const float *__restric
     const int lane = threadIdx.x & 63, sl = threadIdx.x >> 6;
     const int64_t p = (int64_t)blockIdx.x * 64 + lane, npairs = npix / 2, pc = p < npairs ? p : npairs - 1;
     const BandSlice run = band_slice(blockIdx.y, sl, per, nt);
-    const double inv_h = 1.0 / h, jmax = (double)(m - 1);
     double accA = 0.0, accB = 0.0, gacc = 0.0;
     bool bad = false;
     for (int32_t tq = run.begin; tq < run.end; tq += kBbRunBatch) {
@@ -528,7 +552,7 @@ __global__ __launch_bounds__(256) void bb_map_pair_kernel(const float *__restric
         float4 n[kBbRunBatch][4];
 #pragma unroll
         for (int e = 0; e < kBbRunBatch; ++e) {
-            at[e] = bb_at(ta[e], inv_h, jmax, fc);
+            at[e] = bb_at(ta[e], scale);
             const float2 *row = T + (int64_t)min(tq + e, run.end - 1) * G + (m + 1);  // the centre node
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
@@ -567,17 +591,17 @@ __global__ __launch_bounds__(256) void bb_map_pair_kernel(const float *__restric
 // segments' tables staged through LDS, kBbBatch at a time and double-buffered,
 // as (Y(+tau_j), Y(-tau_j)) per node counted from the centre (index j + 1 for
 // j = -1 .. m + 1), so a pair's four nodes are four 16-byte reads.  K: staged
-// entries per thread.  Bound by vector instructions (~90 a pair and segment, a
-// quarter of them float64) just ahead of the seeds' 12 bytes.  Full day,
-// nside 128, 4096 bins, AB: the pass 252 us, 348 us with the nodes read from
-// global memory by each pair.
+// entries per thread.  Bound by the seeds' 12 bytes a pair and segment, with
+// ~85 vector instructions close behind.  Full day, nside 128, 4096 bins, AB: the
+// pass ~230 us (221 us at the copy rate), 348 us with the nodes read from global
+// memory by each pair.
 constexpr int kBbMapThreads = 512;
 constexpr int64_t kBbLdsPairs = 6144;
 
 template <bool GB, int K>
 __global__ __launch_bounds__(kBbMapThreads) void bb_map_pair_lds_kernel(
     const float *__restrict__ gamma, const double *__restrict__ tau, int32_t nt, int32_t npix, int64_t nside,
-    const float2 *__restrict__ T, int32_t G, int32_t m, double h, double bound, double fc, int32_t per,
+    const float2 *__restrict__ T, int32_t G, int32_t m, double bound, BbScale scale, int32_t per,
     const double *__restrict__ flags, double *__restrict__ part, const double *__restrict__ v,
     double *__restrict__ gpart)
 {
@@ -585,7 +609,6 @@ __global__ __launch_bounds__(kBbMapThreads) void bb_map_pair_lds_kernel(
     const int32_t E = m + 3;
     const int64_t p = (int64_t)blockIdx.x * kBbMapThreads + threadIdx.x;
     const int64_t npairs = npix / 2, pc = p < npairs ? p : npairs - 1;
-    const double inv_h = 1.0 / h, jmax = (double)(m - 1);
     double totA = 0.0, totB = 0.0, totG = 0.0, accA = 0.0, accB = 0.0, gacc = 0.0;
     bool bad = false;
 
@@ -652,7 +675,7 @@ __global__ __launch_bounds__(kBbMapThreads) void bb_map_pair_lds_kernel(
 #pragma unroll
         for (int e = 0; e < kBbBatch; ++e) {
             const bool valid = e == 0 || t0 + e < t1;  // a segment past the run repeats its last
-            const BbAt at = bb_at(tc[e], inv_h, jmax, fc);
+            const BbAt at = bb_at(tc[e], scale);
             float4 n[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) n[i] = buf[e * E + at.j + i];
@@ -683,6 +706,11 @@ static hipError_t launch_bb_map_pair(const float *gamma, const double *tau, int3
                                      const double *flags, double *part, const double *v, double *gpart, hipStream_t s)
 {
     const int64_t npairs = npix / 2;
+    BbScale scale;
+    scale.inv_h = 1.0 / g.h;
+    scale.fc4 = 4.0 * fc;
+    scale.jmax = g.m - 1;
+    scale.far = g.m > (1 << 20) - 2 || !(std::fabs(scale.fc4) * g.bound < 2097152.0 - 1.0);
     const int32_t entries = kBbBatch * (g.m + 3), k = (entries + kBbMapThreads - 1) / kBbMapThreads;
     // The LDS form from kBbLdsPairs pixel pairs on, while the tables fit in 64 KB
     // (at most 1021 intervals of |tau|).  Measured, full day, AB, 1531 bins, call
@@ -692,8 +720,8 @@ static hipError_t launch_bb_map_pair(const float *gamma, const double *tau, int3
         const dim3 grid((unsigned)((npairs + kBbMapThreads - 1) / kBbMapThreads), (unsigned)nchunks);
         const size_t lds = 2 * (size_t)entries * sizeof(float4);
         auto go = [&](auto kern) {
-            hipLaunchKernelGGL(kern, grid, dim3(kBbMapThreads), lds, s, gamma, tau, nt, npix, nside, T, g.G, g.m, g.h,
-                               g.bound, fc, per, flags, part, v, gpart);
+            hipLaunchKernelGGL(kern, grid, dim3(kBbMapThreads), lds, s, gamma, tau, nt, npix, nside, T, g.G, g.m,
+                               g.bound, scale, per, flags, part, v, gpart);
         };
         if (k == 1)
             go(bb_map_pair_lds_kernel<GB, 1>);
@@ -703,7 +731,7 @@ static hipError_t launch_bb_map_pair(const float *gamma, const double *tau, int3
             go(bb_map_pair_lds_kernel<GB, 4>);
     } else {
         hipLaunchKernelGGL(bb_map_pair_kernel<GB>, dim3((unsigned)((npairs + 63) / 64), (unsigned)nchunks), dim3(256),
-                           0, s, gamma, tau, nt, npix, nside, T, g.G, g.m, g.h, g.bound, fc, per, flags, part, v,
+                           0, s, gamma, tau, nt, npix, nside, T, g.G, g.m, g.bound, scale, per, flags, part, v,
                            gpart);
     }
     return hipGetLastError();

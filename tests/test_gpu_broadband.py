@@ -224,3 +224,27 @@ def test_pair_pass_forms_vs_oracle(sg, oracle_mod, nb, nt, nside):
     ref, Sb = Xo.reshape(pix.size, nb).sum(axis=1), S.reshape(pix.size, nb).sum(axis=1)
     err = np.abs(Xbb.cpu().numpy()[pix].astype(np.float64) - ref)
     assert np.all(err <= TOL * Sb + 1e-300), float((err / Sb).max())
+
+
+@pytest.mark.parametrize("f0", [20.0, -5.0e7, 5.0e7, 5.5e7])
+@pytest.mark.parametrize("nside", [4, 32])
+def test_fixed_point_cells_and_phases_vs_oracle(sg, oracle_mod, f0, nside):
+    """The pixel-pair pass takes cells and phases in fixed point, up to 2^21 quarter
+    turns (5.2e7 Hz here), and in float64 beyond: within 1e-6 of S_bb on both
+    sides, with a bound that the largest delay meets exactly (the last cell's
+    end), in the split and the LDS form."""
+    nb, nt = 60, 9
+    g, t, C, w, H = _setup(sg, "AB", nside, nt, 0, nb, 0.25, 5)
+    tb = float(t.abs().max())
+    Xbb, _ = sg.broadband_maps(C, w, sg.FGrid(f0, 0.25), 0, g, t, None, 0, nb, tau_bound=tb, want_gamma=False,
+                               route="table")
+    torch.cuda.synchronize()
+    top = int(t.abs().max(dim=0).values.argmax())
+    pix = np.unique(np.concatenate([[0, top, 12 * nside * nside - 1],
+                                    np.random.default_rng(1).integers(0, 12 * nside * nside, 20)]))
+    cols, pp = np.tile(np.arange(nb), pix.size), np.repeat(pix, nb)
+    Xo, _, S = oracle_mod.maps_at(C.cpu().numpy(), w.cpu().numpy(), f0, 0.25, 0, g.cpu().numpy(), t.cpu().numpy(),
+                                  cols, pp)
+    ref, Sb = Xo.reshape(pix.size, nb).sum(axis=1), S.reshape(pix.size, nb).sum(axis=1)
+    err = np.abs(Xbb.cpu().numpy()[pix].astype(np.float64) - ref)
+    assert np.all(err <= TOL * Sb), float((err / Sb).max())
