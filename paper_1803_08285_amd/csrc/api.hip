@@ -154,7 +154,7 @@ static int default_beam_shape()
         const char *e = getenv("SGWB_BEAM_SHAPE");
         if (e && strcmp(e, "4x4") == 0) return kBeamShape4x4;
         if (e && strcmp(e, "2x4") == 0) return kBeamShape2x4;
-        return kBeamShape2x4;
+        return kBeamShapeAuto;
     }();
     return shape;
 }

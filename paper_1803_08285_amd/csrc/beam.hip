@@ -61,19 +61,21 @@ __host__ __device__ inline int64_t frag_index(int64_t blk, int64_t ks, int part,
     return ((blk * nks + ks) * 2 + part) * 64 + lane;
 }
 
-// W[t][ldc] (row t, column = bin) -> fragments; SQUARE squares the value first
-// (used for gamma -> gamma^2).
-template <bool SQUARE>
-__global__ __launch_bounds__(256) void prep_frag_kernel(const float *__restrict__ src, int64_t ld,
-                                                         int32_t nt, int64_t n, FragDims fd,
-                                                         uint4 *__restrict__ dst)
+// Both operands' fragments in one launch: W[t][ldw] (row t, column = bin), then
+// gamma[t][npix] squared.  One lane's 8 segments of one column a thread.
+__global__ __launch_bounds__(256) void prep_frag_kernel(BJob jb, int64_t wblk, int64_t gblk)
 {
-    const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int64_t total = fd.nblk * fd.nks * 64;
-    if (gid >= total) return;
+    const int64_t nks = jb.fm.nks, nw = wblk * nks * 64;
+    int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const bool square = gid >= nw;  // uniform over a wave
+    if (square) gid -= nw;
+    if (gid >= (square ? gblk : wblk) * nks * 64) return;
+    const float *src = square ? jb.gamma : jb.w;
+    const int64_t ld = square ? jb.npix : jb.ldw, n = square ? jb.ncol : jb.nf;
+    uint4 *dst = const_cast<uint4 *>(square ? jb.Gf : jb.Wf);
     const int lane = (int)(gid & 63);
-    const int64_t ks = (gid >> 6) % fd.nks;
-    const int64_t blk = (gid >> 6) / fd.nks;
+    const int64_t ks = (gid >> 6) % nks;
+    const int64_t blk = (gid >> 6) / nks;
     const int64_t col = blk * kBlk + (lane & 31);
     const int64_t t0 = ks * kKs + (lane >> 5) * 8;
     float v[8];
@@ -81,13 +83,13 @@ __global__ __launch_bounds__(256) void prep_frag_kernel(const float *__restrict_
     for (int e = 0; e < 8; ++e) {
         const int64_t t = t0 + e;
         float x = 0.0f;
-        if (col < n && t < nt) x = src[t * ld + col];
-        v[e] = SQUARE ? x * x : x;
+        if (col < n && t < jb.nt) x = src[t * ld + col];
+        v[e] = square ? x * x : x;
     }
     uint4 hi, lo;
     split8(v, &hi, &lo);
-    dst[frag_index(blk, ks, 0, lane, fd.nks)] = hi;
-    dst[frag_index(blk, ks, 1, lane, fd.nks)] = lo;
+    dst[frag_index(blk, ks, 0, lane, nks)] = hi;
+    dst[frag_index(blk, ks, 1, lane, nks)] = lo;
 }
 
 // The three products of a K-step are issued part by part over all WM x WN
@@ -369,6 +371,52 @@ __device__ inline void beam_wave_tile(const BJob &jb, int64_t tm, int64_t tn, in
     }
 }
 
+// Few tiles: one 32 x 32 block a wave, fragments straight from L2, kSmallAhead
+// K-steps in flight, and neighbouring blocks on different XCDs (the patch order
+// above would leave most of them idle).  Bound by the latency of its loads.
+// The same sums in the same order as the larger tiles, so the same bits.
+constexpr int kSmallAhead = 4;
+
+__global__ __launch_bounds__(256) void beam_gemm_small_kernel(BJob jb)
+{
+    const int lane = threadIdx.x & 63;
+    const int64_t nks = jb.fm.nks, tile = (int64_t)blockIdx.x * kWavesPerWg + (threadIdx.x >> 6);
+    const int64_t tm = tile % jb.fm.nblk, tn = tile / jb.fm.nblk;
+    if (tn >= jb.fn.nblk) return;
+    Frags<1, 1> f[kSmallAhead];
+#pragma unroll
+    for (int d = 0; d < kSmallAhead; ++d)
+        load_frags<1, 1>(f[d], jb.Wf, jb.Gf, tm, tn, min((int64_t)d, nks - 1), jb.fm, jb.fn, lane);
+    f32x16 acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+    for (int64_t ks = 0; ks < nks; ks += kSmallAhead) {
+#pragma unroll
+        for (int d = 0; d < kSmallAhead; ++d) {
+            if (ks + d < nks) {
+#pragma unroll
+                for (int part = 0; part < 3; ++part)
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                        __builtin_bit_cast(bf16x8, f[d].a[0][part == 0 ? 1 : 0]),
+                        __builtin_bit_cast(bf16x8, f[d].b[0][part == 1 ? 1 : 0]), acc, 0, 0, 0);
+                // past the end the last K-step again, unused
+                load_frags<1, 1>(f[d], jb.Wf, jb.Gf, tm, tn, min(ks + d + kSmallAhead, nks - 1), jb.fm, jb.fn, lane);
+            }
+        }
+    }
+    const int64_t n = tn * kBlk + (lane & 31);
+    if (n >= jb.ncol) return;
+    const int64_t nB = jb.nside > 0 ? antipode_north(ring_of_north(n, jb.nside), jb.npix) : -1;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int64_t m = tm * kBlk + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+        if (m >= jb.nf) continue;
+        float *row = jb.Gam + m * (int64_t)jb.npix;
+        __builtin_nontemporal_store(acc[r], &row[n]);
+        if (nB >= 0) __builtin_nontemporal_store(acc[r], &row[nB]);
+    }
+}
+
 template <int WM, int WN>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WM == 2 ? 2 : 1))) void beam_gemm_kernel(BJob jb)
 {
@@ -445,16 +493,27 @@ hipError_t launch_beam_prep(const BJob &jb, hipStream_t s)
 {
     // the padding blocks are written too (their columns lie past the data: zeros)
     const FragDims pm{padded_blocks(jb.fm.nblk), jb.fm.nks}, pn{padded_blocks(jb.fn.nblk), jb.fn.nks};
-    const int64_t nw = pm.nblk * pm.nks * 64, ng = pn.nblk * pn.nks * 64;
-    hipLaunchKernelGGL(prep_frag_kernel<false>, dim3((unsigned)((nw + 255) / 256)), dim3(256), 0, s, jb.w, jb.ldw,
-                       jb.nt, (int64_t)jb.nf, pm, const_cast<uint4 *>(jb.Wf));
-    hipLaunchKernelGGL(prep_frag_kernel<true>, dim3((unsigned)((ng + 255) / 256)), dim3(256), 0, s, jb.gamma,
-                       (int64_t)jb.npix, jb.nt, jb.ncol, pn, const_cast<uint4 *>(jb.Gf));
+    const int64_t n = (pm.nblk + pn.nblk) * pm.nks * 64;
+    hipLaunchKernelGGL(prep_frag_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, jb, pm.nblk, pn.nblk);
     return hipGetLastError();
 }
 
+// Without a requested shape, calls of up to 4096 blocks of 32 x 32 outputs take one
+// block a wave, larger ones 2 x 4.  Measured, the beam call with its preparation
+// (2 x 4 / one block), 240 and 898 segments: 384 blocks 23 / 14 and 48 / 21 us,
+// 1536 25 / 14 and 51 / 28, 3072 25 / 19 and 51 / 40, 6144 35 / 31 and 62 / 69,
+// 12288 48 / 52 and 95 / 125.
+constexpr int64_t kSmallBlocks = 4096;
+
 hipError_t launch_beam_gemm(const BJob &jb, int shape, hipStream_t s)
 {
+    const int64_t blocks = jb.fm.nblk * jb.fn.nblk;
+    if (shape == kBeamShapeAuto && blocks <= kSmallBlocks) {
+        hipLaunchKernelGGL(beam_gemm_small_kernel, dim3((unsigned)((blocks + kWavesPerWg - 1) / kWavesPerWg)),
+                           dim3(256), 0, s, jb);
+        return hipGetLastError();
+    }
+    if (shape == kBeamShapeAuto) shape = kBeamShape2x4;
     const unsigned grid = (unsigned)bjob_workgroups(jb, shape);
     if (shape == kBeamShape2x4)
         hipLaunchKernelGGL((beam_gemm_kernel<2, 4>), dim3(grid), dim3(256), 0, s, jb);

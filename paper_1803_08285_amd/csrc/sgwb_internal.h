@@ -314,7 +314,8 @@ __host__ __device__ inline FragDims frag_dims(int64_t n, int64_t nt)
     return FragDims{(n + kBlk - 1) / kBlk, (nt + kKs - 1) / kKs};
 }
 // wave-tile shapes of the beam GEMM (blocks of 32 x 32 outputs per wave):
-// kBeamShape4x4, kBeamShape2x4 (tune_cache.h)
+// kBeamShape4x4, kBeamShape2x4 (tune_cache.h), or by the call's size
+constexpr int kBeamShapeAuto = -1;
 struct BJob {
     const uint4 *Wf, *Gf;  // fragment arrays in the job's workspace
     FragDims fm, fn;

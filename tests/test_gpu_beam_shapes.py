@@ -101,3 +101,28 @@ def test_float64_beam_at_tile_edges(nt, nf, npix):
     torch.cuda.synchronize()
     ref = (w.astype(np.longdouble).T @ (g.astype(np.longdouble) ** 2)).astype(np.float64)
     assert np.all(np.abs(G.cpu().numpy() - ref) <= 64 * 2.0 ** -53 * ref)
+
+
+@pytest.mark.parametrize("nt", [1, 17, 64, 65, 129])
+@pytest.mark.parametrize("nside,nf,antipodal", [(32, 720, True), (16, 1400, False)])
+def test_small_calls_are_rows_of_large_ones(sg, nt, nside, nf, antipodal):
+    """Calls of up to 4096 blocks of 32 x 32 outputs take one block a wave, larger
+    ones 2 x 4: a small call's rows are bitwise those of the large one (1 to 9
+    K-steps, the small form holds four in flight), which
+    meet a float64 sum."""
+    npix = 12 * nside * nside
+    assert (nf + 31) // 32 * (npix // (64 if antipodal else 32)) > 4096
+    g, t = sg.build_geometry(synth.baseline_sites("AB"), nside, sg.TGrid(nt, 0.0, 300.0, 300.0))
+    w = torch.rand((nt, nf), generator=torch.Generator().manual_seed(nt), dtype=torch.float32).cuda()
+    C = torch.zeros(w.shape, dtype=torch.complex64, device="cuda")
+
+    def beam(lo, n):
+        cut = slice(lo, lo + n)
+        return sg.make_maps(C[:, cut].contiguous(), w[:, cut].contiguous(), sg.FGrid(20.0, 0.25), lo, g, t,
+                            antipodal=antipodal, want_x=False)[1]
+
+    G = beam(0, nf)
+    for lo, n in ((0, 1), (31, 33), (5, 96), (nf - 64, 64)):
+        assert torch.equal(beam(lo, n), G[lo:lo + n]), (lo, n)
+    ref = w.cpu().double().T @ g.cpu().double() ** 2
+    assert float(((G.cpu().double() - ref).abs() / ref.clamp_min(1e-300)).max()) <= 1e-4
