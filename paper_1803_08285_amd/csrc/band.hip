@@ -187,6 +187,7 @@ __global__ __launch_bounds__(256) void band_finish_kernel(const double *__restri
     const int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (c >= npix) return;
     double tx = 0.0, tg = 0.0;
+#pragma unroll 8
     for (int64_t s = 0; s < nsplit; ++s) {
         tx += part[s * 2 * npix + c];
         tg += part[s * 2 * npix + npix + c];
@@ -244,8 +245,18 @@ __global__ __launch_bounds__(64 * kFinishWaves) void band_partial_finish_kernel(
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int32_t p = blockIdx.x * 64 + lane;
     double acc = 0.0;
-    if (p < npix)
-        for (int64_t r = wv; r < nrows; r += kFinishWaves) acc += part[r * npix + p];
+    if (p < npix) {
+        // eight rows' loads go out together, added in their order
+        int64_t r = wv;
+        for (; r + 7 * kFinishWaves < nrows; r += 8 * kFinishWaves) {
+            double v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = part[(r + u * kFinishWaves) * npix + p];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) acc += v[u];
+        }
+        for (; r < nrows; r += kFinishWaves) acc += part[r * npix + p];
+    }
     red[wv][lane] = acc;
     __syncthreads();
     if (wv != 0 || p >= npix) return;

@@ -121,17 +121,18 @@ size_t xm_workspace_bytes(int64_t k0, int32_t nt, int32_t nf, int32_t npix)
     return up256_(frags) + up256_(scales) + up256_(tmax) + up256_(items * sizeof(float4)) + up256_(items * sizeof(float));
 }
 
-// Largest |tau| of the seeds, in two passes without atomics: per-block maxima,
-// then one block; out[0] holds the result.
-__global__ __launch_bounds__(256) void xm_tmax_kernel(const double *__restrict__ tau, int64_t n,
-                                                      double *__restrict__ part)
+constexpr int kXmPrepThreads = 1024;
+
+// Largest |tau| of a block's share of the seeds (block b of n), without atomics;
+// xm_tmax_final_kernel takes the largest of the blocks' (a maximum is exact in
+// any order).
+__device__ __forceinline__ void xm_tmax_block(const double *__restrict__ tau, int64_t n, int64_t b, int64_t nb,
+                                              double *__restrict__ part, double *red)
 {
-    __shared__ double red[256];
     // four independent maxima per thread, so that their loads go out together
-    // (a maximum is exact in any order)
     double m[4] = {0.0, 0.0, 0.0, 0.0};
-    const int64_t stride = (int64_t)gridDim.x * 256;
-    int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int64_t stride = nb * kXmPrepThreads;
+    int64_t i = b * kXmPrepThreads + threadIdx.x;
     for (; i + 3 * stride < n; i += 4 * stride) {
 #pragma unroll
         for (int u = 0; u < 4; ++u) m[u] = fmax(m[u], fabs(tau[i + u * stride]));
@@ -139,11 +140,11 @@ __global__ __launch_bounds__(256) void xm_tmax_kernel(const double *__restrict__
     for (; i < n; i += stride) m[0] = fmax(m[0], fabs(tau[i]));
     red[threadIdx.x] = fmax(fmax(m[0], m[1]), fmax(m[2], m[3]));
     __syncthreads();
-    for (int st = 128; st > 0; st >>= 1) {
+    for (int st = kXmPrepThreads / 2; st > 0; st >>= 1) {
         if ((int)threadIdx.x < st) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + st]);
         __syncthreads();
     }
-    if (threadIdx.x == 0) part[blockIdx.x] = red[0];
+    if (threadIdx.x == 0) part[b] = red[0];
 }
 
 constexpr int kSymThreads = 1024;
@@ -205,14 +206,13 @@ __global__ __launch_bounds__(256) void xm_tmax_final_kernel(const double *__rest
 // the waves' maxima meet in LDS (a maximum is exact in any order).
 constexpr int kXmScaleWaves = 16;
 
-__global__ __launch_bounds__(64 * kXmScaleWaves) void xm_scale_kernel(XmArgs x, const float2 *__restrict__ C,
-                                                                      const float *__restrict__ w,
-                                                                      int *__restrict__ e_out)
+__device__ __forceinline__ void xm_scale_strip(const XmArgs &x, int64_t strip, const float2 *__restrict__ C,
+                                               const float *__restrict__ w, int *__restrict__ e_out,
+                                               float (*red)[64])
 {
     static_assert(kXmS == 64, "one lane per bin of the strip");
-    __shared__ float red[kXmScaleWaves][64];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int64_t i = (int64_t)blockIdx.x * kXmS + lane;  // strip-local bin index over all strips
+    const int64_t i = strip * kXmS + lane;  // strip-local bin index over all strips
     const int64_t c = (x.strip_first * kXmS + i) - x.a.k0;  // column in C
     float mx = 0.0f;
     if (c >= 0 && c < x.a.nf) {
@@ -248,6 +248,31 @@ __global__ __launch_bounds__(64 * kXmScaleWaves) void xm_scale_kernel(XmArgs x, 
     e_out[i] = e;
 }
 
+// First preparation launch of a call, kXmPrepThreads a workgroup: the strips'
+// scales, the antipodal spot check and the largest |tau|, none of which needs
+// another; a call with prepared seeds, or seeds alone, has only its part.  (As
+// launches of their own they took 20, 5 and 7 us of a 6272-bin sub-band's call at
+// nside 16, none of which fills the chip.)
+__global__ __launch_bounds__(kXmPrepThreads) void xm_prep_kernel(XmArgs x, const float2 *__restrict__ C,
+                                                                 const float *__restrict__ w, int *__restrict__ e_out,
+                                                                 const float *__restrict__ gamma,
+                                                                 const double *__restrict__ tau,
+                                                                 double *__restrict__ flags, double *__restrict__ part,
+                                                                 int64_t nscale, int64_t nsym, int64_t ntmax)
+{
+    static_assert(64 * kXmScaleWaves == kXmPrepThreads, "one workgroup a strip");
+    __shared__ double red[kXmPrepThreads];
+    int64_t b = blockIdx.x;
+    if (b < nscale) {
+        xm_scale_strip(x, b, C, w, e_out, reinterpret_cast<float(*)[64]>(red));
+    } else if ((b -= nscale) < nsym) {
+        const int bad = __syncthreads_or(antipodal_mismatch(gamma, tau, x.a.nt, x.a.npix, x.a.nside, b, kSymParts));
+        if (threadIdx.x == 0) flags[b] = bad ? 1.0 : 0.0;
+    } else {
+        xm_tmax_block(tau, (int64_t)x.a.nt * x.a.npix, b - nsym, ntmax, part, red);
+    }
+}
+
 __device__ __forceinline__ float cheb(int m, float s)
 {
     const float s2 = s * s;
@@ -270,15 +295,15 @@ __device__ __forceinline__ int64_t xm_wide_strips(const XmArgs &x)
 // the parts that the call's form reads (none, if it is not a matrix-core form).
 // Bound by what it writes: 48 of the 64 bytes per segment, bin and component
 // in the four-term form.
-__global__ __launch_bounds__(256) void xm_afrag_kernel(XmArgs x, const float2 *__restrict__ C,
-                                                       const float *__restrict__ w, const int *__restrict__ e_in,
-                                                       const double *__restrict__ rec, uint4 *__restrict__ A)
+__device__ __forceinline__ void xm_afrag(const XmArgs &x, int64_t block, const float2 *__restrict__ C,
+                                         const float *__restrict__ w, const int *__restrict__ e_in,
+                                         const double *__restrict__ rec, uint4 *__restrict__ A)
 {
 #pragma clang fp contract(off)  // hi and lo from the same rounded float32 value
     const int form = (int)rec[1];
     const bool wide = form == kXFormWide;
     if (!wide && form != SGWB_XFORM_MFMA4 && form != SGWB_XFORM_MFMA5 && form != SGWB_XFORM_MFMA5S) return;
-    const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int64_t gid = block * 256 + threadIdx.x;
     const int64_t total = (wide ? xm_wide_strips(x) : x.nstrips) * x.nchunks * 4 * 64;
     if (gid >= total) return;
     const int lane = (int)(gid & 63);
@@ -385,12 +410,12 @@ __device__ __forceinline__ void xm_amps(float g, double ta, float eta_scale, flo
 
 // amp[t][q] = (a_0, a_1, a_2, a_3), amp4[t][q] = a_4 for segment t and pixel
 // pair q (the pair's first pixel carries the seeds).
-__global__ __launch_bounds__(256) void xm_amp_kernel(XmArgs x, const float *__restrict__ gamma,
-                                                     const double *__restrict__ tau, const double *__restrict__ rec,
-                                                     float4 *__restrict__ amp, float *__restrict__ amp4)
+__device__ __forceinline__ void xm_amp(const XmArgs &x, int64_t block, const float *__restrict__ gamma,
+                                       const double *__restrict__ tau, const double *__restrict__ rec,
+                                       float4 *__restrict__ amp, float *__restrict__ amp4)
 {
     const int64_t npairs = x.a.npix / 2;
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int64_t i = block * 256 + threadIdx.x;
     if (i >= (int64_t)x.a.nt * npairs) return;
     const int64_t t = i / npairs, q = i - t * npairs;
     const int64_t off = t * x.a.npix + q;
@@ -399,6 +424,20 @@ __global__ __launch_bounds__(256) void xm_amp_kernel(XmArgs x, const float *__re
     xm_amps(gamma[off], tau[off], (float)(wide ? x.eta_scale * kXmWideScale : x.eta_scale), a);
     amp[i] = make_float4(a[0], a[1], a[2], a[3]);
     if (!wide) amp4[i] = a[4];
+}
+
+// Second preparation launch, once the form is known: nfrag workgroups of data-side
+// fragments, the rest amplitudes.
+__global__ __launch_bounds__(256) void xm_operands_kernel(XmArgs x, const float2 *__restrict__ C,
+                                                          const float *__restrict__ w, const int *__restrict__ e_in,
+                                                          const float *__restrict__ gamma,
+                                                          const double *__restrict__ tau,
+                                                          const double *__restrict__ rec, uint4 *__restrict__ A,
+                                                          float4 *__restrict__ amp, float *__restrict__ amp4,
+                                                          int64_t nfrag)
+{
+    if (blockIdx.x < nfrag) xm_afrag(x, blockIdx.x, C, w, e_in, rec, A);
+    else xm_amp(x, blockIdx.x - nfrag, gamma, tau, rec, amp, amp4);
 }
 
 // Split a float32 value into float16 hi + lo with plain float32 arithmetic: hi
@@ -955,43 +994,29 @@ void fill_xmjob(XmJob *j, const MapArgs &a, const float *C, const float *w, cons
 
 int64_t xmjob_tiles(const XmJob &j) { return j.x.nstrips * j.npblocks; }
 
-// Data-side preparation of a call: per-bin scales and the A fragments (after
-// the seed side, whose form says which of them are needed).
-static hipError_t launch_xm_data_prep(const XmJob &j, hipStream_t s)
+// Preparation of a call: of its data (per-bin scales and the A fragments), of its
+// seeds (the form record and the Bessel amplitudes, which depend on the seeds
+// and the frequency spacing alone), or of both.
+static hipError_t launch_xm_prep_parts(const XmJob &j, bool data, bool seeds, hipStream_t s)
 {
     const float2 *Cc = reinterpret_cast<const float2 *>(j.C);
-    hipLaunchKernelGGL(xm_scale_kernel, dim3((unsigned)j.x.nstrips), dim3(64 * kXmScaleWaves), 0, s, j.x, Cc, j.w,
-                       const_cast<int *>(j.e));
-    const int64_t na = j.x.nstrips * j.x.nchunks * 4 * 64;
-    hipLaunchKernelGGL(xm_afrag_kernel, dim3((unsigned)((na + 255) / 256)), dim3(256), 0, s, j.x, Cc, j.w, j.e,
-                       j.tmax, const_cast<uint4 *>(j.A));
-    return hipGetLastError();
-}
-
-// Seed-side preparation: the form record (largest |tau|, the antipodal spot
-// check, the form) and the Bessel amplitudes.  They depend on the seeds and
-// the frequency spacing alone, not on the data or the band.
-static hipError_t launch_xm_seed_prep(const XmJob &j, hipStream_t s)
-{
-    const int64_t nt = (int64_t)j.x.a.nt * j.x.a.npix;
-    const int parts = (int)std::min<int64_t>(kTmaxParts, (nt + 255) / 256);
+    const int64_t n = (int64_t)j.x.a.nt * j.x.a.npix;
+    const int64_t nscale = data ? j.x.nstrips : 0, nsym = seeds ? kSymParts : 0;
+    const int64_t ntmax = seeds ? std::min<int64_t>(kTmaxParts, (n + 4 * kXmPrepThreads - 1) / (4 * kXmPrepThreads)) : 0;
     double *part = j.tmax + 2, *flags = j.tmax + 2 + kTmaxParts;
-    hipLaunchKernelGGL(xm_tmax_kernel, dim3((unsigned)parts), dim3(256), 0, s, j.tau, nt, part);
-    hipLaunchKernelGGL(xm_symcheck_kernel, dim3(kSymParts), dim3(kSymThreads), 0, s, j.gamma, j.tau, j.x.a.nt,
-                       (int64_t)j.x.a.npix, j.x.a.nside, flags);
-    hipLaunchKernelGGL(xm_tmax_final_kernel, dim3(1), dim3(256), 0, s, part, parts, flags, j.x.eta_scale,
-                       j.x.a.tau_limit, j.x.a.unit_c, j.tmax);
-    const int64_t ni = (int64_t)j.x.a.nt * (j.x.a.npix / 2);
-    hipLaunchKernelGGL(xm_amp_kernel, dim3((unsigned)((ni + 255) / 256)), dim3(256), 0, s, j.x, j.gamma, j.tau, j.tmax,
-                       j.amp, j.amp4);
+    hipLaunchKernelGGL(xm_prep_kernel, dim3((unsigned)(nscale + nsym + ntmax)), dim3(kXmPrepThreads), 0, s, j.x, Cc,
+                       j.w, const_cast<int *>(j.e), j.gamma, j.tau, flags, part, nscale, nsym, ntmax);
+    if (seeds)
+        hipLaunchKernelGGL(xm_tmax_final_kernel, dim3(1), dim3(256), 0, s, part, (int)ntmax, flags, j.x.eta_scale,
+                           j.x.a.tau_limit, j.x.a.unit_c, j.tmax);
+    const int64_t nfrag = data ? j.x.nstrips * j.x.nchunks : 0;  // 4 x 64 threads each
+    const int64_t namp = seeds ? ((int64_t)j.x.a.nt * (j.x.a.npix / 2) + 255) / 256 : 0;
+    hipLaunchKernelGGL(xm_operands_kernel, dim3((unsigned)(nfrag + namp)), dim3(256), 0, s, j.x, Cc, j.w, j.e, j.gamma,
+                       j.tau, j.tmax, const_cast<uint4 *>(j.A), j.amp, j.amp4, nfrag);
     return hipGetLastError();
 }
 
-hipError_t launch_xm_prep(const XmJob &j, hipStream_t s)
-{
-    const hipError_t e = launch_xm_seed_prep(j, s);
-    return e != hipSuccess ? e : launch_xm_data_prep(j, s);
-}
+hipError_t launch_xm_prep(const XmJob &j, hipStream_t s) { return launch_xm_prep_parts(j, true, true, s); }
 
 size_t xm_seed_bytes(int32_t nt, int32_t npix)
 {
@@ -1015,7 +1040,7 @@ hipError_t launch_xm_seed_products(const MapArgs &a, const float *gamma, const d
     XmJob j;
     fill_xmjob(&j, a, nullptr, nullptr, gamma, tau, nullptr, nullptr);
     use_seed_buffer(&j, seeds);
-    return launch_xm_seed_prep(j, s);
+    return launch_xm_prep_parts(j, false, true, s);
 }
 
 hipError_t launch_xm_batched(const XmJob *jobs_dev, int32_t njobs, int64_t grid, hipStream_t s)
@@ -1052,7 +1077,7 @@ hipError_t launch_dirty_map_mfma(const MapArgs &a, const float *C, const float *
     fill_xmjob(&j, a, C, w, gamma, tau, X, work);
     if (seeds) use_seed_buffer(&j, const_cast<void *>(seeds));
     if (form_rec) *form_rec = j.tmax;
-    hipError_t err = seeds ? launch_xm_data_prep(j, s) : launch_xm_prep(j, s);
+    hipError_t err = launch_xm_prep_parts(j, true, !seeds, s);
     if (err != hipSuccess) return err;
     return launch_xm_main(j, s);
 }

@@ -17,23 +17,24 @@
 
 namespace sgwb {
 
-__global__ __launch_bounds__(256) void pair_seeds_kernel(const float *__restrict__ gamma,
-                                                         const double *__restrict__ tau, int64_t n, int64_t npix,
-                                                         float *__restrict__ g2, double *__restrict__ t2)
+// The pairs' seeds (workgroups [0, gs), a grid-stride loop over n items) and data
+// (the rest) in one launch.
+__global__ __launch_bounds__(256) void pair_kernel(const float *__restrict__ gamma, const double *__restrict__ tau,
+                                                   int64_t n, int64_t npix, float *__restrict__ g2,
+                                                   double *__restrict__ t2, const float *__restrict__ u,
+                                                   const float *__restrict__ wn, int64_t ldc, int32_t nq, int32_t nf,
+                                                   float *__restrict__ y, int64_t gs)
 {
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
-        const int64_t j = i + npix < n ? i + npix : i + npix - n;  // same pixel, next segment (periodic)
-        g2[i] = gamma[i] * gamma[j];
-        t2[i] = tau[j] - tau[i];
+    if (blockIdx.x < gs) {
+        for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += gs * 256) {
+            const int64_t j = i + npix < n ? i + npix : i + npix - n;  // same pixel, next segment (periodic)
+            g2[i] = gamma[i] * gamma[j];
+            t2[i] = tau[j] - tau[i];
+        }
+        return;
     }
-}
-
-__global__ __launch_bounds__(256) void pair_weights_kernel(const float *__restrict__ u, const float *__restrict__ wn,
-                                                           int64_t ldc, int32_t nq, int32_t nf,
-                                                           float *__restrict__ y)
-{
-    const int64_t n = (int64_t)nq * nf;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+    const int64_t nw = (int64_t)nq * nf;
+    for (int64_t i = ((int64_t)blockIdx.x - gs) * 256 + threadIdx.x; i < nw; i += (gridDim.x - gs) * 256) {
         const int64_t q = i / nf, c = i - q * nf, qn = q + 1 < nq ? q + 1 : 0;
         y[i] = -(u[qn * ldc + c] + wn[q * ldc + c]);
     }
@@ -61,10 +62,9 @@ hipError_t launch_fisher_neighbours(const MapArgs &a, const float *u, const floa
     float *y = reinterpret_cast<float *>(p);
 
     const int64_t ns = (int64_t)nq * a.npix, nw = (int64_t)nq * a.nf;
-    const unsigned gs = (unsigned)std::min<int64_t>((ns + 255) / 256, 65536);
-    const unsigned gw = (unsigned)std::min<int64_t>((nw + 255) / 256, 65536);
-    hipLaunchKernelGGL(pair_seeds_kernel, dim3(gs), dim3(256), 0, s, gamma, tau, ns, (int64_t)a.npix, g2, t2);
-    hipLaunchKernelGGL(pair_weights_kernel, dim3(gw), dim3(256), 0, s, u, wn, a.ldc, nq, a.nf, y);
+    const int64_t gs = std::min<int64_t>((ns + 255) / 256, 65536), gw = std::min<int64_t>((nw + 255) / 256, 65536);
+    hipLaunchKernelGGL(pair_kernel, dim3((unsigned)(gs + gw)), dim3(256), 0, s, gamma, tau, ns, (int64_t)a.npix, g2, t2, u,
+                       wn, a.ldc, nq, a.nf, y, gs);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
 
