@@ -869,11 +869,13 @@ constexpr int kXcds = 8;
 
 // Order of the (strip, pixel block) tiles: blocks of kXmPB pixel blocks, all
 // strips inside a block, pixel blocks fastest.  The ~64 workgroups resident on
-// one XCD then cover 8 strips x 8 pixel blocks and share, chunk by chunk, the
-// seeds of 8 pixel blocks (24 KB each) and the data operands of 8 strips
+// one XCD then cover 16 strips x 4 pixel blocks and share, chunk by chunk, the
+// seeds of 4 pixel blocks (49 KB each) and the data operands of 16 strips
 // (24-32 KB each) through that XCD's L2.  A bijection for any strip and block
-// counts.
-constexpr uint32_t kXmPB = 8;
+// counts.  Measured with 2 / 4 / 8 / 16 pixel blocks: the full band at nside 32
+// 14.9 / 14.9 / 15.3 / 18.6 ms, at nside 64 (X and Gam) 60.0 / 57.8 / 58.7 ms / -,
+// 6272 bins at nside 16 620 / 618 / 629 / 635 us.
+constexpr uint32_t kXmPB = 4;
 __device__ __forceinline__ void xm_tile_coords(uint32_t T, uint32_t nstrips, uint32_t npb, uint32_t &strip,
                                                uint32_t &pb)
 {
