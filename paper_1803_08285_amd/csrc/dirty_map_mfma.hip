@@ -31,10 +31,10 @@
 // (its largest |y| lands in [2^13, 2^14)), 2^12 on the pixel side, and 2^g_m
 // per term.
 //
-// Data-side operands A (per strip, 16-segment chunk, component, 32-bin block,
-// part, lane: the operand layout of the instruction) are prepared once per call
-// by two small kernels; a third evaluates the Bessel amplitudes, which depend
-// on the seed alone, once per (segment, pixel pair).  The pixel-side operands
+// Data-side operands A (per strip, 16-segment chunk, component, part, 32-bin
+// block, lane: the operand layout of the instruction) are prepared once per
+// call, and with them the Bessel amplitudes, which depend on the seed alone,
+// once per (segment, pixel pair).  The pixel-side operands
 // B are generated by each wave for its 32 pixel pairs and 16 segments (one
 // lane = one pixel x 8 segments) from those amplitudes and the strip's
 // phasor, term by term, so the matrix cores work on term m while the vector
@@ -911,7 +911,8 @@ __device__ __forceinline__ int64_t xcd_tile(int64_t L, int64_t n)
 // diagonal of that band 1210 -> 1008 us, the full band 16.04 -> 15.45 ms, against
 // one eight-wave workgroup with 64-bit seed addresses, every part copied and the
 // phase reduced by four float64 instructions (eight waves with the other changes:
-// 725 and 1164 us).
+// 725 and 1164 us).  With what came since (strips of 128 bins for the overlap
+// terms, one preparation launch, the tile order): 618 us, 834 us, 14.9 ms.
 template <int NC, bool EXT>
 __global__ __launch_bounds__(64 * kXmWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void xm_main_kernel(
     XmArgs x, int64_t npblocks, const uint4 *__restrict__ A, const int *__restrict__ e_in,
