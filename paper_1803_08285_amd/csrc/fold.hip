@@ -7,9 +7,9 @@
 //   x_tau = sum_d [ s_a C_a - eps_{a-1} (s_a + s_{a-1}) / 2 C_{a-1}
 //                           - eps_{a+1} (s_a + s_{a+1}) / 2 C_{a+1} ]
 // The neighbour of a day's first segment is the previous day's last segment.
-// One thread per (group of kFoldT consecutive folded segments, bin): per day it
-// reads the group's rows and the two neighbouring rows (kFoldT + 2 rows for
-// kFoldT outputs, where one thread per segment read three rows per output)
+// One thread per (group of T consecutive folded segments, bin): per day it
+// reads the group's rows and the two neighbouring rows (T + 2 rows for
+// T outputs, where one thread per segment read three rows per output)
 // and accumulates each output in float64 in the oracle's order; one rounding
 // to float32 at the end.  Loads are issued ahead of the uniform presence
 // branches, so the waves keep enough loads in flight for an HBM-bound sweep.
@@ -17,8 +17,14 @@
 
 namespace sgwb {
 
-constexpr int kFoldT = 4;  // consecutive folded segments per thread
+// Consecutive folded segments per thread: six (fewer rows read twice) where that
+// leaves 2400 workgroups, else four.  Measured (four / six), ten
+// days: 898 segments x 16411 bins 477 / 465 us, 240 x 16384 121 / 111, 898 x 300
+// (300 workgroups of six) 24.7 / 28.9, 898 x 3584 (2100) 103.4 / 104.9; five days,
+// 898 x 4096 (2400) 57.5 / 55.5.
+constexpr int64_t kFoldSixMin = 2400;
 
+template <int kFoldT>
 __global__ __launch_bounds__(256) void fold_kernel(const float2 *__restrict__ C, const float *__restrict__ sv,
                                                    const uint8_t *__restrict__ present, int64_t ldc, int32_t ndays,
                                                    int32_t nt, int32_t nf, double W, float *__restrict__ v,
@@ -91,9 +97,16 @@ __global__ __launch_bounds__(256) void fold_kernel(const float2 *__restrict__ C,
 hipError_t launch_fold(const float *C, const float *sv, const uint8_t *present, int64_t ldc, int32_t ndays, int32_t nt,
                        int32_t nf, double W, float *v, float *u, float *w, float *x, hipStream_t s)
 {
-    const dim3 grid((unsigned)((nf + 255) / 256), (unsigned)((nt + kFoldT - 1) / kFoldT));
-    hipLaunchKernelGGL(fold_kernel, grid, dim3(256), 0, s, reinterpret_cast<const float2 *>(C), sv, present, ldc,
-                       ndays, nt, nf, W, v, u, w, reinterpret_cast<float2 *>(x));
+    const int64_t cols = ((int64_t)nf + 255) / 256;
+    auto go = [&](auto kernel, int32_t t) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)cols, (unsigned)((nt + t - 1) / t)), dim3(256), 0, s,
+                           reinterpret_cast<const float2 *>(C), sv, present, ldc, ndays, nt, nf, W, v, u, w,
+                           reinterpret_cast<float2 *>(x));
+    };
+    if (cols * ((nt + 5) / 6) >= kFoldSixMin)
+        go(fold_kernel<6>, 6);
+    else
+        go(fold_kernel<4>, 4);
     return hipGetLastError();
 }
 

@@ -61,3 +61,22 @@ def test_fold_column_window(sg, oracle_mod):
     torch.cuda.synchronize()
     for a, b in zip(full, win):
         assert torch.equal(a[:, 50:130], b)
+
+
+@pytest.mark.parametrize("nt,nf", [(898, 4100), (37, 87900), (6, 614300)])
+def test_large_folds_are_columns_of_small_ones(sg, nt, nf):
+    """From 2400 workgroups on a thread folds six segments instead of four (898 =
+    149 x 6 + 4, 37 = 6 x 6 + 1): the first and last columns are bitwise those of
+    folds of these columns alone, which meet the oracle above."""
+    assert (nf + 255) // 256 * ((nt + 5) // 6) >= 2400
+    ndays = 2
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(nt)
+    C = torch.view_as_complex(torch.randn((ndays, nt, nf, 2), generator=gen, device="cuda"))
+    s = torch.rand((ndays, nt, nf), generator=gen, device="cuda")
+    present = (torch.rand((ndays, nt), generator=gen, device="cuda") >= 0.1).to(torch.uint8)
+    large = sg.fold(C, s, present, W)
+    for cut in (slice(0, 130), slice(nf - 67, nf)):
+        small = sg.fold(C[:, :, cut].contiguous(), s[:, :, cut].contiguous(), present, W)
+        for a, b in zip(large, small):
+            assert torch.equal(a[:, cut], b)
