@@ -44,6 +44,7 @@
 // On request the epilogue also writes the float64 sum of each strip's band
 // columns per pixel (the broadband map without reading X back); with no X
 // (a broadband-only call) those sums are all it writes.
+#include "seed_rows.h"
 #include "sgwb_internal.h"
 
 namespace sgwb {
@@ -54,7 +55,6 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kXmS = 64;       // bins per strip
-constexpr int kXmT = 16;       // segments per chunk (MFMA K)
 constexpr int kXmParts = 8;    // m0h m0l m1h m1l m2h m3 m4 m2l: a four-term form needs the first six
 constexpr int kXmWaves = 4;    // waves per workgroup
 constexpr int kXmPairs = 32 * kXmWaves;  // pixel pairs per workgroup
@@ -316,7 +316,7 @@ __device__ __forceinline__ void xm_afrag(const XmArgs &x, int64_t block, const f
     const int64_t c = wide ? (x.a.k0 / kXmWideS + strip) * kXmWideS + j - x.a.k0
                            : (x.strip_first + strip) * kXmS + j - x.a.k0;
     const bool inside = c >= 0 && c < x.a.nf;
-    const int t0 = (int)chunk * kXmT + (lane >> 5) * 8;
+    const int half = lane >> 5, t0 = (int)chunk_row(x.a.nt, chunk) + half * half_row(x.a.nt);
     const float scale = inside ? ldexpf(1.0f, e_in[c + x.a.k0 - x.strip_first * kXmS]) : 0.0f;
     const float s = wide ? ((float)j - 63.5f) * (1.0f / 63.5f) : ((float)j - 31.5f) * (1.0f / 31.5f);
     float y[8];
@@ -324,7 +324,7 @@ __device__ __forceinline__ void xm_afrag(const XmArgs &x, int64_t block, const f
     for (int e = 0; e < 8; ++e) {
         const int t = t0 + e;
         float v = 0.0f;
-        if (inside && t < x.a.nt) {
+        if (inside && slot_is_new(x.a.nt, chunk, half, e)) {
             const int64_t off = (int64_t)t * x.a.ldc + c;
             const float2 cv = x.a.unit_c ? make_float2(1.0f, 0.0f) : C[off];
             v = w[off] * (comp && !wide ? cv.y : cv.x) * scale;
@@ -563,8 +563,8 @@ __device__ __forceinline__ __attribute__((address_space(3))) T *lds_ptr(T *p)
     return (__attribute__((address_space(3))) T *)p;
 }
 
-// A bounded view of global memory at a wave-uniform address: loads beyond
-// `bytes` give zero.
+// A view of `bytes` bytes of global memory at a wave-uniform address; its users
+// stay inside it.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_view(const void *p, int64_t bytes)
 {
     const uint64_t a = (uint64_t)(uintptr_t)p;
@@ -627,24 +627,27 @@ __device__ __forceinline__ void xm_tile_n(const XmArgs &x, int64_t strip_rel, in
 
     // Seeds (delays and amplitudes) of this lane's 8 segments, loaded one chunk
     // ahead through buffer views: the chunk's first row is the view's base, the
-    // row within the chunk a scalar offset and the lane's place a vector offset
+    // row within a half a scalar offset and the lane's place a vector offset
     // that never changes, so a load costs no vector instruction for its address
-    // (64-bit row addresses took 40 per chunk, 16 of them quarter-rate).  A view
-    // ends with the last segment: padding rows of the last chunk read zero,
-    // which their zero data-side operands turn into exactly nothing.  A row of
-    // delays and one of amplitudes have the same number of bytes.
+    // (64-bit row addresses took 40 per chunk, 16 of them quarter-rate).  Every
+    // row lies inside the day (seed_rows.h): a view's range check need not take
+    // the scalar offset into account.  (Scalar offsets that also repeat the last
+    // row of a day of fewer than eight segments made the full band 1.5 % slower;
+    // such a day is EXT.)  A row of delays and one of amplitudes have the same
+    // number of bytes.
     f32x4 aN[8];
     float a4N[8];
     double tN[8];
     const uint32_t row = (uint32_t)npairs * 16u;
-    const uint32_t aoff = (uint32_t)(lane >> 5) * 8u * row + (uint32_t)pc * 16u;
+    const uint32_t aoff = (uint32_t)(lane >> 5) * (uint32_t)half_row(x.a.nt) * row + (uint32_t)pc * 16u;
     const uint32_t toff = aoff - (uint32_t)pc * 8u, a4off = aoff >> 2;
     auto load_seeds = [&](int64_t ch) {
-        if constexpr (EXT) {  // a chunk's rows may span more than 32 bits of bytes
-            const int t0 = (int)ch * kXmT + (lane >> 5) * 8;
+        const int64_t first = chunk_row(x.a.nt, ch), left = x.a.nt - first;  // the window's first row, rows to the end
+        if constexpr (EXT) {  // a chunk's rows may span more than 32 bits of bytes, or be fewer than eight
+            const int t0 = (int)first + (lane >> 5) * half_row(x.a.nt);
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                const int t = min(t0 + e, x.a.nt - 1);
+                const int t = t0 + slot_row(x.a.nt, e);
                 const int64_t q = (int64_t)t * npairs + pc;
                 aN[e] = gmem(reinterpret_cast<const f32x4 *>(amp))[q];
                 if (NT == 5) a4N[e] = gmem(amp4)[q];
@@ -652,7 +655,6 @@ __device__ __forceinline__ void xm_tile_n(const XmArgs &x, int64_t strip_rel, in
             }
             return;
         }
-        const int64_t first = ch * kXmT, left = x.a.nt - first;  // rows from the chunk's first to the end
         const auto va = buffer_view(amp + first * npairs, left * row);
         const auto vt = buffer_view(tau + first * x.a.npix, left * row);
         const auto v4 = buffer_view(amp4 + first * npairs, left * (row >> 2));
@@ -937,7 +939,7 @@ __global__ __launch_bounds__(64 * kXmWaves) __attribute__((amdgpu_waves_per_eu(2
 // 8 sum_j ceil(n_j / 8) workgroups: the few slots past an XCD's share exit.
 // (A persistent loop over tiles was measured slower: its state pushed the
 // kernel to the register limit.)  A tile's result does not depend on which
-// workgroup computes it.  No job is XmArgs::ext (a plan with one launches job by
+// workgroup computes it.  No job is XmArgs::ext (a plan launches those job by
 // job).
 __global__ __launch_bounds__(64 * kXmWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void xm_batched_kernel(
     const XmJob *__restrict__ jobs, int32_t njobs)
@@ -976,7 +978,8 @@ void fill_xmjob(XmJob *j, const MapArgs &a, const float *C, const float *w, cons
     const double fmax = std::max(std::fabs(a.f0 + a.df * (double)(a.k0 - kXmS)),
                                  std::fabs(a.f0 + a.df * (double)(a.k0 + a.nf + kXmS)));
     // delays reach 2 R / c, the overlap terms' differences of two 4 R / c
-    x.ext = !(fmax * 4.0 * kEarthRadius / kLightSpeed < kXmMaxTurns) || (int64_t)(a.npix / 2) * 16 * kXmT > 0xffffffffll;
+    x.ext = !(fmax * 4.0 * kEarthRadius / kLightSpeed < kXmMaxTurns) ||
+            (int64_t)(a.npix / 2) * 16 * kXmT > 0xffffffffll || a.nt < kXmHalf;
     const size_t frag_bytes = (size_t)x.nstrips * x.nchunks * kXmFrags * 64 * sizeof(uint4);
     j->A = reinterpret_cast<uint4 *>(work);
     j->e = reinterpret_cast<int *>(reinterpret_cast<char *>(work) + (frag_bytes + 255) / 256 * 256);

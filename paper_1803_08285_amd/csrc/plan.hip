@@ -131,17 +131,17 @@ static hipError_t enqueue(sgwb_plan *p, hipStream_t s, int parts)
     if ((parts & 1) && p->xm_tiles > 0) {
         for (auto &x : p->xmjobs)
             if ((e = launch_xm_prep(x, s)) != hipSuccess) return e;
-        bool per_job = p->tun.xm_per_job;
-        for (auto &x : p->xmjobs) per_job = per_job || x.x.ext;
-        if (per_job) {
-            // the single-call kernel per job: the same tiles, so the same bits
-            for (auto &x : p->xmjobs)
-                if ((e = launch_xm_main(x, s)) != hipSuccess) return e;
-        } else {
-            const int64_t grid = xm_batched_grid(p->xmjobs.data(), (int32_t)p->xmjobs.size());
-            if ((e = launch_xm_batched(p->d_xmjobs, (int32_t)p->xmjobs.size(), grid, s)) != hipSuccess)
-                return e;
+        // jobs the multi-job kernel takes (the rest, XmArgs::ext, stand behind them)
+        int32_t batched = 0;
+        if (!p->tun.xm_per_job)
+            while (batched < (int32_t)p->xmjobs.size() && !p->xmjobs[batched].x.ext) ++batched;
+        if (batched > 0) {
+            const int64_t grid = xm_batched_grid(p->xmjobs.data(), batched);
+            if ((e = launch_xm_batched(p->d_xmjobs, batched, grid, s)) != hipSuccess) return e;
         }
+        // the single-call kernel per job: the same tiles, so the same bits
+        for (size_t i = batched; i < p->xmjobs.size(); ++i)
+            if ((e = launch_xm_main(p->xmjobs[i], s)) != hipSuccess) return e;
     }
     if (parts & 1) {
         const int64_t cap = (int64_t)p->num_cus * p->tun.x_grid_per_cu;
@@ -464,6 +464,7 @@ int sgwb_plan_create(const sgwb_job *jobs, int32_t njobs, uint32_t flags, sgwb_p
             p->bjobs.push_back(b);
         }
     }
+    std::stable_partition(p->xmjobs.begin(), p->xmjobs.end(), [](const XmJob &x) { return !x.x.ext; });
     if (!p->xjobs.empty()) e = hipMalloc(&p->d_xjobs, p->xjobs.size() * sizeof(XJob));
     if (e == hipSuccess && !p->xmjobs.empty()) e = hipMalloc(&p->d_xmjobs, p->xmjobs.size() * sizeof(XmJob));
     if (e == hipSuccess && !p->bjobs.empty()) e = hipMalloc(&p->d_bjobs, p->bjobs.size() * sizeof(BJob));

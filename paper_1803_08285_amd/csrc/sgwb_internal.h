@@ -257,8 +257,8 @@ struct XmArgs {
     MapArgs a;
     int64_t strip_first, nstrips, nchunks;
     double eta_scale;  // 2 pi 31.5 df
-    // phases beyond the fixed-point reduction (frequencies above 6 MHz) or chunks
-    // of seeds beyond 32-bit offsets (nside >= 2048)
+    // phases beyond the fixed-point reduction (frequencies above 6 MHz), chunks of
+    // seeds beyond 32-bit offsets (nside >= 2048), or days of fewer than eight segments
     int32_t ext;
 };
 // One job of the multi-job matrix-core dirty map: operands prepared per job,

@@ -164,3 +164,32 @@ def test_plan_rejects_bad_jobs(sg):
     jobs[1].band = (5, 10_000)
     with pytest.raises(sg.SgwbError, match="band"):
         sg.Plan(jobs, autotune=False)
+
+
+def test_plan_with_jobs_beyond_the_multi_job_kernel(sg):
+    """Jobs whose frequencies pass the fixed-point phase (6.3 MHz), or whose day has
+    fewer than eight segments, are launched by themselves beside the multi-job
+    kernel of the others: every job's bits are those of its own call, on every
+    replay."""
+    jobs, refs = [], []
+    for i, (bl, nside, nt, nf, f0) in enumerate([("AB", 8, 40, 200, F0), ("AC", 4, 33, 130, 6.3e6),
+                                                 ("AB", 4, 5, 70, F0), ("AC", 8, 18, 64, F0)]):
+        g, t = sg.build_geometry(synth.baseline_sites(bl), nside, sg.TGrid(nt, 0.0, 86164.0905 / nt, 86164.0905 / nt))
+        C, w = make_csd(80 + i, nt, freqs(F0, 1 / 32, 3, nf))
+        Cd, wd, fg = torch.from_numpy(C).cuda(), torch.from_numpy(w).cuda(), sg.FGrid(f0, 1 / 32)
+        X, Xbb = torch.empty((nf, 12 * nside ** 2), device="cuda"), torch.empty(12 * nside ** 2, device="cuda")
+        jobs.append(sg.Job(Cd, wd, fg, 3, g, t, X=X, band=(1, nf), Xbb=Xbb))
+        Xr, _, Xbr, _ = sg.make_maps_band(Cd, wd, fg, 3, g, t, None, 1, nf, want_gamma=False)
+        assert sg.last_x_form().startswith("mfma")
+        refs.append((Xr, Xbr))
+    plan = sg.Plan(jobs, autotune=False)
+    for _ in range(3):
+        for j in jobs:
+            j.X.fill_(float("nan"))
+            j.Xbb.fill_(float("nan"))
+        torch.randn(1 << 16, device="cuda").sum().item()  # eager work between replays
+        plan.launch()
+        torch.cuda.synchronize()
+        for j, (Xr, Xbr) in zip(jobs, refs):
+            assert torch.equal(j.X, Xr) and torch.equal(j.Xbb, Xbr)
+    plan.close()
