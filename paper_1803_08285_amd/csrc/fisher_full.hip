@@ -25,6 +25,7 @@
 #include <cstring>
 
 #include "fisher_general.h"
+#include "node_count.h"
 
 namespace sgwb {
 
@@ -272,21 +273,6 @@ __global__ __launch_bounds__(256) void delay_cubic_kernel(const double2 *__restr
 typedef double dbl4 __attribute__((ext_vector_type(4)));
 
 constexpr int kNodesMax = 512;
-
-// Chebyshev nodes for a function of frequencies within F on an interval of
-// length L, half = pi F L / 2: the least N with 4 half^N / N! <= 1e-13, or one
-// more (Stirling's form of N!; Newton's iteration from above on a convex
-// function stays above the root), at most `most`.  float32 will do.
-__host__ __device__ inline int32_t node_count(double half, int32_t most)
-{
-    const float h = half > 1e-2 ? (float)half : 1e-2f;
-    float n = 5.5f * h + 40.0f;
-    for (int i = 0; i < 6; ++i) {
-        const float l = logf(n / h), f = n * (l - 1.0f) + 0.5f * logf(6.2831853f * n) - 31.4f;
-        n -= f / (l + 0.5f / n);
-    }
-    return n < most ? (int32_t)ceilf(n + 0.01f) : most;
-}
 
 constexpr int kTgM = 64;          // segments per tile (16 per wave)
 constexpr int kTgN = 64;          // grid points per tile (four 16-wide blocks)

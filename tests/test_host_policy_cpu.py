@@ -33,3 +33,7 @@ def test_serve_policy_under_sanitizers(tmp_path):
 
 def test_tune_cache_under_sanitizers(tmp_path):
     assert "all checks passed" in _build_and_run(tmp_path, "tune_cache_test")
+
+
+def test_node_count_under_sanitizers(tmp_path):
+    assert "all checks passed" in _build_and_run(tmp_path, "node_count_test")
