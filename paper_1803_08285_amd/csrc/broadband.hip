@@ -568,7 +568,10 @@ __global__ __launch_bounds__(256) void bb_map_pair_kernel(const float *__restric
             const double wg = valid ? (double)g[e] : 0.0;
             accA = fma(wg, (double)val.x, accA);
             accB = fma(wg, (double)val.y, accB);
-            if (GB) gacc = fma(v[min(tq + e, run.end - 1)], wg * (double)g[e], gacc);
+            if (GB) {  // (not a product with zero: the weight or the seed may be infinite)
+                const double gd = (double)g[e], ga = fma(v[min(tq + e, run.end - 1)], gd * gd, gacc);
+                gacc = valid ? ga : gacc;
+            }
         }
     }
     red[0][sl][lane] = accA;
@@ -684,7 +687,10 @@ __global__ __launch_bounds__(kBbMapThreads) void bb_map_pair_lds_kernel(
             const double gd = (double)gc[e], wg = valid ? gd : 0.0;
             accA = fma(wg, (double)val.x, accA);
             accB = fma(wg, (double)val.y, accB);
-            if (GB) gacc = fma(v[min(t0 + e, t1 - 1)], wg * gd, gacc);
+            if (GB) {  // (not a product with zero: the weight or the seed may be infinite)
+                const double ga = fma(v[min(t0 + e, t1 - 1)], gd * gd, gacc);
+                gacc = valid ? ga : gacc;
+            }
         }
         if (!more || sl != sl0) {  // the run is done
             totA += accA;

@@ -248,3 +248,33 @@ def test_fixed_point_cells_and_phases_vs_oracle(sg, oracle_mod, f0, nside):
     ref, Sb = Xo.reshape(pix.size, nb).sum(axis=1), S.reshape(pix.size, nb).sum(axis=1)
     err = np.abs(Xbb.cpu().numpy()[pix].astype(np.float64) - ref)
     assert np.all(err <= TOL * Sb), float((err / Sb).max())
+
+
+@pytest.mark.parametrize("nside", [4, 32])
+def test_infinite_seed_or_weight_gives_infinite_gbb(sg, nside):
+    """Gbb is a sum of terms >= 0: an infinite seed makes its pixels' sums infinite
+    and no others', an infinite weight all of them, in both forms of the pixel-pair
+    pass (whose last batch of a run repeats a segment) as in the call that computes
+    Gbb alone."""
+    nb, nt = 60, 33
+    g, t, C, w, H = _setup(sg, "AB", nside, nt, 0, nb, 0.25, 5)
+    fg = sg.FGrid(F0, 0.25)
+    _, anti = sg.healpix_centres(nside)
+    north = torch.arange(nt, device="cuda")  # pixel i is infinite in segment i
+    gi = g.clone()
+    gi[north, north] = float("inf")
+    gi[north, anti[north].long()] = float("inf")
+    _, ok = sg.broadband_maps(C, w, fg, 0, g, t, H, 0, nb, route="table")
+    _, got = sg.broadband_maps(C, w, fg, 0, gi, t, H, 0, nb, route="table")
+    _, alone = sg.broadband_maps(C, w, fg, 0, gi, t, H, 0, nb, want_x=False, route="table")
+    expect = ok.clone()
+    expect[north] = float("inf")
+    expect[anti[north].long()] = float("inf")
+    torch.cuda.synchronize()
+    assert torch.equal(alone, expect)
+    assert torch.equal(got, expect)
+    Hi = H.clone()
+    Hi[2] = float("inf")
+    _, got = sg.broadband_maps(C, w, fg, 0, g, t, Hi, 0, nb, route="table")
+    torch.cuda.synchronize()
+    assert torch.isinf(got).all()
