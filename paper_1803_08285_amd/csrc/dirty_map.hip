@@ -2,14 +2,17 @@
 // (Eq. eq_dirtymap split per frequency bin as in Eq. eq:narrowband) on gfx950.
 //
 // Work decomposition
-//   * A workgroup owns 64 pixel columns (one per lane) and one strip of S
-//     consecutive frequency bins that starts at an absolute bin k = 0 mod S
-//     (S = 64 in float32, 32 in float64).  Its eight waves take an eighth of the
-//     segments each (consecutive ones), so that a small map still fills the
-//     chip; their sums meet in LDS and are added in wave order.
-//   * Per wave the weighted CSD y(t,k) = w(t,k) C(t,k) of the strip is staged in
-//     LDS, XTC segments at a time, the next ones' loads in flight; every lane
-//     reads the same y (LDS broadcast).
+//   * A wave owns 64 pixel columns (one per lane) and one strip of S consecutive
+//     frequency bins that starts at an absolute bin k = 0 mod S (S = 64 in
+//     float32, 32 in float64).
+//   * Short days: a workgroup's four waves walk the whole day for neighbouring
+//     columns, and each writes its sums.  Longer days (dm_slices) are split: four
+//     or eight waves take a share of the segments each (consecutive ones) for the
+//     same columns, so that a small map still fills the chip; their sums meet in
+//     LDS and are added in wave order.
+//   * The weighted CSD y(t,k) = w(t,k) C(t,k) of the strip is staged in LDS, WTC
+//     segments at a time per workgroup, or XTC per wave of a split day with the
+//     next ones' loads in flight; every lane reads the same y (LDS broadcast).
 //   * Per (t, pixel) the phase is reduced once per strip in float64,
 //     frac(f_anchor tau), and turned into the anchor phasor z = gamma e^{i phi};
 //     the remaining S-1 bins advance z by the rotor 1 + eps = e^{i 2 pi df tau},
@@ -23,11 +26,14 @@
 //   * Fixed summation order over t, no atomics: bitwise reproducible, and the
 //     absolute anchor grid makes a sub-band bitwise equal to the full band.
 // Bound by the vector instructions: six FMAs per segment, bin and pixel pair
-// (at one per lane and cycle and 64 lanes a compute unit, 1.5 of the 1.8 ms
-// below); in float64 also by the LDS broadcasts, 16 bytes a bin.  Measured, against
-// 256 columns a workgroup that walked the whole day: 240 segments, nside 32, 6823
-// bins of 0.25 Hz 1.87 against 2.12 ms; nside 8, 1024 bins 46 against 302 us (96
-// workgroups instead of 32); float64, nside 16, 1001 bins 163 against 322 us.
+// (at one per lane and cycle and 64 lanes a compute unit, 1.5 of the 1.75 ms
+// below); in float64 also by the LDS broadcasts, 16 bytes a bin; a day of a few
+// segments by the map's write (one segment, nside 32, 6823 bins, 335 MB: 69 us).
+// Measured, split against whole days: 240 segments, nside 32, 6823 bins of 0.25 Hz
+// 1.75 against 2.04 ms; nside 8, 1024 bins 44 against 302 us; float64, nside 16,
+// 1001 bins 141 against 263 us.
+#include <type_traits>
+
 #include "sgwb_internal.h"
 
 namespace sgwb {
@@ -48,19 +54,61 @@ struct StripTraits;
 template <>
 struct StripTraits<float> {
     static constexpr int S = 64;     // bins per anchor strip
-    static constexpr int XTC = 8;    // segments per LDS stage
+    static constexpr int WTC = 32;   // segments per LDS stage of a workgroup (whole days)
+    static constexpr int XTC = 8;    // and of a wave (split days)
     static constexpr int SLAB = 16;  // bins per round of the final sums
 };
 template <>
 struct StripTraits<double> {
     static constexpr int S = 32;
+    static constexpr int WTC = 16;
     static constexpr int XTC = 4;
     static constexpr int SLAB = 8;
 };
 
-constexpr int kDmWaves = 8;      // waves, and segment slices, per workgroup
-constexpr int kDmCols = 64;      // pixel columns per workgroup
-constexpr int kDmLds = 65536;    // the waves' stages, then the final sums' rounds
+constexpr int kDmWaves = 8;      // waves per workgroup, at most, and segment slices, at most
+constexpr int kDmCols = 64;      // pixel columns per wave
+constexpr int kDmLds = 65536;    // of kDmWaves waves of a split day: their stages, then the final sums' rounds
+
+// Segment slices of a map: one (whole days), four or eight.  They depend on the
+// segments and the pixel columns alone, so that a sub-band's rows are the whole
+// band's.  Slices fill the chip where columns and bins are few, but their final
+// sums cost the same for every day: some 85 (four) and 195 us (eight) for nside 32 and
+// 6823 bins.  So a day is split where that was no slower for the widest band,
+// measured at 1 to 6823 bins (paired, 64 / 6823 bins, whole / four / eight slices):
+// nside 8, 16 segments 27/12/11 and 31/25/28 us; nside 16, 32 segments 46/16/12 and
+// 101/92/113, 60 segments 80/24/16 and 175/139/165; nside 32, 32 segments 46/17/12
+// and 305/319/417, 60 segments 80/24/17 and 533/490/609, 100 segments 128/35/23
+// and 862/747/860; nside 64, 60 segments 84/29/33 and 1983/1982/2407.  Without
+// pairs whole days hold more waves a unit: nside 32, 60 segments 751/760/855, 240
+// segments 2961/2909/3092; nside 64, 100 segments of 1024 bins 748/758/818, 160
+// 1181/1174/1231.  float64 gains earlier and takes the same rule.
+inline int dm_slices(int32_t nt, int64_t ncol, bool pair)
+{
+    struct Row {
+        int64_t cols;
+        int32_t four, eight;  // segments from which the day is split
+    };
+    constexpr int32_t kNever = 0x7fffffff;
+    const Row rows[] = {
+        {1024, 16, 16},
+        {4096, 32, 60},
+        {16384, pair ? 48 : 80, pair ? 100 : kNever},
+        {0x7fffffffffff, pair ? 80 : 160, kNever},
+    };
+    for (const Row &r : rows)
+        if (ncol <= r.cols) return nt >= r.eight ? kDmWaves : nt >= r.four ? 4 : 1;
+    return 1;
+}
+
+// f(std::integral_constant<int, slices>)
+template <typename F>
+inline void dm_with_slices(int slices, const F &f)
+{
+    if (slices == 1) f(std::integral_constant<int, 1>());
+    else if (slices == 4) f(std::integral_constant<int, 4>());
+    else f(std::integral_constant<int, kDmWaves>());
+}
 
 // Rotor 1 + eps = e^{i d} for the per-bin phase step d = 2 pi df tau:
 // eps_re = cos d - 1, eps_im = sin d, each with full relative precision.
@@ -162,10 +210,140 @@ __device__ __forceinline__ void wave_fence()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// One tile: 64 pixel columns (coltile) x one S-bin strip (absolute index strip).
-// Called by every thread of the workgroup; lds is its kDmLds bytes of LDS.
+// z advanced by a bin: z <- z (1 + eps), and the bin's terms y z.
 template <typename T, bool PAIR>
-__device__ inline void dirty_map_tile(const MapArgs &a, int64_t strip, int64_t coltile,
+__device__ __forceinline__ void add_bin(T yr, T yi, T &zr, T &zi, T er, T ei, T &a, T &b)
+{
+    a = fma(yr, zr, a);
+    if (PAIR) b = fma(yi, zi, b);
+    else a = fma(-yi, zi, a);
+    T nr = fma(zr, er, zr);
+    nr = fma(-zi, ei, nr);
+    T ni = fma(zi, er, zi);
+    ni = fma(zr, ei, ni);
+    zr = nr;
+    zi = ni;
+}
+
+// One output of a column's strip (column c of the band, pixels col and colB).
+template <typename T, bool PAIR>
+__device__ __forceinline__ void put_bin(const MapArgs &a, T *__restrict__ X, int64_t c, int64_t col, int64_t colB,
+                                        T va, T vb)
+{
+    auto row = gmem(X + c * (int64_t)a.npix);
+    const T xa = va - vb, xb = va + vb;
+    row[col] = a.accumulate ? row[col] + xa : xa;
+    if (PAIR) row[colB] = a.accumulate ? row[colB] + xb : xb;
+}
+
+// The strip's bins [lo, hi) that lie in the band of the broadband sums, and a bin's
+// share of them.
+template <int S>
+struct BandBins {
+    int lo, hi;
+    __device__ __forceinline__ BandBins(const MapArgs &a, int64_t c0)
+        : lo((int)min(max((int64_t)a.band_lo - c0, (int64_t)0), (int64_t)S)),
+          hi((int)min(max((int64_t)a.band_hi - c0, (int64_t)0), (int64_t)S))
+    {
+    }
+    template <typename T>
+    __device__ __forceinline__ void add(int j, T va, T vb, double &sa, double &sb) const
+    {
+        if (j < lo || j >= hi) return;
+        sa += (double)(va - vb);
+        sb += (double)(va + vb);
+    }
+};
+
+// One tile of a map whose day is not split: 64 NW pixel columns (the coltile-th
+// block) x one S-bin strip (absolute index strip), the strip's y staged by the
+// whole workgroup of NW waves.
+template <typename T, bool PAIR, int NW>
+__device__ inline void dirty_map_whole_tile(const MapArgs &a, int64_t strip, int64_t coltile,
+                                            const typename Cplx<T>::type *__restrict__ C, const T *__restrict__ w,
+                                            const T *__restrict__ gamma, const double *__restrict__ tau,
+                                            T *__restrict__ X, double *__restrict__ band_row, char *lds)
+{
+    using C2 = typename Cplx<T>::type;
+    constexpr int S = StripTraits<T>::S;
+    constexpr int WTC = StripTraits<T>::WTC;
+    C2(*ys)[S] = reinterpret_cast<C2(*)[S]>(lds);
+
+    const int64_t ncol = PAIR ? (int64_t)a.npix / 2 : (int64_t)a.npix;
+    const int64_t col = coltile * (NW * kDmCols) + threadIdx.x;
+    const bool active = col < ncol;
+    const int64_t kabs0 = strip * S;                          // absolute first bin of the strip
+    const int64_t c0 = kabs0 - a.k0;                           // its column in C (may be < 0)
+    const double fa4 = 4.0 * (a.f0 + (double)kabs0 * a.df);   // anchor frequency, quarter turns
+    const double two_pi_df = kTwoPi * a.df;
+
+    T acc_a[S], acc_b[PAIR ? S : 1];
+#pragma unroll
+    for (int j = 0; j < S; ++j) acc_a[j] = T(0);
+#pragma unroll
+    for (int j = 0; j < (PAIR ? S : 1); ++j) acc_b[j] = T(0);
+
+    const int64_t pcol = active ? col : 0;
+    for (int tc = 0; tc < a.nt; tc += WTC) {
+        const int tn = min(WTC, a.nt - tc);
+        __syncthreads();
+        for (int e = threadIdx.x; e < WTC * S; e += NW * 64) {
+            const int tt = e / S, kk = e % S;
+            const int64_t c = c0 + kk;
+            C2 y;
+            y.x = T(0);
+            y.y = T(0);
+            if (tt < tn && c >= 0 && c < a.nf) {
+                const int64_t off = (int64_t)(tc + tt) * a.ldc + c;
+                const T wv = gmem(w)[off];
+                if (a.unit_c) {
+                    y.x = wv;
+                } else {
+                    const C2 cv = gload_c(C, off);
+                    y.x = wv * cv.x;
+                    y.y = wv * cv.y;
+                }
+            }
+            ys[tt][kk] = y;
+        }
+        __syncthreads();
+        if (!active) continue;
+        for (int tt = 0; tt < tn; ++tt) {
+            const int64_t o = (int64_t)(tc + tt) * a.npix + pcol;
+            const T g = gmem(gamma)[o];
+            const double tv = gmem(tau)[o];
+            T zr, zi, er, ei;
+            anchor4(g, fa4 * tv, &zr, &zi);
+            rotor((T)(two_pi_df * tv), &er, &ei);
+#pragma unroll
+            for (int j = 0; j < S; ++j)
+                add_bin<T, PAIR>(ys[tt][j].x, ys[tt][j].y, zr, zi, er, ei, acc_a[j], acc_b[PAIR ? j : 0]);
+        }
+    }
+    if (!active) return;
+    int64_t colB = 0;
+    if (PAIR) colB = antipode_north(ring_of_north(col, a.nside), a.npix);
+#pragma unroll
+    for (int j = 0; j < S; ++j) {
+        const int64_t c = c0 + j;
+        if (c < 0 || c >= a.nf) continue;
+        put_bin<T, PAIR>(a, X, c, col, colB, acc_a[j], PAIR ? acc_b[PAIR ? j : 0] : T(0));
+    }
+    if (!band_row) return;
+    double sa = 0.0, sb = 0.0;
+    const BandBins<S> band(a, c0);
+#pragma unroll
+    for (int j = 0; j < S; ++j) band.add(j, acc_a[j], PAIR ? acc_b[PAIR ? j : 0] : T(0), sa, sb);
+    gmem(band_row)[col] = sa;
+    if (PAIR) gmem(band_row)[colB] = sb;
+}
+
+// One tile of a map whose day is split: one S-bin strip (absolute index strip) x W
+// slices of the segments for NW / W neighbouring blocks of 64 pixel columns (the
+// coltile-th group of them).  Both tiles are called by every thread of a workgroup
+// of NW waves; lds is its dm_lds bytes of LDS.
+template <typename T, bool PAIR, int W, int NW>
+__device__ inline void dirty_map_split_tile(const MapArgs &a, int64_t strip, int64_t coltile,
                                       const typename Cplx<T>::type *__restrict__ C, const T *__restrict__ w,
                                       const T *__restrict__ gamma, const double *__restrict__ tau,
                                       T *__restrict__ X, double *__restrict__ band_row, char *lds)
@@ -176,21 +354,23 @@ __device__ inline void dirty_map_tile(const MapArgs &a, int64_t strip, int64_t c
     constexpr int SLAB = StripTraits<T>::SLAB;
     constexpr int NLD = XTC * S / 64;  // staged values per lane
     constexpr int NA = PAIR ? 2 : 1;   // sums per bin
-    static_assert(kDmWaves * XTC * S * sizeof(C2) <= kDmLds, "the waves' stages");
-    static_assert(kDmWaves * NA * SLAB * kDmCols * sizeof(T) <= kDmLds, "a round of the final sums");
-    static_assert(S % SLAB == 0 && SLAB % kDmWaves == 0, "whole rounds");
+    static_assert(NW * XTC * S * sizeof(C2) <= kDmLds / kDmWaves * NW, "the waves' stages");
+    static_assert(NW * NA * SLAB * kDmCols * sizeof(T) <= kDmLds / kDmWaves * NW, "a round of the final sums");
+    static_assert(S % SLAB == 0 && SLAB % W == 0 && NW % W == 0, "whole rounds");
 
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    // the wave's number as a scalar, so that its loops and row addresses are scalar
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int sl = wv % W, ct = wv / W;
     const int64_t ncol = PAIR ? (int64_t)a.npix / 2 : (int64_t)a.npix;
-    const int64_t col = coltile * kDmCols + lane;
+    const int64_t col = (coltile * (NW / W) + ct) * kDmCols + lane;
     const bool active = col < ncol;
     const int64_t pcol = active ? col : 0;
     const int64_t kabs0 = strip * S;                          // absolute first bin of the strip
     const int64_t c0 = kabs0 - a.k0;                           // its column in C (may be < 0)
     const double fa4 = 4.0 * (a.f0 + (double)kabs0 * a.df);   // anchor frequency, quarter turns
     const double two_pi_df = kTwoPi * a.df;
-    const int per = (a.nt + kDmWaves - 1) / kDmWaves;
-    const int ta = min(wv * per, a.nt), tb = min(ta + per, a.nt);  // this wave's segments
+    const int per = (a.nt + W - 1) / W;
+    const int ta = min(sl * per, a.nt), tb = min(ta + per, a.nt);  // this wave's segments
 
     T acc_a[S], acc_b[PAIR ? S : 1];
 #pragma unroll
@@ -246,32 +426,19 @@ __device__ inline void dirty_map_tile(const MapArgs &a, int64_t strip, int64_t c
                 anchor4(g, fa4 * tv, &zr, &zi);
                 rotor((T)(two_pi_df * tv), &er, &ei);
 #pragma unroll
-                for (int j = 0; j < S; ++j) {
-                    const C2 y = ys[tt][j];
-                    if (PAIR) {
-                        acc_a[j] = fma(y.x, zr, acc_a[j]);
-                        acc_b[j] = fma(y.y, zi, acc_b[j]);
-                    } else {
-                        acc_a[j] = fma(y.x, zr, acc_a[j]);
-                        acc_a[j] = fma(-y.y, zi, acc_a[j]);
-                    }
-                    // z <- z (1 + eps)
-                    T nr = fma(zr, er, zr);
-                    nr = fma(-zi, ei, nr);
-                    T ni = fma(zi, er, zi);
-                    ni = fma(zr, ei, ni);
-                    zr = nr;
-                    zi = ni;
-                }
+                for (int j = 0; j < S; ++j)
+                    add_bin<T, PAIR>(ys[tt][j].x, ys[tt][j].y, zr, zi, er, ei, acc_a[j], acc_b[PAIR ? j : 0]);
             }
         }
     }
-    // the slices' sums, SLAB bins a round: [wave][sum][bin][column], every thread
-    // then adds the waves' for its column and every eighth bin
     int64_t colB = 0;
     if (PAIR && active) colB = antipode_north(ring_of_north(col, a.nside), a.npix);
-    T(*sum)[NA][SLAB][kDmCols] = reinterpret_cast<T(*)[NA][SLAB][kDmCols]>(lds);
     double sa = 0.0, sb = 0.0;  // this thread's share of the strip's broadband sums
+    const BandBins<S> band(a, c0);
+    // the slices' sums, SLAB bins a round: [wave][sum][bin][column], every thread
+    // then adds the slices' for its column and every W-th bin
+    T(*sum)[NA][SLAB][kDmCols] = reinterpret_cast<T(*)[NA][SLAB][kDmCols]>(lds);
+    T(*mine)[NA][SLAB][kDmCols] = sum + ct * W;  // its columns' slices
 #pragma unroll
     for (int j0 = 0; j0 < S; j0 += SLAB) {
         __syncthreads();  // the stages, or the previous round, are read
@@ -281,23 +448,17 @@ __device__ inline void dirty_map_tile(const MapArgs &a, int64_t strip, int64_t c
             if (PAIR) sum[wv][NA - 1][j][lane] = acc_b[PAIR ? j0 + j : 0];
         }
         __syncthreads();
-        for (int j = wv; j < SLAB; j += kDmWaves) {
+        for (int j = sl; j < SLAB; j += W) {
             const int64_t c = c0 + j0 + j;
             if (!active || c < 0 || c >= a.nf) continue;
-            T va = sum[0][0][j][lane], vb = PAIR ? sum[0][NA - 1][j][lane] : T(0);
+            T va = mine[0][0][j][lane], vb = PAIR ? mine[0][NA - 1][j][lane] : T(0);
 #pragma unroll
-            for (int k = 1; k < kDmWaves; ++k) {
-                va += sum[k][0][j][lane];
-                if (PAIR) vb += sum[k][NA - 1][j][lane];
+            for (int k = 1; k < W; ++k) {
+                va += mine[k][0][j][lane];
+                if (PAIR) vb += mine[k][NA - 1][j][lane];
             }
-            auto row = gmem(X + c * (int64_t)a.npix);
-            const T xa = va - vb, xb = va + vb;
-            row[col] = a.accumulate ? row[col] + xa : xa;
-            if (PAIR) row[colB] = a.accumulate ? row[colB] + xb : xb;
-            if (c >= a.band_lo && c < a.band_hi) {
-                sa += (double)xa;
-                sb += (double)xb;
-            }
+            put_bin<T, PAIR>(a, X, c, col, colB, va, vb);
+            if (band_row) band.add(j0 + j, va, vb, sa, sb);
         }
     }
     if (!band_row) return;
@@ -306,11 +467,11 @@ __device__ inline void dirty_map_tile(const MapArgs &a, int64_t strip, int64_t c
     bs[wv][0][lane] = sa;
     bs[wv][1][lane] = sb;
     __syncthreads();
-    if (wv != 0 || !active) return;
+    if (sl != 0 || !active) return;
 #pragma unroll
-    for (int k = 1; k < kDmWaves; ++k) {
-        sa += bs[k][0][lane];
-        sb += bs[k][1][lane];
+    for (int k = 1; k < W; ++k) {
+        sa += bs[wv + k][0][lane];
+        sb += bs[wv + k][1][lane];
     }
     gmem(band_row)[col] = sa;
     if (PAIR) gmem(band_row)[colB] = sb;
@@ -323,34 +484,66 @@ __device__ inline double *band_row_of(const MapArgs &a, int64_t strip, int S)
     return a.band_part ? a.band_part + (strip - a.k0 / S) * (int64_t)a.npix : nullptr;
 }
 
-template <typename T, bool PAIR>
-__global__ __launch_bounds__(64 * kDmWaves) __attribute__((amdgpu_waves_per_eu(2))) void dirty_map_kernel(MapArgs a, int64_t strip0,
+// Either kind of tile.
+template <typename T, bool PAIR, int W, int NW>
+__device__ __forceinline__ void dirty_map_tile(const MapArgs &a, int64_t strip, int64_t coltile,
+                                               const typename Cplx<T>::type *__restrict__ C, const T *__restrict__ w,
+                                               const T *__restrict__ gamma, const double *__restrict__ tau,
+                                               T *__restrict__ X, char *lds)
+{
+    double *band_row = band_row_of(a, strip, StripTraits<T>::S);
+    if constexpr (W == 1)
+        dirty_map_whole_tile<T, PAIR, NW>(a, strip, coltile, C, w, gamma, tau, X, band_row, lds);
+    else
+        dirty_map_split_tile<T, PAIR, W, NW>(a, strip, coltile, C, w, gamma, tau, X, band_row, lds);
+}
+
+// Waves per workgroup of a single call: four, or one a slice.
+constexpr int dm_waves(int slices) { return slices > 4 ? slices : 4; }
+// Its LDS: the whole-day tile's stage, or the waves' stages and the final sums.
+template <typename T>
+constexpr int dm_lds(int slices)
+{
+    return slices > 1 ? kDmLds / kDmWaves * dm_waves(slices)
+                      : StripTraits<T>::WTC * StripTraits<T>::S * (int)sizeof(typename Cplx<T>::type);
+}
+// Waves per SIMD that the registers have to leave room for: the split tile's two
+// sums a bin take half of them, its one sum a quarter.
+constexpr int dm_occupancy(bool one_sum, int slices) { return slices == 1 ? 1 : one_sum ? 4 : 2; }
+
+template <typename T, bool PAIR, int W>
+__global__ __launch_bounds__(64 * dm_waves(W)) __attribute__((
+    amdgpu_waves_per_eu(dm_occupancy(!PAIR && sizeof(T) == 4, W)))) void dirty_map_kernel(MapArgs a, int64_t strip0,
                                                          const typename Cplx<T>::type *__restrict__ C,
                                                          const T *__restrict__ w,
                                                          const T *__restrict__ gamma,
                                                          const double *__restrict__ tau,
                                                          T *__restrict__ X, const double *__restrict__ gate)
 {
-    __shared__ __attribute__((aligned(16))) char lds[kDmLds];
+    constexpr int NW = dm_waves(W);
+    __shared__ __attribute__((aligned(16))) char lds[dm_lds<T>(W)];
     // gated launch: only where the matrix-core prep found no accurate form
     if (gate && (int)gmem(gate)[1] != SGWB_XFORM_VALU) return;
-    const int64_t strip = strip0 + (int64_t)blockIdx.y;
-    dirty_map_tile<T, PAIR>(a, strip, blockIdx.x, C, w, gamma, tau, X, band_row_of(a, strip, StripTraits<T>::S), lds);
+    dirty_map_tile<T, PAIR, W, NW>(a, strip0 + (int64_t)blockIdx.y, blockIdx.x, C, w, gamma, tau, X, lds);
 }
 
-// Persistent multi-job form: workgroup b takes tiles b, b + grid, b + 2 grid, ...
-// of the concatenated tile list of all jobs (each job: its column tiles fastest
-// within a strip, or its strips fastest, as the plan chose).  A tile's result
-// does not depend on which workgroup computes it or when.  PAIR is uniform
-// over the job table (the plan launches one table per pairing).
-template <bool PAIR>
-__global__ __launch_bounds__(64 * kDmWaves) __attribute__((amdgpu_waves_per_eu(2))) void dirty_map_batched_kernel(
-    const XJob *__restrict__ jobs, int32_t njobs, int64_t ntiles)
+// Multi-job form over the concatenated tile list of the jobs (each job: its column
+// tiles fastest within a strip, or its strips fastest, as the plan chose).  Whole
+// days: persistent, workgroup b takes tiles b, b + grid, b + 2 grid, ...  Split
+// days: one workgroup a tile.  A tile's result does not depend on which workgroup
+// computes it or when.  PAIR and the slices W are uniform over the jobs (the plan
+// launches one table per pairing and slices).
+template <bool PAIR, int W>
+__global__ __launch_bounds__(64 * dm_waves(W)) __attribute__((
+    amdgpu_waves_per_eu(dm_occupancy(!PAIR, W)))) void dirty_map_batched_kernel(const XJob *__restrict__ jobs,
+                                                                               int32_t njobs, int64_t ntiles)
 {
-    __shared__ __attribute__((aligned(16))) char lds[kDmLds];
+    constexpr int NW = dm_waves(W);
+    __shared__ __attribute__((aligned(16))) char lds[dm_lds<float>(W)];
     for (int64_t g = blockIdx.x; g < ntiles; g += gridDim.x) {
         int j = 0;
         while (j + 1 < njobs && g >= jobs[j + 1].tile_begin) ++j;
+        j = __builtin_amdgcn_readfirstlane(j);
         // read the job's fields as scalars (uniform over the workgroup)
         const MapArgs a = jobs[j].a;
         const int64_t local = g - jobs[j].tile_begin;
@@ -365,8 +558,9 @@ __global__ __launch_bounds__(64 * kDmWaves) __attribute__((amdgpu_waves_per_eu(2
             strip = strip0 + local % nstrips;
         }
         const float2 *C = reinterpret_cast<const float2 *>(jobs[j].C);
-        dirty_map_tile<float, PAIR>(a, strip, coltile, C, jobs[j].w, jobs[j].gamma, jobs[j].tau, jobs[j].X,
-                                    band_row_of(a, strip, StripTraits<float>::S), lds);
+        dirty_map_tile<float, PAIR, W, NW>(a, strip, coltile, C, jobs[j].w, jobs[j].gamma, jobs[j].tau, jobs[j].X,
+                                           lds);
+        if (W > 1) break;
     }
 }
 
@@ -383,20 +577,23 @@ void fill_xjob(XJob *j, const MapArgs &a, const float *C, const float *w, const 
     j->strip_first = a.k0 / S;
     j->nstrips = (a.k0 + a.nf - 1) / S - j->strip_first + 1;
     const int64_t ncol = a.nside > 0 ? a.npix / 2 : a.npix;
-    j->ncoltiles = (ncol + kDmCols - 1) / kDmCols;
+    j->slices = dm_slices(a.nt, ncol, a.nside > 0);
+    const int64_t cols = kDmCols * dm_waves(j->slices) / j->slices;  // per workgroup
+    j->ncoltiles = (ncol + cols - 1) / cols;
     j->strip_major = strip_major ? 1 : 0;
     j->tile_begin = 0;
 }
 
 hipError_t launch_dirty_map_batched(const XJob *jobs_dev, int32_t njobs, int64_t ntiles, int64_t grid, bool pair,
-                                    hipStream_t s)
+                                    int32_t slices, hipStream_t s)
 {
-    if (pair)
-        hipLaunchKernelGGL(dirty_map_batched_kernel<true>, dim3((unsigned)grid), dim3(64 * kDmWaves), 0, s, jobs_dev, njobs,
-                           ntiles);
-    else
-        hipLaunchKernelGGL(dirty_map_batched_kernel<false>, dim3((unsigned)grid), dim3(64 * kDmWaves), 0, s, jobs_dev, njobs,
-                           ntiles);
+    decltype(&dirty_map_batched_kernel<true, 1>) kernel = nullptr;
+    dm_with_slices(slices, [&](auto n) {
+        constexpr int W = decltype(n)::value;
+        kernel = pair ? dirty_map_batched_kernel<true, W> : dirty_map_batched_kernel<false, W>;
+    });
+    if (slices > 1) grid = ntiles;  // (not persistent)
+    hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(64 * dm_waves(slices)), 0, s, jobs_dev, njobs, ntiles);
     return hipGetLastError();
 }
 
@@ -412,16 +609,18 @@ hipError_t launch_dirty_map(const MapArgs &a, const T *C, const T *w, const T *g
     const int64_t strip_last = (a.k0 + a.nf - 1) / S;
     const int64_t nstrips = strip_last - strip_first + 1;
     const C2 *Cc = reinterpret_cast<const C2 *>(C);
+    const int slices = dm_slices(a.nt, ncol, pair), waves = dm_waves(slices);
+    const int64_t cols = kDmCols * waves / slices;  // per workgroup
+    decltype(&dirty_map_kernel<T, true, 1>) kernel = nullptr;
+    dm_with_slices(slices, [&](auto n) {
+        constexpr int W = decltype(n)::value;
+        kernel = pair ? dirty_map_kernel<T, true, W> : dirty_map_kernel<T, false, W>;
+    });
     // grid.y is limited to 65535 strips per launch; larger bands are split.
     for (int64_t s0 = 0; s0 < nstrips; s0 += 65535) {
         const int64_t ns = nstrips - s0 < 65535 ? nstrips - s0 : 65535;
-        dim3 grid((unsigned)((ncol + kDmCols - 1) / kDmCols), (unsigned)ns);
-        if (pair)
-            hipLaunchKernelGGL((dirty_map_kernel<T, true>), grid, dim3(64 * kDmWaves), 0, s, a, strip_first + s0, Cc,
-                               w, gamma, tau, X, gate);
-        else
-            hipLaunchKernelGGL((dirty_map_kernel<T, false>), grid, dim3(64 * kDmWaves), 0, s, a, strip_first + s0,
-                               Cc, w, gamma, tau, X, gate);
+        dim3 grid((unsigned)((ncol + cols - 1) / cols), (unsigned)ns);
+        hipLaunchKernelGGL(kernel, grid, dim3(64 * waves), 0, s, a, strip_first + s0, Cc, w, gamma, tau, X, gate);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

@@ -27,11 +27,14 @@ struct sgwb_plan {
     std::vector<sgwb_job> jobs;
     std::vector<MapArgs> args;
     // dirty map
-    std::vector<XJob> xjobs;  // host copy, tile_begin filled; antipodal jobs first
+    std::vector<XJob> xjobs;  // host copy, tile_begin filled; one class after another
     XJob *d_xjobs = nullptr;
     int64_t x_tiles = 0;
-    int32_t nx_pair = 0;         // xjobs[0, nx_pair) use antipodal pairs
-    int64_t x_tiles_pair = 0;    // tiles of those jobs
+    struct XClass {  // jobs [first, first + count): one pairing, one count of slices, one launch
+        int32_t first = 0, count = 0;
+        int64_t tiles = 0;
+    };
+    std::vector<XClass> xclasses;
     // dirty map on the matrix cores (jobs where that form applies)
     std::vector<XmJob> xmjobs;
     XmJob *d_xmjobs = nullptr;
@@ -80,23 +83,18 @@ int validate_job(const sgwb_job &j, MapArgs *a)
 // (Re)build the device job tables for the current tunables.
 static int upload_tables(sgwb_plan *p)
 {
-    // each pairing class is its own launch, so each numbers its tiles from 0
-    int64_t t = 0;
-    for (size_t i = 0; i < p->xjobs.size(); ++i) {
-        if ((int32_t)i == p->nx_pair) {
-            p->x_tiles_pair = t;
-            t = 0;
+    // each class is its own launch, so each numbers its tiles from 0
+    p->x_tiles = 0;
+    for (auto &c : p->xclasses) {
+        c.tiles = 0;
+        for (int32_t i = c.first; i < c.first + c.count; ++i) {
+            XJob &x = p->xjobs[i];
+            x.strip_major = p->tun.x_strip_major;
+            x.tile_begin = c.tiles;
+            c.tiles += xjob_tiles(x);
         }
-        XJob &x = p->xjobs[i];
-        x.strip_major = p->tun.x_strip_major;
-        x.tile_begin = t;
-        t += xjob_tiles(x);
+        p->x_tiles += c.tiles;
     }
-    if ((size_t)p->nx_pair == p->xjobs.size()) {
-        p->x_tiles_pair = t;
-        t = 0;
-    }
-    p->x_tiles = p->x_tiles_pair + t;
     int64_t tx = 0;
     for (auto &x : p->xmjobs) {
         x.tile_begin = tx;
@@ -145,14 +143,12 @@ static hipError_t enqueue(sgwb_plan *p, hipStream_t s, int parts)
     }
     if (parts & 1) {
         const int64_t cap = (int64_t)p->num_cus * p->tun.x_grid_per_cu;
-        const int64_t tp = p->x_tiles_pair, tn = p->x_tiles - p->x_tiles_pair;
-        if (tp > 0 && (e = launch_dirty_map_batched(p->d_xjobs, p->nx_pair, tp, std::min(tp, cap), true, s)) !=
-                          hipSuccess)
-            return e;
-        const int32_t nn = (int32_t)p->xjobs.size() - p->nx_pair;
-        if (tn > 0 && (e = launch_dirty_map_batched(p->d_xjobs + p->nx_pair, nn, tn, std::min(tn, cap), false, s)) !=
-                          hipSuccess)
-            return e;
+        for (const auto &c : p->xclasses) {
+            const XJob &x = p->xjobs[c.first];
+            if ((e = launch_dirty_map_batched(p->d_xjobs + c.first, c.count, c.tiles, std::min(c.tiles, cap),
+                                              x.a.nside > 0, x.slices, s)) != hipSuccess)
+                return e;
+        }
     }
     if ((parts & 2) && p->b_wgs > 0) {
         // 0 workgroups per CU: one workgroup per tile group, no persistent loop
@@ -438,18 +434,24 @@ int sgwb_plan_create(const sgwb_job *jobs, int32_t njobs, uint32_t flags, sgwb_p
         a->band_lo = j.band_lo;
         a->band_hi = j.band_hi;
     };
-    for (int pass = 0; pass < 2; ++pass)
-        for (int i : order) {
-            const sgwb_job &j = p->jobs[i];
-            const bool pair = p->args[i].nside > 0;
-            if (j.X && !use_xm[i] && pair == (pass == 0)) {
-                XJob x;
-                fill_xjob(&x, p->args[i], j.C, j.w, j.gamma, j.tau, j.X, true);
-                band_sums(i, &x.a);
-                p->xjobs.push_back(x);
-                if (pair) p->nx_pair++;
-            }
+    for (int i : order) {
+        const sgwb_job &j = p->jobs[i];
+        if (!j.X || use_xm[i]) continue;
+        XJob x;
+        fill_xjob(&x, p->args[i], j.C, j.w, j.gamma, j.tau, j.X, true);
+        band_sums(i, &x.a);
+        p->xjobs.push_back(x);
+    }
+    auto xclass = [](const XJob &x) { return std::make_pair(x.a.nside == 0, x.slices); };
+    std::stable_sort(p->xjobs.begin(), p->xjobs.end(),
+                     [&](const XJob &x, const XJob &y) { return xclass(x) < xclass(y); });
+    for (int32_t i = 0; i < (int32_t)p->xjobs.size(); ++i) {
+        if (i == 0 || xclass(p->xjobs[i]) != xclass(p->xjobs[i - 1])) {
+            p->xclasses.emplace_back();
+            p->xclasses.back().first = i;
         }
+        p->xclasses.back().count++;
+    }
     for (int i : order) {
         const sgwb_job &j = p->jobs[i];
         if (use_xm[i]) {

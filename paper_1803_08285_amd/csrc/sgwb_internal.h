@@ -293,12 +293,13 @@ struct XJob {
     int64_t strip_first, nstrips, ncoltiles;
     int64_t tile_begin;  // first global tile index of this job
     int32_t strip_major; // 1: column tiles fastest within a strip
+    int32_t slices;      // segment slices of its tiles
 };
 void fill_xjob(XJob *j, const MapArgs &a, const float *C, const float *w, const float *gamma, const double *tau,
                float *X, bool strip_major);
 inline int64_t xjob_tiles(const XJob &j) { return j.nstrips * j.ncoltiles; }
 hipError_t launch_dirty_map_batched(const XJob *jobs_dev, int32_t njobs, int64_t ntiles, int64_t grid, bool pair,
-                                    hipStream_t s);
+                                    int32_t slices, hipStream_t s);
 
 size_t beam_workspace_bytes(int32_t nt, int32_t nf, int32_t ncol);
 
