@@ -17,11 +17,13 @@
 
 namespace sgwb {
 
-// Consecutive folded segments per thread: six (fewer rows read twice) where that
-// leaves 2400 workgroups, else four.  Measured (four / six), ten
-// days: 898 segments x 16411 bins 477 / 465 us, 240 x 16384 121 / 111, 898 x 300
-// (300 workgroups of six) 24.7 / 28.9, 898 x 3584 (2100) 103.4 / 104.9; five days,
-// 898 x 4096 (2400) 57.5 / 55.5.
+// Consecutive folded segments per thread: six where that leaves 2400 workgroups and
+// reads fewer rows (each group its own and two neighbours), else four.  Measured
+// (four / six), ten days: 898 segments x 16411 bins 477 / 465 us, 240 x 16384 121 /
+// 111, 898 x 300 (300 workgroups of six) 24.7 / 28.9, 898 x 3584 (2100) 103.4 /
+// 104.9, 12 x 400 000 (16 rows against 18) 180 / 173, 13 x 300 000 (24 against 24)
+// 161 / 164, 8 x 400 000 (16 against 12) 106 / 155; five days, 898 x 4096 (2400)
+// 57.5 / 55.5.
 constexpr int64_t kFoldSixMin = 2400;
 
 template <int kFoldT>
@@ -103,7 +105,8 @@ hipError_t launch_fold(const float *C, const float *sv, const uint8_t *present, 
                            reinterpret_cast<const float2 *>(C), sv, present, ldc, ndays, nt, nf, W, v, u, w,
                            reinterpret_cast<float2 *>(x));
     };
-    if (cols * ((nt + 5) / 6) >= kFoldSixMin)
+    const int64_t fours = ((int64_t)nt + 3) / 4, sixes = ((int64_t)nt + 5) / 6;
+    if (cols * sixes >= kFoldSixMin && sixes * 8 < fours * 6)
         go(fold_kernel<6>, 6);
     else
         go(fold_kernel<4>, 4);
