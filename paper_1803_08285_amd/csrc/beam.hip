@@ -549,7 +549,8 @@ hipError_t launch_beam_bf16x3(const MapArgs &a, const float *w, const float *gam
 // that each value loaded serves 32 multiply-adds; operands straight from
 // memory (lane l: row or column l % 16, segment l / 16 of four), kF64Steps steps
 // of four segments ahead in registers.  Segments past the day are zeros; bins
-// and columns past the map are computed and not stored.  240 segments, nside
+// and columns past the map are computed and not stored, waves past it leave (three
+// bins, nside 128: 49 us, with them 75).  240 segments, nside
 // 16, 1001 bins: 36 us (one thread per output, bound by its two loads per
 // multiply-add, 185 us; 16 bins a lane with scalar loads of w 214 us).
 typedef double dbl4 __attribute__((ext_vector_type(4)));
@@ -562,6 +563,7 @@ __global__ __launch_bounds__(256) void beam_f64_kernel(MapArgs a, const double *
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, idx = lane & 15, kq = lane >> 4;
     const int64_t ncol = a.nside > 0 ? a.npix / 2 : a.npix;
     const int64_t k0 = (int64_t)blockIdx.y * 64 + (wv & 1) * 32, c0 = (int64_t)blockIdx.x * 64 + (wv >> 1) * 32;
+    if (k0 >= a.nf || c0 >= ncol) return;  // (no barrier below)
     const double *wp[2], *gp[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
