@@ -493,8 +493,16 @@ hipError_t launch_beam_prep(const BJob &jb, hipStream_t s)
 {
     // the padding blocks are written too (their columns lie past the data: zeros)
     const FragDims pm{padded_blocks(jb.fm.nblk), jb.fm.nks}, pn{padded_blocks(jb.fn.nblk), jb.fn.nks};
-    const int64_t n = (pm.nblk + pn.nblk) * pm.nks * 64;
-    hipLaunchKernelGGL(prep_frag_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, jb, pm.nblk, pn.nblk);
+    auto prep = [&](int64_t wblk, int64_t gblk) {
+        const int64_t n = (wblk + gblk) * pm.nks * 64;
+        hipLaunchKernelGGL(prep_frag_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, jb, wblk, gblk);
+    };
+    if (fits_launch(((pm.nblk + pn.nblk) * pm.nks * 64 + 255) / 256, 256)) {
+        prep(pm.nblk, pn.nblk);
+    } else {
+        prep(pm.nblk, 0);
+        prep(0, pn.nblk);
+    }
     return hipGetLastError();
 }
 

@@ -32,6 +32,7 @@
 // Measured, split against whole days: 240 segments, nside 32, 6823 bins of 0.25 Hz
 // 1.75 against 2.04 ms; nside 8, 1024 bins 44 against 302 us; float64, nside 16,
 // 1001 bins 141 against 263 us.
+#include <algorithm>
 #include <type_traits>
 
 #include "sgwb_internal.h"
@@ -530,17 +531,18 @@ __global__ __launch_bounds__(64 * dm_waves(W)) __attribute__((
 // Multi-job form over the concatenated tile list of the jobs (each job: its column
 // tiles fastest within a strip, or its strips fastest, as the plan chose).  Whole
 // days: persistent, workgroup b takes tiles b, b + grid, b + 2 grid, ...  Split
-// days: one workgroup a tile.  A tile's result does not depend on which workgroup
+// days: one workgroup a tile, from tile `first` on.  A tile's result does not depend on which workgroup
 // computes it or when.  PAIR and the slices W are uniform over the jobs (the plan
 // launches one table per pairing and slices).
 template <bool PAIR, int W>
 __global__ __launch_bounds__(64 * dm_waves(W)) __attribute__((
     amdgpu_waves_per_eu(dm_occupancy(!PAIR, W)))) void dirty_map_batched_kernel(const XJob *__restrict__ jobs,
-                                                                               int32_t njobs, int64_t ntiles)
+                                                                               int32_t njobs, int64_t first,
+                                                                               int64_t ntiles)
 {
     constexpr int NW = dm_waves(W);
     __shared__ __attribute__((aligned(16))) char lds[dm_lds<float>(W)];
-    for (int64_t g = blockIdx.x; g < ntiles; g += gridDim.x) {
+    for (int64_t g = first + blockIdx.x; g < ntiles; g += gridDim.x) {
         int j = 0;
         while (j + 1 < njobs && g >= jobs[j + 1].tile_begin) ++j;
         j = __builtin_amdgcn_readfirstlane(j);
@@ -592,8 +594,12 @@ hipError_t launch_dirty_map_batched(const XJob *jobs_dev, int32_t njobs, int64_t
         constexpr int W = decltype(n)::value;
         kernel = pair ? dirty_map_batched_kernel<true, W> : dirty_map_batched_kernel<false, W>;
     });
-    if (slices > 1) grid = ntiles;  // (not persistent)
-    hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(64 * dm_waves(slices)), 0, s, jobs_dev, njobs, ntiles);
+    const int64_t step = slices > 1 ? 1 << 22 : ntiles;  // tiles a launch
+    for (int64_t first = 0; first < ntiles; first += step) {
+        const int64_t n = slices > 1 ? std::min(step, ntiles - first) : grid;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)n), dim3(64 * dm_waves(slices)), 0, s, jobs_dev, njobs, first,
+                           ntiles);
+    }
     return hipGetLastError();
 }
 

@@ -1010,15 +1010,31 @@ static hipError_t launch_xm_prep_parts(const XmJob &j, bool data, bool seeds, hi
     const int64_t nscale = data ? j.x.nstrips : 0, nsym = seeds ? kSymParts : 0;
     const int64_t ntmax = seeds ? std::min<int64_t>(kTmaxParts, (n + 4 * kXmPrepThreads - 1) / (4 * kXmPrepThreads)) : 0;
     double *part = j.tmax + 2, *flags = j.tmax + 2 + kTmaxParts;
-    hipLaunchKernelGGL(xm_prep_kernel, dim3((unsigned)(nscale + nsym + ntmax)), dim3(kXmPrepThreads), 0, s, j.x, Cc,
-                       j.w, const_cast<int *>(j.e), j.gamma, j.tau, flags, part, nscale, nsym, ntmax);
+    auto prep = [&](int64_t scale, int64_t sym, int64_t tmax) {
+        hipLaunchKernelGGL(xm_prep_kernel, dim3((unsigned)(scale + sym + tmax)), dim3(kXmPrepThreads), 0, s, j.x, Cc,
+                           j.w, const_cast<int *>(j.e), j.gamma, j.tau, flags, part, scale, sym, tmax);
+    };
+    if (!data || !seeds || fits_launch(nscale + nsym + ntmax, kXmPrepThreads)) {
+        prep(nscale, nsym, ntmax);
+    } else {
+        prep(nscale, 0, 0);
+        prep(0, nsym, ntmax);
+    }
     if (seeds)
         hipLaunchKernelGGL(xm_tmax_final_kernel, dim3(1), dim3(256), 0, s, part, (int)ntmax, flags, j.x.eta_scale,
                            j.x.a.tau_limit, j.x.a.unit_c, j.tmax);
     const int64_t nfrag = data ? j.x.nstrips * j.x.nchunks : 0;  // 4 x 64 threads each
     const int64_t namp = seeds ? ((int64_t)j.x.a.nt * (j.x.a.npix / 2) + 255) / 256 : 0;
-    hipLaunchKernelGGL(xm_operands_kernel, dim3((unsigned)(nfrag + namp)), dim3(256), 0, s, j.x, Cc, j.w, j.e, j.gamma,
-                       j.tau, j.tmax, const_cast<uint4 *>(j.A), j.amp, j.amp4, nfrag);
+    auto operands = [&](int64_t frag, int64_t amp) {
+        hipLaunchKernelGGL(xm_operands_kernel, dim3((unsigned)(frag + amp)), dim3(256), 0, s, j.x, Cc, j.w, j.e,
+                           j.gamma, j.tau, j.tmax, const_cast<uint4 *>(j.A), j.amp, j.amp4, frag);
+    };
+    if (!data || !seeds || fits_launch(nfrag + namp, 256)) {
+        operands(nfrag, namp);
+    } else {
+        operands(nfrag, 0);
+        operands(0, namp);
+    }
     return hipGetLastError();
 }
 

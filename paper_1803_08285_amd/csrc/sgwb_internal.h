@@ -148,6 +148,10 @@ hipError_t launch_network_sum(const MapList &l, int64_t n, float *out, hipStream
 hipError_t launch_contract(const float *M, int32_t nf, int32_t npix, const int32_t *pix, int32_t nsel, float *out,
                            hipStream_t s);
 
+// Whether a launch stays below the 2^32 work items that HIP takes (merged launches
+// that would not are issued in their parts).
+inline bool fits_launch(int64_t workgroups, int threads) { return workgroups * threads <= 0xffffffffll; }
+
 // fused broadband sums: out[p] = sum_{r < nrows} part[r][p] (float64, fixed order, rounded once);
 // with out1 also out1 from part1, of as many rows
 hipError_t launch_band_partial_finish(const double *part, int64_t nrows, int32_t npix, float *out, hipStream_t s,
