@@ -165,13 +165,23 @@ def _check(rc: int, what: str):
         raise SgwbError(f"{what}: {L.sgwb_status_string(rc).decode()} ({rc}): {L.sgwb_last_error().decode()}")
 
 
+# torch's own short cuts past the Stream and device objects (a small query's call is
+# bound by its host work: 4 us of 26).  They are not public: where a torch has none,
+# the public calls do the same.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+_exchange_device = getattr(torch.cuda, "_exchange_device", None)
+_restore_device = getattr(torch.cuda, "_maybe_exchange_device", None)
+
+
 def _stream() -> int:
-    """The current stream of the current device.  (Its raw handle, without the
-    Stream object: a small query's call is bound by its host work.)"""
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    """The current stream of the current device."""
+    if _raw_stream is None or _current_device is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_current_device())
 
 
-class _on:
+class _on_device:
     """``with _on(tensor)``: its device is current (torch.cuda.device for a tensor's
     own device, whose index needs no look-up)."""
 
@@ -183,11 +193,18 @@ class _on:
             raise ValueError(f"Expected a cuda device, but got: {t.device}")
 
     def __enter__(self):
-        self.prev = torch.cuda._exchange_device(self.idx)
+        self.prev = _exchange_device(self.idx)
 
     def __exit__(self, *exc):
-        torch.cuda._maybe_exchange_device(self.prev)
+        _restore_device(self.prev)
         return False
+
+
+if _exchange_device is None or _restore_device is None:
+    def _on(t: torch.Tensor):
+        return torch.cuda.device(t.device)
+else:
+    _on = _on_device
 
 
 def _ptr(t):
