@@ -26,11 +26,11 @@
 //   * Fixed summation order over t, no atomics: bitwise reproducible, and the
 //     absolute anchor grid makes a sub-band bitwise equal to the full band.
 // Bound by the vector instructions: six FMAs per segment, bin and pixel pair
-// (at one per lane and cycle and 64 lanes a compute unit, 1.5 of the 1.75 ms
+// (at one per lane and cycle and 64 lanes a compute unit, 1.5 of the 1.72 ms
 // below); in float64 also by the LDS broadcasts, 16 bytes a bin; a day of a few
 // segments by the map's write (one segment, nside 32, 6823 bins, 335 MB: 69 us).
 // Measured, split against whole days: 240 segments, nside 32, 6823 bins of 0.25 Hz
-// 1.75 against 2.04 ms; nside 8, 1024 bins 44 against 302 us; float64, nside 16,
+// 1.72 against 2.04 ms; nside 8, 1024 bins 44 against 302 us; float64, nside 16,
 // 1001 bins 141 against 263 us.
 #include <algorithm>
 #include <type_traits>
@@ -67,9 +67,8 @@ struct StripTraits<double> {
     static constexpr int SLAB = 8;
 };
 
-constexpr int kDmWaves = 8;      // waves per workgroup, at most, and segment slices, at most
-constexpr int kDmCols = 64;      // pixel columns per wave
-constexpr int kDmLds = 65536;    // of kDmWaves waves of a split day: their stages, then the final sums' rounds
+constexpr int kDmCols = 64;       // pixel columns per wave
+constexpr int kDmWaveLds = 8192;  // of a split day's wave: its stage, then its share of a round of the final sums
 
 // Segment slices of a map: one (whole days), four or eight.  They depend on the
 // segments and the pixel columns alone, so that a sub-band's rows are the whole
@@ -98,7 +97,7 @@ inline int dm_slices(int32_t nt, int64_t ncol, bool pair)
         {0x7fffffffffff, pair ? 80 : 160, kNever},
     };
     for (const Row &r : rows)
-        if (ncol <= r.cols) return nt >= r.eight ? kDmWaves : nt >= r.four ? 4 : 1;
+        if (ncol <= r.cols) return nt >= r.eight ? 8 : nt >= r.four ? 4 : 1;
     return 1;
 }
 
@@ -108,9 +107,18 @@ inline void dm_with_slices(int slices, const F &f)
 {
     if (slices == 1) f(std::integral_constant<int, 1>());
     else if (slices == 4) f(std::integral_constant<int, 4>());
-    else f(std::integral_constant<int, kDmWaves>());
+    else f(std::integral_constant<int, 8>());
 }
 
+// Waves per workgroup: four, or one a slice.
+constexpr int dm_waves(int slices) { return slices > 4 ? slices : 4; }
+// Its LDS: the whole-day tile's stage, or the waves' stages and the final sums.
+template <typename T>
+constexpr int dm_lds(int slices)
+{
+    return slices > 1 ? kDmWaveLds * slices
+                      : StripTraits<T>::WTC * StripTraits<T>::S * (int)sizeof(typename Cplx<T>::type);
+}
 // Rotor 1 + eps = e^{i d} for the per-bin phase step d = 2 pi df tau:
 // eps_re = cos d - 1, eps_im = sin d, each with full relative precision.
 __device__ inline void rotor(float d, float *er, float *ei)
@@ -339,11 +347,11 @@ __device__ inline void dirty_map_whole_tile(const MapArgs &a, int64_t strip, int
     if (PAIR) gmem(band_row)[colB] = sb;
 }
 
-// One tile of a map whose day is split: one S-bin strip (absolute index strip) x W
-// slices of the segments for NW / W neighbouring blocks of 64 pixel columns (the
-// coltile-th group of them).  Both tiles are called by every thread of a workgroup
-// of NW waves; lds is its dm_lds bytes of LDS.
-template <typename T, bool PAIR, int W, int NW>
+// One tile of a map whose day is split: 64 pixel columns (the coltile-th block) x one
+// S-bin strip (absolute index strip), a slice of the segments for each of the
+// workgroup's W waves.  Both tiles are called by every thread of the workgroup; lds
+// is its dm_lds bytes of LDS.
+template <typename T, bool PAIR, int W>
 __device__ inline void dirty_map_split_tile(const MapArgs &a, int64_t strip, int64_t coltile,
                                       const typename Cplx<T>::type *__restrict__ C, const T *__restrict__ w,
                                       const T *__restrict__ gamma, const double *__restrict__ tau,
@@ -355,15 +363,19 @@ __device__ inline void dirty_map_split_tile(const MapArgs &a, int64_t strip, int
     constexpr int SLAB = StripTraits<T>::SLAB;
     constexpr int NLD = XTC * S / 64;  // staged values per lane
     constexpr int NA = PAIR ? 2 : 1;   // sums per bin
-    static_assert(NW * XTC * S * sizeof(C2) <= kDmLds / kDmWaves * NW, "the waves' stages");
-    static_assert(NW * NA * SLAB * kDmCols * sizeof(T) <= kDmLds / kDmWaves * NW, "a round of the final sums");
-    static_assert(S % SLAB == 0 && SLAB % W == 0 && NW % W == 0, "whole rounds");
+    static_assert(XTC * S * sizeof(C2) <= kDmWaveLds, "the waves' stages");
+    static_assert(NA * SLAB * kDmCols * sizeof(T) <= kDmWaveLds, "a round of the final sums");
+    static_assert(S % SLAB == 0 && SLAB % W == 0, "whole rounds");
 
-    // the wave's number as a scalar, so that its loops and row addresses are scalar
-    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const int sl = wv % W, ct = wv / W;
+    // The wave's number as a scalar makes its loops and row addresses scalar: without
+    // pairs 7-15 % faster (240 segments, nside 32, 6823 bins 3.02 against 3.55 ms),
+    // float64 5 %; the float32 pairs' tile is 1-3 % faster with it in a vector register
+    // (1.71 against 1.73 ms).
+    constexpr bool kScalarWave = !PAIR || sizeof(T) == 8;
+    const int lane = threadIdx.x & 63;
+    const int wv = kScalarWave ? __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) : (int)threadIdx.x >> 6;
     const int64_t ncol = PAIR ? (int64_t)a.npix / 2 : (int64_t)a.npix;
-    const int64_t col = (coltile * (NW / W) + ct) * kDmCols + lane;
+    const int64_t col = coltile * kDmCols + lane;
     const bool active = col < ncol;
     const int64_t pcol = active ? col : 0;
     const int64_t kabs0 = strip * S;                          // absolute first bin of the strip
@@ -371,7 +383,7 @@ __device__ inline void dirty_map_split_tile(const MapArgs &a, int64_t strip, int
     const double fa4 = 4.0 * (a.f0 + (double)kabs0 * a.df);   // anchor frequency, quarter turns
     const double two_pi_df = kTwoPi * a.df;
     const int per = (a.nt + W - 1) / W;
-    const int ta = min(sl * per, a.nt), tb = min(ta + per, a.nt);  // this wave's segments
+    const int ta = min(wv * per, a.nt), tb = min(ta + per, a.nt);  // this wave's segments
 
     T acc_a[S], acc_b[PAIR ? S : 1];
 #pragma unroll
@@ -436,10 +448,9 @@ __device__ inline void dirty_map_split_tile(const MapArgs &a, int64_t strip, int
     if (PAIR && active) colB = antipode_north(ring_of_north(col, a.nside), a.npix);
     double sa = 0.0, sb = 0.0;  // this thread's share of the strip's broadband sums
     const BandBins<S> band(a, c0);
-    // the slices' sums, SLAB bins a round: [wave][sum][bin][column], every thread
-    // then adds the slices' for its column and every W-th bin
+    // the slices' sums, SLAB bins a round: [slice][sum][bin][column], every thread
+    // then adds them for its column and every W-th bin
     T(*sum)[NA][SLAB][kDmCols] = reinterpret_cast<T(*)[NA][SLAB][kDmCols]>(lds);
-    T(*mine)[NA][SLAB][kDmCols] = sum + ct * W;  // its columns' slices
 #pragma unroll
     for (int j0 = 0; j0 < S; j0 += SLAB) {
         __syncthreads();  // the stages, or the previous round, are read
@@ -449,14 +460,14 @@ __device__ inline void dirty_map_split_tile(const MapArgs &a, int64_t strip, int
             if (PAIR) sum[wv][NA - 1][j][lane] = acc_b[PAIR ? j0 + j : 0];
         }
         __syncthreads();
-        for (int j = sl; j < SLAB; j += W) {
+        for (int j = wv; j < SLAB; j += W) {
             const int64_t c = c0 + j0 + j;
             if (!active || c < 0 || c >= a.nf) continue;
-            T va = mine[0][0][j][lane], vb = PAIR ? mine[0][NA - 1][j][lane] : T(0);
+            T va = sum[0][0][j][lane], vb = PAIR ? sum[0][NA - 1][j][lane] : T(0);
 #pragma unroll
             for (int k = 1; k < W; ++k) {
-                va += mine[k][0][j][lane];
-                if (PAIR) vb += mine[k][NA - 1][j][lane];
+                va += sum[k][0][j][lane];
+                if (PAIR) vb += sum[k][NA - 1][j][lane];
             }
             put_bin<T, PAIR>(a, X, c, col, colB, va, vb);
             if (band_row) band.add(j0 + j, va, vb, sa, sb);
@@ -468,11 +479,11 @@ __device__ inline void dirty_map_split_tile(const MapArgs &a, int64_t strip, int
     bs[wv][0][lane] = sa;
     bs[wv][1][lane] = sb;
     __syncthreads();
-    if (sl != 0 || !active) return;
+    if (wv != 0 || !active) return;
 #pragma unroll
     for (int k = 1; k < W; ++k) {
-        sa += bs[wv + k][0][lane];
-        sb += bs[wv + k][1][lane];
+        sa += bs[k][0][lane];
+        sb += bs[k][1][lane];
     }
     gmem(band_row)[col] = sa;
     if (PAIR) gmem(band_row)[colB] = sb;
@@ -486,7 +497,7 @@ __device__ inline double *band_row_of(const MapArgs &a, int64_t strip, int S)
 }
 
 // Either kind of tile.
-template <typename T, bool PAIR, int W, int NW>
+template <typename T, bool PAIR, int W>
 __device__ __forceinline__ void dirty_map_tile(const MapArgs &a, int64_t strip, int64_t coltile,
                                                const typename Cplx<T>::type *__restrict__ C, const T *__restrict__ w,
                                                const T *__restrict__ gamma, const double *__restrict__ tau,
@@ -494,20 +505,11 @@ __device__ __forceinline__ void dirty_map_tile(const MapArgs &a, int64_t strip, 
 {
     double *band_row = band_row_of(a, strip, StripTraits<T>::S);
     if constexpr (W == 1)
-        dirty_map_whole_tile<T, PAIR, NW>(a, strip, coltile, C, w, gamma, tau, X, band_row, lds);
+        dirty_map_whole_tile<T, PAIR, dm_waves(W)>(a, strip, coltile, C, w, gamma, tau, X, band_row, lds);
     else
-        dirty_map_split_tile<T, PAIR, W, NW>(a, strip, coltile, C, w, gamma, tau, X, band_row, lds);
+        dirty_map_split_tile<T, PAIR, W>(a, strip, coltile, C, w, gamma, tau, X, band_row, lds);
 }
 
-// Waves per workgroup of a single call: four, or one a slice.
-constexpr int dm_waves(int slices) { return slices > 4 ? slices : 4; }
-// Its LDS: the whole-day tile's stage, or the waves' stages and the final sums.
-template <typename T>
-constexpr int dm_lds(int slices)
-{
-    return slices > 1 ? kDmLds / kDmWaves * dm_waves(slices)
-                      : StripTraits<T>::WTC * StripTraits<T>::S * (int)sizeof(typename Cplx<T>::type);
-}
 // Waves per SIMD that the registers have to leave room for: the split tile's two
 // sums a bin take half of them, its one sum a quarter.
 constexpr int dm_occupancy(bool one_sum, int slices) { return slices == 1 ? 1 : one_sum ? 4 : 2; }
@@ -521,11 +523,10 @@ __global__ __launch_bounds__(64 * dm_waves(W)) __attribute__((
                                                          const double *__restrict__ tau,
                                                          T *__restrict__ X, const double *__restrict__ gate)
 {
-    constexpr int NW = dm_waves(W);
     __shared__ __attribute__((aligned(16))) char lds[dm_lds<T>(W)];
     // gated launch: only where the matrix-core prep found no accurate form
     if (gate && (int)gmem(gate)[1] != SGWB_XFORM_VALU) return;
-    dirty_map_tile<T, PAIR, W, NW>(a, strip0 + (int64_t)blockIdx.y, blockIdx.x, C, w, gamma, tau, X, lds);
+    dirty_map_tile<T, PAIR, W>(a, strip0 + (int64_t)blockIdx.y, blockIdx.x, C, w, gamma, tau, X, lds);
 }
 
 // Multi-job form over the concatenated tile list of the jobs (each job: its column
@@ -540,7 +541,6 @@ __global__ __launch_bounds__(64 * dm_waves(W)) __attribute__((
                                                                                int32_t njobs, int64_t first,
                                                                                int64_t ntiles)
 {
-    constexpr int NW = dm_waves(W);
     __shared__ __attribute__((aligned(16))) char lds[dm_lds<float>(W)];
     for (int64_t g = first + blockIdx.x; g < ntiles; g += gridDim.x) {
         int j = 0;
@@ -560,7 +560,7 @@ __global__ __launch_bounds__(64 * dm_waves(W)) __attribute__((
             strip = strip0 + local % nstrips;
         }
         const float2 *C = reinterpret_cast<const float2 *>(jobs[j].C);
-        dirty_map_tile<float, PAIR, W, NW>(a, strip, coltile, C, jobs[j].w, jobs[j].gamma, jobs[j].tau, jobs[j].X,
+        dirty_map_tile<float, PAIR, W>(a, strip, coltile, C, jobs[j].w, jobs[j].gamma, jobs[j].tau, jobs[j].X,
                                            lds);
         if (W > 1) break;
     }
