@@ -692,9 +692,13 @@ static int bb_route(int32_t nt, int32_t nf, int32_t npix, uint32_t flags, const 
     // launches, ~1.5e13 float64 FMAs/s for the tables (4 per segment, bin and
     // node; the rate rises to ~2e13 with more nodes) and ~3.3e11 items/s in
     // the map pass (twice that for antipodal seeds, read once per pixel pair).
-    // (The rates are those of the direct table sums; summed at Chebyshev nodes
-    // the tables take a fifth of that.  The rule is kept as it is: a query's
-    // route, and with it its bits, stays the same.)
+    // The tables' rate is that of the direct sums: summed at Chebyshev nodes they
+    // take a fifth of that or less, so the estimate keeps the strips where the
+    // tables are faster by now (strips / tables, ms, full day: nside 8, 4096 bins
+    // AB 0.158 / 0.043, AC 0.179 / 0.056; nside 16, 4096 bins AC 0.394 / 0.062, 3000
+    // bins 0.325 / 0.051; nside 8, 2300 bins AC 0.169 / 0.038), and ranks a server's
+    // queries by the same figures.  Of the bands timed (16 to 4096 bins, nside 8 to
+    // 128) it picks the faster route everywhere else.
     const double strip_cols = (double)(((int64_t)nf + 63) / 64 * 64);
     const double strips = 1.9e-4 + (double)nt * npix / 1.2e11 + (double)nt * strip_cols * npix / 4.2e13;
     const double table = have_grid ? 3e-5 + (double)nt * nb * r->grid.G * 4.0 / 1.5e13 +

@@ -317,10 +317,10 @@ __global__ __launch_bounds__(256) void band_gamma_kernel(const float *__restrict
     part[(int64_t)blockIdx.y * npix + p] = acc;
 }
 
-// Up to kBandTChunks chunks (what the scratch holds), halved while the pixel
-// pass that shares them (512 pixel pairs a workgroup) still has 1536 workgroups,
-// two full rounds of the chip: every chunk writes and reads back 16 bytes a
-// pixel.  Full-day query, nside 128, 4096 bins, with 32 / 16 / 8 chunks: 363 / 350 / 332 us.
+// Up to kBandTChunks chunks (what the scratch holds), halved (to four at least) while
+// the pixel pass that shares them (512 pixel pairs a workgroup) has more than 1536
+// workgroups, so that more than 768 are left, a full round of the chip: every chunk
+// writes and reads back 16 bytes a pixel.  Full-day query, nside 128, 4096 bins, with 32 / 16 / 8 chunks: 363 / 350 / 332 us.
 int32_t band_gamma_chunks(int32_t npix)
 {
     const int64_t blocks = ((int64_t)npix / 2 + 511) / 512;

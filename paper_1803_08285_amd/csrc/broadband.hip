@@ -11,9 +11,11 @@
 //
 // Kernels: the tables (float64: Y_t by Horner's rule at the few Chebyshev nodes
 // that determine it, its Chebyshev series evaluated at the grid's nodes; or
-// Horner's rule at every grid node), and the map pass (one pixel a thread, one
-// chunk of segments a workgroup row, float64 partial sums added in a fixed
-// order by the band finish kernel).
+// Horner's rule at every grid node), and the map pass (antipodal seeds: a pixel
+// pair a thread, the tables through LDS, or for few pixels or long tables a run of
+// the segments a wave; any seeds: one pixel a thread), one chunk of segments a
+// workgroup row, float64 partial sums added in a fixed order by the band finish
+// kernel.
 #include <math.h>
 #include <stdint.h>
 

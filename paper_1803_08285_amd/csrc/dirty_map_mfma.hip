@@ -903,14 +903,14 @@ __device__ __forceinline__ int64_t xcd_tile(int64_t L, int64_t n)
     return xcd_range_begin(L % kXcds, n) + L / kXcds;
 }
 
-// Bound by the matrix products (36 % of the cycles) and the vector work that
-// builds their pixel-side operands (40 %), and on the full band by the package's
-// power cap.  Four waves a workgroup, so that two workgroups share a compute unit
+// Bound by the matrix products (43 % of a SIMD's cycles at nside 64) and the vector
+// work that builds their pixel-side operands (57 %), and on the full band by the
+// package's power cap.  Four waves a workgroup, so that two workgroups share a compute unit
 // and one's vector phase runs beside the other's products (eight waves of one
 // workgroup meet at every chunk's barrier in the same phase), and so that the
-// last round of tiles is half as long.  Measured, a day at 1/32 Hz and nside 32,
-// whole calls: 98 strips with their Fisher diagonal 744 -> 633 us, the overlap
-// diagonal of that band 1210 -> 1008 us, the full band 16.04 -> 15.45 ms, against
+// last round of tiles is half as long.  Measured, a day at 1/32 Hz, whole calls: 98
+// strips at nside 16 with their Fisher diagonal 744 -> 633 us, at nside 32 the
+// overlap diagonal of 4101 bins 1210 -> 1008 us and the full band 16.04 -> 15.45 ms, against
 // one eight-wave workgroup with 64-bit seed addresses, every part copied and the
 // phase reduced by four float64 instructions (eight waves with the other changes:
 // 725 and 1164 us).  With what came since (strips of 128 bins for the overlap

@@ -1795,7 +1795,7 @@ __global__ __launch_bounds__(256) void cg_out_kernel(const double *__restrict__ 
 // then its own rows: q' = G p', their shares of p'.q', x + alpha p, and stores r',
 // p', q', x there.  Vectors and partial sums alternate between two sets, so a
 // workgroup never reads what another writes.  Every sum runs in the order of the
-// three-kernel form below, so the iterates are the same bits (an iterate of an
+// three-kernel form above, so the iterates are the same bits (an iterate of an
 // ill-conditioned matrix can turn a last bit into its leading ones).  That form
 // is bound by its launches (nside 16: 5.8 + 4.0 + 2.7 us and the gaps between
 // them, 15 us an iteration, of which the matrix's 38 MB are ~5); this takes 10.3
