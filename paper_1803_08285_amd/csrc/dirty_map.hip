@@ -521,12 +521,33 @@ __global__ __launch_bounds__(64 * dm_waves(W)) __attribute__((
                                                          const T *__restrict__ w,
                                                          const T *__restrict__ gamma,
                                                          const double *__restrict__ tau,
-                                                         T *__restrict__ X, const double *__restrict__ gate)
+                                                         T *__restrict__ X)
 {
     __shared__ __attribute__((aligned(16))) char lds[dm_lds<T>(W)];
-    // gated launch: only where the matrix-core prep found no accurate form
-    if (gate && (int)gmem(gate)[1] != SGWB_XFORM_VALU) return;
     dirty_map_tile<T, PAIR, W>(a, strip0 + (int64_t)blockIdx.y, blockIdx.x, C, w, gamma, tau, X, lds);
+}
+
+// The same tiles of paired float32 seeds where the matrix-core prep found no
+// accurate form (gate).  Nearly every launch finds one and has nothing to do, so
+// the tiles share kDmGated workgroups at most: one a tile took 46 us to leave at
+// the full band of nside 32, these 5.
+constexpr int64_t kDmGated = 8192;
+
+template <int W>
+__global__ __launch_bounds__(64 * dm_waves(W)) __attribute__((
+    amdgpu_waves_per_eu(dm_occupancy(false, W)))) void dirty_map_gated_kernel(MapArgs a, int64_t strip0,
+                                                                             int64_t ncoltiles, int64_t ntiles,
+                                                                             const float2 *__restrict__ C,
+                                                                             const float *__restrict__ w,
+                                                                             const float *__restrict__ gamma,
+                                                                             const double *__restrict__ tau,
+                                                                             float *__restrict__ X,
+                                                                             const double *__restrict__ gate)
+{
+    __shared__ __attribute__((aligned(16))) char lds[dm_lds<float>(W)];
+    if ((int)gate[1] != SGWB_XFORM_VALU) return;
+    for (int64_t g = blockIdx.x; g < ntiles; g += gridDim.x)
+        dirty_map_tile<float, true, W>(a, strip0 + g / ncoltiles, g % ncoltiles, C, w, gamma, tau, X, lds);
 }
 
 // Multi-job form over the concatenated tile list of the jobs (each job: its column
@@ -605,7 +626,7 @@ hipError_t launch_dirty_map_batched(const XJob *jobs_dev, int32_t njobs, int64_t
 
 template <typename T>
 hipError_t launch_dirty_map(const MapArgs &a, const T *C, const T *w, const T *gamma,
-                            const double *tau, T *X, hipStream_t s, const double *gate)
+                            const double *tau, T *X, hipStream_t s)
 {
     using C2 = typename Cplx<T>::type;
     constexpr int S = StripTraits<T>::S;
@@ -626,16 +647,29 @@ hipError_t launch_dirty_map(const MapArgs &a, const T *C, const T *w, const T *g
     for (int64_t s0 = 0; s0 < nstrips; s0 += 65535) {
         const int64_t ns = nstrips - s0 < 65535 ? nstrips - s0 : 65535;
         dim3 grid((unsigned)((ncol + cols - 1) / cols), (unsigned)ns);
-        hipLaunchKernelGGL(kernel, grid, dim3(64 * waves), 0, s, a, strip_first + s0, Cc, w, gamma, tau, X, gate);
+        hipLaunchKernelGGL(kernel, grid, dim3(64 * waves), 0, s, a, strip_first + s0, Cc, w, gamma, tau, X);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
 }
 template hipError_t launch_dirty_map<float>(const MapArgs &, const float *, const float *,
-                                            const float *, const double *, float *, hipStream_t, const double *);
+                                            const float *, const double *, float *, hipStream_t);
 template hipError_t launch_dirty_map<double>(const MapArgs &, const double *, const double *,
-                                             const double *, const double *, double *, hipStream_t,
-                                             const double *);
+                                             const double *, const double *, double *, hipStream_t);
+
+hipError_t launch_dirty_map_gated(const MapArgs &a, const float *C, const float *w, const float *gamma,
+                                  const double *tau, float *X, hipStream_t s, const double *gate)
+{
+    if (a.nside <= 0) return hipErrorInvalidValue;
+    XJob j;
+    fill_xjob(&j, a, C, w, gamma, tau, X, true);
+    decltype(&dirty_map_gated_kernel<1>) kernel = nullptr;
+    dm_with_slices(j.slices, [&](auto n) { kernel = dirty_map_gated_kernel<decltype(n)::value>; });
+    hipLaunchKernelGGL(kernel, dim3((unsigned)std::min(kDmGated, xjob_tiles(j))), dim3(64 * dm_waves(j.slices)), 0, s, a,
+                       j.strip_first, j.ncoltiles, xjob_tiles(j), reinterpret_cast<const float2 *>(C), w, gamma, tau,
+                       X, gate);
+    return hipGetLastError();
+}
 
 }  // namespace sgwb

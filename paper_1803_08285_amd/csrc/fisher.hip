@@ -84,7 +84,7 @@ hipError_t launch_fisher_neighbours(const MapArgs &a, const float *u, const floa
     e = launch_dirty_map_mfma(b, nullptr, y, g2, t2, Gam, xm_ws, s, &rec);
     if (e != hipSuccess) return e;
     if (form_rec) *form_rec = rec;
-    if (kTwoPi * 31.5 * b.df * b.tau_limit > kXmEtaMax) e = launch_dirty_map<float>(b, nullptr, y, g2, t2, Gam, s, rec);
+    if (kTwoPi * 31.5 * b.df * b.tau_limit > kXmEtaMax) e = launch_dirty_map_gated(b, nullptr, y, g2, t2, Gam, s, rec);
     return e;
 }
 

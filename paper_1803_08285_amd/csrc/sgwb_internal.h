@@ -130,13 +130,14 @@ struct MapArgs {
     // delays of a baseline on the Earth, 4 R / c for differences of two.
     double tau_limit = 2.0 * kEarthRadius / kLightSpeed;
 };
-// gate (optional): the dirty-map form record of a matrix-core launch on the
-// same seeds ([0] largest |tau|, [1] form code); with it the kernel computes
-// only where that record selected the vector-unit form (its workgroups exit
-// at once otherwise).
 template <typename T>
 hipError_t launch_dirty_map(const MapArgs &a, const T *C, const T *w, const T *gamma,
-                            const double *tau, T *X, hipStream_t s, const double *gate = nullptr);
+                            const double *tau, T *X, hipStream_t s);
+// The same where the dirty-map form record of a matrix-core launch on the same
+// (antipodal) seeds ([0] largest |tau|, [1] form code) selected the vector-unit
+// form; nothing otherwise.
+hipError_t launch_dirty_map_gated(const MapArgs &a, const float *C, const float *w, const float *gamma,
+                                  const double *tau, float *X, hipStream_t s, const double *gate);
 
 // Network sums and pixel contractions.
 constexpr int kMaxNetworkMaps = 32;

@@ -177,3 +177,33 @@ def test_overlap_sub_bands_are_rows_of_the_band_and_meet_the_oracle(sg, oracle_m
         cut = slice(lo, lo + n)
         part = sg.fisher_overlap(*(a[:, cut].contiguous() for a in (vd, ud, wd)), sg.FGrid(F0, df), k0 + lo, g, t)
         assert torch.equal(part, G[cut]), (lo, n)
+
+
+@pytest.mark.parametrize("nside,nt,nf", [
+    (4, 10, 150),     # whole days
+    (8, 20, 150),     # eight slices
+    (16, 40, 150),    # four slices
+    (16, 40, 21950),  # more tiles than workgroups
+])
+def test_overlap_with_delays_beyond_the_matrix_cores(sg, oracle_mod, nside, nt, nf):
+    """Segments far apart have pair delays beyond every matrix-core form: the gated
+    vector-unit launch computes the neighbour terms, bitwise as the call that asks
+    for the vector units, and within the tolerances of the oracle."""
+    k0, df = 40, 1 / 32
+    tg = sg.TGrid(nt, 0.0, 0.4 * 86164.0905, 800.0)
+    g, t = sg.build_geometry(synth.baseline_sites("AD"), nside, tg)
+    rng = np.random.default_rng(nt + nf)
+    f = freqs(F0, df, k0, nf)
+    v = (rng.uniform(0.5, 1.5, (nt, 1)) * (synth.spectrum_H(f) / synth.noise_psd(f) ** 2)).astype(np.float32)
+    u, w = (a.astype(np.float32) for a in synth.overlap_series(v.astype(np.float64)))
+    d = [torch.from_numpy(a).cuda() for a in (v, u, w)]
+    fg, npix = sg.FGrid(F0, df), 12 * nside * nside
+    ws = torch.empty(sg.fisher_overlap_workspace_bytes(nt, nf, npix), dtype=torch.uint8, device="cuda")
+    G = sg.fisher_overlap(*d, fg, k0, g, t, workspace=ws)
+    assert sg.last_x_form() == "valu"
+    assert torch.equal(G, sg.fisher_overlap(*d, fg, k0, g, t, x_kernel="valu"))
+    rows = np.concatenate([[0, nf - 1], rng.integers(0, nf, 30)])
+    cols = rng.integers(0, npix, rows.size)
+    Go, _, S = oracle_mod.fisher_overlap_at(v, u, w, F0, df, k0, g.cpu().numpy(), t.cpu().numpy(), rows, cols)
+    err = np.abs(G.cpu().numpy()[rows, cols].astype(np.float64) - Go) / S
+    assert err.max() <= 1e-4
