@@ -65,14 +65,14 @@ def test_no_seed_beyond_the_day(oracle_mod, nt, bl, df, f0, form):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("nt", [898, 905])
-def test_no_seed_beyond_the_day_overlap(oracle_mod, nt):
+@pytest.mark.parametrize("nt,stride", [(898, 86164.0905 / 898), (905, 86164.0905 / 905), (5, 96.0), (9, 96.0), (20, 96.0)])
+def test_no_seed_beyond_the_day_overlap(oracle_mod, nt, stride):
     """The overlap terms (pairs' seeds in the workspace, 128-bin strips)."""
     if not torch.cuda.is_available():
         pytest.fail("GPU tests need a GPU")
     import paper_1803_08285_amd as sg
 
-    g, t = sg.build_geometry(synth.baseline_sites("AB"), NSIDE, sg.TGrid(nt, 0.0, 86164.0905 / nt, 2 * 86164.0905 / nt))
+    g, t = sg.build_geometry(synth.baseline_sites("AB"), NSIDE, sg.TGrid(nt, 0.0, stride, 2 * stride))
     f = freqs(F0, 1 / 32, K0, NF)
     rng = np.random.default_rng(nt)
     v = (rng.uniform(0.5, 1.5, (nt, 1)) * (synth.spectrum_H(f) / synth.noise_psd(f) ** 2)).astype(np.float32)
